@@ -86,6 +86,11 @@ struct PosTile {
   int base;
 };
 
+// LDS written by one lane and read by another lane of the same wavefront: a
+// wavefront's LDS instructions complete in issue order, so it is enough that
+// the compiler keeps every memory access on its side of this point.
+__device__ __forceinline__ void lds_lane_exchange() { asm volatile("" ::: "memory"); }
+
 // A value the compiler cannot see through.  The float64 paths below run for
 // few candidates of the single-image scan; taking their inputs through this
 // keeps their conversions inside the branch instead of being computed ahead
@@ -386,11 +391,94 @@ __device__ __forceinline__ CellCheck init_ctx(const NbrArgs& a, int st, int i, f
   return ck;
 }
 
+// Candidates of the single-image scan: bit b of mask[c] tells whether atom
+// jb + 32 c + b of [jb, je) (at most 128) may lie within rc + delta, its
+// single-precision distance being below that bound.  In an orthorhombic cell
+// the nearest image along an axis is min(|e|, L - |e|).  Atom j is at tile
+// slot j - t.base; up to 7 slots past the range are read and masked off.
+constexpr int kNbrMasks = 4;
+template <bool kTri>
+__device__ __forceinline__ void scan_hits(const ScanCtx& c, const PosTile& t, int jb, int je,
+                                          uint32_t (&mask)[kNbrMasks]) {
+#pragma unroll
+  for (int k = 0; k < kNbrMasks; ++k) {
+    uint32_t m = 0;
+    const int n = min(je - jb - 32 * k, 32);   // candidates of this mask
+    const int q0 = jb + 32 * k - t.base;
+    for (int b = 0; b < n; b += 8) {
+      uint32_t m8 = 0;
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const int q = q0 + b + u;
+        float ex = t.x[q] - c.xf, ey = t.y[q] - c.yf, ez = t.z[q] - c.zf;
+        if constexpr (kTri) {
+          float kx, ky, kz;
+          min_image<true>(c, ex, ey, ez, kx, ky, kz);
+        } else {
+          ex = fminf(fabsf(ex), fabsf(c.Lxf - fabsf(ex)));
+          ey = fminf(fabsf(ey), fabsf(c.Lyf - fabsf(ey)));
+          ez = fminf(fabsf(ez), fabsf(c.Lzf - fabsf(ez)));
+        }
+        m8 |= (ex * ex + ey * ey + ez * ez < c.outR2) ? (1u << u) : 0u;
+      }
+      m |= m8 << b;
+    }
+    mask[k] = n >= 32 ? m : (n > 0 ? m & ((1u << n) - 1u) : 0u);
+  }
+}
+
+// Lists of atom c.i from its T hits, tile slots in canonical order at
+// slot k in buf[kNbrThreads (k / 8) + k % 8] (buf: the first of the atom's 8
+// lane columns).  Lane s takes entries s, s + 8, ...; a ballot over the
+// atom's lanes gives each kept entry its place, so 8 consecutive entries are
+// stored together.
+template <bool kTri>
+__device__ __forceinline__ void write_hits(const NbrArgs& a, const ScanCtx& c, const PosTile& t, const uint32_t* buf,
+                                           int T, int s, int& totR, int& totA) {
+  const size_t col = (size_t)c.i;
+  const int sh = threadIdx.x & 24;
+  const bool up = threadIdx.x & 32;
+  const uint32_t below = (1u << s) - 1u;
+  int nR = 0, nA = 0;
+  for (int k0 = 0; k0 < T; k0 += 8) {
+    const bool on = k0 + s < T;
+    const int q = on ? (int)buf[kNbrThreads * (k0 >> 3) + s] : c.i - t.base;
+    const int j = t.base + q;
+    const float px = t.x[q], py = t.y[q], pz = t.z[q];
+    float ex = px - c.xf, ey = py - c.yf, ez = pz - c.zf, kx, ky, kz;
+    min_image<kTri>(c, ex, ey, ez, kx, ky, kz);
+    const float r2 = ex * ex + ey * ey + ez * ez;
+    const int code = 13 - (int)fmaf(9.f, kx, fmaf(3.f, ky, kz));
+    bool in = on & ((j != c.i) | (code != 13));
+    bool ang = r2 < c.inA2;
+    // inside either shell the float64 predicate decides
+    const bool shR = r2 >= c.inR2, shA = !ang && r2 < c.outA2;
+    if (in && (shR || shA)) {
+      const double d2 = image_d2<kTri>(c, px, py, pz, kx, ky, kz);
+      if (shR) in = d2 < c.rcR2;
+      if (shA) ang = d2 < c.rcA2;
+    }
+    ang = ang && in;
+    const unsigned long long bR = __ballot(in), bA = __ballot(ang);
+    const uint32_t mR = ((up ? (uint32_t)(bR >> 32) : (uint32_t)bR) >> sh) & 255u;
+    const uint32_t mA = ((up ? (uint32_t)(bA >> 32) : (uint32_t)bA) >> sh) & 255u;
+    const uint32_t e = ((uint32_t)j << 5) | (uint32_t)(code & 31);
+    const int oR = nR + __popc(mR & below), oA = nA + __popc(mA & below);
+    if (in && oR < a.capR) a.idxR[col * a.capR + oR] = e;
+    if (ang && oA < a.capA) a.idxA[col * a.capA + oA] = e;
+    nR += __popc(mR);
+    nA += __popc(mA);
+  }
+  totR = nR;
+  totA = nA;
+}
+
 // kCells: the cell search ran before and wrote the lists of the atoms with
 // acell[i] >= 0
 template <bool kTri, bool kCells>
 __global__ __launch_bounds__(kNbrThreads) void k_neighbors(NbrArgs a) {
-  __shared__ float tx[kNbrTile], ty[kNbrTile], tz[kNbrTile];
+  // 8 slots past the tile: scan_hits reads candidates eight at a time
+  __shared__ float tx[kNbrTile + 8], ty[kNbrTile + 8], tz[kNbrTile + 8];
   __shared__ uint32_t nbuf[kNbrThreads * (kNbrBuf + 1)];
   __shared__ int jr[2];
   const int s = threadIdx.x & 7;
@@ -398,11 +486,14 @@ __global__ __launch_bounds__(kNbrThreads) void k_neighbors(NbrArgs a) {
   const int i = b0 + (threadIdx.x >> 3);
   const bool live = i < a.N;
   const int ic = live ? i : a.N - 1;
+  // structure of the block's first atom (scalar search), then forward from it
+  const cptr<int> aoff = as_const(a.aoff);
   int lo = 0, hi = a.S;
   while (hi - lo > 1) {
     const int mid = (lo + hi) >> 1;
-    if (a.aoff[mid] <= ic) lo = mid; else hi = mid;
+    if (aoff[mid] <= min(b0, a.N - 1)) lo = mid; else hi = mid;
   }
+  while (lo + 1 < a.S && a.aoff[lo + 1] <= ic) ++lo;
   const int st = lo;
   const int a0 = max(a.aoff[st], 0), a1 = min(a.aoff[st + 1], a.N);
   // the block's atoms are consecutive, so their structures cover [jr[0], jr[1])
@@ -463,8 +554,54 @@ __global__ __launch_bounds__(kNbrThreads) void k_neighbors(NbrArgs a) {
     ++nR;
     nA += ang ? 1 : 0;
   };
-  sweep(jb, je,
-        [&](const PosTile& t, int b2, int e2) { scan_keep<kTri>(c, t, b2, e2, mybuf, nR, nA, angmask, keep); });
+  // Structures of a block that fit one tile (nearly always: at most two of its
+  // structures exceed 32 atoms) take the single-image scan in two parts: a
+  // distance test per candidate that only sets a bit (about 15 instructions),
+  // then the image code, the shell tests and the stores for the hits alone,
+  // spread evenly over the atom's lanes.  Deciding every candidate in one
+  // part took about 40 instructions each for the one in eleven that is kept
+  // (512 structures, 87k atoms: 57 us in one part, 41 us in two).
+  bool done = false;
+  int totR = 0, totA = 0;
+  if (jhi - jlo <= kNbrTile) {
+    for (int q = threadIdx.x; q < jhi - jlo; q += kNbrThreads) {
+      tx[q] = a.pos[jlo + q];
+      ty[q] = a.pos[a.N + jlo + q];
+      tz[q] = a.pos[2 * a.N + jlo + q];
+    }
+    __syncthreads();
+    const PosTile t{tx, ty, tz, jlo};
+    if (c.fast) {   // the same for the atom's 8 lanes
+      uint32_t mask[kNbrMasks];
+      scan_hits<kTri>(c, t, jb, je, mask);
+      int n = 0;
+#pragma unroll
+      for (int k = 0; k < kNbrMasks; ++k) n += __popc(mask[k]);
+      int w = n;
+#pragma unroll
+      for (int d = 1; d < 8; d <<= 1) {
+        const int u = __shfl_up(w, d, 8);
+        if (s >= d) w += u;
+      }
+      const int T = __shfl(w, 7, 8);
+      w -= n;
+      if (T <= 8 * kNbrBuf) {
+        uint32_t* gbuf = nbuf + (threadIdx.x & ~7);   // the atom's columns
+#pragma unroll
+        for (int k = 0; k < kNbrMasks; ++k)
+          for (uint32_t m = mask[k]; m; m &= m - 1u, ++w)
+            gbuf[kNbrThreads * (w >> 3) + (w & 7)] = (uint32_t)(jb - jlo + 32 * k + __builtin_ctz(m));
+        lds_lane_exchange();
+        write_hits<kTri>(a, c, t, gbuf, T, s, totR, totA);
+        done = true;
+      }
+    }
+    if (!done) scan_keep<kTri>(c, t, jb, je, mybuf, nR, nA, angmask, keep);
+    __syncthreads();   // a rescan below loads the tile again
+  } else {
+    sweep(jb, je,
+          [&](const PosTile& t, int b2, int e2) { scan_keep<kTri>(c, t, b2, e2, mybuf, nR, nA, angmask, keep); });
+  }
   // inclusive prefix over the 8 lanes of the atom
   int pR = nR, pA = nA;
 #pragma unroll
@@ -475,10 +612,13 @@ __global__ __launch_bounds__(kNbrThreads) void k_neighbors(NbrArgs a) {
       pA += uA;
     }
   }
-  const int totR = __shfl(pR, 7, 8), totA = __shfl(pA, 7, 8);
+  if (!done) {
+    totR = __shfl(pR, 7, 8);
+    totA = __shfl(pA, 7, 8);
+  }
   int wR = pR - nR, wA = pA - nA;
   const size_t col = (size_t)c.i;
-  const bool spill = nR > kNbrBuf;
+  const bool spill = nR > kNbrBuf;   // never after the two-part scan (nR is 0)
   if (mine && !spill) {
     for (int u = 0; u < nR; ++u) {
       const uint32_t e = mybuf[kNbrThreads * u];
@@ -1187,11 +1327,6 @@ __device__ __forceinline__ PairGeom pair_geom(uint32_t e, const float* __restric
   g.r = r2 * g.inv_r;
   return g;
 }
-
-// LDS written by one lane and read by another lane of the same wavefront: a
-// wavefront's LDS instructions complete in issue order, so it is enough that
-// the compiler keeps every memory access on its side of this point.
-__device__ __forceinline__ void lds_lane_exchange() { asm volatile("" ::: "memory"); }
 
 // ========================================================= atom groups
 // Per-atom kernels run 8 lanes per atom, 8 atoms per wavefront and 32 atoms
