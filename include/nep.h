@@ -164,7 +164,7 @@ int nep_workspace_bytes(const nep_model* model, int32_t n_struct, int32_t n_atom
  * d2 = (dx*dx + dy*dy) + dz*dz < rc*rc without fused multiply-add, so the
  * lists are bit-reproducible.  Sets NEP_FLAG_NBR_OVERFLOW, _BOX, _TYPE,
  * _POSITION in d_flags (required).  Also prepares workspace state that the
- * other calls on this batch read (species order, reverse entries).
+ * other calls on this batch read (species order, packed atoms).
  * Structures of at least 1024 atoms in cells at least 3 (rc_rad + 0.05)
  * wide are searched through cell lists (see nep_batch.max_atoms); the lists
  * are the same bit for bit. */
@@ -281,7 +281,7 @@ typedef struct {
 } nep_adam_config;
 
 /* graph_flags bit NEP_GRAPH_CACHED_NEIGHBORS: the graph leaves out the neighbor
- * build (lists, reverse index and species order) and reuses what an earlier
+ * build (lists and species order) and reuses what an earlier
  * nep_build_neighbors() call with the same nbrs and ws produced.  Training
  * positions never change, so this is the step with cached lists. */
 #define NEP_GRAPH_CACHED_NEIGHBORS 1
@@ -311,13 +311,11 @@ int nep_train_step_graph_create(const nep_model* model, const nep_batch* batch, 
  *   outer_blocks_c  blocks per species of the c_rad outer-product sum, 1..256 [64]
  *   reduce_chunks   chunks per species of the first gradient-partial reduction, 1..512 [128]
  *   cell_min_atoms  smallest structure searched through cell lists, >= 64 [1024]
- *   gather_lanes    lanes per atom of the force gather, 8 or 16 [16]
+ *   gather_lanes    lanes per atom of the force pass, 8 or 16 [16]
  *   forward_waves   wavefronts per SIMD the forward kernel is compiled for, 2 or 3 [3]
  *   adjoint_waves   the same for the adjoint kernel [3; 2 with degrees l > 4]
- *   reverse_branch  where the reverse index of the lists runs: 1 in the launch
- *                   that also counts the species order, 2 on a branch of its
- *                   own that overlaps the species order and the forward pass
- *                   and joins before the force gather [1]
+ *   reverse_branch  0, 1 or 2, without effect: the reverse index it placed is
+ *                   no longer built (the force pass finds partners itself)
  * A value out of range is NEP_ERR_ARG. */
 typedef struct {
   int32_t persistent, outer_blocks_w, outer_blocks_c, reduce_chunks, cell_min_atoms, gather_lanes,

@@ -115,6 +115,50 @@ __device__ __forceinline__ void radial_basis_d(float r, float inv_rc, float (&f)
   }
 }
 
+// Chebyshev space.  With h = f_c / 2, f_k = h T_k + h T_0 for every k, so sums
+// over pairs are taken over h T_k (one multiply-add per order) and the term
+// h T_0 is added once at the end: F_k = A_k + A_0.
+template <int K>
+__device__ __forceinline__ void radial_cheb(float r, float inv_rc, float (&t)[K]) {
+  const float u = r * inv_rc;
+  const float x = u - 1.0f;
+  const float xi = fmaf(2.0f * x, x, -1.0f);
+  const float xi2 = 2.0f * xi;
+  t[0] = fmaf(0.25f, cos_turns(0.5f * u), 0.25f);
+  if (K > 1) t[1] = xi * t[0];
+#pragma unroll
+  for (int k = 2; k < K; ++k) t[k] = fmaf(xi2, t[k - 1], -t[k - 2]);
+}
+
+// d/dr of sum_k c_k f_k(r), for coefficients whose entry 0 holds
+// c_0 + sum_k c_k (the terms h T_0 of every order): h' S + h xi' dS/dxi with
+// S = sum_k c_k T_k, S and dS/dxi by Clenshaw's recurrence.
+template <int K>
+__device__ __forceinline__ float cheb_deriv(const float (&c)[K], float r, float inv_rc) {
+  const float u = r * inv_rc;
+  const float x = u - 1.0f;
+  const float xi = fmaf(2.0f * x, x, -1.0f);
+  const float xi2 = 2.0f * xi;
+  const float hfc = fmaf(0.25f, cos_turns(0.5f * u), 0.25f);
+  const float hfcp = -0.25f * 3.14159265358979f * inv_rc * sin_turns(0.5f * u);
+  float S = c[0], dS = 0.f;
+  if constexpr (K > 1) {
+    float b1 = c[K - 1], b2 = 0.f, e1 = 0.f, e2 = 0.f;
+#pragma unroll
+    for (int k = K - 2; k >= 1; --k) {
+      const float b = fmaf(xi2, b1, c[k] - b2);
+      const float e = fmaf(xi2, e1, fmaf(2.0f, b1, -e2));
+      b2 = b1;
+      b1 = b;
+      e2 = e1;
+      e1 = e;
+    }
+    S = fmaf(xi, b1, c[0] - b2);
+    dS = fmaf(xi, e1, b1 - e2);
+  }
+  return fmaf(hfcp, S, 4.0f * x * inv_rc * hfc * dS);
+}
+
 // ---------------------------------------------------------------- angular
 // C_lm * 4 pi for l = 1..4 in Appendix-B order.  C_lm = 1 / (integral over the
 // unit sphere of b_lm^2), which makes sum_m C_lm B_lm(u) B_lm(v) equal to
@@ -432,12 +476,16 @@ __device__ __forceinline__ int rs_slots_atoms_code() {
   return (l & 1) | ((l >> 1) & 1) << 1 | ((l >> 3) & 1) << 2 | ((l >> 4) & 1) << 3 | ((l >> 5) & 1) << 4;
 }
 
-// Image shift of a neighbor code: code = 9(sx+1) + 3(sy+1) + (sz+1).
+// Image shift of a neighbor code: code = 9(sx+1) + 3(sy+1) + (sz+1).  The
+// quotients of code < 27 by 9 and of the remainder by 3 from 24-bit products
+// (full rate; a division by a constant takes a quarter-rate high product).
 __device__ __forceinline__ void decode_shift(uint32_t code, float& sx, float& sy, float& sz) {
-  const int c = (int)code;
-  sx = (float)(c / 9 - 1);
-  sy = (float)((c / 3) % 3 - 1);
-  sz = (float)(c % 3 - 1);
+  const unsigned qa = __umul24(code, 57u) >> 9;
+  const unsigned r = code - __umul24(qa, 9u);
+  const unsigned qb = __umul24(r, 11u) >> 5;
+  sx = (float)qa - 1.0f;
+  sy = (float)qb - 1.0f;
+  sz = (float)(r - __umul24(qb, 3u)) - 1.0f;
 }
 
 }  // namespace nep

@@ -4,7 +4,7 @@
 // degrees run in kernels of their own around the forward and adjoint passes:
 //
 //   k_high_desc    (before the forward)  S_nlm and q_nl into the G rows
-//   k_high_force   (after the forward)   pair forces and virial of these q_nl
+//   k_high_force   (after the forward)   pair forces of these q_nl
 //   k_high_tangent (before the adjoint)  Sdot_nlm and Gdot of these q_nl
 //   k_high_coef    (after the adjoint)   their share of dL/dc^A
 //
@@ -668,37 +668,27 @@ __device__ __forceinline__ void high_table_stage(const HighArgs& a, const HighGr
   }
 }
 
-// Pair forces and virial of the q_nl of l = 5..L3.  With A_nlm = dE/dS~_nlm
+// Pair forces of the q_nl of l = 5..L3.  With A_nlm = dE/dS~_nlm
 // = 2 E'_nl S~_nlm of the pair's atom, the pair's share of the force is
 //   f_ij = sum_nlm A_nlm (g'_n Y u + g_n (I - u u^T) grad p_lm / r)
 // (grad p: gradient of the harmonic's polynomial).  Per order M the sums
 // over l of sum_n A g'_n Qhat, sum_n A g_n Qhat and sum_n A g_n dQhat are
 // formed first, so the powers (x + iy)^M and their derivatives enter once per
-// order.  The per-atom virial sums the pairs of each slot in list order.
+// order.
 template <class C, bool kTri>
 __global__ __launch_bounds__(256) void k_high_force(HighArgs a) {
   constexpr int T = C::T, NA = C::NA, KA = C::KA, L3 = C::L3, YH = C::YH;
   constexpr int AS = high_table_stride(YH * NA);
-  static_assert(high_factor_words<C, false>() <= 6 * kWave, "the factors are staged in the virial words");
   __shared__ __align__(16) float tabs[4][kAPW * AS];
-  __shared__ __align__(16) float vrs[4][6 * kWave];
+  __shared__ __align__(16) float facs[4][high_factor_words<C, false>()];
   const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
   const int wave = blockIdx.x * 4 + wv;
   float* tab = tabs[wv];
-  float* vr = vrs[wv];
   const HighGroup gr = high_group(a, wave * kAPW);
-  high_table_stage<C, false>(a, gr, tab, AS, vr);
+  high_table_stage<C, false>(a, gr, tab, AS, facs[wv]);
   lds_lane_exchange();
-  float vir[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};   // lanes u < 8: atom slot u
-  int lo = 0, hi = 0;                              // slot lane's pairs in the stream
-#pragma unroll
-  for (int v = 0; v < kAPW; ++v) {
-    lo = lane == v ? gr.cum[v] : lo;
-    hi = lane == v ? gr.cum[v + 1] : hi;
-  }
   for (int c0 = 0; c0 < gr.total; c0 += kWave) {
     const int p = c0 + lane;
-    float fx = 0.f, fy = 0.f, fz = 0.f, dx = 0.f, dy = 0.f, dz = 0.f;
     if (p < gr.total) {
       const HighPair g = high_pair<kTri>(a, gr, p);
       float f[KA], fp[KA];
@@ -748,44 +738,11 @@ __global__ __launch_bounds__(256) void k_high_force(HighArgs a) {
             }
           });
       const float rad = g.ux * Gx + g.uy * Gy + g.uz * Gz;
-      fx = vv * g.ux + (Gx - rad * g.ux) * g.ir;
-      fy = vv * g.uy + (Gy - rad * g.uy) * g.ir;
-      fz = vv * g.uz + (Gz - rad * g.uz) * g.ir;
       float* fo = a.fA + 3 * ((size_t)g.i * a.nb.capA + g.k);
-      fo[0] += fx;
-      fo[1] += fy;
-      fo[2] += fz;
-      dx = g.dx;
-      dy = g.dy;
-      dz = g.dz;
+      fo[0] += vv * g.ux + (Gx - rad * g.ux) * g.ir;
+      fo[1] += vv * g.uy + (Gy - rad * g.uy) * g.ir;
+      fo[2] += vv * g.uz + (Gz - rad * g.uz) * g.ir;
     }
-    vr[0 * kWave + lane] = fx;
-    vr[1 * kWave + lane] = fy;
-    vr[2 * kWave + lane] = fz;
-    vr[3 * kWave + lane] = dx;
-    vr[4 * kWave + lane] = dy;
-    vr[5 * kWave + lane] = dz;
-    lds_lane_exchange();
-    if (lane < kAPW) {
-      const int j1 = min(hi - c0, kWave);
-      for (int jj = max(lo - c0, 0); jj < j1; ++jj) {
-        const float px = vr[jj], py = vr[kWave + jj], pz = vr[2 * kWave + jj];
-        const float qx = vr[3 * kWave + jj], qy = vr[4 * kWave + jj], qz = vr[5 * kWave + jj];
-        vir[0] -= px * qx;
-        vir[1] -= py * qy;
-        vir[2] -= pz * qz;
-        vir[3] -= px * qy;
-        vir[4] -= py * qz;
-        vir[5] -= pz * qx;
-      }
-    }
-    lds_lane_exchange();
-  }
-  if (lane < kAPW) {
-    const int i = a.order[gr.pa0 + lane];
-    if (i >= 0)
-#pragma unroll
-      for (int c = 0; c < 6; ++c) a.wv[(size_t)c * a.N + i] += vir[c];
   }
 }
 

@@ -2,7 +2,7 @@
 //
 // Data flow of one loss-and-gradient evaluation:
 //   neighbors -> species order -> forward (descriptors, network, partial forces)
-//   -> force gather -> per-structure loss and cotangents -> adjoint (tangent
+//   -> forces and virials -> per-structure loss and cotangents -> adjoint (tangent
 //   pass, network adjoint, parameter partials) -> W0 reduction -> final gradient
 //   reduction -> Adam.
 // Per-atom kernels run in "species order": atoms grouped by species, each
@@ -30,6 +30,7 @@ struct NbrArgs {
   uint32_t* idxA;
   int* cntA;
   int* astruct;
+  float4* p4;    // [N] packed atoms (atom_word)
   int* flags;
   // cell-list search of structures of at least cell_min atoms (cells = 0:
   // all-pairs only)
@@ -47,10 +48,17 @@ struct PairLists {
   const int* cntR;
   const uint32_t* idxA;
   const int* cntA;
-  const int* revR;
-  const int* revA;
   int capR, capA;
 };
+
+// A packed atom (x, y, z, word): one 16-byte gather per neighbor.  The word
+// holds the species in its low bits and whether the atom's radial or angular
+// list overflowed its capacity.
+constexpr uint32_t kAtomOverR = 1u << 8, kAtomOverA = 1u << 9;
+__device__ __forceinline__ float atom_word(int type, int T, bool over_r, bool over_a) {
+  const uint32_t t = (type >= 0 && type < T) ? (uint32_t)type : 0u;   // others are flagged
+  return __uint_as_float(t | (over_r ? kAtomOverR : 0u) | (over_a ? kAtomOverA : 0u));
+}
 
 struct FwdArgs {
   int N, Npad, H;
@@ -61,6 +69,8 @@ struct FwdArgs {
   const float* tilt;  // null: every cell orthorhombic
   const float* pos;
   const int* type;
+  const float4* p4;  // packed atoms of this call's neighbor build; null: gather pos and type
+  float4* p4out;     // then written here for the kernels that follow
   PairLists nb;
   const float* cR;
   const float* cA;
@@ -73,10 +83,26 @@ struct FwdArgs {
   float* X;        // [H][Npad] (may be null)
   float* eatom;    // [N] atom order (may be null)
   float* eatom2;   // second copy for the caller (may be null)
-  float* fR;       // [3][capR][N]
-  float* fA;       // [3][capA][N]
-  float* wv;       // [6][N]
+  float* hrow;     // [N][T][KP] radial force coefficients (atom order)
+  float* fA;       // [N][capA][3] angular pair forces
   int do_mlp, do_force;
+};
+
+// Forces and per-atom virials from the forward's radial force coefficients
+// and angular pair forces.
+struct ForceArgs {
+  int N;
+  float inv_rcR;
+  PairLists nb;
+  const float4* p4;
+  const int* astruct;
+  const float* box;
+  const float* tilt;  // null: every cell orthorhombic
+  const float* hrow;  // [N][T][KP]
+  const float* fA;    // [N][capA][3]
+  float* F;           // [3][N]
+  float* Fuser;       // second copy for the caller (may be null)
+  float* wv;          // [6][N]
 };
 
 struct AdjArgs {
@@ -128,7 +154,6 @@ struct HighArgs {
   float* Gd;          // [D][Npad] descriptor tangents
   const float* Gb;    // [D][Npad] Gbar (rows of l > 4)
   float* fA;          // [N][capA][3] angular pair forces (added to)
-  float* wv;          // [6][N] per-atom virials (added to)
   const float* fbar;  // [3][N]
   const float* wbar;  // [S][6]
   float* part;        // [n_waves][PW] (c^A slots added to)

@@ -645,10 +645,16 @@ __global__ __launch_bounds__(kNbrThreads) void k_neighbors(NbrArgs a) {
     sweep(wr ? jb : 0, wr ? je : 0,
           [&](const PosTile& t, int b2, int e2) { scan_range<kTri>(c, t, b2, e2, write); });
   }
-  if (mine && s == 0) {
-    a.cntR[i] = totR;
-    a.cntA[i] = totA;
-    if (totR > a.capR || totA > a.capA) fl |= FL_OVERFLOW;
+  if (live && s == 0) {
+    if (mine) {
+      a.cntR[i] = totR;
+      a.cntA[i] = totA;
+      if (totR > a.capR || totA > a.capA) fl |= FL_OVERFLOW;
+    } else {   // counted by the cell search
+      totR = a.cntR[i];
+      totA = a.cntA[i];
+    }
+    a.p4[i] = make_float4(c.xf, c.yf, c.zf, atom_word(a.type[i], a.T, totR > a.capR, totA > a.capA));
   }
   if (live && s == 0 && fl) atomicOr(a.flags, fl);
 }
@@ -978,67 +984,6 @@ __device__ __forceinline__ int row_find(const uint32_t* __restrict__ row, int m,
   return pos;
 }
 
-// Reverse index: for entry k = (j, s) of atom i, the position of (i, -s) in
-// j's list (-1 if the capacity cut it off).  The two entries of a pair are
-// found by one search: the one with the larger key, (j, s) > (i, self) (j > i,
-// or j = i and s past the zero shift), searches j's list and writes both
-// slots.  Those entries are the tail of i's sorted list, so LPA lanes per
-// atom take only them; an entry below (i, self) searches for itself only
-// when its partner may be missing, i.e. j's list overflowed.
-template <int LPA>
-__device__ __forceinline__ void reverse_block(int blk, int N, const uint32_t* __restrict__ idx,
-                                              const int* __restrict__ cnt, int cap, int* __restrict__ rev) {
-  const int s = threadIdx.x % LPA;
-  const int i = blk * (256 / LPA) + threadIdx.x / LPA;
-  if (i >= N) return;
-  const int n = min(cnt[i], cap);
-  const uint32_t self = ((uint32_t)i << 5) | 13u;
-  const uint32_t* li = idx + (size_t)i * cap;
-  int low = 0;
-  for (int k = s; k < n; k += LPA) {
-    const uint32_t e = li[k];
-    if (e < self) {
-      ++low;
-      const int j = (int)(e >> 5);
-      if (cnt[j] > cap)
-        rev[(size_t)i * cap + k] = row_find(idx + (size_t)j * cap, cap, cap, ((uint32_t)i << 5) | (26u - (e & 31u)));
-    }
-  }
-#pragma unroll
-  for (int d = 1; d < LPA; d <<= 1) low += __shfl_xor(low, d, LPA);
-  for (int k = low + s; k < n; k += LPA) {
-    const uint32_t e = li[k];
-    const int j = (int)(e >> 5);
-    const int pos = row_find(idx + (size_t)j * cap, min(cnt[j], cap), cap, ((uint32_t)i << 5) | (26u - (e & 31u)));
-    rev[(size_t)i * cap + k] = pos;
-    if (pos >= 0) rev[(size_t)j * cap + pos] = k;
-  }
-}
-
-constexpr int kRevLPAR = 16, kRevLPAA = 4;   // lanes per atom: radial, angular lists
-
-// Both lists in one launch (they are independent, and neither fills the GPU
-// alone): the first nbR blocks, in XCD-aware order, take the radial list.
-struct RevArgs {
-  int N, nbR;
-  const uint32_t* idxR;
-  const int* cntR;
-  int capR;
-  int* revR;
-  const uint32_t* idxA;
-  const int* cntA;
-  int capA;
-  int* revA;
-};
-
-__global__ __launch_bounds__(256) void k_reverse(RevArgs a) {
-  const int b = xcd_block();
-  if (b < a.nbR)
-    reverse_block<kRevLPAR>(b, a.N, a.idxR, a.cntR, a.capR, a.revR);
-  else
-    reverse_block<kRevLPAA>(b - a.nbR, a.N, a.idxA, a.cntA, a.capA, a.revA);
-}
-
 // ============================================================ species order
 // Atoms are laid out by (species, angular neighbor count descending), with
 // ties in atom order: every wavefront then holds one species and atoms of
@@ -1224,7 +1169,7 @@ __device__ __forceinline__ void order_scatter_body(const OrderArgs& a, int ob, i
 }
 
 // the separate kernels: a block of kOrdBlk threads per order block, 512
-// threads for the scan (the counts run in k_reverse_count)
+// threads for the scan
 __global__ __launch_bounds__(512) void k_order_scan(OrderArgs a) {
   __shared__ int sh[kOrdScanLds];
   order_scan_body<512>(a, sh);
@@ -1235,21 +1180,9 @@ __global__ __launch_bounds__(kOrdBlk) void k_order_scatter(OrderArgs a) {
   order_scatter_body<kOrdBlk>(a, blockIdx.x, wcnt);
 }
 
-// The reverse index and the species-order counts in one launch (both read
-// only the neighbor lists): the first nrev blocks, numbered XCD-aware among
-// themselves, take the reverse index; the rest count one order block each
-// and clear the order slots.
-__global__ __launch_bounds__(256) void k_reverse_count(RevArgs r, OrderArgs o, int nrev) {
+__global__ __launch_bounds__(256) void k_order_count(OrderArgs o) {
   __shared__ int cnt[kOrdCountLds];
-  if ((int)blockIdx.x < nrev) {
-    const int b = xcd_block_of(blockIdx.x, nrev);
-    if (b < r.nbR)
-      reverse_block<kRevLPAR>(b, r.N, r.idxR, r.cntR, r.capR, r.revR);
-    else
-      reverse_block<kRevLPAA>(b - r.nbR, r.N, r.idxA, r.cntA, r.capA, r.revA);
-    return;
-  }
-  const int ob = blockIdx.x - nrev;
+  const int ob = blockIdx.x;
   for (int q = ob * 256 + threadIdx.x; q < o.Npad; q += o.nblk * 256) o.order[q] = -1;
   order_count_body<256>(o, ob, cnt);
 }
@@ -1328,6 +1261,42 @@ __device__ __forceinline__ PairGeom pair_geom(uint32_t e, const float* __restric
   return g;
 }
 
+// d = x_j - x_i + the entry's image shift, from the packed atom pj
+template <bool kTri>
+__device__ __forceinline__ PairGeom packed_geom(uint32_t e, const float4& pj, float xi, float yi, float zi,
+                                                const Cell& cl) {
+  PairGeom g;
+  g.j = (int)(e >> 5);
+  float sx, sy, sz;
+  decode_shift(e & 31u, sx, sy, sz);
+  g.dx = (pj.x - xi) + sx * cl.Lx;
+  g.dy = (pj.y - yi) + sy * cl.Ly;
+  g.dz = (pj.z - zi) + sz * cl.Lz;
+  if constexpr (kTri) {
+    g.dx += sy * cl.xy + sz * cl.xz;
+    g.dy += sz * cl.yz;
+  }
+  const float r2 = g.dx * g.dx + g.dy * g.dy + g.dz * g.dz;
+  g.inv_r = rsq_hw(r2);
+  g.r = r2 * g.inv_r;
+  return g;
+}
+
+// species of a packed atom; T is 1, 2 or 4 in every compiled shape, so the
+// mask also keeps it inside the tables
+template <int T>
+__device__ __forceinline__ int packed_type(const float4& p) {
+  static_assert((T & (T - 1)) == 0, "species index masked to a power of two");
+  return (int)(__float_as_uint(p.w) & (uint32_t)(T - 1));
+}
+
+// Atom j, packed: one 16-byte load, or (packed atoms not built by this call)
+// gathered from the caller's arrays.
+__device__ __forceinline__ float4 load_atom(const float4* p4, const float* pos, const int* type, int N, int j) {
+  if (p4) return p4[j];
+  return make_float4(pos[j], pos[N + j], pos[2 * N + j], __uint_as_float((uint32_t)type[j]));
+}
+
 // ========================================================= atom groups
 // Per-atom kernels run 8 lanes per atom, 8 atoms per wavefront and 32 atoms
 // per block.  Lane s = l & 7 of an atom's group splits the radial pairs
@@ -1344,6 +1313,12 @@ static_assert(kSegAlign % kAPB == 0, "species segments must align to blocks (one
 }  // namespace nep
 #include "nep_highl.h"
 namespace nep {
+
+// Row of radial force coefficients of one (atom, neighbor species): KP words
+template <class C>
+struct HRad {
+  static constexpr int KP = (C::KR + 3) & ~3;
+};
 
 template <int LM>
 struct HSplit {
@@ -1457,9 +1432,9 @@ __device__ __forceinline__ void wait_weights() { __builtin_amdgcn_s_waitcnt(0); 
 // Per atom: radial sums F[J][k] = sum_{j of type J} f_k(r_ij) give
 // q_n = sum_{J,k} c^R_{IJnk} F[J][k] (Eqs. 5-6); angular sums S_nlm (Eq. 8)
 // give q_nl (Eq. 7) and the 4-/5-body invariants; the per-species network
-// gives E_i and E' = dE_i/dG (D1.1-D1.5).  With forces on, every listed
-// pair's partial force f_ij = dE_i/dr_ij is stored (C3.6) with this atom's
-// share -sum_j f_ij (x) r_ij of the virial.
+// gives E_i and E' = dE_i/dG (D1.1-D1.5).  With forces on, the atom's radial
+// force coefficients and every angular pair's partial force f_ij = dE_i/dr_ij
+// (C3.6) are stored for the force pass.
 // Block vb (32 atoms of the species order); lds: lds_forward bytes.
 template <class C, bool kTri>
 __device__ __forceinline__ void forward_body(const FwdArgs& a, int vb, float* lds) {
@@ -1491,18 +1466,21 @@ __device__ __forceinline__ void forward_body(const FwdArgs& a, int vb, float* ld
   const int nR = w.valid ? min(cR_i, a.nb.capR) : 0;
   const int nA = w.valid ? min(cA_i, a.nb.capA) : 0;
   const cptr<float> cRI = as_const(a.cR) + (size_t)I * T * NR * KR;
+  if (!a.p4 && w.valid && s == 0) a.p4out[i] = make_float4(xi, yi, zi, atom_word(I, T, cR_i > a.nb.capR, cA_i > a.nb.capA));
 
-  // ---- radial sums, pairs split over the 8 lanes
+  // ---- radial sums in Chebyshev space, pairs split over the 8 lanes
   float FR[T][KR];
 #pragma unroll
   for (int t = 0; t < T; ++t)
 #pragma unroll
     for (int k = 0; k < KR; ++k) FR[t][k] = 0.f;
   for (int k = s; k < nR; k += kLPA) {
-    const PairGeom q = pair_geom<kTri>(a.nb.idxR[(size_t)i * a.nb.capR + k], a.pos, N, xi, yi, zi, cell);
+    const uint32_t e = a.nb.idxR[(size_t)i * a.nb.capR + k];
+    const float4 pj = load_atom(a.p4, a.pos, a.type, N, (int)(e >> 5));
+    const PairGeom q = packed_geom<kTri>(e, pj, xi, yi, zi, cell);
     float f[KR];
-    radial_basis<KR>(q.r, a.inv_rcR, f);
-    const int J = a.type[q.j];
+    radial_cheb<KR>(q.r, a.inv_rcR, f);
+    const int J = packed_type<T>(pj);
 #pragma unroll
     for (int t = 0; t < T; ++t) {
       const float m = (T == 1 || J == t) ? 1.f : 0.f;
@@ -1513,9 +1491,13 @@ __device__ __forceinline__ void forward_body(const FwdArgs& a, int vb, float* ld
   // the basis sums over the 8 lanes, then q_n = sum c^R F by lane n & 7
   {
 #pragma unroll
-    for (int t = 0; t < T; ++t)
+    for (int t = 0; t < T; ++t) {
 #pragma unroll
       for (int k = 0; k < KR; ++k) FR[t][k] = grp8_sum(FR[t][k]);
+      const float A0 = FR[t][0];
+#pragma unroll
+      for (int k = 0; k < KR; ++k) FR[t][k] += A0;
+    }
 #pragma unroll
     for (int n0 = 0; n0 < NR; n0 += kLPA) {
       const int n = n0 + s;
@@ -1538,10 +1520,12 @@ __device__ __forceinline__ void forward_body(const FwdArgs& a, int vb, float* ld
 #pragma unroll
     for (int e = 0; e < YG; ++e) Sg[n][e] = 0.f;
   for (int k = w.p; k < nA; k += 4) {
-    const PairGeom q = pair_geom<kTri>(a.nb.idxA[(size_t)i * a.nb.capA + k], a.pos, N, xi, yi, zi, cell);
+    const uint32_t e = a.nb.idxA[(size_t)i * a.nb.capA + k];
+    const float4 pj = load_atom(a.p4, a.pos, a.type, N, (int)(e >> 5));
+    const PairGeom q = packed_geom<kTri>(e, pj, xi, yi, zi, cell);
     float f[KA];
     radial_basis<KA>(q.r, a.inv_rcA, f);
-    const int J = a.type[q.j];
+    const int J = packed_type<T>(pj);
     const float* cJ = ctab + (I * T + J) * NA * CT::KAP;
     float gn[NA];
 #pragma unroll
@@ -1674,39 +1658,39 @@ __device__ __forceinline__ void forward_body(const FwdArgs& a, int vb, float* ld
   }
   if (!a.do_force) return;
 
-  // ---- radial partial forces: f_ij = (sum_k h_Jk f'_k(r)) r_hat, h_Jk = sum_n E'_n c^R_{IJnk}
-  float hR[T][KR];
+  // ---- radial force coefficients h_Jk = sum_n E'_n c^R_{IJnk} for the force
+  //      pass, entry (J, k) by lane (J KP + k) mod 8; entry (J, 0) also takes
+  //      sum_k h_Jk (the terms h T_0 of every order)
+  {
+    constexpr int KP = HRad<C>::KP, NE = (T * KP + kLPA - 1) / kLPA;
+    float hv[NE], sum[T];
 #pragma unroll
-  for (int t = 0; t < T; ++t)
+    for (int t = 0; t < T; ++t) sum[t] = 0.f;
 #pragma unroll
-    for (int k = 0; k < KR; ++k) {
+    for (int r = 0; r < NE; ++r) {
+      const int e = r * kLPA + s, t = e / KP, kk = e % KP;
+      const bool on = t < T && kk < KR;
+      const cptr<float> c = cRI + (on ? t * NR * KR + kk : 0);
       float acc = 0.f;
 #pragma unroll
-      for (int n = 0; n < NR; ++n) acc = fmaf(Ep[n], cRI[(t * NR + n) * KR + k], acc);
-      hR[t][k] = acc;
-    }
-  float vxx = 0.f, vyy = 0.f, vzz = 0.f, vxy = 0.f, vyz = 0.f, vzx = 0.f;
-  for (int k = s; k < nR; k += kLPA) {
-    const PairGeom q = pair_geom<kTri>(a.nb.idxR[(size_t)i * a.nb.capR + k], a.pos, N, xi, yi, zi, cell);
-    float f[KR], fp[KR];
-    radial_basis_d<KR>(q.r, a.inv_rcR, f, fp);
-    const int J = a.type[q.j];
-    float sc = 0.f;
+      for (int n = 0; n < NR; ++n) acc = fmaf(Ep[n], c[n * KR], acc);
+      hv[r] = on ? acc : 0.f;
 #pragma unroll
-    for (int kk = 0; kk < KR; ++kk) {
-      float h = hR[0][kk];
-#pragma unroll
-      for (int t = 1; t < T; ++t) h = (J == t) ? hR[t][kk] : h;
-      sc = fmaf(h, fp[kk], sc);
+      for (int u = 0; u < T; ++u) sum[u] += t == u ? hv[r] : 0.f;
     }
-    sc *= q.inv_r;
-    const float fx = sc * q.dx, fy = sc * q.dy, fz = sc * q.dz;
-    float* fo = a.fR + 3 * ((size_t)i * a.nb.capR + k);
-    fo[0] = fx;
-    fo[1] = fy;
-    fo[2] = fz;
-    vxx -= fx * q.dx; vyy -= fy * q.dy; vzz -= fz * q.dz;
-    vxy -= fx * q.dy; vyz -= fy * q.dz; vzx -= fz * q.dx;
+#pragma unroll
+    for (int t = 0; t < T; ++t) sum[t] = grp8_sum(sum[t]);
+    if (w.valid) {
+      float* ho = a.hrow + (size_t)i * T * KP;
+#pragma unroll
+      for (int r = 0; r < NE; ++r) {
+        const int e = r * kLPA + s, t = e / KP;
+        float v = hv[r];
+#pragma unroll
+        for (int u = 0; u < T; ++u) v += (t == u && e == u * KP) ? sum[u] : 0.f;
+        if (e < T * KP) ho[e] = v;
+      }
+    }
   }
 
   // ---- A_nlm = sum_v E'_v dG_v/dS_nlm for this lane's harmonics
@@ -1748,11 +1732,13 @@ __device__ __forceinline__ void forward_body(const FwdArgs& a, int vb, float* ld
   // ---- angular partial forces: f_ij = sum_nlm A_nlm (g'_n r_hat B_lm + g_n grad B_lm);
   //      each harmonic group adds its half, the two halves are summed across lanes
   for (int k = w.p; k < nA; k += 4) {
-    const PairGeom q = pair_geom<kTri>(a.nb.idxA[(size_t)i * a.nb.capA + k], a.pos, N, xi, yi, zi, cell);
+    const uint32_t e = a.nb.idxA[(size_t)i * a.nb.capA + k];
+    const float4 pj = load_atom(a.p4, a.pos, a.type, N, (int)(e >> 5));
+    const PairGeom q = packed_geom<kTri>(e, pj, xi, yi, zi, cell);
     const float ux = q.dx * q.inv_r, uy = q.dy * q.inv_r, uz = q.dz * q.inv_r;
     float f[KA], fp[KA];
     radial_basis_d<KA>(q.r, a.inv_rcA, f, fp);
-    const int J = a.type[q.j];
+    const int J = packed_type<T>(pj);
     const float* cJ = ctab + (I * T + J) * NA * CT::KAP;
     float gn[NA], gp[NA];
 #pragma unroll
@@ -1802,19 +1788,7 @@ __device__ __forceinline__ void forward_body(const FwdArgs& a, int vb, float* ld
       fo[0] = fx;
       fo[1] = fy;
       fo[2] = fz;
-      vxx -= fx * q.dx; vyy -= fy * q.dy; vzz -= fz * q.dz;
-      vxy -= fx * q.dy; vyz -= fy * q.dz; vzx -= fz * q.dx;
     }
-  }
-  vxx = grp8_sum(vxx); vyy = grp8_sum(vyy); vzz = grp8_sum(vzz);
-  vxy = grp8_sum(vxy); vyz = grp8_sum(vyz); vzx = grp8_sum(vzx);
-  if (w.valid && s == 0) {
-    a.wv[i] = vxx;
-    a.wv[(size_t)N + i] = vyy;
-    a.wv[(size_t)2 * N + i] = vzz;
-    a.wv[(size_t)3 * N + i] = vxy;
-    a.wv[(size_t)4 * N + i] = vyz;
-    a.wv[(size_t)5 * N + i] = vzx;
   }
 }
 
@@ -1824,71 +1798,153 @@ __global__ __launch_bounds__(256, W) void k_forward(FwdArgs a) {
   forward_body<C, kTri>(a, blockIdx.x, lds);
 }
 
-// F_i = sum_j f_ij - f_ji (Eq. 3), gathering f_ji through the reverse index;
-// 16 lanes per atom take list slots s, s + 16, ... (more loads in flight for
-// the dependent reverse reads) and are summed by DPP.
-constexpr int kGatherLPA = 16;   // default lanes per atom (8 or 16)
-template <int LPA>
-__device__ __forceinline__ void gather_list(int i, int s, const uint32_t* __restrict__ idx, const int* __restrict__ cnt,
-                                            const int* __restrict__ rev, int cap, const float* __restrict__ f,
-                                            float& fx, float& fy, float& fz) {
-  const int n = min(cnt[i], cap);
-  for (int k = s; k < n; k += LPA) {
-    const size_t o = (size_t)i * cap + k;
-    const int j = (int)(idx[o] >> 5);
-    const int rk = rev[o];
-    const float* a = f + 3 * o;
-    fx += a[0];
-    fy += a[1];
-    fz += a[2];
-    if (rk >= 0) {
-      const float* b = f + 3 * ((size_t)j * cap + rk);
-      fx -= b[0];
-      fy -= b[1];
-      fz -= b[2];
-    }
-  }
+// Forces F_i = sum_j f_ij - f_ji (Eq. 3) and the atom's share of the virial.
+//
+// Radial part: f_ij = (sum_k h_i,Jk f'_k(r)) r_hat, and f_ji has the same
+// basis at the same distance, so f_ij - f_ji = (sum_k (h_i,Jk + h_j,Ik) f'_k) r_hat
+// needs only the neighbor's 12-word coefficient row: no pair force is stored
+// and no reverse index is searched.  (Storing 12 bytes per pair, searching
+// the reverse index and gathering both took 33 + 25 us and 13 us of the
+// forward at 512 structures, 87k atoms; this kernel takes 29 us.)  Angular part: the
+// stored pair forces, the partner's entry found in its short sorted list.
+//
+// A pair whose partner entry was cut off by the capacity counts with f_ij
+// alone; only then does the partner's list have to be searched.  The virial
+// -sum f_ij (x) r_ij over both entries of a pair equals -1/2 (f_ij - f_ji) (x) r_ij
+// summed over both, so the radial part uses the total pair force.
+//
+// LPA lanes per atom take list slots s, s + LPA, ...; the rows of the block's
+// own atoms are staged in LDS.
+constexpr int kForceLPA = 16;   // default lanes per atom (8 or 16)
+template <class C, int LPA>
+constexpr int force_lds_words() {
+  return 256 / LPA * C::T * HRad<C>::KP;
 }
 
-// logical block vb: atoms vb * (256 / LPA) ..
-template <int LPA>
-__device__ __forceinline__ void gather_body(int vb, int N, const PairLists& nb, const float* __restrict__ fR,
-                                            const float* __restrict__ fA, float* __restrict__ F,
-                                            float* __restrict__ Fuser) {
+// Position of key in the angular list of atom j (m entries, row 16-byte
+// aligned when vec), -1 if it was cut off: the count of smaller entries, 8 per
+// step.
+__device__ __forceinline__ int partner_find(const uint32_t* __restrict__ row, int m, int cap, bool vec, uint32_t key) {
+  int below = 0;
+  bool hit = false;
+  for (int b = 0; b < m; b += 8) {
+    uint32_t v[8];
+    if (vec && b + 8 <= cap) {
+      const uint4 x = *reinterpret_cast<const uint4*>(row + b);
+      const uint4 y = *reinterpret_cast<const uint4*>(row + b + 4);
+      v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w;
+      v[4] = y.x; v[5] = y.y; v[6] = y.z; v[7] = y.w;
+    } else {
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = row[min(b + u, cap - 1)];
+    }
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const bool in = b + u < m;
+      below += (in && v[u] < key) ? 1 : 0;
+      hit |= in && v[u] == key;
+    }
+  }
+  return hit ? below : -1;
+}
+
+template <class C, bool kTri, int LPA>
+__device__ __forceinline__ void force_body(const ForceArgs& a, int vb, float* own) {
   static_assert(LPA == 8 || LPA == 16, "8 or 16 lanes per atom");
-  const int s = threadIdx.x % LPA;
-  const int i = vb * (256 / LPA) + threadIdx.x / LPA;
+  constexpr int T = C::T, KR = C::KR, KP = HRad<C>::KP, TK = T * KP, APB = 256 / LPA;
+  const int s = threadIdx.x % LPA, al = threadIdx.x / LPA;
+  const int i0 = vb * APB, i = i0 + al, N = a.N;
+  {
+    const float4* src = reinterpret_cast<const float4*>(a.hrow + (size_t)i0 * TK);
+    const int n4 = min(APB, N - i0) * (TK / 4);
+    for (int q = threadIdx.x; q < n4; q += 256) reinterpret_cast<float4*>(own)[q] = src[q];
+  }
+  __syncthreads();
   float fx = 0.f, fy = 0.f, fz = 0.f;
+  float v[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   if (i < N) {
-    gather_list<LPA>(i, s, nb.idxR, nb.cntR, nb.revR, nb.capR, fR, fx, fy, fz);
-    gather_list<LPA>(i, s, nb.idxA, nb.cntA, nb.revA, nb.capA, fA, fx, fy, fz);
+    const float4 pi = a.p4[i];
+    const int I = packed_type<T>(pi);
+    const Cell cell = load_cell<kTri>(a.box, a.tilt, a.astruct[i]);
+    const int nR = min(a.nb.cntR[i], a.nb.capR), nA = min(a.nb.cntA[i], a.nb.capA);
+    const uint32_t self = (uint32_t)i << 5;
+    const size_t oR = (size_t)i * a.nb.capR, oA = (size_t)i * a.nb.capA;
+    for (int k = s; k < nR; k += LPA) {
+      const uint32_t e = a.nb.idxR[oR + k];
+      const int j = (int)(e >> 5);
+      const float4 pj = a.p4[j];
+      const float4* hj = reinterpret_cast<const float4*>(a.hrow + ((size_t)j * T + I) * KP);
+      const float4* hi = reinterpret_cast<const float4*>(own + (al * T + packed_type<T>(pj)) * KP);
+      float wp = 1.f;   // 0: the partner's list does not hold this pair
+      if (__float_as_uint(pj.w) & kAtomOverR)
+        wp = row_find(a.nb.idxR + (size_t)j * a.nb.capR, a.nb.capR, a.nb.capR, self | (26u - (e & 31u))) >= 0 ? 1.f : 0.f;
+      float c[KR];
+#pragma unroll
+      for (int q = 0; q < KP / 4; ++q) {
+        const float4 x = hj[q], y = hi[q];
+        if (4 * q < KR) c[4 * q] = fmaf(wp, x.x, y.x);
+        if (4 * q + 1 < KR) c[4 * q + 1] = fmaf(wp, x.y, y.y);
+        if (4 * q + 2 < KR) c[4 * q + 2] = fmaf(wp, x.z, y.z);
+        if (4 * q + 3 < KR) c[4 * q + 3] = fmaf(wp, x.w, y.w);
+      }
+      const PairGeom q = packed_geom<kTri>(e, pj, pi.x, pi.y, pi.z, cell);
+      const float sc = cheb_deriv<KR>(c, q.r, a.inv_rcR) * q.inv_r;
+      const float gx = sc * q.dx, gy = sc * q.dy, gz = sc * q.dz;
+      fx += gx;
+      fy += gy;
+      fz += gz;
+      const float wv = fmaf(-0.5f, wp, 1.f);   // half a pair, or all of it without its partner
+      const float hx = wv * gx, hy = wv * gy, hz = wv * gz;
+      v[0] -= hx * q.dx; v[1] -= hy * q.dy; v[2] -= hz * q.dz;
+      v[3] -= hx * q.dy; v[4] -= hy * q.dz; v[5] -= hz * q.dx;
+    }
+    const bool vec = (a.nb.capA & 3) == 0 && (reinterpret_cast<uintptr_t>(a.nb.idxA) & 15) == 0;
+    for (int k = s; k < nA; k += LPA) {
+      const uint32_t e = a.nb.idxA[oA + k];
+      const int j = (int)(e >> 5);
+      const float* f = a.fA + 3 * (oA + k);
+      const float ax = f[0], ay = f[1], az = f[2];
+      const float4 pj = a.p4[j];
+      const int m = min(a.nb.cntA[j], a.nb.capA);
+      const size_t oj = (size_t)j * a.nb.capA;
+      const int pos = partner_find(a.nb.idxA + oj, m, a.nb.capA, vec, self | (26u - (e & 31u)));
+      fx += ax;
+      fy += ay;
+      fz += az;
+      if (pos >= 0) {
+        const float* b = a.fA + 3 * (oj + pos);
+        fx -= b[0];
+        fy -= b[1];
+        fz -= b[2];
+      }
+      const PairGeom q = packed_geom<kTri>(e, pj, pi.x, pi.y, pi.z, cell);
+      v[0] -= ax * q.dx; v[1] -= ay * q.dy; v[2] -= az * q.dz;
+      v[3] -= ax * q.dy; v[4] -= ay * q.dz; v[5] -= az * q.dx;
+    }
   }
   // the lanes of an atom: 8-lane groups, then (16 lanes) the other half of the row
-  fx = grp8_sum(fx);
-  fy = grp8_sum(fy);
-  fz = grp8_sum(fz);
-  if (LPA == 16) {
-    fx += dpp<kDppRowRor8>(fx);
-    fy += dpp<kDppRowRor8>(fy);
-    fz += dpp<kDppRowRor8>(fz);
+  float r[9] = {fx, fy, fz, v[0], v[1], v[2], v[3], v[4], v[5]};
+#pragma unroll
+  for (int q = 0; q < 9; ++q) {
+    r[q] = grp8_sum(r[q]);
+    if (LPA == 16) r[q] += dpp<kDppRowRor8>(r[q]);
   }
   if (i < N && s == 0) {
-    F[i] = fx;
-    F[N + i] = fy;
-    F[2 * N + i] = fz;
-    if (Fuser) {
-      Fuser[i] = fx;
-      Fuser[N + i] = fy;
-      Fuser[2 * N + i] = fz;
-    }
+    const size_t n = (size_t)N;
+#pragma unroll
+    for (int q = 0; q < 3; ++q) a.F[q * n + i] = r[q];
+    if (a.Fuser)
+#pragma unroll
+      for (int q = 0; q < 3; ++q) a.Fuser[q * n + i] = r[q];
+#pragma unroll
+    for (int q = 0; q < 6; ++q) a.wv[q * n + i] = r[3 + q];
   }
 }
 
-template <int LPA>
-__global__ __launch_bounds__(256) void k_force_gather(int N, PairLists nb, const float* __restrict__ fR,
-                                                      const float* __restrict__ fA, float* __restrict__ F,
-                                                      float* __restrict__ Fuser) {
-  gather_body<LPA>(xcd_block(), N, nb, fR, fA, F, Fuser);
+template <class C, bool kTri, int LPA>
+__global__ __launch_bounds__(256) void k_force(ForceArgs a) {
+  __shared__ __align__(16) float own[force_lds_words<C, LPA>()];
+  force_body<C, kTri, LPA>(a, xcd_block(), own);
 }
 
 // ==================================================================== loss
@@ -2996,8 +3052,7 @@ __device__ __forceinline__ void for_items(int n, F&& f) {
 struct StepArgs {
   OrderArgs ord;
   FwdArgs fwd;
-  PairLists nb;
-  float* F;
+  ForceArgs frc;
   StructArgs st;
   AdjArgs adj;
   OuterArgs ow, oc;
@@ -3045,10 +3100,9 @@ __global__ __launch_bounds__(256, 2) void k_step(const StepArgs* pa) {
     __syncthreads();
   });
   NEP_BARRIER();
-  for_items((a.fwd.N + 256 / kGatherLPA - 1) / (256 / kGatherLPA), [&](int vb) {
-    const PairLists nb = item_args(a.nb);
-    const FwdArgs f = item_args(a.fwd);
-    gather_body<kGatherLPA>(vb, f.N, nb, f.fR, f.fA, a.F, nullptr);
+  for_items((a.fwd.N + 256 / kForceLPA - 1) / (256 / kForceLPA), [&](int vb) {
+    force_body<C, false, kForceLPA>(item_args(a.frc), vb, lds);
+    __syncthreads();
   });
   NEP_BARRIER();
   // per-structure sums, loss partials and cotangents
@@ -3276,7 +3330,9 @@ enum HighKernel { kHighDesc, kHighForce, kHighTangent, kHighCoef };
 struct Ops {
   int T, NR, NA, KR, KA, L3, L4, L5, D, Y, PS, YH, YR;
   void (*forward)(const FwdArgs&, dim3, hipStream_t, int);
+  void (*force)(const ForceArgs&, hipStream_t, int);
   void (*adjoint)(const AdjArgs&, dim3, hipStream_t, int);
+  int KP;   // words of a radial force coefficient row
   size_t (*lds_fwd)(int);
   size_t (*lds_adj)(int);
   void (*high)(HighKernel, const HighArgs&, dim3, hipStream_t);   // null without degrees l > 4
@@ -3328,6 +3384,22 @@ static void launch_forward(const FwdArgs& a, dim3 grid, hipStream_t st, int wave
     launch_forward_w<C, 2>(a, grid, st);
   else
     launch_forward_w<C, 3>(a, grid, st);
+}
+template <class C, bool kTri>
+static void launch_force_t(const ForceArgs& a, hipStream_t st, int lanes) {
+  const int apb = 256 / lanes;
+  const dim3 grid((a.N + apb - 1) / apb);
+  if (lanes == 8)
+    hipLaunchKernelGGL(HIP_KERNEL_NAME(k_force<C, kTri, 8>), grid, dim3(256), 0, st, a);
+  else
+    hipLaunchKernelGGL(HIP_KERNEL_NAME(k_force<C, kTri, 16>), grid, dim3(256), 0, st, a);
+}
+template <class C>
+static void launch_force(const ForceArgs& a, hipStream_t st, int lanes) {
+  if (a.tilt)
+    launch_force_t<C, true>(a, st, lanes);
+  else
+    launch_force_t<C, false>(a, st, lanes);
 }
 template <class C, int W>
 static void launch_adjoint_w(const AdjArgs& a, dim3 grid, hipStream_t st) {
@@ -3393,7 +3465,7 @@ static Ops make_ops() {
     occ = &step_occupancy<C>;
   }
   return Ops{C::T, C::NR, C::NA, C::KR, C::KA, C::L3, C::L4, C::L5, C::D, C::Y, C::PS, C::YH,
-             HRow<C::LMAX>::YR, &launch_forward<C>, &launch_adjoint<C>, &lds_forward<C>, &lds_adjoint<C>, high, step, occ,
+             HRow<C::LMAX>::YR, &launch_forward<C>, &launch_force<C>, &launch_adjoint<C>, HRad<C>::KP, &lds_forward<C>, &lds_adjoint<C>, high, step, occ,
              C::FIXED_WAVES != 0};
 }
 
@@ -3484,7 +3556,7 @@ size_t al(size_t x) { return (x + 255) & ~(size_t)255; }
 
 struct Layout {
   int N, S, T, D, Y, H, NR, TKR, Npad, nwaves, nblk, PW, NA, capR, capA;
-  size_t order, seg, blk, astruct, revR, revA, G, Sst, Ep, X, eatom, fR, fA, wv, F, fbar, Es, Ws, eps, wbar, lpart,
+  size_t order, seg, blk, astruct, p4, G, Sst, Ep, X, eatom, hrow, fA, wv, F, fbar, Es, Ws, eps, wbar, lpart,
       Gd, FRst, FPst, Gbr, beta, w1s, part, pp, w0part, crpart, Sh, Sdh, cgrid, cell, cpart, acell, aslot, cpos, spart,
       cur_step, bar, sargs, prm, grd, Gtmp, total;
 };
@@ -3521,14 +3593,13 @@ Layout make_layout(const nep_model* m, const Ops* o, int S, int N, bool pad = fa
   L.seg = take(4 * 2 * 8);
   L.blk = take(4 * (size_t)L.nblk * L.T * kOrdBuckets);
   L.astruct = take(4 * Nn);
-  L.revR = take(4 * (size_t)L.capR * Nn);
-  L.revA = take(4 * (size_t)L.capA * Nn);
+  L.p4 = take(16 * Nn);
   L.G = take(4 * (size_t)L.D * Np);
   L.Sst = take(4 * (size_t)L.NA * o->YR * Np);
   L.Ep = take(4 * (size_t)L.D * Np);
   L.X = take(4 * (size_t)L.H * Np);
   L.eatom = take(4 * Nn);
-  L.fR = take(4 * 3 * (size_t)L.capR * Nn);
+  L.hrow = take(4 * (size_t)L.T * o->KP * Nn);
   L.fA = take(4 * 3 * (size_t)L.capA * Nn);
   L.wv = take(4 * 6 * Nn);
   L.F = take(4 * 3 * Nn);
@@ -3623,12 +3694,11 @@ int hip_ok() { return hipGetLastError() == hipSuccess ? NEP_OK : NEP_ERR_HIP; }
 
 // Launch choices of one evaluation (nep_tuning with the defaults filled in).
 struct Tune {
-  int persistent, outer_w, outer_c, reduce_chunks, cell_min, gather_lanes, forward_waves, adjoint_waves,
-      reverse_branch;
+  int persistent, outer_w, outer_c, reduce_chunks, cell_min, gather_lanes, forward_waves, adjoint_waves;
 };
 
 Tune default_tune(const Ops* o) {
-  return Tune{0, kOSBlocksW, kOSBlocksC, kPRChunks, kCellMinAtoms, kGatherLPA, 3, o->YH > 0 ? 2 : 3, 1};
+  return Tune{0, kOSBlocksW, kOSBlocksC, kPRChunks, kCellMinAtoms, kForceLPA, 3, o->YH > 0 ? 2 : 3};
 }
 
 struct Ctx {
@@ -3646,11 +3716,8 @@ struct Ctx {
   // the captured training step: Adam after the gradient, fused into its
   // final reduction
   const struct AdamFuse* adam = nullptr;
-  // the captured step's side branch: the reverse index runs there, beside the
-  // species order and the forward pass, and rejoins before the force gather
-  hipStream_t side = nullptr;
-  hipEvent_t fork = nullptr, join = nullptr;
-  mutable bool rev_pending = false;
+  // the packed atoms were written by this call's own neighbor build
+  mutable bool packed = false;
 };
 
 struct AdamFuse {
@@ -3671,8 +3738,6 @@ PairLists pair_lists(const Ctx& c, const nep_neighbors* nb) {
   p.cntR = nb->cnt_rad;
   p.idxA = nb->idx_ang;
   p.cntA = nb->cnt_ang;
-  p.revR = at<int>(c.ws, c.L.revR);
-  p.revA = at<int>(c.ws, c.L.revA);
   p.capR = c.m->cap_rad;
   p.capA = c.m->cap_ang;
   return p;
@@ -3686,6 +3751,7 @@ OrderArgs order_args(const Ctx& c, const nep_neighbors* nb) {
 void run_neighbors(const Ctx& c, nep_neighbors* nb, int32_t* flags, Prof* pr, bool with_order = true) {
   const int N = c.L.N;
   if (N == 0) return;
+  c.packed = true;
   NbrArgs a;
   a.N = N;
   a.S = c.b->n_struct;
@@ -3704,6 +3770,7 @@ void run_neighbors(const Ctx& c, nep_neighbors* nb, int32_t* flags, Prof* pr, bo
   a.idxA = nb->idx_ang;
   a.cntA = nb->cnt_ang;
   a.astruct = at<int>(c.ws, c.L.astruct);
+  a.p4 = at<float4>(c.ws, c.L.p4);
   a.flags = flags;
   // the cell-list kernels run unless the caller's bound rules out every structure
   const int S = c.b->n_struct;
@@ -3743,26 +3810,9 @@ void run_neighbors(const Ctx& c, nep_neighbors* nb, int32_t* flags, Prof* pr, bo
                      : (a.cells ? k_neighbors<false, true> : k_neighbors<false, false>);
     NEP_LAUNCH(pr, "neighbors", hipLaunchKernelGGL(k, dim3(grid1(N, kNbrAPB)), dim3(kNbrThreads), 0, c.st, a));
   }
-  const RevArgs r{N, grid1(N, 256 / kRevLPAR), nb->idx_rad, nb->cnt_rad, c.m->cap_rad, at<int>(c.ws, c.L.revR),
-                  nb->idx_ang, nb->cnt_ang, c.m->cap_ang, at<int>(c.ws, c.L.revA)};
-  const int nrev = r.nbR + grid1(N, 256 / kRevLPAA);
-  if (!with_order) {   // the persistent step computes the species order itself
-    NEP_LAUNCH(pr, "reverse", hipLaunchKernelGGL(k_reverse, dim3(nrev), dim3(256), 0, c.st, r));
-    return;
-  }
+  if (!with_order) return;   // the persistent step computes the species order itself
   const OrderArgs oa = order_args(c, nb);
-  if (c.side) {
-    (void)hipEventRecord(c.fork, c.st);
-    (void)hipStreamWaitEvent(c.side, c.fork, 0);
-    NEP_LAUNCH(pr, "reverse", hipLaunchKernelGGL(k_reverse, dim3(nrev), dim3(256), 0, c.side, r));
-    (void)hipEventRecord(c.join, c.side);
-    c.rev_pending = true;
-    NEP_LAUNCH(pr, "order_count",
-               hipLaunchKernelGGL(k_reverse_count, dim3(c.L.nblk), dim3(256), 0, c.st, r, oa, 0));
-  } else {
-    NEP_LAUNCH(pr, "reverse_order_count",
-               hipLaunchKernelGGL(k_reverse_count, dim3(nrev + c.L.nblk), dim3(256), 0, c.st, r, oa, nrev));
-  }
+  NEP_LAUNCH(pr, "order_count", hipLaunchKernelGGL(k_order_count, dim3(c.L.nblk), dim3(256), 0, c.st, oa));
   NEP_LAUNCH(pr, "order_scan", hipLaunchKernelGGL(k_order_scan, dim3(1), dim3(512), 0, c.st, oa));
   NEP_LAUNCH(pr, "order_scatter",
              hipLaunchKernelGGL(k_order_scatter, dim3(c.L.nblk), dim3(kOrdBlk), 0, c.st, oa));
@@ -3782,6 +3832,8 @@ FwdArgs fwd_args(const Ctx& c, const nep_neighbors* nb, const float* params) {
   a.tilt = c.b->tilt;
   a.pos = c.b->pos;
   a.type = c.b->type;
+  a.p4 = c.packed ? at<float4>(c.ws, c.L.p4) : nullptr;
+  a.p4out = at<float4>(c.ws, c.L.p4);
   a.nb = pair_lists(c, nb);
   const int T = m->n_types;
   a.cR = params;
@@ -3795,15 +3847,31 @@ FwdArgs fwd_args(const Ctx& c, const nep_neighbors* nb, const float* params) {
   a.X = at<float>(c.ws, c.L.X);
   a.eatom = at<float>(c.ws, c.L.eatom);
   a.eatom2 = nullptr;
-  a.fR = at<float>(c.ws, c.L.fR);
+  a.hrow = at<float>(c.ws, c.L.hrow);
   a.fA = at<float>(c.ws, c.L.fA);
-  a.wv = at<float>(c.ws, c.L.wv);
   a.do_mlp = 1;
   a.do_force = 1;
   return a;
 }
 
-// forward + force gather + per-structure sums (+ loss when labels given)
+ForceArgs force_args(const Ctx& c, const FwdArgs& f, float* user) {
+  ForceArgs a;
+  a.N = f.N;
+  a.inv_rcR = f.inv_rcR;
+  a.nb = f.nb;
+  a.p4 = at<float4>(c.ws, c.L.p4);
+  a.astruct = f.astruct;
+  a.box = f.box;
+  a.tilt = f.tilt;
+  a.hrow = f.hrow;
+  a.fA = f.fA;
+  a.F = at<float>(c.ws, c.L.F);
+  a.Fuser = user;
+  a.wv = at<float>(c.ws, c.L.wv);
+  return a;
+}
+
+// forward + forces + per-structure sums (+ loss when labels given)
 // arguments of the kernels of degrees l > 4 (fbar/wbar only for the adjoint's)
 HighArgs high_args(const Ctx& c, const nep_neighbors* nb, const float* params, const float* fbar = nullptr,
                    const float* wbar = nullptr) {
@@ -3828,7 +3896,6 @@ HighArgs high_args(const Ctx& c, const nep_neighbors* nb, const float* params, c
   h.Gd = at<float>(c.ws, c.L.Gd);
   h.Gb = at<float>(c.ws, c.L.Gbr);
   h.fA = at<float>(c.ws, c.L.fA);
-  h.wv = at<float>(c.ws, c.L.wv);
   h.fbar = fbar;
   h.wbar = wbar;
   h.part = at<float>(c.ws, c.L.part);
@@ -3885,16 +3952,7 @@ void run_forward(const Ctx& c, const nep_neighbors* nb, const float* params, flo
     FwdArgs a = fwd_args(c, nb, params);
     a.eatom2 = e_atom;
     launch_forward_pass(c, nb, params, a, pr);
-    if (c.rev_pending) {
-      (void)hipStreamWaitEvent(c.st, c.join, 0);
-      c.rev_pending = false;
-    }
-    if (c.tune.gather_lanes == 8)
-      NEP_LAUNCH(pr, "force_gather", hipLaunchKernelGGL(k_force_gather<8>, dim3(grid1(N, 256 / 8)), dim3(256), 0, c.st,
-                                                        N, a.nb, a.fR, a.fA, at<float>(c.ws, c.L.F), force));
-    else
-      NEP_LAUNCH(pr, "force_gather", hipLaunchKernelGGL(k_force_gather<16>, dim3(grid1(N, 256 / 16)), dim3(256), 0,
-                                                        c.st, N, a.nb, a.fR, a.fA, at<float>(c.ws, c.L.F), force));
+    NEP_LAUNCH(pr, "force", c.o->force(force_args(c, a, force), c.st, c.tune.gather_lanes));
   }
   if (S > 0) {
     const StructArgs s = struct_args(c, e_struct, virial, lab, lam);
@@ -4175,8 +4233,7 @@ StepArgs step_args(const Ctx& c, nep_neighbors* nb, const float* params, const n
   StepArgs a;
   a.ord = order_args(c, nb);
   a.fwd = fwd_args(c, nb, params);
-  a.nb = a.fwd.nb;
-  a.F = at<float>(c.ws, c.L.F);
+  a.frc = force_args(c, a.fwd, nullptr);
   a.st = struct_args(c, nullptr, nullptr, labels, lam);
   a.adj = adj_args(c, nb, params, at<float>(c.ws, c.L.eps), at<float>(c.ws, c.L.fbar), at<float>(c.ws, c.L.wbar));
   outer_args(c, a.adj, a.ow, a.oc);
@@ -4224,7 +4281,7 @@ int apply_tuning(Tune& t, const nep_tuning* u) {
   if (u->gather_lanes) t.gather_lanes = u->gather_lanes;
   ok = ok && set(t.forward_waves, u->forward_waves, 2, 3);
   ok = ok && set(t.adjoint_waves, u->adjoint_waves, 2, 3);
-  ok = ok && set(t.reverse_branch, u->reverse_branch, 1, 2);
+  ok = ok && u->reverse_branch >= 0 && u->reverse_branch <= 2;   // no launch to place any more
   return ok ? NEP_OK : NEP_ERR_ARG;
 }
 
@@ -4467,23 +4524,8 @@ int nep_train_step_graph_create_tuned(const nep_model* m, const nep_batch* b, ne
   hipStream_t cap;
   if (hipStreamCreateWithFlags(&cap, hipStreamNonBlocking) != hipSuccess) return NEP_ERR_HIP;
   c.st = cap;
-  // the reverse index's own branch (a stream of default priority, as every stream here)
-  auto drop_side = [&c]() {
-    if (c.side) (void)hipStreamDestroy(c.side);
-    if (c.fork) (void)hipEventDestroy(c.fork);
-    if (c.join) (void)hipEventDestroy(c.join);
-    c.side = nullptr;
-  };
-  if (!persistent && c.tune.reverse_branch == 2 && (hipStreamCreateWithFlags(&c.side, hipStreamNonBlocking) != hipSuccess ||
-                      hipEventCreateWithFlags(&c.fork, hipEventDisableTiming) != hipSuccess ||
-                      hipEventCreateWithFlags(&c.join, hipEventDisableTiming) != hipSuccess)) {
-    drop_side();
-    (void)hipStreamDestroy(cap);
-    return NEP_ERR_HIP;
-  }
   hipGraph_t g = nullptr;
   if (hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal) != hipSuccess) {
-    drop_side();
     (void)hipStreamDestroy(cap);
     return NEP_ERR_HIP;
   }
@@ -4495,6 +4537,7 @@ int nep_train_step_graph_create_tuned(const nep_model* m, const nep_batch* b, ne
                     d_flags};
   c.adam = &af;
   if (persistent) {
+    c.packed = (graph_flags & NEP_GRAPH_CACHED_NEIGHBORS) == 0;   // by the build launched below
     StepArgs* sa = at<StepArgs>(c.ws, c.L.sargs);
     hipLaunchKernelGGL(k_step_head, dim3(1), dim3(64), 0, cap,
                        step_args(c, nb, params, labels, lambda, loss, grad, d_flags), sa, d_flags, d_step, cur);
@@ -4508,7 +4551,6 @@ int nep_train_step_graph_create_tuned(const nep_model* m, const nep_batch* b, ne
   }
   const hipError_t e1 = hipStreamEndCapture(cap, &g);
   (void)hipStreamDestroy(cap);
-  drop_side();
   if (e1 != hipSuccess || !g) return NEP_ERR_HIP;
   hipGraphExec_t ex;
   if (hipGraphInstantiate(&ex, g, nullptr, nullptr, 0) != hipSuccess) {
