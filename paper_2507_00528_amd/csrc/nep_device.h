@@ -130,6 +130,35 @@ __device__ __forceinline__ void radial_cheb(float r, float inv_rc, float (&t)[K]
   for (int k = 2; k < K; ++k) t[k] = fmaf(xi2, t[k - 1], -t[k - 2]);
 }
 
+// t[k] = h T_k and q[k] = h' T_k + h xi' dT_k/dxi, so f_k = t[k] + t[0] and
+// f'_k = q[k] + q[0]; dT_k/dxi = k U_{k-1} with U from the same recurrence.
+template <int K>
+__device__ __forceinline__ void radial_cheb_d(float r, float inv_rc, float (&t)[K], float (&q)[K]) {
+  const float u = r * inv_rc;
+  const float x = u - 1.0f;
+  const float xi = fmaf(2.0f * x, x, -1.0f);
+  const float xi2 = 2.0f * xi;
+  t[0] = fmaf(0.25f, cos_turns(0.5f * u), 0.25f);
+  q[0] = -0.25f * 3.14159265358979f * inv_rc * sin_turns(0.5f * u);
+  if constexpr (K > 1) {
+    float p0 = q[0], p1 = xi * q[0];                  // h' T_k
+    float u0 = 0.f, u1 = 4.0f * x * inv_rc * t[0];    // h xi' U_{k-1}
+    t[1] = xi * t[0];
+    q[1] = p1 + u1;
+#pragma unroll
+    for (int k = 2; k < K; ++k) {
+      t[k] = fmaf(xi2, t[k - 1], -t[k - 2]);
+      const float p2 = fmaf(xi2, p1, -p0);
+      const float u2 = fmaf(xi2, u1, -u0);
+      q[k] = fmaf((float)k, u2, p2);
+      p0 = p1;
+      p1 = p2;
+      u0 = u1;
+      u1 = u2;
+    }
+  }
+}
+
 // d/dr of sum_k c_k f_k(r), for coefficients whose entry 0 holds
 // c_0 + sum_k c_k (the terms h T_0 of every order): h' S + h xi' dS/dxi with
 // S = sum_k c_k T_k, S and dS/dxi by Clenshaw's recurrence.

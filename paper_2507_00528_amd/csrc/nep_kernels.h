@@ -67,10 +67,7 @@ struct FwdArgs {
   const int* astruct;
   const float* box;
   const float* tilt;  // null: every cell orthorhombic
-  const float* pos;
-  const int* type;
-  const float4* p4;  // packed atoms of this call's neighbor build; null: gather pos and type
-  float4* p4out;     // then written here for the kernels that follow
+  const float4* p4;  // packed atoms
   PairLists nb;
   const float* cR;
   const float* cA;
@@ -78,7 +75,7 @@ struct FwdArgs {
   int nn_stride;
   float* G;        // [D][Npad] species order (may be null)
   float* Guser;    // [D][N] atom order (may be null)
-  float* Sst;      // [NA*Y][Npad] (may be null)
+  float* Sst;      // [NA*YR][Npad] (may be null)
   float* Ep;       // [D][Npad] (may be null)
   float* X;        // [H][Npad] (may be null)
   float* eatom;    // [N] atom order (may be null)
@@ -114,12 +111,13 @@ struct AdjArgs {
   const float* tilt;  // null: every cell orthorhombic
   const float* pos;
   const int* type;
+  const float4* p4;   // packed atoms
   PairLists nb;
   const float* cR;
   const float* cA;
   const float* nn;
   int nn_stride;
-  const float* Sst;   // [NA*Y][Npad]
+  const float* Sst;   // [NA*YR][Npad]
   const float* Ep;    // [D][Npad]
   const float* X;     // [H][Npad]
   const float* eps;   // [S] dL/dE(n)

@@ -90,6 +90,9 @@ struct PosTile {
 // wavefront's LDS instructions complete in issue order, so it is enough that
 // the compiler keeps every memory access on its side of this point.
 __device__ __forceinline__ void lds_lane_exchange() { asm volatile("" ::: "memory"); }
+// Block barrier that orders LDS only: __syncthreads would also wait for the
+// wavefront's outstanding global stores.
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 // A value the compiler cannot see through.  The float64 paths below run for
 // few candidates of the single-image scan; taking their inputs through this
@@ -1197,23 +1200,23 @@ struct CTab {
   static constexpr int size = T * T * NA * KAP;
 };
 
-template <int T, int NA, int KA>
+// With kCheb, entry 0 of a row holds c_0 + sum_k c_k (the terms h T_0 of every
+// order), so g_n = sum_k row[k] h T_k.
+template <int T, int NA, int KA, bool kCheb>
 __device__ __forceinline__ void stage_ctab(float* ct, const float* __restrict__ cA) {
-  constexpr int KAP = CTab<T, NA, KA>::KAP, SZ = CTab<T, NA, KA>::size, U = 8;
-  // U words per thread per round, the loads issued before the stores
-  for (int base = 0; base < SZ; base += U * (int)blockDim.x) {
-    float v[U];
+  constexpr int KAP = CTab<T, NA, KA>::KAP, R = T * T * NA;
+  // a row per thread: its loads are in flight together
+  for (int r = threadIdx.x; r < R; r += blockDim.x) {
+    float v[KAP], sum = 0.f;
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int q = base + u * (int)blockDim.x + (int)threadIdx.x;
-      const int k = q % KAP, r = q / KAP;
-      v[u] = (q < SZ && k < KA) ? cA[r * KA + k] : 0.f;
+    for (int k = 0; k < KAP; ++k) v[k] = k < KA ? cA[r * KA + (k < KA ? k : 0)] : 0.f;
+    if (kCheb) {
+#pragma unroll
+      for (int k = 0; k < KA; ++k) sum += v[k];
+      v[0] += sum;
     }
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int q = base + u * (int)blockDim.x + (int)threadIdx.x;
-      if (q < SZ) ct[q] = v[u];
-    }
+    for (int k = 0; k < KAP; ++k) ct[r * KAP + k] = v[k];
   }
 }
 
@@ -1290,11 +1293,14 @@ __device__ __forceinline__ int packed_type(const float4& p) {
   return (int)(__float_as_uint(p.w) & (uint32_t)(T - 1));
 }
 
-// Atom j, packed: one 16-byte load, or (packed atoms not built by this call)
-// gathered from the caller's arrays.
-__device__ __forceinline__ float4 load_atom(const float4* p4, const float* pos, const int* type, int N, int j) {
-  if (p4) return p4[j];
-  return make_float4(pos[j], pos[N + j], pos[2 * N + j], __uint_as_float((uint32_t)type[j]));
+// Packed atoms of a call that did not build its lists (the neighbor build
+// packs them otherwise): positions and species are the caller's at this call.
+__global__ __launch_bounds__(256) void k_pack(int N, int T, const float* __restrict__ pos, const int* __restrict__ type,
+                                              PairLists nb, float4* __restrict__ p4) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i >= N) return;
+  p4[i] = make_float4(pos[i], pos[N + i], pos[2 * N + i],
+                      atom_word(type[i], T, nb.cntR[i] > nb.capR, nb.cntA[i] > nb.capA));
 }
 
 // ========================================================= atom groups
@@ -1360,26 +1366,14 @@ struct HRow {
   static constexpr bool real(int g, int e) { return HSplit<LM>::q(g, e) >= 0; }
 };
 
-// E' of q_nl for the two l blocks of harmonic group g (l = 1, 4 or l = 2, 3)
-template <int NR, int NA, int L3, int D>
-__device__ __forceinline__ void ep_blocks(const float (&Ep)[D], int n, int g, float& eA, float& eB) {
-  float e1 = 0.f, e2 = 0.f, e3 = 0.f, e4 = 0.f;
-  if constexpr (L3 >= 1) e1 = Ep[NR + n];
-  if constexpr (L3 >= 2) e2 = Ep[NR + NA + n];
-  if constexpr (L3 >= 3) e3 = Ep[NR + 2 * NA + n];
-  if constexpr (L3 >= 4) e4 = Ep[NR + 3 * NA + n];
-  eA = g ? e2 : e1;
-  eB = g ? e3 : e4;
-}
-
 struct GroupCtx {
-  int s, g, p, al, pa, i, I;
+  int s, g, p, al, pa, i;
   bool valid;
 };
 
 // lane roles and the atom of this lane; every lane of the block stays alive
-__device__ __forceinline__ GroupCtx group_ctx(const int* __restrict__ order, const int* __restrict__ type, int Npad,
-                                              int vb) {
+// (lanes without an atom repeat one of the wavefront's, or atom 0)
+__device__ __forceinline__ GroupCtx group_ctx(const int* __restrict__ order, int Npad, int vb) {
   GroupCtx c;
   c.s = threadIdx.x & (kLPA - 1);
   c.g = c.s >> 2;
@@ -1392,16 +1386,16 @@ __device__ __forceinline__ GroupCtx group_ctx(const int* __restrict__ order, con
   const int lead = vm ? __ffsll(vm) - 1 : 0;
   const int ilead = vm ? __shfl(iraw, lead, kWave) : 0;
   c.i = c.valid ? iraw : ilead;
-  c.I = __builtin_amdgcn_readfirstlane(vm ? type[ilead] : 0);
   return c;
 }
 
 // Species of block vb's atoms.  Segments start on block boundaries, so a
 // block holds one species, and its first position is an atom unless the
 // whole block is padding.
-__device__ __forceinline__ int block_species(const int* __restrict__ order, const int* __restrict__ type, int vb) {
+template <int T>
+__device__ __forceinline__ int block_species(const int* __restrict__ order, const float4* __restrict__ p4, int vb) {
   const int ip = order[vb * kAPB];
-  return ip >= 0 ? type[ip] : 0;
+  return ip >= 0 ? packed_type<T>(p4[ip]) : 0;
 }
 
 // LDS words of the staged weights: whole 64-word rows, so that the direct
@@ -1428,6 +1422,118 @@ __device__ __forceinline__ void stage_weights_async(float* wl, const float* __re
 }
 __device__ __forceinline__ void wait_weights() { __builtin_amdgcn_s_waitcnt(0); }
 
+// ======================================================== angular pair stream
+// The angular pairs of a wavefront's 8 atoms form one stream, taken 64 at a
+// time with one pair per lane: geometry, basis and harmonics are evaluated
+// once per pair.  (With the pairs split over 4 slots of an atom's lanes, both
+// harmonic groups evaluated them, and an atom with 5 pairs took as long as
+// one with 8.)  Atoms are sorted by pair count, so most wavefronts of the
+// mean 7.3 pairs per atom need one chunk.  The lanes of an atom then sum 3
+// harmonics each over its pairs, read back from LDS (15 sums a lane instead of
+// 60).  Forward at 512 structures (87k atoms): 5540 -> 3570 VALU instructions
+// per wavefront with the radial forces moved out, 168 -> 128 registers (four
+// wavefronts per SIMD), 111 -> 87 us.  A table of the 8 atom slots in LDS
+// serves the lanes whose pair belongs to another lane's atom.
+constexpr int kSlotX = 0, kSlotI = 3, kSlotL = 4, kSlotBase = 7, kSlotTilt = 8;
+template <bool kTri>
+constexpr int slot_words() {
+  return 12;   // x y z i | Lx Ly Lz base | xy xz yz -; 4 mod 8, so the 8 slots start in different banks
+}
+
+struct PairStream {
+  int cum[kAPW];   // stream position of slot v's first pair (wave-uniform)
+  int total;
+  int lo, hi;      // this lane's own atom's pairs
+};
+
+// nA: the pairs of this lane's atom (the same in its 8 lanes)
+__device__ __forceinline__ PairStream pair_stream(int nA) {
+  PairStream st;
+  const int slot = (threadIdx.x & (kWave - 1)) / kLPA;
+  int at = 0;
+  st.lo = 0;
+#pragma unroll
+  for (int v = 0; v < kAPW; ++v) {
+    st.cum[v] = at;
+    st.lo = v == slot ? at : st.lo;
+    at += __builtin_amdgcn_readlane(nA, v * kLPA);
+  }
+  st.total = at;
+  st.hi = st.lo + nA;
+  return st;
+}
+
+// atom slot of stream position p
+__device__ __forceinline__ int pair_slot(const PairStream& st, int p) {
+  int u = 0;
+#pragma unroll
+  for (int v = 1; v < kAPW; ++v) u += p >= st.cum[v] ? 1 : 0;
+  return u;
+}
+
+template <bool kTri>
+__device__ __forceinline__ void slot_store(float* sl, int i, float x, float y, float z, const Cell& c, int base) {
+  *reinterpret_cast<float4*>(sl + kSlotX) = make_float4(x, y, z, __int_as_float(i));
+  *reinterpret_cast<float4*>(sl + kSlotL) = make_float4(c.Lx, c.Ly, c.Lz, __int_as_float(base));
+  if constexpr (kTri) *reinterpret_cast<float4*>(sl + kSlotTilt) = make_float4(c.xy, c.xz, c.yz, 0.f);
+}
+
+// list offset of stream position p and its geometry, from the slot's words
+struct StreamPair {
+  size_t off;
+  int J;
+  PairGeom q;
+};
+template <int T, bool kTri>
+__device__ __forceinline__ StreamPair stream_pair(const float* sl, int p, const PairLists& nb, const float4* p4) {
+  const float4 x = *reinterpret_cast<const float4*>(sl + kSlotX);
+  const float4 l = *reinterpret_cast<const float4*>(sl + kSlotL);
+  Cell c{l.x, l.y, l.z, 0.f, 0.f, 0.f};
+  if constexpr (kTri) {
+    const float4 t = *reinterpret_cast<const float4*>(sl + kSlotTilt);
+    c.xy = t.x;
+    c.xz = t.y;
+    c.yz = t.z;
+  }
+  StreamPair r;
+  r.off = (size_t)__float_as_int(x.w) * nb.capA + (p - __float_as_int(l.w));
+  const uint32_t e = nb.idxA[r.off];
+  const float4 pj = p4[e >> 5];
+  r.J = packed_type<T>(pj);
+  r.q = packed_geom<kTri>(e, pj, x.x, x.y, x.z, c);
+  return r;
+}
+
+// LDS of the forward per wavefront: the slot table, then the pair records of
+// the angular sums (g_n and the harmonics, odd stride) and, once they are
+// summed, the atoms' rows (G, then S or A in group order; stride 4 mod 8)
+template <class C>
+struct FwdLds {
+  static constexpr int DP = (C::D + 3) & ~3, YR = HRow<C::LMAX>::YR;
+  static constexpr int RS = (C::NA + YR) | 1;
+  static constexpr int RW = (DP + C::NA * YR + 7) / 8 * 8 + 4;
+  static constexpr int BUF = (kWave * RS > kAPW * RW ? kWave * RS : kAPW * RW) + 3 & ~3;
+  static constexpr int WAVE = kAPW * slot_words<true>() + BUF;
+};
+
+// words [base + e], e = 0..W-1 (16-byte reads when the row allows)
+template <int W, bool kVec>
+__device__ __forceinline__ void row_load(const float* p, float (&v)[W]) {
+  if constexpr (kVec && W % 4 == 0) {
+#pragma unroll
+    for (int e = 0; e < W; e += 4) {
+      const float4 c = *reinterpret_cast<const float4*>(p + e);
+      v[e] = c.x;
+      v[e + 1] = c.y;
+      v[e + 2] = c.z;
+      v[e + 3] = c.w;
+    }
+  } else {
+#pragma unroll
+    for (int e = 0; e < W; ++e) v[e] = p[e];
+  }
+}
+
 // ================================================================= forward
 // Per atom: radial sums F[J][k] = sum_{j of type J} f_k(r_ij) give
 // q_n = sum_{J,k} c^R_{IJnk} F[J][k] (Eqs. 5-6); angular sums S_nlm (Eq. 8)
@@ -1441,55 +1547,71 @@ __device__ __forceinline__ void forward_body(const FwdArgs& a, int vb, float* ld
   constexpr int T = C::T, NR = C::NR, NA = C::NA, KR = C::KR, KA = C::KA, Y = C::Y, D = C::D, LM = C::LMAX;
   constexpr int L3 = C::L3, L4 = C::L4, L5 = C::L5;
   using HS = HSplit<LM>;
-  constexpr int YG = HS::YG;
-  constexpr int DP = (D + 3) & ~3;
+  using FL = FwdLds<C>;
+  constexpr int YG = HS::YG, YR = HRow<LM>::YR, DP = FL::DP, RS = FL::RS, RW = FL::RW;
+  constexpr int NE = (YR + kLPA - 1) / kLPA;   // harmonics summed per lane
+  constexpr bool kVec = YR % 4 == 0;
   const int H = a.H;
-  constexpr int YR = HRow<LM>::YR;
-  constexpr int RW = DP + NA * YR;        // LDS row per atom: G, S (group order)
   using CT = CTab<T, NA, KA>;
   float* ctab = lds;                     // [T][T][NA][KAP]
   float* wl = lds + CT::size;            // weights of the block's species
-  float* rows = wl + weights_words(H, DP);   // [kAPB][RW]
-  stage_ctab<T, NA, KA>(ctab, a.cA);
-  __syncthreads();
-  // issued after the barrier (a barrier waits for every outstanding load) and
-  // waited for before the next one, ahead of the network
-  if (a.do_mlp) stage_weights_async(wl, a.nn, a.nn_stride, block_species(a.order, a.type, vb), H, D, DP);
-  const GroupCtx w = group_ctx(a.order, a.type, a.Npad, vb);
-  const int N = a.N, i = w.i, I = w.I, pa = w.pa, s = w.s, g = w.g;
-  float* row = rows + w.al * RW;
+  float* slots = wl + weights_words(H, DP) + (threadIdx.x / kWave) * FL::WAVE;
+  float* buf = slots + kAPW * slot_words<kTri>();
+  // issued here, waited for after the angular sums: their latency overlaps the
+  // pair passes
+  if (a.do_mlp) stage_weights_async(wl, a.nn, a.nn_stride, block_species<T>(a.order, a.p4, vb), H, D, DP);
+  const GroupCtx w = group_ctx(a.order, a.Npad, vb);
+  const int N = a.N, i = w.i, pa = w.pa, s = w.s, g = w.g;
+  const int lane = threadIdx.x & (kWave - 1), slot = lane / kLPA;
+  const float4 me = a.p4[i];
+  const int I = __builtin_amdgcn_readfirstlane(packed_type<T>(me));   // one species per wavefront
+  float* row = buf + slot * RW;
   float* rowS = row + DP;
   const int st = a.astruct[i];
   const Cell cell = load_cell<kTri>(a.box, a.tilt, st);
-  const float xi = a.pos[i], yi = a.pos[N + i], zi = a.pos[2 * N + i];
+  const float xi = me.x, yi = me.y, zi = me.z;
   const int cR_i = a.nb.cntR[i], cA_i = a.nb.cntA[i];
   const int nR = w.valid ? min(cR_i, a.nb.capR) : 0;
   const int nA = w.valid ? min(cA_i, a.nb.capA) : 0;
   const cptr<float> cRI = as_const(a.cR) + (size_t)I * T * NR * KR;
-  if (!a.p4 && w.valid && s == 0) a.p4out[i] = make_float4(xi, yi, zi, atom_word(I, T, cR_i > a.nb.capR, cA_i > a.nb.capA));
+  stage_ctab<T, NA, KA, true>(ctab, a.cA);
 
   // ---- radial sums in Chebyshev space, pairs split over the 8 lanes
-  float FR[T][KR];
-#pragma unroll
-  for (int t = 0; t < T; ++t)
-#pragma unroll
-    for (int k = 0; k < KR; ++k) FR[t][k] = 0.f;
-  for (int k = s; k < nR; k += kLPA) {
-    const uint32_t e = a.nb.idxR[(size_t)i * a.nb.capR + k];
-    const float4 pj = load_atom(a.p4, a.pos, a.type, N, (int)(e >> 5));
-    const PairGeom q = packed_geom<kTri>(e, pj, xi, yi, zi, cell);
-    float f[KR];
-    radial_cheb<KR>(q.r, a.inv_rcR, f);
-    const int J = packed_type<T>(pj);
-#pragma unroll
-    for (int t = 0; t < T; ++t) {
-      const float m = (T == 1 || J == t) ? 1.f : 0.f;
-#pragma unroll
-      for (int kk = 0; kk < KR; ++kk) FR[t][kk] = fmaf(m, f[kk], FR[t][kk]);
-    }
-  }
-  // the basis sums over the 8 lanes, then q_n = sum c^R F by lane n & 7
+  constexpr int NQ = (NR + kLPA - 1) / kLPA;
+  float qn[NQ];   // channels s, s + 8, ...
   {
+    float FR[T][KR];
+#pragma unroll
+    for (int t = 0; t < T; ++t)
+#pragma unroll
+      for (int k = 0; k < KR; ++k) FR[t][k] = 0.f;
+    // the next pair's atom and the list entry after it are loaded ahead
+    const uint32_t* li = a.nb.idxR + (size_t)i * a.nb.capR;
+    uint32_t e0 = 0, e1 = 0;
+    float4 p0 = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (s < nR) {
+      e0 = li[s];
+      e1 = li[min(s + kLPA, nR - 1)];
+      p0 = a.p4[e0 >> 5];
+    }
+    for (int k = s; k < nR; k += kLPA) {
+      const uint32_t e = e0;
+      const float4 pj = p0;
+      e0 = e1;
+      p0 = a.p4[e1 >> 5];
+      e1 = li[min(k + 2 * kLPA, nR - 1)];
+      const PairGeom q = packed_geom<kTri>(e, pj, xi, yi, zi, cell);
+      float f[KR];
+      radial_cheb<KR>(q.r, a.inv_rcR, f);
+      const int J = packed_type<T>(pj);
+#pragma unroll
+      for (int t = 0; t < T; ++t) {
+        const float m = (T == 1 || J == t) ? 1.f : 0.f;
+#pragma unroll
+        for (int kk = 0; kk < KR; ++kk) FR[t][kk] = fmaf(m, f[kk], FR[t][kk]);
+      }
+    }
+    // the basis sums over the 8 lanes, then q_n = sum c^R F by lane n & 7
 #pragma unroll
     for (int t = 0; t < T; ++t) {
 #pragma unroll
@@ -1499,97 +1621,118 @@ __device__ __forceinline__ void forward_body(const FwdArgs& a, int vb, float* ld
       for (int k = 0; k < KR; ++k) FR[t][k] += A0;
     }
 #pragma unroll
-    for (int n0 = 0; n0 < NR; n0 += kLPA) {
-      const int n = n0 + s;
-      if (n < NR) {
-        const cptr<float> cn = cRI + n * KR;
-        float acc = 0.f;
-#pragma unroll
-        for (int t = 0; t < T; ++t)
-#pragma unroll
-          for (int k = 0; k < KR; ++k) acc = fmaf(cn[t * NR * KR + k], FR[t][k], acc);
-        row[n] = acc;
-      }
-    }
-  }
-
-  // ---- angular sums S_nlm: harmonic group g, pairs p, p+4, ...
-  float Sg[NA][YG];
-#pragma unroll
-  for (int n = 0; n < NA; ++n)
-#pragma unroll
-    for (int e = 0; e < YG; ++e) Sg[n][e] = 0.f;
-  for (int k = w.p; k < nA; k += 4) {
-    const uint32_t e = a.nb.idxA[(size_t)i * a.nb.capA + k];
-    const float4 pj = load_atom(a.p4, a.pos, a.type, N, (int)(e >> 5));
-    const PairGeom q = packed_geom<kTri>(e, pj, xi, yi, zi, cell);
-    float f[KA];
-    radial_basis<KA>(q.r, a.inv_rcA, f);
-    const int J = packed_type<T>(pj);
-    const float* cJ = ctab + (I * T + J) * NA * CT::KAP;
-    float gn[NA];
-#pragma unroll
-    for (int n = 0; n < NA; ++n) {
+    for (int r = 0; r < NQ; ++r) {
+      const int n = r * kLPA + s;
+      const cptr<float> cn = cRI + (n < NR ? n : 0) * KR;
       float acc = 0.f;
 #pragma unroll
-      for (int kk = 0; kk < KA; ++kk) acc = fmaf(cJ[n * CT::KAP + kk], f[kk], acc);
-      gn[n] = acc;
+      for (int t = 0; t < T; ++t)
+#pragma unroll
+        for (int k = 0; k < KR; ++k) acc = fmaf(cn[t * NR * KR + k], FR[t][k], acc);
+      qn[r] = acc;
     }
-    float B[Y];
-    harm_val<LM>(q.dx * q.inv_r, q.dy * q.inv_r, q.dz * q.inv_r, B);
+  }
+
+  // ---- angular sums S_nlm: one pair per lane writes g_n and B_lm, then lane s
+  //      of an atom sums its pairs for the harmonics s, s + 8, ...
+  const PairStream ps = pair_stream(nA);
+  if (s == 0) slot_store<kTri>(slots + slot * slot_words<kTri>(), i, xi, yi, zi, cell, ps.lo);
+  lds_barrier();   // the block's coefficient table
+  {
+    float S[NE][NA];
+#pragma unroll
+    for (int r = 0; r < NE; ++r)
+#pragma unroll
+      for (int n = 0; n < NA; ++n) S[r][n] = 0.f;
+    for (int c0 = 0; c0 < ps.total; c0 += kWave) {
+      const int p = c0 + lane;
+      if (p < ps.total) {
+        const StreamPair sp = stream_pair<T, kTri>(slots + pair_slot(ps, p) * slot_words<kTri>(), p, a.nb, a.p4);
+        float f[KA];
+        radial_cheb<KA>(sp.q.r, a.inv_rcA, f);
+        const float* cJ = ctab + (I * T + sp.J) * NA * CT::KAP;
+        float* rec = buf + lane * RS;
+#pragma unroll
+        for (int n = 0; n < NA; ++n) {
+          float acc = 0.f;
+#pragma unroll
+          for (int kk = 0; kk < KA; ++kk) acc = fmaf(cJ[n * CT::KAP + kk], f[kk], acc);
+          rec[n] = acc;
+        }
+        float B[Y];
+        harm_val<LM>(sp.q.dx * sp.q.inv_r, sp.q.dy * sp.q.inv_r, sp.q.dz * sp.q.inv_r, B);
+#pragma unroll
+        for (int gg = 0; gg < 2; ++gg)
+#pragma unroll
+          for (int e = 0; e < YG; ++e) {
+            const int q = HS::q(gg, e);
+            rec[NA + gg * YG + e] = q >= 0 ? B[q] : 0.f;
+          }
+      }
+      lds_lane_exchange();
+      const int t1 = min(ps.hi - c0, kWave);
+#pragma unroll 2
+      for (int t = max(ps.lo - c0, 0); t < t1; ++t) {
+        const float* rec = buf + t * RS;
+        float gn[NA];
+#pragma unroll
+        for (int n = 0; n < NA; ++n) gn[n] = rec[n];
+#pragma unroll
+        for (int r = 0; r < NE; ++r) {
+          const int e = r * kLPA + s;
+          const float b = rec[NA + (YR % kLPA == 0 || e < YR ? e : 0)];
+#pragma unroll
+          for (int n = 0; n < NA; ++n) S[r][n] = fmaf(gn[n], b, S[r][n]);
+        }
+      }
+      lds_lane_exchange();
+    }
+    // This wavefront's weight loads have landed (before any store is issued, so
+    // that none is waited for); the barrier ahead of the network covers the
+    // other wavefronts'.
+    wait_weights();
+    // the atoms' rows take the records' place
+#pragma unroll
+    for (int r = 0; r < NE; ++r) {
+      const int e = r * kLPA + s;
+      if (YR % kLPA == 0 || e < YR) {
+#pragma unroll
+        for (int n = 0; n < NA; ++n) {
+          rowS[n * YR + e] = S[r][n];   // zero at padding entries
+          if (w.valid && a.Sst) a.Sst[(size_t)(n * YR + e) * a.Npad + pa] = S[r][n];
+        }
+      }
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < NQ; ++r)
+    if (r * kLPA + s < NR) row[r * kLPA + s] = qn[r];
+  lds_lane_exchange();
+
+  // ---- angular descriptors, channel n and harmonic group g by the lane of
+  //      pair slot n mod 4 and group g
+  const int lA = g ? 2 : 1, lB = g ? 3 : 4;
+  const int nAg = g ? HS::nA1 : HS::nA0;     // size of the first l block
+  for (int n = w.p; n < NA; n += 4) {
+    float Sn[YG];
+    row_load<YG, kVec>(rowS + n * YR + g * YG, Sn);
+    float qa = 0.f, qb = 0.f;
 #pragma unroll
     for (int e = 0; e < YG; ++e) {
-      const float b = hsel<HS, Y>(g, e, B);
-#pragma unroll
-      for (int n = 0; n < NA; ++n) Sg[n][e] = fmaf(gn[n], b, Sg[n][e]);
+      const float v = csel<HS>(g, e) * Sn[e] * Sn[e];
+      if (e < nAg) qa += v; else qb += v;
     }
-  }
-#pragma unroll
-  for (int n = 0; n < NA; ++n)
-#pragma unroll
-    for (int e = 0; e < YG; ++e) Sg[n][e] = quad_sum(Sg[n][e]);
-
-  // ---- angular descriptors of this lane's harmonic group
-  {
-    const int nAg = g ? HS::nA1 : HS::nA0;     // size of the first l block
-    const int lA = g ? 2 : 1, lB = g ? 3 : 4;
-#pragma unroll
-    for (int n = 0; n < NA; ++n) {
-      float qa = 0.f, qb = 0.f;
-#pragma unroll
-      for (int e = 0; e < YG; ++e) {
-        const float v = csel<HS>(g, e) * Sg[n][e] * Sg[n][e];
-        if (e < nAg) qa += v; else qb += v;
-      }
-      if (w.p == 0) {
-        if (lA <= L3) row[NR + (lA - 1) * NA + n] = qa;
-        if (lB <= L3) row[NR + (lB - 1) * NA + n] = qb;
-      }
-    }
+    if (lA <= L3) row[NR + (lA - 1) * NA + n] = qa;
+    if (lB <= L3) row[NR + (lB - 1) * NA + n] = qb;
     if constexpr (L4 != 0) {
-#pragma unroll
-      for (int n = 0; n < NA; ++n) {
-        const Sym3 M = sym_of(Sg[n][0], Sg[n][1], Sg[n][2], Sg[n][3], Sg[n][4]);
-        const float q4 = sym_dot(sym_mul(M, M), M);
-        if (g == 1 && w.p == 0) row[NR + L3 * NA + n] = q4;
-      }
+      const Sym3 M = sym_of(Sn[0], Sn[1], Sn[2], Sn[3], Sn[4]);
+      const float q4 = sym_dot(sym_mul(M, M), M);
+      if (g == 1) row[NR + L3 * NA + n] = q4;
     }
     if constexpr (L5 != 0) {
-#pragma unroll
-      for (int n = 0; n < NA; ++n) {
-        const float P = Sg[n][0] * Sg[n][0] + Sg[n][1] * Sg[n][1] + Sg[n][2] * Sg[n][2];
-        if (g == 0 && w.p == 0) row[NR + L3 * NA + (L4 ? NA : 0) + n] = P * P;
-      }
+      const float P = Sn[0] * Sn[0] + Sn[1] * Sn[1] + Sn[2] * Sn[2];
+      if (g == 0) row[NR + L3 * NA + (L4 ? NA : 0) + n] = P * P;
     }
-  }
-  if (w.p == 0) {
-#pragma unroll
-    for (int n = 0; n < NA; ++n)
-#pragma unroll
-      for (int e = 0; e < YG; ++e) {
-        rowS[n * YR + g * YG + e] = Sg[n][e];   // zero at padding entries
-        if (w.valid && a.Sst) a.Sst[(size_t)(n * YR + g * YG + e) * a.Npad + pa] = Sg[n][e];
-      }
   }
   if constexpr (C::YH > 0) {
     // q_nl of l = 5..L3, from k_high_desc
@@ -1598,18 +1741,19 @@ __device__ __forceinline__ void forward_body(const FwdArgs& a, int vb, float* ld
       row[v] = w.valid ? x : 0.f;
     }
   }
-  wait_weights();   // this wavefront's weight loads have landed; the barrier covers the others'
-  __syncthreads();
-  float G[D];
-#pragma unroll
-  for (int v = 0; v < D; ++v) G[v] = row[v];
+  lds_barrier();
+  float G[DP];
+  row_load<DP, true>(row, G);   // words past D are not used
   if (w.valid) {
 #pragma unroll
-    for (int v = 0; v < D; ++v)
-      if (s == (v & 7)) {
-        if (a.G) a.G[(size_t)v * a.Npad + pa] = G[v];
-        if (a.Guser) a.Guser[(size_t)v * N + i] = G[v];
+    for (int r = 0; r < (D + kLPA - 1) / kLPA; ++r) {
+      const int v = r * kLPA + s;
+      if (D % kLPA == 0 || v < D) {
+        const float x = row[v];
+        if (a.G) a.G[(size_t)v * a.Npad + pa] = x;
+        if (a.Guser) a.Guser[(size_t)v * N + i] = x;
       }
+    }
   }
   if (!a.do_mlp) return;
 
@@ -1646,8 +1790,6 @@ __device__ __forceinline__ void forward_body(const FwdArgs& a, int vb, float* ld
       }
     }
     lds_lane_exchange();
-#pragma unroll
-    for (int v = 0; v < D; ++v) Ep[v] = row[v];
   }
   E = grp8_sum(E) + a.nn[(size_t)I * a.nn_stride + H * D + 2 * H];
   if (w.valid) {
@@ -1662,18 +1804,18 @@ __device__ __forceinline__ void forward_body(const FwdArgs& a, int vb, float* ld
   //      pass, entry (J, k) by lane (J KP + k) mod 8; entry (J, 0) also takes
   //      sum_k h_Jk (the terms h T_0 of every order)
   {
-    constexpr int KP = HRad<C>::KP, NE = (T * KP + kLPA - 1) / kLPA;
-    float hv[NE], sum[T];
+    constexpr int KP = HRad<C>::KP, NH = (T * KP + kLPA - 1) / kLPA;
+    float hv[NH], sum[T];
 #pragma unroll
     for (int t = 0; t < T; ++t) sum[t] = 0.f;
 #pragma unroll
-    for (int r = 0; r < NE; ++r) {
+    for (int r = 0; r < NH; ++r) {
       const int e = r * kLPA + s, t = e / KP, kk = e % KP;
       const bool on = t < T && kk < KR;
       const cptr<float> c = cRI + (on ? t * NR * KR + kk : 0);
       float acc = 0.f;
 #pragma unroll
-      for (int n = 0; n < NR; ++n) acc = fmaf(Ep[n], c[n * KR], acc);
+      for (int n = 0; n < NR; ++n) acc = fmaf(row[n], c[n * KR], acc);
       hv[r] = on ? acc : 0.f;
 #pragma unroll
       for (int u = 0; u < T; ++u) sum[u] += t == u ? hv[r] : 0.f;
@@ -1683,7 +1825,7 @@ __device__ __forceinline__ void forward_body(const FwdArgs& a, int vb, float* ld
     if (w.valid) {
       float* ho = a.hrow + (size_t)i * T * KP;
 #pragma unroll
-      for (int r = 0; r < NE; ++r) {
+      for (int r = 0; r < NH; ++r) {
         const int e = r * kLPA + s, t = e / KP;
         float v = hv[r];
 #pragma unroll
@@ -1693,102 +1835,87 @@ __device__ __forceinline__ void forward_body(const FwdArgs& a, int vb, float* ld
     }
   }
 
-  // ---- A_nlm = sum_v E'_v dG_v/dS_nlm for this lane's harmonics
-  float Ag[NA][YG];
-  {
-    const int nAg = g ? HS::nA1 : HS::nA0;
+  // ---- A_nlm = sum_v E'_v dG_v/dS_nlm in place of S_nlm, lanes as for the
+  //      angular descriptors
+  for (int n = w.p; n < NA; n += 4) {
+    float Sn[YG];
+    row_load<YG, kVec>(rowS + n * YR + g * YG, Sn);
+    const float eA = lA <= L3 ? row[NR + ((lA <= L3 ? lA : 1) - 1) * NA + n] : 0.f;
+    const float eB = lB <= L3 ? row[NR + ((lB <= L3 ? lB : 1) - 1) * NA + n] : 0.f;
+    float a4[5] = {0.f, 0.f, 0.f, 0.f, 0.f}, a5[3] = {0.f, 0.f, 0.f};
+    if constexpr (L4 != 0) {
+      const Sym3 M = sym_of(Sn[0], Sn[1], Sn[2], Sn[3], Sn[4]);
+      float o[5];
+      sym_proj(sym_mul(M, M), o);
+      const float e4 = g == 1 ? 3.0f * row[NR + L3 * NA + n] : 0.f;
 #pragma unroll
-    for (int n = 0; n < NA; ++n) {
-      float Sn[YG];
+      for (int m = 0; m < 5; ++m) a4[m] = e4 * o[m];
+    }
+    if constexpr (L5 != 0) {
+      const float P = Sn[0] * Sn[0] + Sn[1] * Sn[1] + Sn[2] * Sn[2];
+      const float e5 = g == 0 ? 4.0f * row[NR + L3 * NA + (L4 ? NA : 0) + n] * P : 0.f;
 #pragma unroll
-      for (int e = 0; e < YG; ++e) Sn[e] = rowS[n * YR + g * YG + e];
-      float eA, eBv;
-      ep_blocks<NR, NA, L3, D>(Ep, n, g, eA, eBv);
-      float a4[5] = {0.f, 0.f, 0.f, 0.f, 0.f}, a5[3] = {0.f, 0.f, 0.f};
-      if constexpr (L4 != 0) {
-        const Sym3 M = sym_of(Sn[0], Sn[1], Sn[2], Sn[3], Sn[4]);
-        float o[5];
-        sym_proj(sym_mul(M, M), o);
-        const float e4 = g == 1 ? 3.0f * Ep[NR + L3 * NA + n] : 0.f;
+      for (int m = 0; m < 3; ++m) a5[m] = e5 * Sn[m];
+    }
 #pragma unroll
-        for (int m = 0; m < 5; ++m) a4[m] = e4 * o[m];
-      }
-      if constexpr (L5 != 0) {
-        const float P = Sn[0] * Sn[0] + Sn[1] * Sn[1] + Sn[2] * Sn[2];
-        const float e5 = g == 0 ? 4.0f * Ep[NR + L3 * NA + (L4 ? NA : 0) + n] * P : 0.f;
-#pragma unroll
-        for (int m = 0; m < 3; ++m) a5[m] = e5 * Sn[m];
-      }
-#pragma unroll
-      for (int e = 0; e < YG; ++e) {
-        float v = 2.0f * csel<HS>(g, e) * (e < nAg ? eA : eBv) * Sn[e];
-        if (e < 5) v += a4[e];
-        if (e < 3) v += a5[e];
-        Ag[n][e] = v;
-      }
+    for (int e = 0; e < YG; ++e) {
+      float v = 2.0f * csel<HS>(g, e) * (e < nAg ? eA : eB) * Sn[e];
+      if (e < 5) v += a4[e];
+      if (e < 3) v += a5[e];
+      rowS[n * YR + g * YG + e] = v;
     }
   }
+  lds_lane_exchange();
 
-  // ---- angular partial forces: f_ij = sum_nlm A_nlm (g'_n r_hat B_lm + g_n grad B_lm);
-  //      each harmonic group adds its half, the two halves are summed across lanes
-  for (int k = w.p; k < nA; k += 4) {
-    const uint32_t e = a.nb.idxA[(size_t)i * a.nb.capA + k];
-    const float4 pj = load_atom(a.p4, a.pos, a.type, N, (int)(e >> 5));
-    const PairGeom q = packed_geom<kTri>(e, pj, xi, yi, zi, cell);
+  // ---- angular partial forces, one pair per lane:
+  //      f_ij = sum_nlm A_nlm (g'_n r_hat B_lm + g_n grad B_lm)
+  for (int c0 = 0; c0 < ps.total; c0 += kWave) {
+    const int p = c0 + lane;
+    if (p >= ps.total) break;
+    const int u = pair_slot(ps, p);
+    const StreamPair sp = stream_pair<T, kTri>(slots + u * slot_words<kTri>(), p, a.nb, a.p4);
+    const PairGeom& q = sp.q;
     const float ux = q.dx * q.inv_r, uy = q.dy * q.inv_r, uz = q.dz * q.inv_r;
     float f[KA], fp[KA];
-    radial_basis_d<KA>(q.r, a.inv_rcA, f, fp);
-    const int J = packed_type<T>(pj);
-    const float* cJ = ctab + (I * T + J) * NA * CT::KAP;
-    float gn[NA], gp[NA];
+    radial_cheb_d<KA>(q.r, a.inv_rcA, f, fp);
+    const float* cJ = ctab + (I * T + sp.J) * NA * CT::KAP;
+    const float* rowA = buf + u * RW + DP;
+    float B[Y], uf[Y];
+    harm_val<LM>(ux, uy, uz, B);
+#pragma unroll
+    for (int qq = 0; qq < Y; ++qq) uf[qq] = 0.f;
+    float vv = 0.f;
 #pragma unroll
     for (int n = 0; n < NA; ++n) {
-      float s0 = 0.f, s1 = 0.f;
+      float gn = 0.f, gp = 0.f;
 #pragma unroll
       for (int kk = 0; kk < KA; ++kk) {
         const float c = cJ[n * CT::KAP + kk];
-        s0 = fmaf(c, f[kk], s0);
-        s1 = fmaf(c, fp[kk], s1);
+        gn = fmaf(c, f[kk], gn);
+        gp = fmaf(c, fp[kk], gp);
       }
-      gn[n] = s0;
-      gp[n] = s1;
-    }
-    float B[Y];
-    harm_val<LM>(ux, uy, uz, B);
-    float vv = 0.f;
-    float uf[Y];
+      float An[YR];
+      row_load<YR, kVec>(rowA + n * YR, An);
+      float wn = 0.f;   // sum_lm A_nlm B_lm
 #pragma unroll
-    for (int qq = 0; qq < Y; ++qq) uf[qq] = 0.f;
+      for (int gg = 0; gg < 2; ++gg)
 #pragma unroll
-    for (int e = 0; e < YG; ++e) {
-      float su = 0.f, sv = 0.f;
-#pragma unroll
-      for (int n = 0; n < NA; ++n) {
-        su = fmaf(Ag[n][e], gn[n], su);
-        sv = fmaf(Ag[n][e], gp[n], sv);
-      }
-      vv = fmaf(sv, hsel<HS, Y>(g, e, B), vv);
-      const int q0 = HS::q(0, e), q1 = HS::q(1, e);
-      if (q0 >= 0) uf[q0] = g ? uf[q0] : su;
-      if (q1 >= 0) uf[q1] = g ? su : uf[q1];
+        for (int e = 0; e < YG; ++e) {
+          const int qq = HS::q(gg, e);
+          if (qq >= 0) {
+            wn = fmaf(An[gg * YG + e], B[qq], wn);
+            uf[qq] = fmaf(An[gg * YG + e], gn, uf[qq]);
+          }
+        }
+      vv = fmaf(gp, wn, vv);
     }
     float gx, gy, gz;
     harm_grad_sum<LM>(ux, uy, uz, uf, gx, gy, gz);
     const float rad = ux * gx + uy * gy + uz * gz;
-    float fx = vv * ux + (gx - rad * ux) * q.inv_r;
-    float fy = vv * uy + (gy - rad * uy) * q.inv_r;
-    float fz = vv * uz + (gz - rad * uz) * q.inv_r;
-    // the partner lane (other harmonic group, same pair) runs the same
-    // iterations, so the DPP read below only touches active lanes
-    fx += xor4_val(fx);
-    fy += xor4_val(fy);
-    fz += xor4_val(fz);
-    if (g == 0) {
-      float* fo = a.fA + 3 * ((size_t)i * a.nb.capA + k);
-      fo[0] = fx;
-      fo[1] = fy;
-      fo[2] = fz;
-    }
+    float* fo = a.fA + 3 * sp.off;
+    fo[0] = vv * ux + (gx - rad * ux) * q.inv_r;
+    fo[1] = vv * uy + (gy - rad * uy) * q.inv_r;
+    fo[2] = vv * uz + (gz - rad * uz) * q.inv_r;
   }
 }
 
@@ -2175,12 +2302,14 @@ __device__ __forceinline__ void adjoint_body(const AdjArgs& a, int vb, float* ld
   float* ctab = lds;                     // [T][T][NA][KAP]
   float* wl = lds + CT::size;            // weights of the block's species
   float* rows = wl + weights_words(H, DP);   // [kAPB][RW]
-  stage_ctab<T, NA, KA>(ctab, a.cA);
+  stage_ctab<T, NA, KA, false>(ctab, a.cA);
   __syncthreads();
   // as in the forward: issued after the barrier, waited for before the next
-  stage_weights_async(wl, a.nn, a.nn_stride, block_species(a.order, a.type, vb), H, D, DP);
-  const GroupCtx w = group_ctx(a.order, a.type, a.Npad, vb);
-  const int N = a.N, i = w.i, I = w.I, pa = w.pa, s = w.s, g = w.g;
+  stage_weights_async(wl, a.nn, a.nn_stride, block_species<T>(a.order, a.p4, vb), H, D, DP);
+  const GroupCtx w = group_ctx(a.order, a.Npad, vb);
+  const int N = a.N, i = w.i, pa = w.pa, s = w.s, g = w.g;
+  const float4 me = a.p4[i];
+  const int I = __builtin_amdgcn_readfirstlane(packed_type<T>(me));
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = (vb * 256 + (int)threadIdx.x) / kWave;
   const bool first_atom = (lane >> 3) == 0;   // atom slot 0 of the wavefront writes the sums
@@ -2190,7 +2319,7 @@ __device__ __forceinline__ void adjoint_body(const AdjArgs& a, int vb, float* ld
   float* rowA = rowSb + NA * YR;
   const int st = a.astruct[i];
   const Cell cell = load_cell<kTri>(a.box, a.tilt, st);
-  const float xi = a.pos[i], yi = a.pos[N + i], zi = a.pos[2 * N + i];
+  const float xi = me.x, yi = me.y, zi = me.z;
   const int cR_i = a.nb.cntR[i], cA_i = a.nb.cntA[i];
   const int nR = w.valid ? min(cR_i, a.nb.capR) : 0;
   const int nA = w.valid ? min(cA_i, a.nb.capA) : 0;
@@ -3344,9 +3473,9 @@ struct Ops {
 
 template <class C>
 static size_t lds_forward(int H) {
-  const int DP = (C::D + 3) & ~3;
-  return sizeof(float) * ((size_t)CTab<C::T, C::NA, C::KA>::size + (size_t)weights_words(H, DP) +
-                          (size_t)kAPB * (DP + C::NA * HRow<C::LMAX>::YR));
+  using FL = FwdLds<C>;
+  return sizeof(float) * ((size_t)CTab<C::T, C::NA, C::KA>::size + (size_t)weights_words(H, FL::DP) +
+                          (size_t)(256 / kWave) * FL::WAVE);
 }
 template <class C>
 static size_t lds_adjoint(int H) {
@@ -3364,7 +3493,8 @@ static void allow_lds(K* k, size_t bytes) {
                               (int)bytes);
 }
 
-// the per-atom kernels are compiled for 2 and 3 wavefronts per SIMD
+// forward_waves 2 and 3 are the forward compiled for 3 and for 4 wavefronts
+// per SIMD (168 and 128 registers); the adjoint is compiled for 2 and 3
 template <class C, int W>
 static void launch_forward_w(const FwdArgs& a, dim3 grid, hipStream_t st) {
   const size_t lds = lds_forward<C>(a.H);
@@ -3381,9 +3511,9 @@ static void launch_forward(const FwdArgs& a, dim3 grid, hipStream_t st, int wave
   if constexpr (C::FIXED_WAVES != 0)
     launch_forward_w<C, C::FIXED_WAVES>(a, grid, st);
   else if (waves == 2)
-    launch_forward_w<C, 2>(a, grid, st);
-  else
     launch_forward_w<C, 3>(a, grid, st);
+  else
+    launch_forward_w<C, 4>(a, grid, st);
 }
 template <class C, bool kTri>
 static void launch_force_t(const ForceArgs& a, hipStream_t st, int lanes) {
@@ -3698,7 +3828,7 @@ struct Tune {
 };
 
 Tune default_tune(const Ops* o) {
-  return Tune{0, kOSBlocksW, kOSBlocksC, kPRChunks, kCellMinAtoms, kForceLPA, 3, o->YH > 0 ? 2 : 3};
+  return Tune{0, kOSBlocksW, kOSBlocksC, kPRChunks, kCellMinAtoms, kForceLPA, o->YH > 0 ? 2 : 3, o->YH > 0 ? 2 : 3};
 }
 
 struct Ctx {
@@ -3716,7 +3846,7 @@ struct Ctx {
   // the captured training step: Adam after the gradient, fused into its
   // final reduction
   const struct AdamFuse* adam = nullptr;
-  // the packed atoms were written by this call's own neighbor build
+  // the packed atoms of this call are in the workspace
   mutable bool packed = false;
 };
 
@@ -3830,10 +3960,7 @@ FwdArgs fwd_args(const Ctx& c, const nep_neighbors* nb, const float* params) {
   a.astruct = at<int>(c.ws, c.L.astruct);
   a.box = c.b->box;
   a.tilt = c.b->tilt;
-  a.pos = c.b->pos;
-  a.type = c.b->type;
-  a.p4 = c.packed ? at<float4>(c.ws, c.L.p4) : nullptr;
-  a.p4out = at<float4>(c.ws, c.L.p4);
+  a.p4 = at<float4>(c.ws, c.L.p4);
   a.nb = pair_lists(c, nb);
   const int T = m->n_types;
   a.cR = params;
@@ -3907,9 +4034,19 @@ void run_high(const Ctx& c, HighKernel k, const HighArgs& h, Prof* pr) {
   if (c.o->high) NEP_LAUNCH(pr, names[k], c.o->high(k, h, dim3(c.L.Npad / kAPB), c.st));
 }
 
+// packs the atoms unless this call's neighbor build did
+void run_pack(const Ctx& c, const nep_neighbors* nb, Prof* pr) {
+  const int N = c.L.N;
+  if (c.packed || N == 0) return;
+  NEP_LAUNCH(pr, "pack", hipLaunchKernelGGL(k_pack, dim3(grid1(N)), dim3(256), 0, c.st, N, c.m->n_types, c.b->pos,
+                                            c.b->type, pair_lists(c, nb), at<float4>(c.ws, c.L.p4)));
+  c.packed = true;
+}
+
 // forward pass with the degrees l > 4 around it
 void launch_forward_pass(const Ctx& c, const nep_neighbors* nb, const float* params, const FwdArgs& a, Prof* pr) {
   const HighArgs h = high_args(c, nb, params);
+  run_pack(c, nb, pr);
   run_high(c, kHighDesc, h, pr);
   NEP_LAUNCH(pr, "forward", c.o->forward(a, dim3(c.L.Npad / kAPB), c.st, c.tune.forward_waves));
   if (a.do_mlp && a.do_force) run_high(c, kHighForce, h, pr);
@@ -3984,6 +4121,7 @@ AdjArgs adj_args(const Ctx& c, const nep_neighbors* nb, const float* params, con
   a.tilt = c.b->tilt;
   a.pos = c.b->pos;
   a.type = c.b->type;
+  a.p4 = at<float4>(c.ws, c.L.p4);
   a.nb = pair_lists(c, nb);
   const int T = m->n_types;
   a.cR = params;
@@ -4537,11 +4675,11 @@ int nep_train_step_graph_create_tuned(const nep_model* m, const nep_batch* b, ne
                     d_flags};
   c.adam = &af;
   if (persistent) {
-    c.packed = (graph_flags & NEP_GRAPH_CACHED_NEIGHBORS) == 0;   // by the build launched below
     StepArgs* sa = at<StepArgs>(c.ws, c.L.sargs);
     hipLaunchKernelGGL(k_step_head, dim3(1), dim3(64), 0, cap,
                        step_args(c, nb, params, labels, lambda, loss, grad, d_flags), sa, d_flags, d_step, cur);
     if ((graph_flags & NEP_GRAPH_CACHED_NEIGHBORS) == 0) run_neighbors(c, nb, d_flags, nullptr, false);
+    run_pack(c, nb, nullptr);
     c.o->step(sa, sgrid, slds, cap);
   } else {
     hipLaunchKernelGGL(k_graph_head, dim3(1), dim3(64), 0, cap, d_flags, d_step, cur);
