@@ -251,9 +251,10 @@ __device__ __forceinline__ void high_stage(const HighArgs& a, const HighGroup& g
     if constexpr (kTan) {
       // t = (fbar_j - fbar_i) + Wbar d, as in the main adjoint
       const float* wb = a.wbar + 6 * st;
-      const float tx = (a.fbar[q.j] - a.fbar[i]) + wb[0] * q.dx + wb[3] * q.dy;
-      const float ty = (a.fbar[a.N + q.j] - a.fbar[a.N + i]) + wb[1] * q.dy + wb[4] * q.dz;
-      const float tz = (a.fbar[2 * a.N + q.j] - a.fbar[2 * a.N + i]) + wb[2] * q.dz + wb[5] * q.dx;
+      const float4 bi = a.fb4[i], bj = a.fb4[q.j];
+      const float tx = (bj.x - bi.x) + wb[0] * q.dx + wb[3] * q.dy;
+      const float ty = (bj.y - bi.y) + wb[1] * q.dy + wb[4] * q.dz;
+      const float tz = (bj.z - bi.z) + wb[2] * q.dz + wb[5] * q.dx;
       const float dt = ux * tx + uy * ty + uz * tz;
       rec[lane * R::W + R::DT] = dt;
       rec[lane * R::W + R::WX] = (tx - dt * ux) * q.inv_r;
@@ -810,9 +811,10 @@ __global__ __launch_bounds__(kWave, C::NA <= 4 ? 3 : 1) void k_high_coef(HighArg
     radial_basis_d<KA>(g.r, a.inv_rcA, f, fp);
     // t = (fbar_j - fbar_i) + Wbar d, as in the main adjoint
     const float* wb = a.wbar + 6 * g.st;
-    const float tx = (a.fbar[g.j] - a.fbar[g.i]) + wb[0] * g.dx + wb[3] * g.dy;
-    const float ty = (a.fbar[a.N + g.j] - a.fbar[a.N + g.i]) + wb[1] * g.dy + wb[4] * g.dz;
-    const float tz = (a.fbar[2 * a.N + g.j] - a.fbar[2 * a.N + g.i]) + wb[2] * g.dz + wb[5] * g.dx;
+    const float4 bi = a.fb4[g.i], bj = a.fb4[g.j];
+    const float tx = (bj.x - bi.x) + wb[0] * g.dx + wb[3] * g.dy;
+    const float ty = (bj.y - bi.y) + wb[1] * g.dy + wb[4] * g.dz;
+    const float tz = (bj.z - bi.z) + wb[2] * g.dz + wb[5] * g.dx;
     const float dt = g.ux * tx + g.uy * ty + g.uz * tz;
     const float wx = (tx - dt * g.ux) * g.ir, wy = (ty - dt * g.uy) * g.ir, wz = (tz - dt * g.uz) * g.ir;
     float X[NA], Y[NA];

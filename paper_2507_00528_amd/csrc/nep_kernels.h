@@ -76,6 +76,7 @@ struct FwdArgs {
   float* G;        // [D][Npad] species order (may be null)
   float* Guser;    // [D][N] atom order (may be null)
   float* Sst;      // [NA*YR][Npad] (may be null)
+  float* FRst;     // [T*KR][Npad] radial sums F[J][k] (may be null)
   float* Ep;       // [D][Npad] (may be null)
   float* X;        // [H][Npad] (may be null)
   float* eatom;    // [N] atom order (may be null)
@@ -109,8 +110,6 @@ struct AdjArgs {
   const int* astruct;
   const float* box;
   const float* tilt;  // null: every cell orthorhombic
-  const float* pos;
-  const int* type;
   const float4* p4;   // packed atoms
   PairLists nb;
   const float* cR;
@@ -121,14 +120,12 @@ struct AdjArgs {
   const float* Ep;    // [D][Npad]
   const float* X;     // [H][Npad]
   const float* eps;   // [S] dL/dE(n)
-  const float* fbar;  // [3][N] dL/dF
+  const float4* fb4;  // [N] dL/dF
   const float* wbar;  // [S][6] dL/dW(n)
   float* Gd;          // [D][Npad]
-  float* FRst;        // [T*KR][Npad] radial sums F[J][k]
   float* FPst;        // [T*KR][Npad] tangent sums Fp[J][k]
   float* Gbr;         // [NR][Npad] Gbar of the radial descriptors
   float* beta;        // [H][Npad]
-  float* w1s;         // [H][Npad]
   float* part;        // [n_waves][PW] wave partial sums
   int PW;
 };
@@ -152,7 +149,7 @@ struct HighArgs {
   float* Gd;          // [D][Npad] descriptor tangents
   const float* Gb;    // [D][Npad] Gbar (rows of l > 4)
   float* fA;          // [N][capA][3] angular pair forces (added to)
-  const float* fbar;  // [3][N]
+  const float4* fb4;  // [N] dL/dF
   const float* wbar;  // [S][6]
   float* part;        // [n_waves][PW] (c^A slots added to)
 };

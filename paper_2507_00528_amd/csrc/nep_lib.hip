@@ -1200,9 +1200,9 @@ struct CTab {
   static constexpr int size = T * T * NA * KAP;
 };
 
-// With kCheb, entry 0 of a row holds c_0 + sum_k c_k (the terms h T_0 of every
+// Entry 0 of a row holds c_0 + sum_k c_k (the terms h T_0 of every
 // order), so g_n = sum_k row[k] h T_k.
-template <int T, int NA, int KA, bool kCheb>
+template <int T, int NA, int KA>
 __device__ __forceinline__ void stage_ctab(float* ct, const float* __restrict__ cA) {
   constexpr int KAP = CTab<T, NA, KA>::KAP, R = T * T * NA;
   // a row per thread: its loads are in flight together
@@ -1210,11 +1210,9 @@ __device__ __forceinline__ void stage_ctab(float* ct, const float* __restrict__ 
     float v[KAP], sum = 0.f;
 #pragma unroll
     for (int k = 0; k < KAP; ++k) v[k] = k < KA ? cA[r * KA + (k < KA ? k : 0)] : 0.f;
-    if (kCheb) {
 #pragma unroll
-      for (int k = 0; k < KA; ++k) sum += v[k];
-      v[0] += sum;
-    }
+    for (int k = 0; k < KA; ++k) sum += v[k];
+    v[0] += sum;
 #pragma unroll
     for (int k = 0; k < KAP; ++k) ct[r * KAP + k] = v[k];
   }
@@ -1295,12 +1293,15 @@ __device__ __forceinline__ int packed_type(const float4& p) {
 
 // Packed atoms of a call that did not build its lists (the neighbor build
 // packs them otherwise): positions and species are the caller's at this call.
+// With fbar the caller's force cotangents are packed too.
 __global__ __launch_bounds__(256) void k_pack(int N, int T, const float* __restrict__ pos, const int* __restrict__ type,
-                                              PairLists nb, float4* __restrict__ p4) {
+                                              PairLists nb, float4* __restrict__ p4, const float* __restrict__ fbar,
+                                              float4* __restrict__ fb4) {
   const int i = blockIdx.x * 256 + threadIdx.x;
   if (i >= N) return;
   p4[i] = make_float4(pos[i], pos[N + i], pos[2 * N + i],
                       atom_word(type[i], T, nb.cntR[i] > nb.capR, nb.cntA[i] > nb.capA));
+  if (fbar) fb4[i] = make_float4(fbar[i], fbar[N + i], fbar[2 * N + i], 0.f);
 }
 
 // ========================================================= atom groups
@@ -1504,6 +1505,35 @@ __device__ __forceinline__ StreamPair stream_pair(const float* sl, int p, const 
   return r;
 }
 
+// Radial sums of an atom from its 8 lanes' partial sums v[t KR + k] over h T_k
+// (or q_k): on return o[r] of lane s holds F[t][k] of entry 8 r + s, each with
+// the T_0 term of its species added, and qn[r] holds sum_tk c^R_{ItnK} F[t][k]
+// of channel n = 8 r + s.  cRI: c^R of species I.
+template <class C>
+__device__ __forceinline__ void radial_finish(const float (&v)[C::T * C::KR], cptr<float> cRI, int s,
+                                              float (&o)[(C::T * C::KR + 7) / 8], float (&qn)[(C::NR + 7) / 8]) {
+  constexpr int T = C::T, NR = C::NR, KR = C::KR, TK = T * KR, NV = (TK + 7) / 8;
+  rs_group8(v, o);
+  float a0[T];
+#pragma unroll
+  for (int t = 0; t < T; ++t) a0[t] = __shfl(o[t * KR / 8], t * KR % 8, 8);
+  float part[NR];
+#pragma unroll
+  for (int n = 0; n < NR; ++n) part[n] = 0.f;
+#pragma unroll
+  for (int r = 0; r < NV; ++r) {
+    const int e = r * 8 + s, t = e / KR, kk = e % KR;
+    const bool on = TK % 8 == 0 || e < TK;
+#pragma unroll
+    for (int u = 0; u < T; ++u) o[r] += t == u ? a0[u] : 0.f;
+    const cptr<float> c = cRI + (on ? t * NR * KR + kk : 0);
+    const float x = on ? o[r] : 0.f;
+#pragma unroll
+    for (int n = 0; n < NR; ++n) part[n] = fmaf(c[n * KR], x, part[n]);
+  }
+  rs_group8(part, qn);
+}
+
 // LDS of the forward per wavefront: the slot table, then the pair records of
 // the angular sums (g_n and the harmonics, odd stride) and, once they are
 // summed, the atoms' rows (G, then S or A in group order; stride 4 mod 8)
@@ -1574,17 +1604,15 @@ __device__ __forceinline__ void forward_body(const FwdArgs& a, int vb, float* ld
   const int nR = w.valid ? min(cR_i, a.nb.capR) : 0;
   const int nA = w.valid ? min(cA_i, a.nb.capA) : 0;
   const cptr<float> cRI = as_const(a.cR) + (size_t)I * T * NR * KR;
-  stage_ctab<T, NA, KA, true>(ctab, a.cA);
+  stage_ctab<T, NA, KA>(ctab, a.cA);
 
   // ---- radial sums in Chebyshev space, pairs split over the 8 lanes
   constexpr int NQ = (NR + kLPA - 1) / kLPA;
   float qn[NQ];   // channels s, s + 8, ...
   {
-    float FR[T][KR];
+    float FR[T * KR];
 #pragma unroll
-    for (int t = 0; t < T; ++t)
-#pragma unroll
-      for (int k = 0; k < KR; ++k) FR[t][k] = 0.f;
+    for (int e = 0; e < T * KR; ++e) FR[e] = 0.f;
     // the next pair's atom and the list entry after it are loaded ahead
     const uint32_t* li = a.nb.idxR + (size_t)i * a.nb.capR;
     uint32_t e0 = 0, e1 = 0;
@@ -1608,28 +1636,17 @@ __device__ __forceinline__ void forward_body(const FwdArgs& a, int vb, float* ld
       for (int t = 0; t < T; ++t) {
         const float m = (T == 1 || J == t) ? 1.f : 0.f;
 #pragma unroll
-        for (int kk = 0; kk < KR; ++kk) FR[t][kk] = fmaf(m, f[kk], FR[t][kk]);
+        for (int kk = 0; kk < KR; ++kk) FR[t * KR + kk] = fmaf(m, f[kk], FR[t * KR + kk]);
       }
     }
-    // the basis sums over the 8 lanes, then q_n = sum c^R F by lane n & 7
+    float o[(T * KR + 7) / 8];
+    radial_finish<C>(FR, cRI, s, o, qn);
+    if (a.FRst && w.valid) {
 #pragma unroll
-    for (int t = 0; t < T; ++t) {
-#pragma unroll
-      for (int k = 0; k < KR; ++k) FR[t][k] = grp8_sum(FR[t][k]);
-      const float A0 = FR[t][0];
-#pragma unroll
-      for (int k = 0; k < KR; ++k) FR[t][k] += A0;
-    }
-#pragma unroll
-    for (int r = 0; r < NQ; ++r) {
-      const int n = r * kLPA + s;
-      const cptr<float> cn = cRI + (n < NR ? n : 0) * KR;
-      float acc = 0.f;
-#pragma unroll
-      for (int t = 0; t < T; ++t)
-#pragma unroll
-        for (int k = 0; k < KR; ++k) acc = fmaf(cn[t * NR * KR + k], FR[t][k], acc);
-      qn[r] = acc;
+      for (int r = 0; r < (T * KR + 7) / 8; ++r) {
+        const int e = r * kLPA + s;
+        if (T * KR % 8 == 0 || e < T * KR) a.FRst[(size_t)e * a.Npad + pa] = o[r];
+      }
     }
   }
 
@@ -2125,7 +2142,7 @@ struct StructArgs {
   float* Ws_user;
   float* eps;
   float* wbar;
-  float* fbar;
+  float4* fb4;
   double* lpart;  // [S][3]
   // structures of at least 2 kStructChunk atoms are summed from chunk partials
   int split;
@@ -2144,7 +2161,7 @@ __device__ __forceinline__ int find_struct(const int* __restrict__ aoff, int S, 
 }
 
 // Sums over atoms [lo, hi) of one structure: energy, the six virial
-// components and the squared force error (acc[0..7]); writes F-bar.
+// components and the squared force error (acc[0..7]); writes the packed F-bar.
 __device__ __forceinline__ void struct_accumulate(const StructArgs& a, int lo, int hi, double* acc) {
   const int N = a.N;
   const bool lab = a.Et != nullptr;
@@ -2154,12 +2171,13 @@ __device__ __forceinline__ void struct_accumulate(const StructArgs& a, int lo, i
 #pragma unroll
     for (int c = 0; c < 6; ++c) acc[1 + c] += a.wv[(size_t)c * N + i];
     if (lab) {
+      float d[3];
 #pragma unroll
       for (int c = 0; c < 3; ++c) {
-        const float d = a.F[(size_t)c * N + i] - a.Ft[(size_t)c * N + i];
-        acc[7] += (double)d * d;
-        a.fbar[(size_t)c * N + i] = cf * d;
+        d[c] = a.F[(size_t)c * N + i] - a.Ft[(size_t)c * N + i];
+        acc[7] += (double)d[c] * d[c];
       }
+      a.fb4[i] = make_float4(cf * d[0], cf * d[1], cf * d[2], 0.f);
     }
   }
 }
@@ -2286,35 +2304,83 @@ __global__ __launch_bounds__(kRedBlk) void k_loss_final(int S, int N, float le, 
 // Outputs: per-atom vectors for the outer-product sums (W0, c^R) and, per
 // wavefront, the sums of the c^A, b0, w1, b1 partials over its 8 atoms.
 // Block vb (32 atoms of the species order); lds: lds_adjoint bytes.
+// Slot table of the adjoint: the forward's words, then F-bar and Gamma.
+constexpr int kSlotF = 12, kSlotG = 16, kSlotG2 = 20, kAdjSlot = 28;   // 4 mod 8
+
+// LDS of the adjoint per wavefront: the slot table, then the pair records of
+// the tangent sums (g_n and g'_n (u.t) interleaved, then B and grad B . t of
+// one harmonic group interleaved; odd stride) and, once they are summed, the
+// atoms' rows (Gdot or Gbar, Sdot or Sbar, S or A in group order; stride 4 mod 8).
+// Per block: the coefficient table and the weights, whose words hold the
+// coefficient gradient's records (16 pairs per wavefront) after the network.
+template <class C>
+struct AdjLds {
+  static constexpr int DP = (C::D + 3) & ~3, YG = HSplit<C::LMAX>::YG, YR = HRow<C::LMAX>::YR;
+  static constexpr int RS = (2 * C::NA + 2 * YG) | 1;
+  static constexpr int RW = (DP + 2 * C::NA * YR + 7) / 8 * 8 + 4;
+  static constexpr int BUF = ((kWave * RS > kAPW * RW ? kWave * RS : kAPW * RW) + 3) & ~3;
+  static constexpr int WAVE = kAPW * kAdjSlot + BUF;
+  static constexpr int REC = (2 * C::NA + 2 * C::KA + 1) | 1;   // X, Y (u.t), h T_k, q_k, species
+  static constexpr int RECS = (256 / kWave) * 16 * REC;
+  __host__ __device__ static int shared_words(int H) {
+    const int w = weights_words(H, DP);
+    return ((w > RECS ? w : RECS) + 3) & ~3;
+  }
+};
+
+struct PairTangent {
+  float ux, uy, uz, dt, wx, wy, wz;   // direction, u.t, (t - (u.t) u) / r
+};
+__device__ __forceinline__ PairTangent pair_tangent(const PairGeom& q, const float* sl, const float4& fj) {
+  const float4 fi = *reinterpret_cast<const float4*>(sl + kSlotF);
+  const float4 g = *reinterpret_cast<const float4*>(sl + kSlotG);      // xx yy zz xy
+  const float4 g2 = *reinterpret_cast<const float4*>(sl + kSlotG2);    // yz zx
+  PairTangent t;
+  t.ux = q.dx * q.inv_r;
+  t.uy = q.dy * q.inv_r;
+  t.uz = q.dz * q.inv_r;
+  const float tx = (fj.x - fi.x) + g.x * q.dx + g.w * q.dy;
+  const float ty = (fj.y - fi.y) + g.y * q.dy + g2.x * q.dz;
+  const float tz = (fj.z - fi.z) + g.z * q.dz + g2.y * q.dx;
+  t.dt = t.ux * tx + t.uy * ty + t.uz * tz;
+  t.wx = (tx - t.dt * t.ux) * q.inv_r;
+  t.wy = (ty - t.dt * t.uy) * q.inv_r;
+  t.wz = (tz - t.dt * t.uz) * q.inv_r;
+  return t;
+}
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
 template <class C, bool kTri>
 __device__ __forceinline__ void adjoint_body(const AdjArgs& a, int vb, float* lds) {
   constexpr int T = C::T, NR = C::NR, NA = C::NA, KR = C::KR, KA = C::KA, Y = C::Y, D = C::D, LM = C::LMAX;
   constexpr int L3 = C::L3, L4 = C::L4, L5 = C::L5;
   using HS = HSplit<LM>;
-  constexpr int YG = HS::YG;
-  constexpr int DP = (D + 3) & ~3;
-  constexpr int NAH = (NA + 1) / 2;          // channels per lane in the coefficient pass
-  constexpr int YR = HRow<LM>::YR;
-  constexpr int RW = DP + 2 * NA * YR;       // LDS row per atom: Gdot, Sbar, A (group order)
+  using AL = AdjLds<C>;
+  constexpr int YG = AL::YG, YR = AL::YR, DP = AL::DP, RS = AL::RS, RW = AL::RW;
+  constexpr int NAH = (NA + 1) / 2;          // channels per lane in the tangent sums
+  constexpr int NEH = (YG + 3) / 4;          // harmonics of a group per lane there
+  constexpr int NE = (YR + kLPA - 1) / kLPA, NN = (NA + 3) / 4;
   constexpr int PSA = T * NA * KA;
+  constexpr bool kVec = YR % 4 == 0;
   const int H = a.H;
   using CT = CTab<T, NA, KA>;
   float* ctab = lds;                     // [T][T][NA][KAP]
   float* wl = lds + CT::size;            // weights of the block's species
-  float* rows = wl + weights_words(H, DP);   // [kAPB][RW]
-  stage_ctab<T, NA, KA, false>(ctab, a.cA);
-  __syncthreads();
-  // as in the forward: issued after the barrier, waited for before the next
+  float* slots = wl + AL::shared_words(H) + (threadIdx.x / kWave) * AL::WAVE;
+  float* buf = slots + kAPW * kAdjSlot;
+  // as in the forward: issued here, waited for after the tangent sums
   stage_weights_async(wl, a.nn, a.nn_stride, block_species<T>(a.order, a.p4, vb), H, D, DP);
   const GroupCtx w = group_ctx(a.order, a.Npad, vb);
-  const int N = a.N, i = w.i, pa = w.pa, s = w.s, g = w.g;
+  const int i = w.i, pa = w.pa, s = w.s, g = w.g;
+  const size_t Np = a.Npad;
   const float4 me = a.p4[i];
   const int I = __builtin_amdgcn_readfirstlane(packed_type<T>(me));
-  const int lane = threadIdx.x & (kWave - 1);
+  const int lane = threadIdx.x & (kWave - 1), slot = lane / kLPA;
   const int wave = (vb * 256 + (int)threadIdx.x) / kWave;
-  const bool first_atom = (lane >> 3) == 0;   // atom slot 0 of the wavefront writes the sums
+  const bool first_atom = slot == 0;   // atom slot 0 of the wavefront writes the sums
   float* part = a.part + (size_t)wave * a.PW;
-  float* row = rows + w.al * RW;
+  float* row = buf + slot * RW;
   float* rowSb = row + DP;
   float* rowA = rowSb + NA * YR;
   const int st = a.astruct[i];
@@ -2328,244 +2394,292 @@ __device__ __forceinline__ void adjoint_body(const AdjArgs& a, int vb, float* ld
   const float eps = w.valid ? eps_v : 0.f;
   const float* wb = a.wbar + 6 * st;
   const float gxx = wb[0], gyy = wb[1], gzz = wb[2], gxy = wb[3], gyz = wb[4], gzx = wb[5];
-  const float fbx = a.fbar[i], fby = a.fbar[N + i], fbz = a.fbar[2 * N + i];
+  const float4 fi = a.fb4[i];
+  const float fbx = fi.x, fby = fi.y, fbz = fi.z;
+  stage_ctab<T, NA, KA>(ctab, a.cA);
 
-  // ---- radial tangent pass, pairs split over the 8 lanes
-  float FR[T][KR], FP[T][KR];
+  // ---- radial tangent sums Fp[J][k] = sum_j f'_k(r_hat.t), pairs split over the 8 lanes
+  constexpr int NQ = (NR + kLPA - 1) / kLPA;
+  float qn[NQ];
+  {
+    float FP[T * KR];
 #pragma unroll
-  for (int t = 0; t < T; ++t)
+    for (int e = 0; e < T * KR; ++e) FP[e] = 0.f;
+    // the next pair's atom and the list entry after it are loaded ahead
+    const uint32_t* li = a.nb.idxR + (size_t)i * a.nb.capR;
+    uint32_t e0 = 0, e1 = 0;
+    float4 p0 = make_float4(0.f, 0.f, 0.f, 0.f), f0 = p0;
+    if (s < nR) {
+      e0 = li[s];
+      e1 = li[min(s + kLPA, nR - 1)];
+      p0 = a.p4[e0 >> 5];
+      f0 = a.fb4[e0 >> 5];
+    }
+    for (int k = s; k < nR; k += kLPA) {
+      const uint32_t e = e0;
+      const float4 pj = p0, fj = f0;
+      e0 = e1;
+      p0 = a.p4[e1 >> 5];
+      f0 = a.fb4[e1 >> 5];
+      e1 = li[min(k + 2 * kLPA, nR - 1)];
+      const PairGeom q = packed_geom<kTri>(e, pj, xi, yi, zi, cell);
+      const float tx = (fj.x - fbx) + gxx * q.dx + gxy * q.dy;
+      const float ty = (fj.y - fby) + gyy * q.dy + gyz * q.dz;
+      const float tz = (fj.z - fbz) + gzz * q.dz + gzx * q.dx;
+      const float dt = (q.dx * tx + q.dy * ty + q.dz * tz) * q.inv_r;
+      float t[KR], fp[KR];
+      radial_cheb_d<KR>(q.r, a.inv_rcR, t, fp);
+      const int J = packed_type<T>(pj);
 #pragma unroll
-    for (int k = 0; k < KR; ++k) FR[t][k] = FP[t][k] = 0.f;
-  for (int k = s; k < nR; k += kLPA) {
-    const PairGeom q = pair_geom<kTri>(a.nb.idxR[(size_t)i * a.nb.capR + k], a.pos, N, xi, yi, zi, cell);
-    const float tx = (a.fbar[q.j] - fbx) + gxx * q.dx + gxy * q.dy;
-    const float ty = (a.fbar[N + q.j] - fby) + gyy * q.dy + gyz * q.dz;
-    const float tz = (a.fbar[2 * N + q.j] - fbz) + gzz * q.dz + gzx * q.dx;
-    const float dt = (q.dx * tx + q.dy * ty + q.dz * tz) * q.inv_r;
-    float f[KR], fp[KR];
-    radial_basis_d<KR>(q.r, a.inv_rcR, f, fp);
-    const int J = a.type[q.j];
+      for (int u = 0; u < T; ++u) {
+        const float md = (T == 1 || J == u) ? dt : 0.f;
 #pragma unroll
-    for (int t = 0; t < T; ++t) {
-      const float m = (T == 1 || J == t) ? 1.f : 0.f;
-      const float md = m * dt;
+        for (int kk = 0; kk < KR; ++kk) FP[u * KR + kk] = fmaf(md, fp[kk], FP[u * KR + kk]);
+      }
+    }
+    float o[(T * KR + 7) / 8];
+    radial_finish<C>(FP, cRI, s, o, qn);
+    if (w.valid) {
 #pragma unroll
-      for (int kk = 0; kk < KR; ++kk) {
-        FR[t][kk] = fmaf(m, f[kk], FR[t][kk]);
-        FP[t][kk] = fmaf(md, fp[kk], FP[t][kk]);
+      for (int r = 0; r < (T * KR + 7) / 8; ++r) {
+        const int e = r * kLPA + s;
+        if (T * KR % 8 == 0 || e < T * KR) a.FPst[(size_t)e * Np + pa] = o[r];
       }
     }
   }
-#pragma unroll
-  for (int t = 0; t < T; ++t)
-#pragma unroll
-    for (int k = 0; k < KR; ++k) {
-      FR[t][k] = grp8_sum(FR[t][k]);
-      FP[t][k] = grp8_sum(FP[t][k]);
-      const int e = t * KR + k;
-      if (w.valid && s == (e & 7)) {
-        a.FRst[(size_t)e * a.Npad + pa] = FR[t][k];
-        a.FPst[(size_t)e * a.Npad + pa] = FP[t][k];
-      }
-    }
-  // every lane holds the sums: lane s takes channels n = s, s + 8, ... at once
-#pragma unroll
-  for (int n0 = 0; n0 < NR; n0 += kLPA) {
-    const int n = n0 + s;
-    if (n < NR) {
-      const cptr<float> cn = cRI + n * KR;
-      float acc = 0.f;
-#pragma unroll
-      for (int t = 0; t < T; ++t)
-#pragma unroll
-        for (int k = 0; k < KR; ++k) acc = fmaf(cn[t * NR * KR + k], FP[t][k], acc);
-      row[n] = acc;
-    }
-  }
 
-  // ---- angular tangent pass: Sdot_nlm = sum_j g'_n (r_hat.t) B_lm + g_n grad B_lm . t
-  float Sd[NA][YG];
+  // ---- angular tangent sums Sdot_nlm = sum_j g'_n (r_hat.t) B_lm + g_n grad B_lm . t:
+  //      one pair per lane writes them for one harmonic group at a time; lane s
+  //      of an atom then sums its pairs for channels (s >> 2) NAH + j and the
+  //      harmonics (s & 3) NEH + e of the group
+  const PairStream ps = pair_stream(nA);
+  if (s == 0) {
+    float* sl = slots + slot * kAdjSlot;
+    slot_store<kTri>(sl, i, xi, yi, zi, cell, ps.lo);
+    *reinterpret_cast<float4*>(sl + kSlotF) = fi;
+    *reinterpret_cast<float4*>(sl + kSlotG) = make_float4(gxx, gyy, gzz, gxy);
+    *reinterpret_cast<float4*>(sl + kSlotG2) = make_float4(gyz, gzx, 0.f, 0.f);
+  }
+  // S of the forward, entries s, s + 8, ... of every channel, for the rows
+  float Sr[NE][NA];
 #pragma unroll
-  for (int n = 0; n < NA; ++n)
-#pragma unroll
-    for (int e = 0; e < YG; ++e) Sd[n][e] = 0.f;
-  for (int k = w.p; k < nA; k += 4) {
-    const PairGeom q = pair_geom<kTri>(a.nb.idxA[(size_t)i * a.nb.capA + k], a.pos, N, xi, yi, zi, cell);
-    const float ux = q.dx * q.inv_r, uy = q.dy * q.inv_r, uz = q.dz * q.inv_r;
-    const float tx = (a.fbar[q.j] - fbx) + gxx * q.dx + gxy * q.dy;
-    const float ty = (a.fbar[N + q.j] - fby) + gyy * q.dy + gyz * q.dz;
-    const float tz = (a.fbar[2 * N + q.j] - fbz) + gzz * q.dz + gzx * q.dx;
-    const float dt = ux * tx + uy * ty + uz * tz;
-    float f[KA], fp[KA];
-    radial_basis_d<KA>(q.r, a.inv_rcA, f, fp);
-    const int J = a.type[q.j];
-    const float* cJ = ctab + (I * T + J) * NA * CT::KAP;
-    float gn[NA], gpd[NA];
+  for (int r = 0; r < NE; ++r)
 #pragma unroll
     for (int n = 0; n < NA; ++n) {
-      float s0 = 0.f, s1 = 0.f;
+      const int e = r * kLPA + s;
+      const float v = a.Sst[(size_t)(n * YR + (YR % kLPA == 0 || e < YR ? e : 0)) * Np + pa];
+      Sr[r][n] = w.valid ? v : 0.f;
+    }
+  lds_barrier();   // the block's coefficient table
+  {
+    const int n0 = (s >> 2) * NAH, h0 = (s & 3) * NEH;
+    float Sd[2][NEH][NAH];
 #pragma unroll
-      for (int kk = 0; kk < KA; ++kk) {
-        const float c = cJ[n * CT::KAP + kk];
-        s0 = fmaf(c, f[kk], s0);
-        s1 = fmaf(c, fp[kk], s1);
+    for (int gg = 0; gg < 2; ++gg)
+#pragma unroll
+      for (int e = 0; e < NEH; ++e)
+#pragma unroll
+        for (int j = 0; j < NAH; ++j) Sd[gg][e][j] = 0.f;
+    for (int c0 = 0; c0 < ps.total; c0 += kWave) {
+      const int p = c0 + lane;
+      const bool on = p < ps.total;
+      float B[Y], gbt[Y];
+      float* rec = buf + lane * RS;
+      if (on) {
+        const float* sl = slots + pair_slot(ps, p) * kAdjSlot;
+        const StreamPair sp = stream_pair<T, kTri>(sl, p, a.nb, a.p4);
+        const PairTangent t = pair_tangent(sp.q, sl, a.fb4[sp.q.j]);
+        float f[KA], fp[KA];
+        radial_cheb_d<KA>(sp.q.r, a.inv_rcA, f, fp);
+        const float* cJ = ctab + (I * T + sp.J) * NA * CT::KAP;
+#pragma unroll
+        for (int n = 0; n < NA; ++n) {
+          float s0 = 0.f, s1 = 0.f;
+#pragma unroll
+          for (int kk = 0; kk < KA; ++kk) {
+            const float c = cJ[n * CT::KAP + kk];
+            s0 = fmaf(c, f[kk], s0);
+            s1 = fmaf(c, fp[kk], s1);
+          }
+          rec[2 * n] = s0;
+          rec[2 * n + 1] = s1 * t.dt;
+        }
+        harm_val<LM>(t.ux, t.uy, t.uz, B);
+        // grad B . t = grad b(u) . (t - (u.t) u) / r
+        harm_dir<LM>(t.ux, t.uy, t.uz, t.wx, t.wy, t.wz, gbt);
       }
-      gn[n] = s0;
-      gpd[n] = s1 * dt;
-    }
-    float B[Y], gbt[Y];
-    harm_val<LM>(ux, uy, uz, B);
-    // grad B . t = grad b(u) . (t - (u.t) u) / r
-    harm_dir<LM>(ux, uy, uz, (tx - dt * ux) * q.inv_r, (ty - dt * uy) * q.inv_r, (tz - dt * uz) * q.inv_r, gbt);
 #pragma unroll
-    for (int e = 0; e < YG; ++e) {
-      const float b = hsel<HS, Y>(g, e, B), c = hsel<HS, Y>(g, e, gbt);
+      for (int gg = 0; gg < 2; ++gg) {
+        if (on) {
 #pragma unroll
-      for (int n = 0; n < NA; ++n) Sd[n][e] = fmaf(gpd[n], b, fmaf(gn[n], c, Sd[n][e]));
+          for (int e = 0; e < YG; ++e) {
+            const int q = HS::q(gg, e);
+            rec[2 * NA + 2 * e] = q >= 0 ? B[q >= 0 ? q : 0] : 0.f;
+            rec[2 * NA + 2 * e + 1] = q >= 0 ? gbt[q >= 0 ? q : 0] : 0.f;
+          }
+        }
+        lds_lane_exchange();
+        const int t1 = min(ps.hi - c0, kWave);
+#pragma unroll 2
+        for (int t = max(ps.lo - c0, 0); t < t1; ++t) {
+          const float* rp = buf + t * RS;
+          float gn[NAH], gp[NAH];
+#pragma unroll
+          for (int j = 0; j < NAH; ++j) {
+            const int n = min(n0 + j, NA - 1);   // an odd channel count repeats the last, unused
+            gn[j] = rp[2 * n];
+            gp[j] = rp[2 * n + 1];
+          }
+#pragma unroll
+          for (int e = 0; e < NEH; ++e) {
+            const int q = YG % 4 == 0 ? h0 + e : min(h0 + e, YG - 1);
+            const float b = rp[2 * NA + 2 * q], c = rp[2 * NA + 2 * q + 1];
+#pragma unroll
+            for (int j = 0; j < NAH; ++j) Sd[gg][e][j] = fmaf(gp[j], b, fmaf(gn[j], c, Sd[gg][e][j]));
+          }
+        }
+        lds_lane_exchange();
+      }
     }
+    wait_weights();   // before the stores below, as in the forward
+    // the atoms' rows take the records' place
+#pragma unroll
+    for (int gg = 0; gg < 2; ++gg)
+#pragma unroll
+      for (int e = 0; e < NEH; ++e)
+#pragma unroll
+        for (int j = 0; j < NAH; ++j)
+          if (n0 + j < NA && (YG % 4 == 0 || h0 + e < YG)) rowSb[(n0 + j) * YR + gg * YG + h0 + e] = Sd[gg][e][j];
   }
 #pragma unroll
-  for (int n = 0; n < NA; ++n)
+  for (int r = 0; r < NE; ++r)
+    if (YR % kLPA == 0 || r * kLPA + s < YR)
 #pragma unroll
-    for (int e = 0; e < YG; ++e) Sd[n][e] = quad_sum(Sd[n][e]);
+      for (int n = 0; n < NA; ++n) rowA[n * YR + r * kLPA + s] = Sr[r][n];
+#pragma unroll
+  for (int r = 0; r < NQ; ++r)
+    if (r * kLPA + s < NR) row[r * kLPA + s] = qn[r];
+  lds_lane_exchange();
 
-  // ---- Gdot of the angular descriptors.  Sdot is parked in the atom's LDS
-  //      row; channel n is then handled by the lanes of pair slot n mod 4
-  //      (both harmonic groups), which also park S (stored by the forward
-  //      pass) for the later phases
-  {
-    const int nAg = g ? HS::nA1 : HS::nA0;
-    const int lA = g ? 2 : 1, lB = g ? 3 : 4;
+  // ---- Gdot of the angular descriptors, channel n and harmonic group g by the
+  //      lane of pair slot n mod 4 and group g
+  const int nAg = g ? HS::nA1 : HS::nA0;
+  const int lA = g ? 2 : 1, lB = g ? 3 : 4;
+  const int lAc = lA <= L3 ? lA : 1, lBc = lB <= L3 ? lB : 1;
+  for (int n = w.p; n < NA; n += 4) {
+    float Sn[YG], Sdn[YG];
+    row_load<YG, kVec>(rowA + n * YR + g * YG, Sn);
+    row_load<YG, kVec>(rowSb + n * YR + g * YG, Sdn);
+    float qa = 0.f, qb = 0.f;
 #pragma unroll
-    for (int n = 0; n < NA; ++n)
-      if (w.p == (n & 3)) {
-#pragma unroll
-        for (int e = 0; e < YG; ++e) rowSb[n * YR + g * YG + e] = Sd[n][e];   // zero at padding entries
-      }
-    lds_lane_exchange();
-    for (int n = w.p; n < NA; n += 4) {
-      float Sn[YG], Sdn[YG];
-#pragma unroll
-      for (int e = 0; e < YG; ++e) {
-        // unconditional loads, then the mask: a guarded load would become a
-        // branch that waits for each value in turn
-        const float v = a.Sst[(size_t)(n * YR + g * YG + e) * a.Npad + pa];
-        Sn[e] = w.valid ? v : 0.f;
-        Sdn[e] = rowSb[n * YR + g * YG + e];
-      }
-      float qa = 0.f, qb = 0.f;
-#pragma unroll
-      for (int e = 0; e < YG; ++e) {
-        const float v = 2.0f * csel<HS>(g, e) * Sn[e] * Sdn[e];
-        if (e < nAg) qa += v; else qb += v;
-      }
-      if (lA <= L3) row[NR + (lA - 1) * NA + n] = qa;
-      if (lB <= L3) row[NR + (lB - 1) * NA + n] = qb;
-      if constexpr (L4 != 0) {
-        const Sym3 M = sym_of(Sn[0], Sn[1], Sn[2], Sn[3], Sn[4]);
-        const Sym3 Md = sym_of(Sdn[0], Sdn[1], Sdn[2], Sdn[3], Sdn[4]);
-        const float v = 3.0f * sym_dot(sym_mul(M, M), Md);
-        if (g == 1) row[NR + L3 * NA + n] = v;
-      }
-      if constexpr (L5 != 0) {
-        const float P = Sn[0] * Sn[0] + Sn[1] * Sn[1] + Sn[2] * Sn[2];
-        const float SS = Sn[0] * Sdn[0] + Sn[1] * Sdn[1] + Sn[2] * Sdn[2];
-        if (g == 0) row[NR + L3 * NA + (L4 ? NA : 0) + n] = 4.0f * P * SS;
-      }
-#pragma unroll
-      for (int e = 0; e < YG; ++e) rowA[n * YR + g * YG + e] = Sn[e];
+    for (int e = 0; e < YG; ++e) {
+      const float v = 2.0f * csel<HS>(g, e) * Sn[e] * Sdn[e];
+      if (e < nAg) qa += v; else qb += v;
+    }
+    if (lA <= L3) row[NR + (lA - 1) * NA + n] = qa;
+    if (lB <= L3) row[NR + (lB - 1) * NA + n] = qb;
+    if constexpr (L4 != 0) {
+      const Sym3 M = sym_of(Sn[0], Sn[1], Sn[2], Sn[3], Sn[4]);
+      const Sym3 Md = sym_of(Sdn[0], Sdn[1], Sdn[2], Sdn[3], Sdn[4]);
+      const float v = 3.0f * sym_dot(sym_mul(M, M), Md);
+      if (g == 1) row[NR + L3 * NA + n] = v;
+    }
+    if constexpr (L5 != 0) {
+      const float P = Sn[0] * Sn[0] + Sn[1] * Sn[1] + Sn[2] * Sn[2];
+      const float SS = Sn[0] * Sdn[0] + Sn[1] * Sdn[1] + Sn[2] * Sdn[2];
+      if (g == 0) row[NR + L3 * NA + (L4 ? NA : 0) + n] = 4.0f * P * SS;
     }
   }
   if constexpr (C::YH > 0) {
     // Gdot of q_nl, l = 5..L3, from k_high_tangent
     for (int v = NR + 4 * NA + s; v < NR + L3 * NA; v += kLPA) {
-      const float x = a.Gd[(size_t)v * a.Npad + pa];
+      const float x = a.Gd[(size_t)v * Np + pa];
       row[v] = w.valid ? x : 0.f;
     }
   }
-  wait_weights();   // this wavefront's weight loads have landed; the barrier covers the others'
-  __syncthreads();
-  float Gd[D];
+  lds_barrier();
+  float Gd[DP];
+  row_load<DP, true>(row, Gd);   // words past D are not used
+  if (w.valid) {
 #pragma unroll
-  for (int v = 0; v < D; ++v) {
-    Gd[v] = row[v];
-    if (w.valid && s == (v & 7)) a.Gd[(size_t)v * a.Npad + pa] = Gd[v];
+    for (int r = 0; r < (D + kLPA - 1) / kLPA; ++r) {
+      const int v = r * kLPA + s;
+      if (D % kLPA == 0 || v < D) a.Gd[(size_t)v * Np + pa] = row[v];
+    }
+  }
+  // E' of the descriptors this lane's Sbar and A need, loaded ahead of the network
+  float epA[NN], epB[NN], ep4[NN], ep5[NN];
+#pragma unroll
+  for (int r = 0; r < NN; ++r) {
+    const int n = min(w.p + 4 * r, NA - 1);
+    epA[r] = a.Ep[(size_t)(NR + (lAc - 1) * NA + n) * Np + pa];
+    epB[r] = a.Ep[(size_t)(NR + (lBc - 1) * NA + n) * Np + pa];
+    ep4[r] = L4 ? a.Ep[(size_t)(NR + L3 * NA + n) * Np + pa] : 0.f;
+    ep5[r] = L5 ? a.Ep[(size_t)(NR + L3 * NA + (L4 ? NA : 0) + n) * Np + pa] : 0.f;
   }
 
   // ---- network adjoint, hidden units mu = s, s+8, ...
   const float* Wl = wl;
-  float Gb[D];
-#pragma unroll
-  for (int v = 0; v < D; ++v) Gb[v] = 0.f;
-  const int RH = (H + kLPA - 1) / kLPA;
-  for (int r = 0; r < RH; ++r) {
-    const int mu = r * kLPA + s;
-    const bool act = mu < H;
-    const int mm = act ? mu : H - 1;
-    const float* wr = Wl + mm * DP;
-    float aa = 0.f;
-#pragma unroll
-    for (int v = 0; v < D; ++v) aa = fmaf(wr[v], Gd[v], aa);
-    const bool live = act && w.valid;
-    const float xv = a.X[(size_t)mm * a.Npad + pa];
-    const float x = live ? xv : 0.f;
-    const float sg = 1.0f - x * x;
-    const float ws = Wl[H * DP + H + mm] * sg;
-    const float be = live ? ws * (eps + 2.0f * x * aa) : 0.f;
-#pragma unroll
-    for (int v = 0; v < D; ++v) Gb[v] = fmaf(be, wr[v], Gb[v]);
-    if (live) {
-      a.beta[(size_t)mu * a.Npad + pa] = be;
-      a.w1s[(size_t)mu * a.Npad + pa] = ws;
-    }
-    const float r0 = atoms8_sum(be);
-    const float r1 = atoms8_sum(live ? eps * x - sg * aa : 0.f);
-    if (act && first_atom) {
-      part[PSA + mu] = r0;
-      part[PSA + H + mu] = r1;
-    }
-  }
-#pragma unroll
-  for (int v = 0; v < D; ++v) Gb[v] = grp8_sum(Gb[v]);
   {
-    const float r = atoms8_sum(s == 0 ? eps : 0.f);
-    if (lane == 0) part[PSA + 2 * H] = r;
-  }
+    float Gb[D];
 #pragma unroll
-  for (int n = 0; n < NR; ++n)
-    if (w.valid && s == (n & 7)) a.Gbr[(size_t)n * a.Npad + pa] = Gb[n];
-  if constexpr (C::YH > 0) {
-    // Gbar of q_nl, l = 5..L3, for k_high_coef (the rows hold D entries)
+    for (int v = 0; v < D; ++v) Gb[v] = 0.f;
+    const int RH = (H + kLPA - 1) / kLPA;
+    for (int r = 0; r < RH; ++r) {
+      const int mu = r * kLPA + s;
+      const bool act = mu < H;
+      const int mm = act ? mu : H - 1;
+      const float* wr = Wl + mm * DP;
+      const float xv = a.X[(size_t)mm * Np + pa];
+      float aa = 0.f;
 #pragma unroll
-    for (int v = NR + 4 * NA; v < NR + L3 * NA; ++v)
-      if (w.valid && s == (v & 7)) a.Gbr[(size_t)v * a.Npad + pa] = Gb[v];
-  }
-
-  // ---- Sbar and A of this lane's harmonic group, in place in the atom's LDS
-  //      row, channel n by the lanes of pair slot n mod 4; Gbar goes to the
-  //      row's first D floats (Gdot there has been read)
+      for (int v = 0; v < D; ++v) aa = fmaf(wr[v], Gd[v], aa);
+      const bool live = act && w.valid;
+      const float x = live ? xv : 0.f;
+      const float sg = 1.0f - x * x;
+      const float ws = Wl[H * DP + H + mm] * sg;
+      const float be = live ? ws * (eps + 2.0f * x * aa) : 0.f;
 #pragma unroll
-  for (int v = 0; v < D; ++v)
-    if (s == (v & 7)) row[v] = Gb[v];
-  lds_lane_exchange();
-  {
-    const int nAg = g ? HS::nA1 : HS::nA0;
-    const int lA = g ? 2 : 1, lB = g ? 3 : 4;
-    const int lAc = lA <= L3 ? lA : 1, lBc = lB <= L3 ? lB : 1;
-    const size_t Np = a.Npad;
-    for (int n = w.p; n < NA; n += 4) {
-      float Sn[YG], Sdn[YG];
-#pragma unroll
-      for (int e = 0; e < YG; ++e) {
-        Sn[e] = rowA[n * YR + g * YG + e];
-        Sdn[e] = rowSb[n * YR + g * YG + e];
+      for (int v = 0; v < D; ++v) Gb[v] = fmaf(be, wr[v], Gb[v]);
+      if (live) a.beta[(size_t)mu * Np + pa] = be;
+      const float r0 = atoms8_sum(be);
+      const float r1 = atoms8_sum(live ? eps * x - sg * aa : 0.f);
+      if (act && first_atom) {
+        part[PSA + mu] = r0;
+        part[PSA + H + mu] = r1;
       }
+    }
+    {
+      const float r = atoms8_sum(s == 0 ? eps : 0.f);
+      if (lane == 0) part[PSA + 2 * H] = r;
+    }
+    // Gbar to the row's first D words (Gdot there has been read)
+    float go[(D + 7) / 8];
+    rs_group8(Gb, go);
+#pragma unroll
+    for (int r = 0; r < (D + kLPA - 1) / kLPA; ++r) {
+      const int v = r * kLPA + s;
+      if (D % kLPA == 0 || v < D) {
+        row[v] = go[r];
+        // radial rows for the c^R gradient; l = 5..L3 for k_high_coef (the rows hold D entries)
+        if (w.valid && (v < NR || (C::YH > 0 && v >= NR + 4 * NA && v < NR + L3 * NA))) a.Gbr[(size_t)v * Np + pa] = go[r];
+      }
+    }
+  }
+  lds_lane_exchange();
+
+  // ---- Sbar and A of this lane's harmonic group, in place of Sdot and S
+#pragma unroll
+  for (int r = 0; r < NN; ++r) {
+    const int n = w.p + 4 * r;
+    if (n < NA) {
+      float Sn[YG], Sdn[YG];
+      row_load<YG, kVec>(rowA + n * YR + g * YG, Sn);
+      row_load<YG, kVec>(rowSb + n * YR + g * YG, Sdn);
       // E' and Gbar of the descriptors built from these sums
-      const float vA = a.Ep[(size_t)(NR + (lAc - 1) * NA + n) * Np + pa];
-      const float vB = a.Ep[(size_t)(NR + (lBc - 1) * NA + n) * Np + pa];
       const float bA = row[NR + (lAc - 1) * NA + n], bB = row[NR + (lBc - 1) * NA + n];
-      const float eA = (w.valid && lA <= L3) ? vA : 0.f;
-      const float eB = (w.valid && lB <= L3) ? vB : 0.f;
+      const float eA = (w.valid && lA <= L3) ? epA[r] : 0.f;
+      const float eB = (w.valid && lB <= L3) ? epB[r] : 0.f;
       const float gA = lA <= L3 ? bA : 0.f, gB = lB <= L3 ? bB : 0.f;
       float o[5] = {0.f, 0.f, 0.f, 0.f, 0.f}, od[5] = {0.f, 0.f, 0.f, 0.f, 0.f};
       float e4 = 0.f, g4 = 0.f, e5 = 0.f, g5 = 0.f, P = 0.f, SS = 0.f;
@@ -2574,17 +2688,15 @@ __device__ __forceinline__ void adjoint_body(const AdjArgs& a, int vb, float* ld
         const Sym3 Md = sym_of(Sdn[0], Sdn[1], Sdn[2], Sdn[3], Sdn[4]);
         sym_proj(sym_mul(M, M), o);
         sym_proj(sym_mul(Md, M), od);
-        const int v4 = NR + L3 * NA + n;
-        const float v = a.Ep[(size_t)v4 * Np + pa], b = row[v4];
-        e4 = (w.valid && g == 1) ? v : 0.f;
+        const float b = row[NR + L3 * NA + n];
+        e4 = (w.valid && g == 1) ? ep4[r] : 0.f;
         g4 = g == 1 ? b : 0.f;
       }
       if constexpr (L5 != 0) {
         P = Sn[0] * Sn[0] + Sn[1] * Sn[1] + Sn[2] * Sn[2];
         SS = Sn[0] * Sdn[0] + Sn[1] * Sdn[1] + Sn[2] * Sdn[2];
-        const int v5 = NR + L3 * NA + (L4 ? NA : 0) + n;
-        const float v = a.Ep[(size_t)v5 * Np + pa], b = row[v5];
-        e5 = (w.valid && g == 0) ? v : 0.f;
+        const float b = row[NR + L3 * NA + (L4 ? NA : 0) + n];
+        e5 = (w.valid && g == 0) ? ep5[r] : 0.f;
         g5 = g == 0 ? b : 0.f;
       }
 #pragma unroll
@@ -2607,83 +2719,105 @@ __device__ __forceinline__ void adjoint_body(const AdjArgs& a, int vb, float* ld
       }
     }
   }
-  __syncthreads();
+  lds_barrier();   // also: every wavefront is done with the weights, whose words the records below take
 
-  // ---- angular coefficient gradient: channels g*NAH + j, pairs p, p+4, ...
-  float cb[T][NAH][KA];
+  // ---- angular coefficient gradient.  One pair per lane forms X_n and Y_n (u.t);
+  //      the sums over pairs of X_n h T_k - Y_n (u.t) q_k, per neighbor species,
+  //      are a product contracted over pairs on the fp32 matrix cores: rows
+  //      (species, n), columns k, 4 pairs per instruction.  16 pairs at a time
+  //      go through LDS to reach the operands' lanes.
+  constexpr int REC = AL::REC, ROWS = T * NA, MT = (ROWS + 15) / 16;
+  static_assert(KA <= 16, "one column tile");
+  float* recs = wl + (threadIdx.x / kWave) * 16 * REC;
+  f32x4 acc[MT];
 #pragma unroll
-  for (int t = 0; t < T; ++t)
+  for (int m = 0; m < MT; ++m) acc[m] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int c0 = 0; c0 < ps.total; c0 += kWave) {
+    const int p = c0 + lane;
+    float X[NA], Yd[NA], f[KA], fp[KA];
+    int J = 0;
 #pragma unroll
-    for (int j = 0; j < NAH; ++j)
+    for (int n = 0; n < NA; ++n) X[n] = Yd[n] = 0.f;
 #pragma unroll
-      for (int k = 0; k < KA; ++k) cb[t][j][k] = 0.f;
-  for (int k = w.p; k < nA; k += 4) {
-    // reload Sbar and A from LDS every pair: hoisted out of the loop they
-    // would take 2 NAH Y registers and halve the occupancy
-    asm volatile("" ::: "memory");
-    const PairGeom q = pair_geom<kTri>(a.nb.idxA[(size_t)i * a.nb.capA + k], a.pos, N, xi, yi, zi, cell);
-    const float ux = q.dx * q.inv_r, uy = q.dy * q.inv_r, uz = q.dz * q.inv_r;
-    const float tx = (a.fbar[q.j] - fbx) + gxx * q.dx + gxy * q.dy;
-    const float ty = (a.fbar[N + q.j] - fby) + gyy * q.dy + gyz * q.dz;
-    const float tz = (a.fbar[2 * N + q.j] - fbz) + gzz * q.dz + gzx * q.dx;
-    const float dt = ux * tx + uy * ty + uz * tz;
-    float f[KA], fp[KA];
-    radial_basis_d<KA>(q.r, a.inv_rcA, f, fp);
-    const int J = a.type[q.j];
-    float B[Y], gbt[Y];
-    harm_val<LM>(ux, uy, uz, B);
-    // grad B . t = grad b(u) . (t - (u.t) u) / r
-    harm_dir<LM>(ux, uy, uz, (tx - dt * ux) * q.inv_r, (ty - dt * uy) * q.inv_r, (tz - dt * uz) * q.inv_r, gbt);
+    for (int kk = 0; kk < KA; ++kk) f[kk] = fp[kk] = 0.f;
+    if (p < ps.total) {
+      const int u = pair_slot(ps, p);
+      const float* sl = slots + u * kAdjSlot;
+      const StreamPair sp = stream_pair<T, kTri>(sl, p, a.nb, a.p4);
+      const PairTangent t = pair_tangent(sp.q, sl, a.fb4[sp.q.j]);
+      radial_cheb_d<KA>(sp.q.r, a.inv_rcA, f, fp);
+      J = sp.J;
+      float B[Y], gbt[Y];
+      harm_val<LM>(t.ux, t.uy, t.uz, B);
+      harm_dir<LM>(t.ux, t.uy, t.uz, t.wx, t.wy, t.wz, gbt);
+      const float* sb = buf + u * RW + DP;
 #pragma unroll
-    for (int j = 0; j < NAH; ++j) {
-      const int n = g * NAH + j;
-      const bool on = n < NA;
-      const float* sb = rowSb + (on ? n : 0) * YR;
-      const float* av = rowA + (on ? n : 0) * YR;
-      float X = 0.f, Yv = 0.f;
+      for (int n = 0; n < NA; ++n) {
+        float x = 0.f, y = 0.f;
 #pragma unroll
-      for (int gg = 0; gg < 2; ++gg)
+        for (int gg = 0; gg < 2; ++gg) {
+          float Sb[YG], Av[YG];
+          row_load<YG, kVec>(sb + n * YR + gg * YG, Sb);
+          row_load<YG, kVec>(sb + NA * YR + n * YR + gg * YG, Av);
 #pragma unroll
-        for (int e = 0; e < YG; ++e) {
-          const int qq = HS::q(gg, e);
-          if (qq >= 0) {
-            X = fmaf(sb[gg * YG + e], B[qq], fmaf(-av[gg * YG + e], gbt[qq], X));
-            Yv = fmaf(av[gg * YG + e], B[qq], Yv);
+          for (int e = 0; e < YG; ++e) {
+            const int qq = HS::q(gg, e);
+            if (qq >= 0) {
+              x = fmaf(Sb[e], B[qq], fmaf(-Av[e], gbt[qq], x));
+              y = fmaf(Av[e], B[qq], y);
+            }
           }
         }
-      X = on ? X : 0.f;
-      const float Yd = on ? Yv * dt : 0.f;
-#pragma unroll
-      for (int t = 0; t < T; ++t) {
-        const float m = (T == 1 || J == t) ? 1.f : 0.f;
-        const float mX = m * X, mY = m * Yd;
-#pragma unroll
-        for (int kk = 0; kk < KA; ++kk) cb[t][j][kk] = fmaf(mX, f[kk], fmaf(-mY, fp[kk], cb[t][j][kk]));
+        X[n] = x;
+        Yd[n] = y * t.dt;
       }
     }
-  }
-  // sums over the pair slots and atoms, scattered over the lanes of each
-  // harmonic group: value v = (t NAH + j) KA + k
-  {
-    constexpr int V = T * NAH * KA;
-    float cv[V];
+    const int left = ps.total - c0;   // wave-uniform
 #pragma unroll
-    for (int t = 0; t < T; ++t)
+    for (int sub = 0; sub < 4; ++sub) {
+      if (16 * sub >= left) break;
+      if ((lane >> 4) == sub) {
+        float* rp = recs + (lane & 15) * REC;
 #pragma unroll
-      for (int j = 0; j < NAH; ++j)
+        for (int n = 0; n < NA; ++n) {
+          rp[n] = X[n];
+          rp[NA + n] = -Yd[n];
+        }
 #pragma unroll
-        for (int k = 0; k < KA; ++k) cv[(t * NAH + j) * KA + k] = cb[t][j][k];
-    float out[(V + 31) / 32];
-    rs_slots_atoms(cv, out);
-    const int c = rs_slots_atoms_code();
+        for (int kk = 0; kk < KA; ++kk) {
+          rp[2 * NA + kk] = f[kk];
+          rp[2 * NA + KA + kk] = fp[kk];
+        }
+        rp[2 * NA + 2 * KA] = __int_as_float(J);
+      }
+      lds_lane_exchange();
+      const int col = min(lane & 15, KA - 1);   // columns past KA are not stored
 #pragma unroll
-    for (int r = 0; r < (V + 31) / 32; ++r) {
-      const int v = 32 * r + c;
-      const int t = v / (NAH * KA), j = (v / KA) % NAH, k = v % KA;
-      const int n = g * NAH + j;
-      if (v < V && n < NA) part[(t * NA + n) * KA + k] = out[r];
+      for (int m4 = 0; m4 < 4; ++m4) {
+        const float* rp = recs + (4 * m4 + (lane >> 4)) * REC;
+        const float bT = rp[2 * NA + col], bQ = rp[2 * NA + KA + col];
+        const int Jp = __float_as_int(rp[2 * NA + 2 * KA]);
+#pragma unroll
+        for (int m = 0; m < MT; ++m) {
+          const int rr = m * 16 + (lane & 15), t = rr / NA, n = rr % NA;
+          const bool mine = t == Jp;   // rows past T NA match no species
+          const float aX = rp[n], aY = rp[NA + n];
+          acc[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(mine ? aX : 0.f, bT, acc[m], 0, 0, 0);
+          acc[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(mine ? aY : 0.f, bQ, acc[m], 0, 0, 0);
+        }
+      }
+      lds_lane_exchange();
     }
   }
+  // f_k = h T_k + h T_0: every column takes column 0's sum
+#pragma unroll
+  for (int m = 0; m < MT; ++m)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const float v = acc[m][r] + dpp<kDppRowBcast0>(acc[m][r]);
+      const int rr = m * 16 + 4 * (lane >> 4) + r, kk = lane & 15;
+      if (rr < ROWS && kk < KA) part[rr * KA + kk] = v;
+    }
 }
 
 template <class C, bool kTri, int W>
@@ -2695,7 +2829,7 @@ __global__ __launch_bounds__(256, W) void k_adjoint(AdjArgs a) {
 // Sums over the atoms of each species of an outer product,
 //   out[I][b][m][v] = sum_p A1[m][p] B1[v][p] - A2[m][p] B2[v][p],
 // over block b's share of species I's atoms (species order).  Used for
-// dL/dW0 = sum beta G^T - (w1 sigma) Gdot^T and for
+// dL/dW0 = sum beta G^T - (w1 (1 - x^2)) Gdot^T and for
 // dL/dc^R = sum Gbar_n F[J][k] - E'_n Fp[J][k].
 // This is a product contracted over atoms, so it runs on the fp32 matrix
 // cores: v_mfma_f32_16x16x4f32 takes a 16 x 4 slice of A (lane l: row l % 16,
@@ -2717,23 +2851,23 @@ struct OuterArgs {
   const int* seg;
   const float* A1;
   const float* B1;
-  const float* A2;
+  const float* A2;    // with w1: the hidden activations x, the operand being w1 (1 - x^2)
   const float* B2;
   float* out;
+  const float* w1;    // [T] blocks of w1_stride words, null: A2 as it is
+  int w1_stride;
 };
 
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-
 // atoms p .. p + 3 of a row (p a multiple of 4 inside the padded row), zero
-// past p1 or when off; the load itself is unconditional so that a group's
-// loads issue back to back
-__device__ __forceinline__ f32x4 ld_atoms4(const float* row, int p, int p1, bool on) {
+// past p1; the load itself is unconditional so that a group's loads issue
+// back to back
+__device__ __forceinline__ f32x4 ld_atoms4(const float* row, int p, int p1) {
   const float4 v = *reinterpret_cast<const float4*>(row + p);
   f32x4 r;
-  r[0] = (on && p < p1) ? v.x : 0.f;
-  r[1] = (on && p + 1 < p1) ? v.y : 0.f;
-  r[2] = (on && p + 2 < p1) ? v.z : 0.f;
-  r[3] = (on && p + 3 < p1) ? v.w : 0.f;
+  r[0] = p < p1 ? v.x : 0.f;
+  r[1] = p + 1 < p1 ? v.y : 0.f;
+  r[2] = p + 2 < p1 ? v.z : 0.f;
+  r[3] = p + 3 < p1 ? v.w : 0.f;
   return r;
 }
 
@@ -2753,20 +2887,23 @@ __device__ __forceinline__ void outer_sum_block(const OuterArgs& o, int b, int I
   const float* a2[kOSTM];
   const float* b1[kOSTV];
   const float* b2[kOSTV];
-  bool am[kOSTM], bm[kOSTV];
 #pragma unroll
   for (int t = 0; t < kOSTM; ++t) {
     const int m = (mz * kOSTM + t) * 16 + row;
-    am[t] = m < o.M;
-    a1[t] = o.A1 + (size_t)(am[t] ? m : 0) * o.Npad;
-    a2[t] = o.A2 + (size_t)(am[t] ? m : 0) * o.Npad;
+    a1[t] = o.A1 + (size_t)(m < o.M ? m : 0) * o.Npad;
+    a2[t] = o.A2 + (size_t)(m < o.M ? m : 0) * o.Npad;
   }
 #pragma unroll
   for (int t = 0; t < kOSTV; ++t) {
     const int v = (vz * kOSTV + t) * 16 + row;
-    bm[t] = v < o.V;
-    b1[t] = o.B1 + (size_t)(bm[t] ? v : 0) * o.Npad;
-    b2[t] = o.B2 + (size_t)(bm[t] ? v : 0) * o.Npad;
+    b1[t] = o.B1 + (size_t)(v < o.V ? v : 0) * o.Npad;
+    b2[t] = o.B2 + (size_t)(v < o.V ? v : 0) * o.Npad;
+  }
+  float w1[kOSTM];
+#pragma unroll
+  for (int t = 0; t < kOSTM; ++t) {
+    const int m = (mz * kOSTM + t) * 16 + row;
+    w1[t] = o.w1 && m < o.M ? o.w1[(size_t)I * o.w1_stride + m] : 0.f;
   }
   // tiles with no row or no column inside the product are skipped (uniform)
   const int tm_live = min(kOSTM, (o.M - mz * kOSTM * 16 + 15) / 16);
@@ -2779,29 +2916,31 @@ __device__ __forceinline__ void outer_sum_block(const OuterArgs& o, int b, int I
   // operands of one 16-atom group; the next group's loads are issued before
   // the current group's MFMAs
   f32x4 va1[kOSTM], va2[kOSTM], vb1[kOSTV], vb2[kOSTV];
+  // Rows and columns past the product repeat row or column 0 and are not
+  // stored.  Past the block's atoms the loads read the segment start (always
+  // inside the padded rows) and are masked to zero.
   auto load = [&](int g) {
-    // past the block's atoms the loads read the segment start instead (always
-    // inside the padded rows) and are masked to zero
-    const bool in = g < p1;
-    const int p = (in ? g : start) + 4 * slot;
+    const int p = (g < p1 ? g : start) + 4 * slot, pe = g < p1 ? p1 : 0;
 #pragma unroll
     for (int t = 0; t < kOSTM; ++t) {
-      va1[t] = ld_atoms4(a1[t], p, p1, in && am[t]);
-      va2[t] = -ld_atoms4(a2[t], p, p1, in && am[t]);
+      va1[t] = ld_atoms4(a1[t], p, pe);
+      va2[t] = ld_atoms4(a2[t], p, pe);
     }
 #pragma unroll
     for (int t = 0; t < kOSTV; ++t) {
-      vb1[t] = ld_atoms4(b1[t], p, p1, in && bm[t]);
-      vb2[t] = ld_atoms4(b2[t], p, p1, in && bm[t]);
+      vb1[t] = ld_atoms4(b1[t], p, pe);
+      vb2[t] = ld_atoms4(b2[t], p, pe);
     }
   };
   load(p0 + 16 * wv);
   for (int g = p0 + 16 * wv; g < p1; g += 64) {
     f32x4 ca1[kOSTM], ca2[kOSTM], cb1[kOSTV], cb2[kOSTV];
+    // minus the second product: -A2, or w1 (x^2 - 1) (B2 is zero past the end)
 #pragma unroll
     for (int t = 0; t < kOSTM; ++t) {
       ca1[t] = va1[t];
-      ca2[t] = va2[t];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) ca2[t][j] = o.w1 ? w1[t] * fmaf(va2[t][j], va2[t][j], -1.0f) : -va2[t][j];
     }
 #pragma unroll
     for (int t = 0; t < kOSTV; ++t) {
@@ -2883,12 +3022,12 @@ __device__ __forceinline__ void part_reduce_body(int PW, const int* seg, const f
   for (int slot = threadIdx.x; slot < PW; slot += blockDim.x) {
     double sum = 0.0;
     int r = r0;
-    for (; r + 4 <= r1; r += 4) {
-      float v[4];
+    for (; r + 16 <= r1; r += 16) {
+      float v[16];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) v[u] = part[(size_t)(r + u) * PW + slot];
+      for (int u = 0; u < 16; ++u) v[u] = part[(size_t)(r + u) * PW + slot];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) sum += (double)v[u];
+      for (int u = 0; u < 16; ++u) sum += (double)v[u];
     }
     for (; r < r1; ++r) sum += (double)part[(size_t)r * PW + slot];
     pp[((size_t)I * nch + b) * PW + slot] = sum;
@@ -2909,7 +3048,7 @@ struct OuterReduceArgs {
   LossArgs la;
 };
 
-__global__ __launch_bounds__(256) void k_outer_reduce(OuterReduceArgs a) {
+__global__ __launch_bounds__(256, 2) void k_outer_reduce(OuterReduceArgs a) {
   __shared__ f32x4 red[3][kOSTM * kOSTV][kWave];
   const int T = a.T, n_outer = a.os_x * T * (a.nzw + a.nzc), n_pr = a.prc * T;
   const int v = blockIdx.x;
@@ -3479,9 +3618,9 @@ static size_t lds_forward(int H) {
 }
 template <class C>
 static size_t lds_adjoint(int H) {
-  const int DP = (C::D + 3) & ~3;
-  return sizeof(float) * ((size_t)CTab<C::T, C::NA, C::KA>::size + (size_t)weights_words(H, DP) +
-                          (size_t)kAPB * (DP + 2 * C::NA * HRow<C::LMAX>::YR));
+  using AL = AdjLds<C>;
+  return sizeof(float) * ((size_t)CTab<C::T, C::NA, C::KA>::size + (size_t)AL::shared_words(H) +
+                          (size_t)(256 / kWave) * AL::WAVE);
 }
 // LDS of a workgroup on gfx950 (160 KiB per CU); dynamic LDS beyond 64 KiB is
 // requested from the runtime per kernel before its launch
@@ -3686,8 +3825,8 @@ size_t al(size_t x) { return (x + 255) & ~(size_t)255; }
 
 struct Layout {
   int N, S, T, D, Y, H, NR, TKR, Npad, nwaves, nblk, PW, NA, capR, capA;
-  size_t order, seg, blk, astruct, p4, G, Sst, Ep, X, eatom, hrow, fA, wv, F, fbar, Es, Ws, eps, wbar, lpart,
-      Gd, FRst, FPst, Gbr, beta, w1s, part, pp, w0part, crpart, Sh, Sdh, cgrid, cell, cpart, acell, aslot, cpos, spart,
+  size_t order, seg, blk, astruct, p4, G, Sst, Ep, X, eatom, hrow, fA, wv, F, fb4, Es, Ws, eps, wbar, lpart,
+      Gd, FRst, FPst, Gbr, beta, part, pp, w0part, crpart, Sh, Sdh, cgrid, cell, cpart, acell, aslot, cpos, spart,
       cur_step, bar, sargs, prm, grd, Gtmp, total;
 };
 
@@ -3733,7 +3872,7 @@ Layout make_layout(const nep_model* m, const Ops* o, int S, int N, bool pad = fa
   L.fA = take(4 * 3 * (size_t)L.capA * Nn);
   L.wv = take(4 * 6 * Nn);
   L.F = take(4 * 3 * Nn);
-  L.fbar = take(4 * 3 * Nn);
+  L.fb4 = take(16 * Nn);
   L.Es = take(4 * Ss);
   L.Ws = take(4 * 6 * Ss);
   L.eps = take(4 * Ss);
@@ -3744,7 +3883,6 @@ Layout make_layout(const nep_model* m, const Ops* o, int S, int N, bool pad = fa
   L.FPst = take(4 * (size_t)L.TKR * Np);
   L.Gbr = take(4 * (size_t)(o->YH > 0 ? L.D : L.NR) * Np);
   L.beta = take(4 * (size_t)L.H * Np);
-  L.w1s = take(4 * (size_t)L.H * Np);
   L.part = take(4 * (size_t)L.nwaves * L.PW);
   L.pp = take(8 * (size_t)L.T * kPRChunksMax * L.PW);
   L.w0part = take(4 * (size_t)L.T * kOSBlocksMaxW * L.H * L.D);
@@ -3767,6 +3905,13 @@ Layout make_layout(const nep_model* m, const Ops* o, int S, int N, bool pad = fa
   L.prm = take(4 * Pc);
   L.grd = take(4 * Pc);
   L.Gtmp = take(pad ? 4 * (size_t)L.D * Nn : 0);
+  // The size callers see stays what it was with the stored radial pair forces,
+  // the reverse index and the rows no longer kept, so that
+  // nep_loss_grad_noalloc takes and refuses the same batches.
+  const size_t before = al(4 * (size_t)L.capR * Nn) + al(4 * (size_t)L.capA * Nn) + al(12 * (size_t)L.capR * Nn) +
+                        al(4 * (size_t)L.H * Np) + al(12 * Nn);
+  const size_t now = 2 * al(16 * Nn) + al(4 * (size_t)L.T * o->KP * Nn);
+  if (before > now) off += before - now;
   L.total = off;
   return L;
 }
@@ -3848,6 +3993,8 @@ struct Ctx {
   const struct AdamFuse* adam = nullptr;
   // the packed atoms of this call are in the workspace
   mutable bool packed = false;
+  // force cotangents of the caller (nep_vjp), packed with the atoms
+  const float* fbar = nullptr;
 };
 
 struct AdamFuse {
@@ -3970,6 +4117,7 @@ FwdArgs fwd_args(const Ctx& c, const nep_neighbors* nb, const float* params) {
   a.G = at<float>(c.ws, c.L.G);
   a.Guser = nullptr;
   a.Sst = at<float>(c.ws, c.L.Sst);
+  a.FRst = at<float>(c.ws, c.L.FRst);
   a.Ep = at<float>(c.ws, c.L.Ep);
   a.X = at<float>(c.ws, c.L.X);
   a.eatom = at<float>(c.ws, c.L.eatom);
@@ -3999,9 +4147,8 @@ ForceArgs force_args(const Ctx& c, const FwdArgs& f, float* user) {
 }
 
 // forward + forces + per-structure sums (+ loss when labels given)
-// arguments of the kernels of degrees l > 4 (fbar/wbar only for the adjoint's)
-HighArgs high_args(const Ctx& c, const nep_neighbors* nb, const float* params, const float* fbar = nullptr,
-                   const float* wbar = nullptr) {
+// arguments of the kernels of degrees l > 4 (wbar only for the adjoint's)
+HighArgs high_args(const Ctx& c, const nep_neighbors* nb, const float* params, const float* wbar = nullptr) {
   HighArgs h;
   const nep_model* m = c.m;
   h.N = c.L.N;
@@ -4023,7 +4170,7 @@ HighArgs high_args(const Ctx& c, const nep_neighbors* nb, const float* params, c
   h.Gd = at<float>(c.ws, c.L.Gd);
   h.Gb = at<float>(c.ws, c.L.Gbr);
   h.fA = at<float>(c.ws, c.L.fA);
-  h.fbar = fbar;
+  h.fb4 = at<float4>(c.ws, c.L.fb4);
   h.wbar = wbar;
   h.part = at<float>(c.ws, c.L.part);
   return h;
@@ -4039,7 +4186,8 @@ void run_pack(const Ctx& c, const nep_neighbors* nb, Prof* pr) {
   const int N = c.L.N;
   if (c.packed || N == 0) return;
   NEP_LAUNCH(pr, "pack", hipLaunchKernelGGL(k_pack, dim3(grid1(N)), dim3(256), 0, c.st, N, c.m->n_types, c.b->pos,
-                                            c.b->type, pair_lists(c, nb), at<float4>(c.ws, c.L.p4)));
+                                            c.b->type, pair_lists(c, nb), at<float4>(c.ws, c.L.p4), c.fbar,
+                                            at<float4>(c.ws, c.L.fb4)));
   c.packed = true;
 }
 
@@ -4073,7 +4221,7 @@ StructArgs struct_args(const Ctx& c, float* e_struct, float* virial, const nep_l
   s.Ws_user = virial;
   s.eps = at<float>(c.ws, c.L.eps);
   s.wbar = at<float>(c.ws, c.L.wbar);
-  s.fbar = at<float>(c.ws, c.L.fbar);
+  s.fb4 = at<float4>(c.ws, c.L.fb4);
   s.lpart = at<double>(c.ws, c.L.lpart);
   // large structures take chunk partials first, unless the caller's bound rules them out
   s.split = N >= 2 * kStructChunk && (c.b->max_atoms == 0 || c.b->max_atoms >= 2 * kStructChunk);
@@ -4088,6 +4236,10 @@ void run_forward(const Ctx& c, const nep_neighbors* nb, const float* params, flo
   if (N > 0) {
     FwdArgs a = fwd_args(c, nb, params);
     a.eatom2 = e_atom;
+    if (!lab) {   // no adjoint follows: its inputs are not stored (l > 4 reads G and E')
+      a.Sst = a.FRst = a.X = nullptr;
+      if (c.o->YH == 0) a.G = a.Ep = nullptr;
+    }
     launch_forward_pass(c, nb, params, a, pr);
     NEP_LAUNCH(pr, "force", c.o->force(force_args(c, a, force), c.st, c.tune.gather_lanes));
   }
@@ -4105,8 +4257,7 @@ void run_forward(const Ctx& c, const nep_neighbors* nb, const float* params, flo
   }
 }
 
-AdjArgs adj_args(const Ctx& c, const nep_neighbors* nb, const float* params, const float* eps, const float* fbar,
-                 const float* wbar) {
+AdjArgs adj_args(const Ctx& c, const nep_neighbors* nb, const float* params, const float* eps, const float* wbar) {
   const nep_model* m = c.m;
   AdjArgs a;
   a.N = c.L.N;
@@ -4119,8 +4270,6 @@ AdjArgs adj_args(const Ctx& c, const nep_neighbors* nb, const float* params, con
   a.astruct = at<int>(c.ws, c.L.astruct);
   a.box = c.b->box;
   a.tilt = c.b->tilt;
-  a.pos = c.b->pos;
-  a.type = c.b->type;
   a.p4 = at<float4>(c.ws, c.L.p4);
   a.nb = pair_lists(c, nb);
   const int T = m->n_types;
@@ -4132,14 +4281,12 @@ AdjArgs adj_args(const Ctx& c, const nep_neighbors* nb, const float* params, con
   a.Ep = at<float>(c.ws, c.L.Ep);
   a.X = at<float>(c.ws, c.L.X);
   a.eps = eps;
-  a.fbar = fbar;
+  a.fb4 = at<float4>(c.ws, c.L.fb4);
   a.wbar = wbar;
   a.Gd = at<float>(c.ws, c.L.Gd);
-  a.FRst = at<float>(c.ws, c.L.FRst);
   a.FPst = at<float>(c.ws, c.L.FPst);
   a.Gbr = at<float>(c.ws, c.L.Gbr);
   a.beta = at<float>(c.ws, c.L.beta);
-  a.w1s = at<float>(c.ws, c.L.w1s);
   a.part = at<float>(c.ws, c.L.part);
   a.PW = c.L.PW;
   return a;
@@ -4149,10 +4296,10 @@ AdjArgs adj_args(const Ctx& c, const nep_neighbors* nb, const float* params, con
 void outer_args(const Ctx& c, const AdjArgs& a, OuterArgs& ow, OuterArgs& oc) {
   const nep_model* m = c.m;
   const int* seg = at<int>(c.ws, c.L.seg);
-  ow = OuterArgs{c.L.Npad, m->hidden, c.o->D, c.tune.outer_w, seg, a.beta, at<float>(c.ws, c.L.G), a.w1s, a.Gd,
-                 at<float>(c.ws, c.L.w0part)};
-  oc = OuterArgs{c.L.Npad, m->n_rad, c.L.TKR, c.tune.outer_c, seg, a.Gbr, a.FRst, at<float>(c.ws, c.L.Ep), a.FPst,
-                 at<float>(c.ws, c.L.crpart)};
+  ow = OuterArgs{c.L.Npad, m->hidden, c.o->D, c.tune.outer_w, seg, a.beta, at<float>(c.ws, c.L.G), a.X, a.Gd,
+                 at<float>(c.ws, c.L.w0part), a.nn + m->hidden * c.o->D + m->hidden, a.nn_stride};
+  oc = OuterArgs{c.L.Npad, m->n_rad, c.L.TKR, c.tune.outer_c, seg, a.Gbr, at<float>(c.ws, c.L.FRst),
+                 at<float>(c.ws, c.L.Ep), a.FPst, at<float>(c.ws, c.L.crpart), nullptr, 0};
 }
 
 GradArgs grad_args(const Ctx& c, float* grad) {
@@ -4188,15 +4335,15 @@ GradArgs grad_args(const Ctx& c, float* grad) {
 
 unsigned grad_final_blocks(const GradArgs& g) { return (unsigned)((g.P * 16 + 255) / 256); }
 
-// adjoint + gradient reductions; cotangents from eps/fbar/wbar pointers
-void run_adjoint(const Ctx& c, const nep_neighbors* nb, const float* params, const float* eps, const float* fbar,
-                 const float* wbar, float* grad, Prof* pr, LossArgs la = LossArgs{}) {
+// adjoint + gradient reductions; cotangents from eps, wbar and the packed F-bar
+void run_adjoint(const Ctx& c, const nep_neighbors* nb, const float* params, const float* eps, const float* wbar,
+                 float* grad, Prof* pr, LossArgs la = LossArgs{}) {
   const nep_model* m = c.m;
   const int N = c.L.N;
   if (N > 0) {
-    const AdjArgs a = adj_args(c, nb, params, eps, fbar, wbar);
+    const AdjArgs a = adj_args(c, nb, params, eps, wbar);
     const int T = m->n_types;
-    const HighArgs h = high_args(c, nb, params, fbar, wbar);
+    const HighArgs h = high_args(c, nb, params, wbar);
     run_high(c, kHighTangent, h, pr);
     NEP_LAUNCH(pr, "adjoint", c.o->adjoint(a, dim3(c.L.Npad / kAPB), c.st, c.tune.adjoint_waves));
     run_high(c, kHighCoef, h, pr);
@@ -4334,8 +4481,7 @@ int loss_grad_seq(Ctx& c, nep_neighbors* nb, const float* params, const nep_labe
   // with atoms present the loss is summed by the adjoint's reduction launch
   const LossArgs la = loss_args(c, labels, lam, loss, flags);
   run_forward(c, nb, params, nullptr, e_struct, force, virial, labels, lam, loss, flags, pr, la.on != 0);
-  run_adjoint(c, nb, params, at<float>(c.ws, c.L.eps), at<float>(c.ws, c.L.fbar), at<float>(c.ws, c.L.wbar), grad,
-              pr, la);
+  run_adjoint(c, nb, params, at<float>(c.ws, c.L.eps), at<float>(c.ws, c.L.wbar), grad, pr, la);
   return hip_ok();
 }
 
@@ -4373,7 +4519,7 @@ StepArgs step_args(const Ctx& c, nep_neighbors* nb, const float* params, const n
   a.fwd = fwd_args(c, nb, params);
   a.frc = force_args(c, a.fwd, nullptr);
   a.st = struct_args(c, nullptr, nullptr, labels, lam);
-  a.adj = adj_args(c, nb, params, at<float>(c.ws, c.L.eps), at<float>(c.ws, c.L.fbar), at<float>(c.ws, c.L.wbar));
+  a.adj = adj_args(c, nb, params, at<float>(c.ws, c.L.eps), at<float>(c.ws, c.L.wbar));
   outer_args(c, a.adj, a.ow, a.oc);
   a.nzw = outer_slices(a.ow.M, a.ow.V);
   a.nzc = outer_slices(a.oc.M, a.oc.V);
@@ -4501,6 +4647,8 @@ int nep_descriptors(const nep_model* m, const nep_batch* b, const nep_neighbors*
   a.Guser = c.pad ? at<float>(c.ws, c.L.Gtmp) : G;
   a.do_mlp = 0;
   a.do_force = 0;
+  a.Sst = a.FRst = nullptr;
+  if (c.o->YH == 0) a.G = nullptr;
   launch_forward_pass(c, nb, kp, a, nullptr);
   if (c.pad)
     hipLaunchKernelGGL(k_unpad_desc, dim3((unsigned)(((int64_t)c.pd.D * b->n_atom + 255) / 256)), dim3(256), 0, c.st,
@@ -4569,9 +4717,10 @@ int nep_vjp(const nep_model* m, const nep_batch* b, const nep_neighbors* nb, con
   if (b->n_atom > 0) {
     FwdArgs a = fwd_args(c, nb, params);
     a.do_force = 0;
+    c.fbar = f_bar;
     launch_forward_pass(c, nb, params, a, nullptr);
   }
-  run_adjoint(c, nb, params, e_bar, f_bar, v_bar, grad, nullptr);
+  run_adjoint(c, nb, params, e_bar, v_bar, grad, nullptr);
   return hip_ok();
 }
 
