@@ -307,7 +307,8 @@ int nep_train_step_graph_create(const nep_model* model, const nep_batch* batch, 
  * changes a result beyond the order of floating-point sums.  0 in a field
  * keeps the default (in brackets).
  *   persistent      1: the persistent form of NEP_GRAPH_PERSISTENT [0]
- *   outer_blocks_w  blocks per species of the W0 outer-product sum, 1..512 [192]
+ *   outer_blocks_w  blocks per species of the W0 outer-product sum, 1..512 [96]
+ *                   (per output slice; rounded to whole pieces of the atom order's chunks)
  *   outer_blocks_c  blocks per species of the c_rad outer-product sum, 1..256 [64]
  *   reduce_chunks   chunks per species of the first gradient-partial reduction, 1..512 [128]
  *   cell_min_atoms  smallest structure searched through cell lists, >= 64 [1024]

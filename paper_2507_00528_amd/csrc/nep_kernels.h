@@ -31,6 +31,7 @@ struct NbrArgs {
   int* cntA;
   int* astruct;
   float4* p4;    // [N] packed atoms (atom_word)
+  int* bflags;   // [blocks] flag word of each all-pairs block; null: into flags
   int* flags;
   // cell-list search of structures of at least cell_min atoms (cells = 0:
   // all-pairs only)
@@ -64,6 +65,8 @@ struct FwdArgs {
   int N, Npad, H;
   float inv_rcR, inv_rcA;
   const int* order;
+  const int* blist;   // launch order of the blocks
+  int nch;
   const int* astruct;
   const float* box;
   const float* tilt;  // null: every cell orthorhombic
@@ -107,6 +110,8 @@ struct AdjArgs {
   int N, Npad, H, S;
   float inv_rcR, inv_rcA;
   const int* order;
+  const int* blist;   // launch order of the blocks
+  int nch;
   const int* astruct;
   const float* box;
   const float* tilt;  // null: every cell orthorhombic

@@ -652,14 +652,24 @@ __global__ __launch_bounds__(kNbrThreads) void k_neighbors(NbrArgs a) {
     if (mine) {
       a.cntR[i] = totR;
       a.cntA[i] = totA;
-      if (totR > a.capR || totA > a.capA) fl |= FL_OVERFLOW;
     } else {   // counted by the cell search
       totR = a.cntR[i];
       totA = a.cntA[i];
     }
+    if (totR > a.capR || totA > a.capA) fl |= FL_OVERFLOW;
     a.p4[i] = make_float4(c.xf, c.yf, c.zf, atom_word(a.type[i], a.T, totR > a.capR, totA > a.capA));
   }
-  if (live && s == 0 && fl) atomicOr(a.flags, fl);
+  if (!(live && s == 0)) fl = 0;
+  if (a.bflags) {
+    __shared__ int word;
+    if (threadIdx.x == 0) word = 0;
+    __syncthreads();
+    if (fl) atomicOr(&word, fl);
+    __syncthreads();
+    if (threadIdx.x == 0) a.bflags[blockIdx.x] = word;
+  } else if (fl) {
+    atomicOr(a.flags, fl);
+  }
 }
 
 // Cell-list search of large structures.  A structure of at least
@@ -941,8 +951,7 @@ __global__ __launch_bounds__(kNbrThreads) void k_cell_neighbors(NbrArgs a) {
     }
     if (s == 0) {
       a.cntR[i] = totR;
-      a.cntA[i] = totA;
-      if (totR > a.capR || totA > a.capA) atomicOr(a.flags, FL_OVERFLOW);
+      a.cntA[i] = totA;   // an overflow is flagged by the all-pairs launch that follows
     }
   }
   if (live && spill && s == 0) a.acell[i] = -1;
@@ -988,15 +997,22 @@ __device__ __forceinline__ int row_find(const uint32_t* __restrict__ row, int m,
 }
 
 // ============================================================ species order
-// Atoms are laid out by (species, angular neighbor count descending), with
-// ties in atom order: every wavefront then holds one species and atoms of
-// similar pair counts, so the pair loops of its 8 atoms end together.  The
-// key of atom i is t * kOrdBuckets + (kOrdBuckets - 1 - min(nA_i, kOrdBuckets - 1)),
-// and a counting sort over keys keeps the layout deterministic.
-constexpr int kOrdBlk = 1024;      // atoms per order block
+// Atoms are laid out chunk by chunk (kOrdChunk atoms of the batch each), in a
+// chunk by (species, angular neighbor count descending), with ties in atom
+// order: every block of the per-atom kernels holds one species, and a
+// wavefront's 8 atoms have similar pair counts, so their pair loops end
+// together.  A chunk is sorted by one block in one launch (a counting sort
+// over the whole batch took three), its atoms stay close in memory, and the
+// layout is deterministic.  The key of atom i is
+// t * kOrdBuckets + (kOrdBuckets - 1 - min(nA_i, kOrdBuckets - 1)).
+//
+// Chunk c starts at position c * order_stride(T); its species segments start on
+// multiples of kSegAlign positions and the rest holds -1.
+constexpr int kOrdChunk = 2048;
 constexpr int kOrdBuckets = 64;
-constexpr int kOrdMaxK = 8 * kOrdBuckets;   // keys of up to 8 species
+constexpr int kOrdMaxT = 4;    // species of the compiled shapes
 constexpr int kSegAlign = 32;  // species segments start on multiples of the atoms per block
+__host__ __device__ constexpr int order_stride(int T) { return kOrdChunk + T * kSegAlign; }
 
 __device__ __forceinline__ int order_key(int t, int T, int nA) {
   if (t < 0 || t >= T) return -1;
@@ -1004,147 +1020,55 @@ __device__ __forceinline__ int order_key(int t, int T, int nA) {
 }
 
 struct OrderArgs {
-  int N, Npad, T, nblk;
+  int N, Npad, T, nch;
   const int* type;
   const int* cntA;
-  int* blk;     // [nblk][K] key counts, then offsets
-  int* seg;     // [2T] species segment start and count
+  int* seg;     // [nch][T][2] species segment start and count
   int* order;   // [Npad]
+  int* blist;   // [nch][order_blocks(T)] blocks of 32 positions, most pairs first, -1: none
 };
 
-// LDS of the order bodies (ints)
-constexpr int kOrdCountLds = kOrdMaxK;
-constexpr int kOrdScanLds = 2 * kOrdMaxK + 16;
-constexpr int kOrdScatterLds = (kOrdBlk / kWave) * kOrdMaxK;
+// blocks of 32 positions of a chunk
+__host__ __device__ constexpr int order_blocks(int T) { return order_stride(T) / kSegAlign; }
 
-// Key counts of order block ob (kOrdBlk atoms).
-template <int NT>
-__device__ __forceinline__ void order_count_body(const OrderArgs& a, int ob, int* cnt) {
-  const int K = a.T * kOrdBuckets;
-  for (int q = threadIdx.x; q < K; q += NT) cnt[q] = 0;
-  __syncthreads();
-  for (int u = 0; u < kOrdBlk; u += NT) {
-    const int i = ob * kOrdBlk + u + threadIdx.x;
-    if (i < a.N) {
-      const int key = order_key(a.type[i], a.T, a.cntA[i]);
-      if (key >= 0) atomicAdd(&cnt[key], 1);
-    }
-  }
-  __syncthreads();
-  for (int q = threadIdx.x; q < K; q += NT) a.blk[(size_t)ob * K + q] = cnt[q];
-  __syncthreads();
+// Block of 32 positions that launch index b of a per-atom kernel takes, -1 for
+// none: every chunk's block of most pairs first, then every chunk's next one.
+// Blocks of 9 to 12 pairs an atom take two 64-pair rounds per wavefront; started
+// last they left a tail of 30 us on a 130 us adjoint.
+__host__ __device__ inline int order_grid(int nch, int T) { return nch * order_blocks(T); }
+__device__ __forceinline__ int launch_block(const int* __restrict__ blist, int nch, int T, int b) {
+  return blist[(b % nch) * order_blocks(T) + b / nch];
 }
 
-// One block: key totals, their exclusive scan in key order with each species
-// segment starting on a multiple of kSegAlign atoms, then the per-block
-// offsets.  seg[2t], seg[2t+1] = start and count of species t.  Each key's
-// rows are split into P parts; a thread takes (key, part) slots.
-template <int NT>
-__device__ __forceinline__ void order_scan_body(const OrderArgs& a, int* sh) {
-  static_assert(2 * NT >= kOrdMaxK, "two keys per thread");
-  const int K = a.T * kOrdBuckets;
-  const int P = max(1, NT / K);
-  int* part = sh;                 // [K * P] row sums of each slot
-  int* sc = sh + kOrdMaxK;        // [K] inclusive scan of the key totals
-  int* sstart = sc + kOrdMaxK;    // [8]
-  const int nslot = K * P;
-  // slot q = p K + k of this thread: q = threadIdx.x + r NT
-  for (int q = threadIdx.x; q < nslot; q += NT) {
-    const int k = q % K, p = q / K;
-    const int b0 = (int)((long long)a.nblk * p / P), b1 = (int)((long long)a.nblk * (p + 1) / P);
-    int mine = 0;
-    for (int b = b0; b < b1; b += 8) {
-      int v[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) v[u] = b + u < b1 ? a.blk[(size_t)(b + u) * K + k] : 0;
-#pragma unroll
-      for (int u = 0; u < 8; ++u) mine += v[u];
-    }
-    part[q] = mine;
-  }
-  __syncthreads();
-  // key totals, two keys per thread (K <= 512), then an inclusive scan of the
-  // pair sums (Hillis-Steele over the 256 threads)
-  int tot2[2];
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const int k = 2 * threadIdx.x + h;
-    int t = 0;
-    if (k < K)
-      for (int p = 0; p < P; ++p) t += part[p * K + k];
-    tot2[h] = t;
-  }
-  sc[threadIdx.x] = tot2[0] + tot2[1];
-  __syncthreads();
-  for (int d = 1; d < NT; d <<= 1) {
-    const int v = (int)threadIdx.x >= d ? sc[threadIdx.x - d] : 0;
-    __syncthreads();
-    sc[threadIdx.x] += v;
-    __syncthreads();
-  }
-  const int incl_pair = sc[threadIdx.x];
-  __syncthreads();
-  // expand to per-key inclusive sums
-  {
-    const int k0 = 2 * threadIdx.x;
-    if (k0 < K) sc[k0] = incl_pair - tot2[1];
-    if (k0 + 1 < K) sc[k0 + 1] = incl_pair;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    int start = 0;
-    for (int t = 0; t < a.T; ++t) {
-      const int lo = t == 0 ? 0 : sc[t * kOrdBuckets - 1];
-      const int cnt = sc[(t + 1) * kOrdBuckets - 1] - lo;
-      sstart[t] = start - lo;   // aligned start minus the unaligned prefix
-      a.seg[2 * t] = start;
-      a.seg[2 * t + 1] = cnt;
-      start += (cnt + kSegAlign - 1) / kSegAlign * kSegAlign;
-    }
-  }
-  __syncthreads();
-  for (int q = threadIdx.x; q < nslot; q += NT) {
-    const int k = q % K, p = q / K;
-    const int b0 = (int)((long long)a.nblk * p / P), b1 = (int)((long long)a.nblk * (p + 1) / P);
-    int before = 0, tot = 0;   // rows of earlier parts, and the key's total
-    for (int pp = 0; pp < P; ++pp) {
-      const int v = part[pp * K + k];
-      tot += v;
-      before += pp < p ? v : 0;
-    }
-    int off = sstart[k / kOrdBuckets] + sc[k] - tot + before;
-    for (int b = b0; b < b1; b += 8) {
-      int v[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) v[u] = b + u < b1 ? a.blk[(size_t)(b + u) * K + k] : 0;
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        if (b + u < b1) a.blk[(size_t)(b + u) * K + k] = off;
-        off += v[u];
-      }
-    }
-  }
-  __syncthreads();
-}
+// LDS of order_body (ints): counts per 64 atoms and key, key offsets, the
+// chunk's positions, species counts
+constexpr int kOrdLds = (kOrdChunk / kWave + 1) * kOrdMaxT * kOrdBuckets + order_stride(kOrdMaxT) + 8;
 
-// Rank of each atom of order block ob among the atoms of its key: lanes
-// before it in its wavefront (one ballot per distinct key in the wavefront),
-// then the wavefronts before it in the block.  The block's kOrdBlk atoms are
-// taken NT at a time; wcnt holds [kOrdBlk / 64][K] counts.
+// Chunk c with NT threads, which take its atoms NT at a time.  Rank of an atom
+// among the atoms of its key: lanes before it in its wavefront (one ballot per
+// distinct key), then the groups of 64 before it.
 template <int NT>
-__device__ __forceinline__ void order_scatter_body(const OrderArgs& a, int ob, int* wcnt) {
-  constexpr int NR = kOrdBlk / NT;   // rounds
-  constexpr int NWR = NT / kWave;    // wavefronts per round
-  const int K = a.T * kOrdBuckets;
+__device__ __forceinline__ void order_body(const OrderArgs& a, int c, int* lds) {
+  constexpr int NR = kOrdChunk / NT, NWR = NT / kWave, NV = kOrdChunk / kWave;
+  static_assert(NWR >= kOrdMaxT, "a wavefront per species");
+  const int T = a.T, K = T * kOrdBuckets, stride = order_stride(T);
+  int* wcnt = lds;                 // [NV][K] counts, then counts before the group
+  int* off = wcnt + NV * K;        // [K] key totals, then starts in the species segment
+  int* ord = off + K;              // [stride]
+  int* cnt = ord + stride;         // [T]
   const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
-  for (int q = threadIdx.x; q < (kOrdBlk / kWave) * K; q += NT) wcnt[q] = 0;
+  for (int q = threadIdx.x; q < NV * K; q += NT) wcnt[q] = 0;
+  for (int q = threadIdx.x; q < stride; q += NT) ord[q] = -1;
   __syncthreads();
   int key[NR], rank[NR];
   const unsigned long long below = (1ull << lane) - 1ull;
 #pragma unroll
   for (int r = 0; r < NR; ++r) {
-    const int i = ob * kOrdBlk + r * NT + threadIdx.x;
-    key[r] = i < a.N ? order_key(a.type[i], a.T, a.cntA[i]) : -1;
+    const int i = c * kOrdChunk + r * NT + threadIdx.x;
+    key[r] = i < a.N ? order_key(a.type[i], T, a.cntA[i]) : -1;
+  }
+#pragma unroll
+  for (int r = 0; r < NR; ++r) {
     rank[r] = 0;
     const int vw = r * NWR + wid;
     unsigned long long rem = __ballot(key[r] >= 0);
@@ -1158,36 +1082,113 @@ __device__ __forceinline__ void order_scatter_body(const OrderArgs& a, int ob, i
     }
   }
   __syncthreads();
+  for (int q = threadIdx.x; q < K; q += NT) {
+    int v[NV], run = 0;
 #pragma unroll
-  for (int r = 0; r < NR; ++r) {
+    for (int w = 0; w < NV; ++w) v[w] = wcnt[w * K + q];
+#pragma unroll
+    for (int w = 0; w < NV; ++w) {
+      wcnt[w * K + q] = run;
+      run += v[w];
+    }
+    off[q] = run;
+  }
+  __syncthreads();
+  if (wid < T) {   // wavefront t scans the buckets of species t
+    const int v = off[wid * kOrdBuckets + lane];
+    int inc = v;
+#pragma unroll
+    for (int d = 1; d < kWave; d <<= 1) {
+      const int u = __shfl_up(inc, d, kWave);
+      if (lane >= d) inc += u;
+    }
+    off[wid * kOrdBuckets + lane] = inc - v;
+    if (lane == kWave - 1) cnt[wid] = inc;
+  }
+  __syncthreads();
+  int start[kOrdMaxT], at = 0;
+#pragma unroll
+  for (int t = 0; t < kOrdMaxT; ++t) {
+    start[t] = at;
+    if (t < T) at += (cnt[t] + kSegAlign - 1) / kSegAlign * kSegAlign;
+  }
+#pragma unroll
+  for (int t = 0; t < kOrdMaxT; ++t)
+    if (t < T && (int)threadIdx.x == t) {
+      a.seg[2 * (c * T + t)] = c * stride + start[t];
+      a.seg[2 * (c * T + t) + 1] = cnt[t];
+    }
+#pragma unroll
+  for (int r = 0; r < NR; ++r)
     if (key[r] >= 0) {
-      const int i = ob * kOrdBlk + r * NT + threadIdx.x;
-      const int vw = r * NWR + wid;
-      int before = 0;
-      for (int w = 0; w < vw; ++w) before += wcnt[w * K + key[r]];
-      a.order[a.blk[(size_t)ob * K + key[r]] + before + rank[r]] = i;
+      const int t = key[r] / kOrdBuckets;
+      int s0 = 0;
+#pragma unroll
+      for (int u = 1; u < kOrdMaxT; ++u) s0 = t == u ? start[u] : s0;
+      ord[s0 + off[key[r]] + wcnt[(r * NWR + wid) * K + key[r]] + rank[r]] = c * kOrdChunk + r * NT + threadIdx.x;
+    }
+  __syncthreads();
+  const int len = min(stride, a.Npad - c * stride);
+  for (int q = threadIdx.x; q < len; q += NT) a.order[(size_t)c * stride + q] = ord[q];
+  // blocks by their first atom's pair count (its largest), descending; up to 4
+  // chunks give every block a CU of its own, so their order does not matter
+  // (and sorting them took 2 us of a 180-atom MD step)
+  const int nb = order_blocks(T);
+  if (a.nch <= 4) {
+    for (int q = threadIdx.x; q < nb; q += NT)
+      a.blist[c * nb + q] = ord[q * kSegAlign] >= 0 ? (c * stride) / kSegAlign + q : -1;
+    __syncthreads();
+    return;
+  }
+  for (int q = threadIdx.x; q < nb; q += NT) wcnt[q] = ord[q * kSegAlign] >= 0 ? a.cntA[ord[q * kSegAlign]] : -1;
+  __syncthreads();
+  for (int q = threadIdx.x; q < nb; q += NT) {
+    const int v = wcnt[q];
+    int r = 0;
+    for (int o = 0; o < nb; ++o) {
+      const int x = wcnt[o];
+      r += x > v || (x == v && o < q) ? 1 : 0;
+    }
+    a.blist[c * nb + r] = v >= 0 ? (c * stride) / kSegAlign + q : -1;
+  }
+  __syncthreads();
+}
+
+// Flags of a neighbor build: each of its blocks stores its own word, and block
+// 0 of the order launch, which follows, collects them.  In a captured step it
+// also starts the replay's flag word and latches the step (graph_head's part),
+// so the step needs no launch for that.
+struct FlagArgs {
+  const int* bflags;
+  int n;
+  int* flags;
+  int* step;   // null outside a captured step
+  int* cur;
+};
+__device__ __forceinline__ void collect_flags(const FlagArgs& f, int* lds) {
+  if (threadIdx.x == 0) lds[0] = 0;
+  __syncthreads();
+  int v = 0;
+  for (int q = threadIdx.x; q < f.n; q += blockDim.x) v |= f.bflags[q];
+  if (v) atomicOr(&lds[0], v);
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    if (f.step) {
+      const int st = f.step[0];
+      f.flags[0] = lds[0] | (st < 1 ? FL_STEP : 0);
+      f.cur[0] = st;
+      f.step[0] = st + 1;
+    } else if (lds[0]) {
+      atomicOr(f.flags, lds[0]);
     }
   }
   __syncthreads();
 }
 
-// the separate kernels: a block of kOrdBlk threads per order block, 512
-// threads for the scan
-__global__ __launch_bounds__(512) void k_order_scan(OrderArgs a) {
-  __shared__ int sh[kOrdScanLds];
-  order_scan_body<512>(a, sh);
-}
-
-__global__ __launch_bounds__(kOrdBlk) void k_order_scatter(OrderArgs a) {
-  __shared__ int wcnt[kOrdScatterLds];
-  order_scatter_body<kOrdBlk>(a, blockIdx.x, wcnt);
-}
-
-__global__ __launch_bounds__(256) void k_order_count(OrderArgs o) {
-  __shared__ int cnt[kOrdCountLds];
-  const int ob = blockIdx.x;
-  for (int q = ob * 256 + threadIdx.x; q < o.Npad; q += o.nblk * 256) o.order[q] = -1;
-  order_count_body<256>(o, ob, cnt);
+__global__ __launch_bounds__(1024) void k_order(OrderArgs a, FlagArgs f) {
+  __shared__ int lds[kOrdLds];
+  if (blockIdx.x == 0) collect_flags(f, lds);
+  order_body<1024>(a, blockIdx.x, lds);
 }
 
 // ================================================================= helpers
@@ -1571,9 +1572,9 @@ __device__ __forceinline__ void row_load(const float* p, float (&v)[W]) {
 // gives E_i and E' = dE_i/dG (D1.1-D1.5).  With forces on, the atom's radial
 // force coefficients and every angular pair's partial force f_ij = dE_i/dr_ij
 // (C3.6) are stored for the force pass.
-// Block vb (32 atoms of the species order); lds: lds_forward bytes.
+// Launch index b (32 atoms of the species order); lds: lds_forward bytes.
 template <class C, bool kTri>
-__device__ __forceinline__ void forward_body(const FwdArgs& a, int vb, float* lds) {
+__device__ __forceinline__ void forward_body(const FwdArgs& a, int b, float* lds) {
   constexpr int T = C::T, NR = C::NR, NA = C::NA, KR = C::KR, KA = C::KA, Y = C::Y, D = C::D, LM = C::LMAX;
   constexpr int L3 = C::L3, L4 = C::L4, L5 = C::L5;
   using HS = HSplit<LM>;
@@ -1587,6 +1588,8 @@ __device__ __forceinline__ void forward_body(const FwdArgs& a, int vb, float* ld
   float* wl = lds + CT::size;            // weights of the block's species
   float* slots = wl + weights_words(H, DP) + (threadIdx.x / kWave) * FL::WAVE;
   float* buf = slots + kAPW * slot_words<kTri>();
+  const int vb = launch_block(a.blist, a.nch, T, b);
+  if (vb < 0) return;
   // issued here, waited for after the angular sums: their latency overlaps the
   // pair passes
   if (a.do_mlp) stage_weights_async(wl, a.nn, a.nn_stride, block_species<T>(a.order, a.p4, vb), H, D, DP);
@@ -2303,7 +2306,7 @@ __global__ __launch_bounds__(kRedBlk) void k_loss_final(int S, int N, float le, 
 //            coupling that Algorithm 1 enumerates).
 // Outputs: per-atom vectors for the outer-product sums (W0, c^R) and, per
 // wavefront, the sums of the c^A, b0, w1, b1 partials over its 8 atoms.
-// Block vb (32 atoms of the species order); lds: lds_adjoint bytes.
+// Launch index b (32 atoms of the species order); lds: lds_adjoint bytes.
 // Slot table of the adjoint: the forward's words, then F-bar and Gamma.
 constexpr int kSlotF = 12, kSlotG = 16, kSlotG2 = 20, kAdjSlot = 28;   // 4 mod 8
 
@@ -2352,7 +2355,7 @@ __device__ __forceinline__ PairTangent pair_tangent(const PairGeom& q, const flo
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 template <class C, bool kTri>
-__device__ __forceinline__ void adjoint_body(const AdjArgs& a, int vb, float* lds) {
+__device__ __forceinline__ void adjoint_body(const AdjArgs& a, int b, float* lds) {
   constexpr int T = C::T, NR = C::NR, NA = C::NA, KR = C::KR, KA = C::KA, Y = C::Y, D = C::D, LM = C::LMAX;
   constexpr int L3 = C::L3, L4 = C::L4, L5 = C::L5;
   using HS = HSplit<LM>;
@@ -2369,7 +2372,9 @@ __device__ __forceinline__ void adjoint_body(const AdjArgs& a, int vb, float* ld
   float* wl = lds + CT::size;            // weights of the block's species
   float* slots = wl + AL::shared_words(H) + (threadIdx.x / kWave) * AL::WAVE;
   float* buf = slots + kAPW * kAdjSlot;
-  // as in the forward: issued here, waited for after the tangent sums
+  const int vb = launch_block(a.blist, a.nch, T, b);
+  if (vb < 0) return;
+  // issued here, waited for after the tangent sums
   stage_weights_async(wl, a.nn, a.nn_stride, block_species<T>(a.order, a.p4, vb), H, D, DP);
   const GroupCtx w = group_ctx(a.order, a.Npad, vb);
   const int i = w.i, pa = w.pa, s = w.s, g = w.g;
@@ -2837,17 +2842,19 @@ __global__ __launch_bounds__(256, W) void k_adjoint(AdjArgs a) {
 // of which lane l holds rows 4 (l / 16) + r, column l % 16.  Each lane loads
 // float4 runs of 4 consecutive atoms and feeds component j to the j-th of 4
 // MFMAs, so atom slot l / 16 of MFMA j is atom 4 (l / 16) + j of the 16-atom
-// group.  A block covers a 4 x 3 grid of 16 x 16 output tiles (blockIdx.z
+// group.  A block covers a 2 x 3 grid of 16 x 16 output tiles (blockIdx.z
 // picks the grid cell for larger products); its 4 wavefronts take
 // consecutive 16-atom groups and are summed through LDS at the end.
-// blocks per species: the W0 sums stream about three times the data of the
-// c^R sums, so they get more blocks (all blocks are resident at once)
-constexpr int kOSBlocksW = 192, kOSBlocksC = 64;            // defaults
+// Blocks per species and output slice: the W0 sums stream about three times
+// the data of the c^R sums.  At 512 structures (87k atoms) the step takes
+// 315 us with 96 blocks for W0 (two slices), 320 with 128, 326 with 192.
+constexpr int kOSBlocksW = 96, kOSBlocksC = 64;            // defaults
 constexpr int kOSBlocksMaxW = 512, kOSBlocksMaxC = 256;
-constexpr int kOSTM = 4, kOSTV = 3;
+constexpr int kOSTM = 2, kOSTV = 3;
 
 struct OuterArgs {
   int Npad, M, V, NB;
+  int T, nch, Q;      // block b: piece b mod Q of chunks b / Q, b / Q + NB / Q, ...
   const int* seg;
   const float* A1;
   const float* B1;
@@ -2878,11 +2885,8 @@ __device__ __forceinline__ void outer_sum_block(const OuterArgs& o, int b, int I
   const int nzv = (o.V + 16 * kOSTV - 1) / (16 * kOSTV);
   const int mz = z / nzv, vz = z % nzv;
   const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
-  const int start = o.seg[2 * I], count = o.seg[2 * I + 1];
-  const int per = ((count + o.NB - 1) / o.NB + 15) & ~15;   // multiple of 16 atoms
-  const int p0 = start + b * per;
-  const int p1 = min(start + count, p0 + per);
   const int row = lane & 15, slot = lane >> 4;
+  int start = 0, p1 = 0;
   const float* a1[kOSTM];
   const float* a2[kOSTM];
   const float* b1[kOSTV];
@@ -2932,6 +2936,13 @@ __device__ __forceinline__ void outer_sum_block(const OuterArgs& o, int b, int I
       vb2[t] = ld_atoms4(b2[t], p, pe);
     }
   };
+  for (int c = b / o.Q; c < o.nch; c += o.NB / o.Q) {
+  start = o.seg[2 * (c * o.T + I)];
+  const int count = o.seg[2 * (c * o.T + I) + 1];
+  const int per = ((count + o.Q - 1) / o.Q + 15) & ~15;   // multiple of 16 atoms
+  const int p0 = start + b % o.Q * per;
+  p1 = min(start + count, p0 + per);
+  if (p0 >= p1) continue;
   load(p0 + 16 * wv);
   for (int g = p0 + 16 * wv; g < p1; g += 64) {
     f32x4 ca1[kOSTM], ca2[kOSTM], cb1[kOSTV], cb2[kOSTV];
@@ -2961,6 +2972,7 @@ __device__ __forceinline__ void outer_sum_block(const OuterArgs& o, int b, int I
         }
       }
     }
+  }
   }
   if (wv > 0) {
 #pragma unroll
@@ -3012,45 +3024,59 @@ struct LossArgs {
   int* flags;
 };
 
-// chunk b of species I's wavefront partials
-__device__ __forceinline__ void part_reduce_body(int PW, const int* seg, const float* part, double* pp, int b, int I,
-                                                 int nch) {
-  const int start = seg[2 * I], count = seg[2 * I + 1];
-  const int w0 = start / kAPW, w1 = count > 0 ? (start + count + kAPW - 1) / kAPW : w0;
-  const int per = (w1 - w0 + nch - 1) / nch;
-  const int r0 = w0 + b * per, r1 = min(w1, r0 + per);
+// block b of species I's wavefront partials, pieces of the order's chunks as
+// for the outer-product sums
+struct PartArgs {
+  int PW, NB, T, nch, Q;
+  const int* seg;
+  const float* part;
+  double* pp;
+};
+__device__ __forceinline__ void part_reduce_body(const PartArgs& a, int b, int I) {
+  const int PW = a.PW;
   for (int slot = threadIdx.x; slot < PW; slot += blockDim.x) {
     double sum = 0.0;
-    int r = r0;
-    for (; r + 16 <= r1; r += 16) {
-      float v[16];
+    for (int c = b / a.Q; c < a.nch; c += a.NB / a.Q) {
+      const int start = a.seg[2 * (c * a.T + I)], count = a.seg[2 * (c * a.T + I) + 1];
+      const int w0 = start / kAPW, w1 = (start + count + kAPW - 1) / kAPW;
+      const int per = (w1 - w0 + a.Q - 1) / a.Q;
+      int r = w0 + b % a.Q * per;
+      const int r1 = min(w1, r + per);
+      for (; r + 16 <= r1; r += 16) {
+        float v[16];
 #pragma unroll
-      for (int u = 0; u < 16; ++u) v[u] = part[(size_t)(r + u) * PW + slot];
+        for (int u = 0; u < 16; ++u) v[u] = a.part[(size_t)(r + u) * PW + slot];
 #pragma unroll
-      for (int u = 0; u < 16; ++u) sum += (double)v[u];
+        for (int u = 0; u < 16; ++u) sum += (double)v[u];
+      }
+      for (; r + 4 <= r1; r += 4) {
+        float v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = a.part[(size_t)(r + u) * PW + slot];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) sum += (double)v[u];
+      }
+      for (; r < r1; ++r) sum += (double)a.part[(size_t)r * PW + slot];
     }
-    for (; r < r1; ++r) sum += (double)part[(size_t)r * PW + slot];
-    pp[((size_t)I * nch + b) * PW + slot] = sum;
+    a.pp[((size_t)I * a.NB + b) * PW + slot] = sum;
   }
 }
 
 // The outer-product sums, the first stage of the wavefront partial sums and
 // the loss sum in one launch (all three read only the adjoint's outputs):
 // blocks [0, n_outer) take the outer products (block x of species I, output
-// slice z; slices [0, nzw) of dW0, the rest of dc^R), the next prc T blocks
+// slice z; slices [0, nzw) of dW0, the rest of dc^R), the next pr.NB T blocks
 // the partial sums, the last one the loss.
 struct OuterReduceArgs {
   OuterArgs ow, oc;
-  int nzw, nzc, os_x, T, PW, prc;
-  const int* seg;
-  const float* part;
-  double* pp;
+  int nzw, nzc, os_x, T;
+  PartArgs pr;
   LossArgs la;
 };
 
-__global__ __launch_bounds__(256, 2) void k_outer_reduce(OuterReduceArgs a) {
+__global__ __launch_bounds__(256, 3) void k_outer_reduce(OuterReduceArgs a) {
   __shared__ f32x4 red[3][kOSTM * kOSTV][kWave];
-  const int T = a.T, n_outer = a.os_x * T * (a.nzw + a.nzc), n_pr = a.prc * T;
+  const int T = a.T, n_outer = a.os_x * T * (a.nzw + a.nzc), n_pr = a.pr.NB * T;
   const int v = blockIdx.x;
   if (v < n_outer) {
     const int x = v % a.os_x, I = (v / a.os_x) % T, z = v / (a.os_x * T);
@@ -3060,7 +3086,7 @@ __global__ __launch_bounds__(256, 2) void k_outer_reduce(OuterReduceArgs a) {
       outer_sum_block(a.oc, x, I, z - a.nzw, red);
   } else if (v < n_outer + n_pr) {
     const int u = v - n_outer;
-    part_reduce_body(a.PW, a.seg, a.part, a.pp, u % a.prc, u / a.prc, a.prc);
+    part_reduce_body(a.pr, u % a.pr.NB, u / a.pr.NB);
   } else if (a.la.on) {
     loss_final_block(a.la.S, a.la.N, a.la.le, a.la.lf, a.la.lv, a.la.lpart, a.la.loss, a.la.flags, red);
   }
@@ -3103,6 +3129,57 @@ __device__ float lr_at(const AdamDev& c, int64_t s) {
   return c.lr_stop + (c.lr_start - c.lr_stop) * 0.5f * (1.0f + (float)cos(3.14159265358979323846 * fr));
 }
 
+// ------------------------------------------------- padded models: layout maps
+// A model smaller than a compiled size class runs in that class with its
+// parameters zero-padded: radial and angular channels, Chebyshev terms and
+// species the model does not have get zero coefficients, and the network's
+// columns of descriptors it does not have (higher channels, degrees up to the
+// class's, the 4- and 5-body terms) get zero weights.  Every padded quantity
+// then adds an exact zero to the energies, forces and virials, and the
+// gradient entries of the model's own parameters are those of the class run.
+// PadDims maps a parameter of the model to its slot in the class layout.
+struct PadDims {
+  int T, NR, NA, KR, KA, D, H, l3, l4, l5;   // the model
+  int Tc, NRc, NAc, KRc, KAc, Dc, L3c;       // the class (4- and 5-body terms on)
+  int64_t P;                                 // parameters of the model
+};
+
+// class column of descriptor v of the model
+__device__ __forceinline__ int pad_col(const PadDims& d, int v) {
+  if (v < d.NR) return v;
+  v -= d.NR;
+  if (v < d.l3 * d.NA) return d.NRc + (v / d.NA) * d.NAc + v % d.NA;
+  v -= d.l3 * d.NA;
+  if (d.l4) {
+    if (v < d.NA) return d.NRc + d.L3c * d.NAc + v;
+    v -= d.NA;
+  }
+  return d.NRc + d.L3c * d.NAc + d.NAc + v;   // 5-body
+}
+
+__device__ __forceinline__ int64_t pad_index(const PadDims& d, int64_t q) {
+  const int64_t PR = (int64_t)d.T * d.T * d.NR * d.KR, PA = (int64_t)d.T * d.T * d.NA * d.KA;
+  const int64_t PRc = (int64_t)d.Tc * d.Tc * d.NRc * d.KRc, PAc = (int64_t)d.Tc * d.Tc * d.NAc * d.KAc;
+  if (q < PR) {
+    const int64_t k = q % d.KR, n = (q / d.KR) % d.NR, J = (q / ((int64_t)d.KR * d.NR)) % d.T;
+    const int64_t I = q / ((int64_t)d.KR * d.NR * d.T);
+    return ((I * d.Tc + J) * d.NRc + n) * d.KRc + k;
+  }
+  q -= PR;
+  if (q < PA) {
+    const int64_t k = q % d.KA, n = (q / d.KA) % d.NA, J = (q / ((int64_t)d.KA * d.NA)) % d.T;
+    const int64_t I = q / ((int64_t)d.KA * d.NA * d.T);
+    return PRc + ((I * d.Tc + J) * d.NAc + n) * d.KAc + k;
+  }
+  q -= PA;
+  const int64_t HD = (int64_t)d.H * d.D;
+  const int64_t blk = HD + 2 * d.H + 1, blkc = (int64_t)d.H * d.Dc + 2 * d.H + 1;
+  const int64_t I = q / blk, o = q % blk;
+  const int64_t base = PRc + PAc + I * blkc;
+  if (o < HD) return base + (o / d.D) * d.Dc + pad_col(d, (int)(o % d.D));
+  return base + (int64_t)d.H * d.Dc + (o - HD);   // b0, w1, b1
+}
+
 struct GradArgs {
   int T, NR, NA, KR, KA, H, D, PW, NBw, NBc, PRC;
   int64_t P;
@@ -3110,6 +3187,8 @@ struct GradArgs {
   const float* w0part;   // [T][NBw][H*D]
   const float* crpart;   // [T][NBc][NR*T*KR]
   float* grad;
+  int pad;               // a padded model: parameters mapped into the class layout of the sums
+  PadDims pd;
   // Adam on each parameter as soon as its gradient is summed (the captured
   // training step); step is the 1-based device step counter
   int adam;
@@ -3143,7 +3222,7 @@ __device__ __forceinline__ void grad_final_body(const GradArgs& a, int vb) {
   const int HD = a.H * a.D, CR = a.NR * a.T * a.KR;
   double sum = 0.0;
   if (q < a.P) {
-    const int qi = (int)q;
+    const int qi = (int)(a.pad ? pad_index(a.pd, q) : q);
     const float* fsrc = nullptr;
     const double* dsrc = nullptr;
     int stride = 0, rows = 0;
@@ -3325,9 +3404,7 @@ struct StepArgs {
   AdjArgs adj;
   OuterArgs ow, oc;
   int nzw, nzc, os_x;
-  int PW;
-  const int* seg;
-  double* pp;
+  PartArgs pr;
   LossArgs la;
   GradArgs g;
   int n_gf;        // blocks of the final gradient reduction
@@ -3348,22 +3425,14 @@ __global__ __launch_bounds__(256, 2) void k_step(const StepArgs* pa) {
   unsigned k = 0;
 #define NEP_BARRIER() \
   if (!grid_barrier(a.bar, ++k, a.flags, &abort_sh)) return
-  // species order: key counts (and every slot cleared), offsets, ranks
-  for (int q = blockIdx.x * 256 + threadIdx.x; q < a.ord.Npad; q += (int)gridDim.x * 256) a.ord.order[q] = -1;
+  // species order
   {
-    const int nblk = a.ord.nblk;
-    for_items(nblk, [&](int ob) { order_count_body<256>(item_args(a.ord), ob, reinterpret_cast<int*>(lds)); });
-  }
-  NEP_BARRIER();
-  if (blockIdx.x == 0) order_scan_body<256>(item_args(a.ord), reinterpret_cast<int*>(lds));
-  NEP_BARRIER();
-  {
-    const int nblk = a.ord.nblk;
-    for_items(nblk, [&](int ob) { order_scatter_body<256>(item_args(a.ord), ob, reinterpret_cast<int*>(lds)); });
+    const int nch = a.ord.nch;
+    for_items(nch, [&](int c) { order_body<256>(item_args(a.ord), c, reinterpret_cast<int*>(lds)); });
   }
   NEP_BARRIER();
   // forward: descriptors, network, partial forces
-  for_items(a.fwd.Npad / kAPB, [&](int vb) {
+  for_items(order_grid(a.fwd.nch, C::T), [&](int vb) {
     forward_body<C, false>(item_args(a.fwd), vb, lds);
     __syncthreads();
   });
@@ -3381,7 +3450,7 @@ __global__ __launch_bounds__(256, 2) void k_step(const StepArgs* pa) {
   }
   for_items(a.st.S, [&](int s) { struct_body(item_args(a.st), s, lds); });
   NEP_BARRIER();
-  for_items(a.adj.Npad / kAPB, [&](int vb) {
+  for_items(order_grid(a.adj.nch, C::T), [&](int vb) {
     adjoint_body<C, false>(item_args(a.adj), vb, lds);
     __syncthreads();
   });
@@ -3390,7 +3459,7 @@ __global__ __launch_bounds__(256, 2) void k_step(const StepArgs* pa) {
   {
     const int T = a.ord.T;
     const int os_x = a.os_x, nzw = a.nzw;
-    const int prc = a.g.PRC;
+    const int prc = a.pr.NB;
     const int n_outer = os_x * T * (nzw + a.nzc), n_pr = prc * T;
     auto& red = *reinterpret_cast<f32x4(*)[3][kOSTM * kOSTV][kWave]>(lds);
     for_items(n_outer + n_pr + (a.la.on ? 1 : 0), [&](int v) {
@@ -3402,7 +3471,7 @@ __global__ __launch_bounds__(256, 2) void k_step(const StepArgs* pa) {
           outer_sum_block(item_args(a.oc), x, I, z - nzw, red);
       } else if (v < n_outer + n_pr) {
         const int u = v - n_outer;
-        part_reduce_body(a.PW, a.seg, a.adj.part, a.pp, u % prc, u / prc, prc);
+        part_reduce_body(item_args(a.pr), u % prc, u / prc);
       } else {
         const LossArgs la = item_args(a.la);
         loss_final_block(la.S, la.N, la.le, la.lf, la.lv, la.lpart, la.loss, la.flags, lds);
@@ -3428,64 +3497,50 @@ __global__ void k_step_head(StepArgs a, StepArgs* dst, int* flags, int* step, in
 }
 
 // ============================================================ padded models
-// A model smaller than a compiled size class runs in that class with its
-// parameters zero-padded: radial and angular channels, Chebyshev terms and
-// species the model does not have get zero coefficients, and the network's
-// columns of descriptors it does not have (higher channels, degrees up to the
-// class's, the 4- and 5-body terms) get zero weights.  Every padded quantity
-// then adds an exact zero to the energies, forces and virials, and the
-// gradient entries of the model's own parameters are those of the class run.
-// PadDims maps a parameter of the model to its slot in the class layout.
-struct PadDims {
-  int T, NR, NA, KR, KA, D, H, l3, l4, l5;   // the model
-  int Tc, NRc, NAc, KRc, KAc, Dc, L3c;       // the class (4- and 5-body terms on)
-  int64_t P;                                 // parameters of the model
-};
+// (PadDims and the layout maps stand before the final gradient reduction.)
 
-// class column of descriptor v of the model
-__device__ __forceinline__ int pad_col(const PadDims& d, int v) {
-  if (v < d.NR) return v;
-  v -= d.NR;
-  if (v < d.l3 * d.NA) return d.NRc + (v / d.NA) * d.NAc + v % d.NA;
-  v -= d.l3 * d.NA;
-  if (d.l4) {
-    if (v < d.NA) return d.NRc + d.L3c * d.NAc + v;
-    v -= d.NA;
-  }
-  return d.NRc + d.L3c * d.NAc + d.NAc + v;   // 5-body
-}
-
-__device__ __forceinline__ int64_t pad_index(const PadDims& d, int64_t q) {
-  const int64_t PR = (int64_t)d.T * d.T * d.NR * d.KR, PA = (int64_t)d.T * d.T * d.NA * d.KA;
+// class parameter q of the model, -1 where the model has none
+__device__ __forceinline__ int64_t unpad_index(const PadDims& d, int64_t q) {
   const int64_t PRc = (int64_t)d.Tc * d.Tc * d.NRc * d.KRc, PAc = (int64_t)d.Tc * d.Tc * d.NAc * d.KAc;
-  if (q < PR) {
-    const int64_t k = q % d.KR, n = (q / d.KR) % d.NR, J = (q / ((int64_t)d.KR * d.NR)) % d.T;
-    const int64_t I = q / ((int64_t)d.KR * d.NR * d.T);
-    return ((I * d.Tc + J) * d.NRc + n) * d.KRc + k;
+  const int64_t PR = (int64_t)d.T * d.T * d.NR * d.KR, PA = (int64_t)d.T * d.T * d.NA * d.KA;
+  if (q < PRc) {
+    const int64_t k = q % d.KRc, n = (q / d.KRc) % d.NRc, J = (q / ((int64_t)d.KRc * d.NRc)) % d.Tc;
+    const int64_t I = q / ((int64_t)d.KRc * d.NRc * d.Tc);
+    return k < d.KR && n < d.NR && J < d.T && I < d.T ? ((I * d.T + J) * d.NR + n) * d.KR + k : -1;
   }
-  q -= PR;
-  if (q < PA) {
-    const int64_t k = q % d.KA, n = (q / d.KA) % d.NA, J = (q / ((int64_t)d.KA * d.NA)) % d.T;
-    const int64_t I = q / ((int64_t)d.KA * d.NA * d.T);
-    return PRc + ((I * d.Tc + J) * d.NAc + n) * d.KAc + k;
+  q -= PRc;
+  if (q < PAc) {
+    const int64_t k = q % d.KAc, n = (q / d.KAc) % d.NAc, J = (q / ((int64_t)d.KAc * d.NAc)) % d.Tc;
+    const int64_t I = q / ((int64_t)d.KAc * d.NAc * d.Tc);
+    return k < d.KA && n < d.NA && J < d.T && I < d.T ? PR + ((I * d.T + J) * d.NA + n) * d.KA + k : -1;
   }
-  q -= PA;
-  const int64_t HD = (int64_t)d.H * d.D;
-  const int64_t blk = HD + 2 * d.H + 1, blkc = (int64_t)d.H * d.Dc + 2 * d.H + 1;
-  const int64_t I = q / blk, o = q % blk;
-  const int64_t base = PRc + PAc + I * blkc;
-  if (o < HD) return base + (o / d.D) * d.Dc + pad_col(d, (int)(o % d.D));
-  return base + (int64_t)d.H * d.Dc + (o - HD);   // b0, w1, b1
+  q -= PAc;
+  const int64_t blk = (int64_t)d.H * d.D + 2 * d.H + 1, blkc = (int64_t)d.H * d.Dc + 2 * d.H + 1;
+  const int64_t I = q / blkc, o = q % blkc;
+  if (I >= d.T) return -1;
+  const int64_t base = PR + PA + I * blk;
+  if (o >= (int64_t)d.H * d.Dc) return base + (int64_t)d.H * d.D + (o - (int64_t)d.H * d.Dc);   // b0, w1, b1
+  int v = (int)(o % d.Dc), col = -1;
+  if (v < d.NRc) {
+    col = v < d.NR ? v : -1;
+  } else if ((v -= d.NRc) < d.L3c * d.NAc) {
+    col = v / d.NAc < d.l3 && v % d.NAc < d.NA ? d.NR + v / d.NAc * d.NA + v % d.NAc : -1;
+  } else if ((v -= d.L3c * d.NAc) < d.NAc) {
+    col = d.l4 && v < d.NA ? d.NR + d.l3 * d.NA + v : -1;
+  } else {
+    v -= d.NAc;
+    col = d.l5 && v < d.NA ? d.NR + d.l3 * d.NA + (d.l4 ? d.NA : 0) + v : -1;
+  }
+  return col >= 0 ? base + o / d.Dc * d.D + col : -1;
 }
 
-__global__ __launch_bounds__(256) void k_pad_params(PadDims d, const float* __restrict__ p, float* __restrict__ pc) {
+// the class parameters: the model's where it has them, zero elsewhere
+__global__ __launch_bounds__(256) void k_pad_params(PadDims d, int64_t Pc, const float* __restrict__ p,
+                                                    float* __restrict__ pc) {
   const int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (q < d.P) pc[pad_index(d, q)] = p[q];
-}
-
-__global__ __launch_bounds__(256) void k_unpad_grad(PadDims d, const float* __restrict__ gc, float* __restrict__ g) {
-  const int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (q < d.P) g[q] = gc[pad_index(d, q)];
+  if (q >= Pc) return;
+  const int64_t m = unpad_index(d, q);
+  pc[q] = m >= 0 ? p[m] : 0.f;
 }
 
 // descriptor rows [Dc][N] of the class to the model's [D][N]
@@ -3824,11 +3879,31 @@ int64_t param_count(const nep_model* m) {
 size_t al(size_t x) { return (x + 255) & ~(size_t)255; }
 
 struct Layout {
-  int N, S, T, D, Y, H, NR, TKR, Npad, nwaves, nblk, PW, NA, capR, capA;
-  size_t order, seg, blk, astruct, p4, G, Sst, Ep, X, eatom, hrow, fA, wv, F, fb4, Es, Ws, eps, wbar, lpart,
+  int N, S, T, D, Y, H, NR, TKR, Npad, nwaves, nch, PW, NA, capR, capA;
+  size_t order, seg, blist, bflags, astruct, p4, G, Sst, Ep, X, eatom, hrow, fA, wv, F, fb4, Es, Ws, eps, wbar, lpart,
       Gd, FRst, FPst, Gbr, beta, part, pp, w0part, crpart, Sh, Sdh, cgrid, cell, cpart, acell, aslot, cpos, spart,
-      cur_step, bar, sargs, prm, grd, Gtmp, total;
+      cur_step, bar, sargs, prm, Gtmp, total;
 };
+
+// Workspace size callers see.  It is kept at what the library needed when it
+// stored the radial pair forces and a reverse index, which the layout below
+// fits in, so that nep_loss_grad_noalloc takes and refuses the same batches.
+size_t reported_bytes(const Layout& L, const Ops* o, const nep_model* m, bool pad) {
+  const size_t N = L.N > 0 ? L.N : 1, S = L.S > 0 ? L.S : 1, T = L.T, D = L.D, H = L.H, TKR = L.TKR;
+  const size_t n8 = ((size_t)L.N + 31) / 32 * 32 + T * 32 + 16, Np = (n8 + 31) / 32 * 32;
+  const size_t Pc = pad ? (size_t)param_count(m) : 0, capR = L.capR, capA = L.capA, NA = L.NA;
+  const size_t bytes[] = {
+      4 * Np, 64, 4 * ((N + 1023) / 1024) * T * 64, 4 * N, 4 * capR * N, 4 * capA * N, 4 * D * Np,
+      4 * NA * (size_t)o->YR * Np, 4 * D * Np, 4 * H * Np, 4 * N, 12 * capR * N, 12 * capA * N, 24 * N, 12 * N, 12 * N,
+      4 * S, 24 * S, 4 * S, 24 * S, 24 * S, 4 * D * Np, 4 * TKR * Np, 4 * TKR * Np,
+      4 * (o->YH > 0 ? D : (size_t)L.NR) * Np, 4 * H * Np, 4 * H * Np, 4 * (Np / kAPW) * (size_t)L.PW,
+      8 * T * kPRChunksMax * (size_t)L.PW, 4 * T * kOSBlocksMaxW * H * D, 4 * T * kOSBlocksMaxC * (size_t)L.NR * TKR,
+      4 * Np * NA * (size_t)o->YH, 4 * Np * NA * (size_t)o->YH, 16 * S, 4 * (N + 1), 4 * (N / kScanChunk + 1), 4 * N,
+      4 * N, 16 * N, 128 * (N / kStructChunk + 1), 4, 4 * kBarWords, 1024, 4 * Pc, 4 * Pc, pad ? 4 * D * N : 0};
+  size_t sum = 0;
+  for (size_t b : bytes) sum += al(b);
+  return sum;
+}
 
 // m: the model the kernels run (the class model when padded)
 Layout make_layout(const nep_model* m, const Ops* o, int S, int N, bool pad = false) {
@@ -3844,12 +3919,17 @@ Layout make_layout(const nep_model* m, const Ops* o, int S, int N, bool pad = fa
   L.TKR = m->n_types * m->k_rad;
   L.capR = m->cap_rad;
   L.capA = m->cap_ang;
-  // species segments (each rounded up to 32 atoms, one block) plus 16 atoms of slack for
-  // the 16-atom groups of the outer-product sums
-  const int n8 = ((N + kSegAlign - 1) / kSegAlign) * kSegAlign + L.T * kSegAlign + 16;
-  L.Npad = ((n8 + kAPB - 1) / kAPB) * kAPB;
+  // chunks of the species order; the last one with its own atoms only.  A
+  // segment start leaves 16 positions to the end, which the outer-product sums
+  // may read.
+  L.nch = N > 0 ? (N + kOrdChunk - 1) / kOrdChunk : 1;
+  const int last = N - (L.nch - 1) * kOrdChunk;
+  L.Npad = (L.nch - 1) * order_stride(L.T) + (last + kSegAlign - 1) / kSegAlign * kSegAlign + L.T * kSegAlign;
+  // the per-atom vectors are rows of Npad words: an odd number of 256-byte
+  // units, so the rows a wavefront stores start in different memory channels
+  L.Npad = (L.Npad + 63) / 64 * 64;
+  if ((L.Npad / 64) % 2 == 0) L.Npad += 64;
   L.nwaves = L.Npad / kAPW;
-  L.nblk = N > 0 ? (N + kOrdBlk - 1) / kOrdBlk : 1;
   L.PW = L.T * m->n_ang * m->k_ang + 2 * L.H + 1;
   const size_t Np = L.Npad, Nn = (size_t)(N > 0 ? N : 1), Ss = (size_t)(S > 0 ? S : 1);
   size_t off = 0;
@@ -3859,8 +3939,9 @@ Layout make_layout(const nep_model* m, const Ops* o, int S, int N, bool pad = fa
     return r;
   };
   L.order = take(4 * Np);
-  L.seg = take(4 * 2 * 8);
-  L.blk = take(4 * (size_t)L.nblk * L.T * kOrdBuckets);
+  L.seg = take(4 * 2 * (size_t)L.nch * L.T);
+  L.blist = take(4 * (size_t)order_grid(L.nch, L.T));
+  L.bflags = take(4 * (Nn / kNbrAPB + 1));
   L.astruct = take(4 * Nn);
   L.p4 = take(16 * Nn);
   L.G = take(4 * (size_t)L.D * Np);
@@ -3868,7 +3949,6 @@ Layout make_layout(const nep_model* m, const Ops* o, int S, int N, bool pad = fa
   L.Ep = take(4 * (size_t)L.D * Np);
   L.X = take(4 * (size_t)L.H * Np);
   L.eatom = take(4 * Nn);
-  L.hrow = take(4 * (size_t)L.T * o->KP * Nn);
   L.fA = take(4 * 3 * (size_t)L.capA * Nn);
   L.wv = take(4 * 6 * Nn);
   L.F = take(4 * 3 * Nn);
@@ -3878,7 +3958,9 @@ Layout make_layout(const nep_model* m, const Ops* o, int S, int N, bool pad = fa
   L.eps = take(4 * Ss);
   L.wbar = take(4 * 6 * Ss);
   L.lpart = take(8 * 3 * Ss);
-  L.Gd = take(4 * (size_t)L.D * Np);
+  // the radial force coefficients (forward to force pass) end before the
+  // descriptor tangents (adjoint) begin: one region
+  L.hrow = L.Gd = take(4 * std::max((size_t)L.D * Np, (size_t)L.T * o->KP * Nn));
   L.FRst = take(4 * (size_t)L.TKR * Np);
   L.FPst = take(4 * (size_t)L.TKR * Np);
   L.Gbr = take(4 * (size_t)(o->YH > 0 ? L.D : L.NR) * Np);
@@ -3899,20 +3981,12 @@ Layout make_layout(const nep_model* m, const Ops* o, int S, int N, bool pad = fa
   L.cur_step = take(4);
   L.bar = take(4 * kBarWords);
   L.sargs = take(sizeof(StepArgs));
-  // a padded model: the class-layout parameters and gradient, and the class
-  // descriptor rows of nep_descriptors
+  // a padded model: the class-layout parameters, and the class descriptor rows
+  // of nep_descriptors
   const size_t Pc = pad ? (size_t)param_count(m) : 0;
   L.prm = take(4 * Pc);
-  L.grd = take(4 * Pc);
   L.Gtmp = take(pad ? 4 * (size_t)L.D * Nn : 0);
-  // The size callers see stays what it was with the stored radial pair forces,
-  // the reverse index and the rows no longer kept, so that
-  // nep_loss_grad_noalloc takes and refuses the same batches.
-  const size_t before = al(4 * (size_t)L.capR * Nn) + al(4 * (size_t)L.capA * Nn) + al(12 * (size_t)L.capR * Nn) +
-                        al(4 * (size_t)L.H * Np) + al(12 * Nn);
-  const size_t now = 2 * al(16 * Nn) + al(4 * (size_t)L.T * o->KP * Nn);
-  if (before > now) off += before - now;
-  L.total = off;
+  L.total = std::max(off, reported_bytes(L, o, m, pad));
   return L;
 }
 
@@ -3993,6 +4067,9 @@ struct Ctx {
   const struct AdamFuse* adam = nullptr;
   // the packed atoms of this call are in the workspace
   mutable bool packed = false;
+  // a captured step whose neighbor build starts the replay (flags, step latch)
+  int* g_step = nullptr;
+  int* g_cur = nullptr;
   // force cotangents of the caller (nep_vjp), packed with the atoms
   const float* fbar = nullptr;
 };
@@ -4021,8 +4098,8 @@ PairLists pair_lists(const Ctx& c, const nep_neighbors* nb) {
 }
 
 OrderArgs order_args(const Ctx& c, const nep_neighbors* nb) {
-  return OrderArgs{c.L.N, c.L.Npad, c.L.T, c.L.nblk, c.b->type, nb->cnt_ang, at<int>(c.ws, c.L.blk),
-                   at<int>(c.ws, c.L.seg), at<int>(c.ws, c.L.order)};
+  return OrderArgs{c.L.N, c.L.Npad, c.L.T, c.L.nch, c.b->type, nb->cnt_ang, at<int>(c.ws, c.L.seg),
+                   at<int>(c.ws, c.L.order), at<int>(c.ws, c.L.blist)};
 }
 
 void run_neighbors(const Ctx& c, nep_neighbors* nb, int32_t* flags, Prof* pr, bool with_order = true) {
@@ -4048,6 +4125,7 @@ void run_neighbors(const Ctx& c, nep_neighbors* nb, int32_t* flags, Prof* pr, bo
   a.cntA = nb->cnt_ang;
   a.astruct = at<int>(c.ws, c.L.astruct);
   a.p4 = at<float4>(c.ws, c.L.p4);
+  a.bflags = with_order ? at<int>(c.ws, c.L.bflags) : nullptr;
   a.flags = flags;
   // the cell-list kernels run unless the caller's bound rules out every structure
   const int S = c.b->n_struct;
@@ -4088,11 +4166,9 @@ void run_neighbors(const Ctx& c, nep_neighbors* nb, int32_t* flags, Prof* pr, bo
     NEP_LAUNCH(pr, "neighbors", hipLaunchKernelGGL(k, dim3(grid1(N, kNbrAPB)), dim3(kNbrThreads), 0, c.st, a));
   }
   if (!with_order) return;   // the persistent step computes the species order itself
-  const OrderArgs oa = order_args(c, nb);
-  NEP_LAUNCH(pr, "order_count", hipLaunchKernelGGL(k_order_count, dim3(c.L.nblk), dim3(256), 0, c.st, oa));
-  NEP_LAUNCH(pr, "order_scan", hipLaunchKernelGGL(k_order_scan, dim3(1), dim3(512), 0, c.st, oa));
-  NEP_LAUNCH(pr, "order_scatter",
-             hipLaunchKernelGGL(k_order_scatter, dim3(c.L.nblk), dim3(kOrdBlk), 0, c.st, oa));
+  const FlagArgs fa{a.bflags, grid1(N, kNbrAPB), flags, c.g_step, c.g_cur};
+  NEP_LAUNCH(pr, "order",
+             hipLaunchKernelGGL(k_order, dim3(c.L.nch), dim3(1024), 0, c.st, order_args(c, nb), fa));
 }
 
 FwdArgs fwd_args(const Ctx& c, const nep_neighbors* nb, const float* params) {
@@ -4104,6 +4180,8 @@ FwdArgs fwd_args(const Ctx& c, const nep_neighbors* nb, const float* params) {
   a.inv_rcR = 1.0f / m->rc_rad;
   a.inv_rcA = 1.0f / m->rc_ang;
   a.order = at<int>(c.ws, c.L.order);
+  a.blist = at<int>(c.ws, c.L.blist);
+  a.nch = c.L.nch;
   a.astruct = at<int>(c.ws, c.L.astruct);
   a.box = c.b->box;
   a.tilt = c.b->tilt;
@@ -4196,7 +4274,7 @@ void launch_forward_pass(const Ctx& c, const nep_neighbors* nb, const float* par
   const HighArgs h = high_args(c, nb, params);
   run_pack(c, nb, pr);
   run_high(c, kHighDesc, h, pr);
-  NEP_LAUNCH(pr, "forward", c.o->forward(a, dim3(c.L.Npad / kAPB), c.st, c.tune.forward_waves));
+  NEP_LAUNCH(pr, "forward", c.o->forward(a, dim3(order_grid(c.L.nch, c.L.T)), c.st, c.tune.forward_waves));
   if (a.do_mlp && a.do_force) run_high(c, kHighForce, h, pr);
 }
 
@@ -4267,6 +4345,8 @@ AdjArgs adj_args(const Ctx& c, const nep_neighbors* nb, const float* params, con
   a.inv_rcR = 1.0f / m->rc_rad;
   a.inv_rcA = 1.0f / m->rc_ang;
   a.order = at<int>(c.ws, c.L.order);
+  a.blist = at<int>(c.ws, c.L.blist);
+  a.nch = c.L.nch;
   a.astruct = at<int>(c.ws, c.L.astruct);
   a.box = c.b->box;
   a.tilt = c.b->tilt;
@@ -4292,13 +4372,38 @@ AdjArgs adj_args(const Ctx& c, const nep_neighbors* nb, const float* params, con
   return a;
 }
 
+// Blocks per species of a reduction over the order's chunks: each chunk in Q
+// pieces (at most max_q, so that a piece keeps some work) so that there are
+// about `want` blocks, at most `most`; with more chunks than that a block
+// takes several.
+struct Split {
+  int Q, NB;
+};
+Split split_chunks(int want, int most, int nch, int max_q) {
+  int q = std::min(std::max((want + nch / 2) / nch, 1), std::max(max_q, 1));
+  if (nch * q > most) q = std::max(1, most / nch);
+  return Split{q, std::min(nch * q, most)};
+}
+int chunk_atoms(const Ctx& c) { return std::min(c.L.N, kOrdChunk); }
+// 64 atoms (a 16-atom group per wavefront) or 8 wavefront rows to a piece at least
+Split split_w(const Ctx& c) { return split_chunks(c.tune.outer_w, kOSBlocksMaxW, c.L.nch, chunk_atoms(c) / 64); }
+Split split_c(const Ctx& c) { return split_chunks(c.tune.outer_c, kOSBlocksMaxC, c.L.nch, chunk_atoms(c) / 64); }
+Split split_p(const Ctx& c) { return split_chunks(c.tune.reduce_chunks, kPRChunksMax, c.L.nch, chunk_atoms(c) / 64); }
+
+PartArgs part_args(const Ctx& c) {
+  const Split p = split_p(c);
+  return PartArgs{c.L.PW, p.NB, c.L.T, c.L.nch, p.Q, at<int>(c.ws, c.L.seg), at<float>(c.ws, c.L.part),
+                  at<double>(c.ws, c.L.pp)};
+}
+
 // the two outer-product sums: dW0 (W) and dc^R (C)
 void outer_args(const Ctx& c, const AdjArgs& a, OuterArgs& ow, OuterArgs& oc) {
   const nep_model* m = c.m;
   const int* seg = at<int>(c.ws, c.L.seg);
-  ow = OuterArgs{c.L.Npad, m->hidden, c.o->D, c.tune.outer_w, seg, a.beta, at<float>(c.ws, c.L.G), a.X, a.Gd,
+  const Split w = split_w(c), r = split_c(c);
+  ow = OuterArgs{c.L.Npad, m->hidden, c.o->D, w.NB, c.L.T, c.L.nch, w.Q, seg, a.beta, at<float>(c.ws, c.L.G), a.X, a.Gd,
                  at<float>(c.ws, c.L.w0part), a.nn + m->hidden * c.o->D + m->hidden, a.nn_stride};
-  oc = OuterArgs{c.L.Npad, m->n_rad, c.L.TKR, c.tune.outer_c, seg, a.Gbr, at<float>(c.ws, c.L.FRst),
+  oc = OuterArgs{c.L.Npad, m->n_rad, c.L.TKR, r.NB, c.L.T, c.L.nch, r.Q, seg, a.Gbr, at<float>(c.ws, c.L.FRst),
                  at<float>(c.ws, c.L.Ep), a.FPst, at<float>(c.ws, c.L.crpart), nullptr, 0};
 }
 
@@ -4313,15 +4418,17 @@ GradArgs grad_args(const Ctx& c, float* grad) {
   g.H = m->hidden;
   g.D = c.o->D;
   g.PW = c.L.PW;
-  g.NBw = c.tune.outer_w;
-  g.NBc = c.tune.outer_c;
-  g.PRC = c.tune.reduce_chunks;
-  g.P = param_count(m);
+  g.NBw = split_w(c).NB;
+  g.NBc = split_c(c).NB;
+  g.PRC = split_p(c).NB;
+  g.P = param_count(c.mu);
+  g.pad = c.pad;
+  g.pd = c.pd;
   g.pp = at<double>(c.ws, c.L.pp);
   g.w0part = at<float>(c.ws, c.L.w0part);
   g.crpart = at<float>(c.ws, c.L.crpart);
   g.grad = grad;
-  g.adam = c.adam != nullptr && !c.pad;   // a padded model's Adam runs on its own layout
+  g.adam = c.adam != nullptr;
   if (c.adam) {
     g.ad = c.adam->ad;
     g.th = c.adam->th;
@@ -4345,7 +4452,7 @@ void run_adjoint(const Ctx& c, const nep_neighbors* nb, const float* params, con
     const int T = m->n_types;
     const HighArgs h = high_args(c, nb, params, wbar);
     run_high(c, kHighTangent, h, pr);
-    NEP_LAUNCH(pr, "adjoint", c.o->adjoint(a, dim3(c.L.Npad / kAPB), c.st, c.tune.adjoint_waves));
+    NEP_LAUNCH(pr, "adjoint", c.o->adjoint(a, dim3(order_grid(c.L.nch, c.L.T)), c.st, c.tune.adjoint_waves));
     run_high(c, kHighCoef, h, pr);
     {
       OuterReduceArgs ra;
@@ -4354,28 +4461,14 @@ void run_adjoint(const Ctx& c, const nep_neighbors* nb, const float* params, con
       ra.nzc = outer_slices(ra.oc.M, ra.oc.V);
       ra.os_x = std::max(ra.ow.NB, ra.oc.NB);
       ra.T = T;
-      ra.PW = c.L.PW;
-      ra.prc = c.tune.reduce_chunks;
-      ra.seg = at<int>(c.ws, c.L.seg);
-      ra.part = a.part;
-      ra.pp = at<double>(c.ws, c.L.pp);
+      ra.pr = part_args(c);
       ra.la = la;
-      const int nblk = ra.os_x * T * (ra.nzw + ra.nzc) + ra.prc * T + (la.on ? 1 : 0);
+      const int nblk = ra.os_x * T * (ra.nzw + ra.nzc) + ra.pr.NB * T + (la.on ? 1 : 0);
       NEP_LAUNCH(pr, "outer_sums_reduce",
                  hipLaunchKernelGGL(k_outer_reduce, dim3(nblk), dim3(256), 0, c.st, ra));
     }
-    // a padded model: the class gradient in the workspace, then the model's
-    // entries, then Adam on the model's parameters
-    float* gk = c.pad ? at<float>(c.ws, c.L.grd) : grad;
-    const GradArgs g = grad_args(c, gk);
+    const GradArgs g = grad_args(c, grad);
     NEP_LAUNCH(pr, "grad_final", hipLaunchKernelGGL(k_grad_final, dim3(grad_final_blocks(g)), dim3(256), 0, c.st, g));
-    if (c.pad) {
-      const unsigned nb = (unsigned)((c.pd.P + 255) / 256);
-      NEP_LAUNCH(pr, "unpad_grad", hipLaunchKernelGGL(k_unpad_grad, dim3(nb), dim3(256), 0, c.st, c.pd, gk, grad));
-      if (c.adam)
-        hipLaunchKernelGGL(k_adam_dev, dim3(nb), dim3(256), 0, c.st, c.pd.P, c.adam->th, c.adam->mm, c.adam->vv, grad,
-                           c.adam->step, c.adam->flags, c.adam->ad);
-    }
   } else {
     const int64_t P = param_count(c.mu);
     hipLaunchKernelGGL(k_fill_f32, dim3((unsigned)((P + 255) / 256)), dim3(256), 0, c.st, grad, P, 0.f);
@@ -4450,8 +4543,7 @@ const float* kernel_params(const Ctx& c, const float* params) {
   if (!c.pad) return params;
   float* pc = at<float>(c.ws, c.L.prm);
   const int64_t Pc = param_count(c.m);
-  hipLaunchKernelGGL(k_fill_f32, dim3((unsigned)((Pc + 255) / 256)), dim3(256), 0, c.st, pc, Pc, 0.f);
-  hipLaunchKernelGGL(k_pad_params, dim3((unsigned)((c.pd.P + 255) / 256)), dim3(256), 0, c.st, c.pd, params, pc);
+  hipLaunchKernelGGL(k_pad_params, dim3((unsigned)((Pc + 255) / 256)), dim3(256), 0, c.st, c.pd, Pc, params, pc);
   return pc;
 }
 
@@ -4488,8 +4580,7 @@ int loss_grad_seq(Ctx& c, nep_neighbors* nb, const float* params, const nep_labe
 // ---- persistent step: everything after the neighbor build in one launch
 size_t step_lds(const Ctx& c) {
   size_t l = std::max(c.o->lds_fwd(c.m->hidden), c.o->lds_adj(c.m->hidden));
-  l = std::max(l, (size_t)kOrdScatterLds * sizeof(int));
-  l = std::max(l, (size_t)kOrdScanLds * sizeof(int));
+  l = std::max(l, (size_t)kOrdLds * sizeof(int));
   l = std::max(l, (size_t)kStructLds);
   l = std::max(l, (size_t)kOuterLds);
   l = std::max(l, (size_t)kLossLds);
@@ -4524,9 +4615,7 @@ StepArgs step_args(const Ctx& c, nep_neighbors* nb, const float* params, const n
   a.nzw = outer_slices(a.ow.M, a.ow.V);
   a.nzc = outer_slices(a.oc.M, a.oc.V);
   a.os_x = std::max(a.ow.NB, a.oc.NB);
-  a.PW = c.L.PW;
-  a.seg = at<int>(c.ws, c.L.seg);
-  a.pp = at<double>(c.ws, c.L.pp);
+  a.pr = part_args(c);
   a.la = loss_args(c, labels, lam, loss, flags);
   a.g = grad_args(c, grad);
   a.n_gf = (int)grad_final_blocks(a.g);
@@ -4831,7 +4920,12 @@ int nep_train_step_graph_create_tuned(const nep_model* m, const nep_batch* b, ne
     run_pack(c, nb, nullptr);
     c.o->step(sa, sgrid, slds, cap);
   } else {
-    hipLaunchKernelGGL(k_graph_head, dim3(1), dim3(64), 0, cap, d_flags, d_step, cur);
+    if ((graph_flags & NEP_GRAPH_CACHED_NEIGHBORS) != 0 || c.L.N == 0) {
+      hipLaunchKernelGGL(k_graph_head, dim3(1), dim3(64), 0, cap, d_flags, d_step, cur);
+    } else {   // by the order launch of the neighbor build
+      c.g_step = d_step;
+      c.g_cur = cur;
+    }
     // a padded model's class-layout parameters are refreshed by every replay
     loss_grad_seq(c, nb, kernel_params(c, params), labels, lambda, loss, grad, nullptr, nullptr, nullptr, d_flags,
                   nullptr, (graph_flags & NEP_GRAPH_CACHED_NEIGHBORS) == 0);

@@ -32,7 +32,7 @@ SPACE = {
     "persistent": [0, 1],
     "adjoint_waves": [3, 2],
     "forward_waves": [3, 2],
-    "outer_blocks_w": [192, 96, 128, 256, 384],
+    "outer_blocks_w": [96, 64, 128, 192, 256],
     "outer_blocks_c": [64, 32, 128],
     "reduce_chunks": [128, 64, 256],
     "gather_lanes": [16, 8],
