@@ -3576,22 +3576,38 @@ __device__ __forceinline__ float inv_mass(const MDArgs& a, int i) {
   return (t >= 0 && t < a.T) ? kAccel / a.mass[t] : 0.f;
 }
 
-// half kick with the forces at the current positions, drift, wrap into the
-// cell: [0, L) per axis for an orthorhombic cell; for a triclinic one, minus
-// the lattice vector H floor(f) of the fractional coordinates f = H^-1 x
-__global__ __launch_bounds__(256) void k_md_drift(MDArgs a) {
+// One launch between two force evaluations.  With kKick the half kick that
+// ends a step (forces at the current positions); with kDrift the half kick
+// that begins the next one, the drift and the wrap into the cell: [0, L) per
+// axis for an orthorhombic cell; for a triclinic one, minus the lattice vector
+// H floor(f) of the fractional coordinates f = H^-1 x.  The last kick (no
+// drift) also gives the kinetic energy per atom.
+template <bool kKick, bool kDrift>
+__global__ __launch_bounds__(256) void k_md_move(MDArgs a) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= a.N) return;
   const float im = inv_mass(a, i);
-  const int st = a.astruct[i];
-  float x[3];
+  const float k = a.hdt * im;
+  float x[3], v2 = 0.f;
 #pragma unroll
   for (int c = 0; c < 3; ++c) {
     const size_t q = (size_t)c * a.N + i;
-    const float v = fmaf(a.hdt * im, a.F[q], a.vel[q]);
+    const float f = a.F[q];
+    float v = a.vel[q];
+    if (kKick) v = fmaf(k, f, v);
+    if (kDrift) {
+      v = fmaf(k, f, v);
+      x[c] = fmaf(a.dt, v, a.pos[q]);
+    } else {
+      v2 = fmaf(v, v, v2);
+    }
     a.vel[q] = v;
-    x[c] = fmaf(a.dt, v, a.pos[q]);
   }
+  if (!kDrift) {
+    a.ekin[i] = im > 0.f ? 0.5f * v2 / im : 0.f;
+    return;
+  }
+  const int st = a.astruct[i];
   const float Lx = a.box[3 * st], Ly = a.box[3 * st + 1], Lz = a.box[3 * st + 2];
   const float xy = a.tilt ? a.tilt[3 * st] : 0.f, xz = a.tilt ? a.tilt[3 * st + 1] : 0.f,
               yz = a.tilt ? a.tilt[3 * st + 2] : 0.f;
@@ -3614,22 +3630,6 @@ __global__ __launch_bounds__(256) void k_md_drift(MDArgs a) {
   }
 #pragma unroll
   for (int c = 0; c < 3; ++c) a.pos[(size_t)c * a.N + i] = x[c];
-}
-
-// half kick with the forces at the new positions; kinetic energy per atom
-__global__ __launch_bounds__(256) void k_md_kick(MDArgs a) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= a.N) return;
-  const float im = inv_mass(a, i);
-  float v2 = 0.f;
-#pragma unroll
-  for (int c = 0; c < 3; ++c) {
-    const size_t q = (size_t)c * a.N + i;
-    const float v = fmaf(a.hdt * im, a.F[q], a.vel[q]);
-    a.vel[q] = v;
-    v2 = fmaf(v, v, v2);
-  }
-  a.ekin[i] = im > 0.f ? 0.5f * v2 / im : 0.f;
 }
 
 // out[s] = sum of x over the atoms of structure s (float64, one block each)
@@ -4309,7 +4309,7 @@ StructArgs struct_args(const Ctx& c, float* e_struct, float* virial, const nep_l
 
 void run_forward(const Ctx& c, const nep_neighbors* nb, const float* params, float* e_atom, float* e_struct,
                  float* force, float* virial, const nep_labels* lab, const float* lam, float* loss, int32_t* flags,
-                 Prof* pr, bool defer_loss = false) {
+                 Prof* pr, bool defer_loss = false, bool sums = true) {
   const int N = c.L.N, S = c.b->n_struct;
   if (N > 0) {
     FwdArgs a = fwd_args(c, nb, params);
@@ -4321,7 +4321,7 @@ void run_forward(const Ctx& c, const nep_neighbors* nb, const float* params, flo
     launch_forward_pass(c, nb, params, a, pr);
     NEP_LAUNCH(pr, "force", c.o->force(force_args(c, a, force), c.st, c.tune.gather_lanes));
   }
-  if (S > 0) {
+  if (S > 0 && sums) {
     const StructArgs s = struct_args(c, e_struct, virial, lab, lam);
     if (s.split)
       NEP_LAUNCH(pr, "struct_part",
@@ -4783,12 +4783,18 @@ int nep_md_step(const nep_model* m, const nep_batch* b, float* pos, nep_neighbor
   a.hdt = 0.5f * dt;
   a.dt = dt;
   params = kernel_params(c, params);
+  // the energies are those of the last step: no sums before it (they and the
+  // separate kick and drift took 6 of 46 us a step of a 180-atom cell)
   for (int k = 0; k < n_steps; ++k) {
-    hipLaunchKernelGGL(k_md_drift, dim3(grid1(N)), dim3(256), 0, c.st, a);
+    if (k == 0)
+      hipLaunchKernelGGL(HIP_KERNEL_NAME(k_md_move<false, true>), dim3(grid1(N)), dim3(256), 0, c.st, a);
+    else
+      hipLaunchKernelGGL(HIP_KERNEL_NAME(k_md_move<true, true>), dim3(grid1(N)), dim3(256), 0, c.st, a);
     run_neighbors(c, nb, d_flags, nullptr);
-    run_forward(c, nb, params, nullptr, e_pot, force, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr);
-    hipLaunchKernelGGL(k_md_kick, dim3(grid1(N)), dim3(256), 0, c.st, a);
+    run_forward(c, nb, params, nullptr, e_pot, force, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, false,
+                k + 1 == n_steps);
   }
+  hipLaunchKernelGGL(HIP_KERNEL_NAME(k_md_move<true, false>), dim3(grid1(N)), dim3(256), 0, c.st, a);
   if (e_kin && S > 0)
     hipLaunchKernelGGL(k_struct_sum, dim3(S), dim3(256), 0, c.st, b->atom_offset, a.ekin, e_kin);
   return hip_ok();
