@@ -251,10 +251,14 @@ def flags_status(flags_value: int) -> int:
     return int(_lib.load().nep_flags_status(int(flags_value)))
 
 
+def check_flags_value(value: int, where="device"):
+    """Raise NEPError when a flag word already read from the device is set."""
+    _check(flags_status(value), where)
+
+
 def check_flags(flags, where="device"):
     """Raise NEPError when the device flag word (synchronises) is set."""
-    code = flags_status(int(flags.item()))
-    _check(code, where)
+    check_flags_value(int(flags.item()), where)
 
 
 def md_step(model, batch, nbrs, params, mass, vel, force, dt, n_steps, e_pot, ws, flags, e_kin=None, stream=None):

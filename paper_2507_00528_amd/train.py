@@ -181,15 +181,18 @@ class Trainer:
         self.stream.synchronize()
         secs = time.perf_counter() - t0
         w = np.array([st.n_atom for st in order], np.float64)
-        ls = torch.stack([st.loss for st in order]).cpu().numpy().astype(np.float64)
-        for st in order:
-            self.nep.check_flags(st.flags, "training step")
+        # one copy to the host for the losses, flag words and step (flags as float64: exact)
+        host = torch.cat([torch.stack([st.loss for st in order]).double().view(-1),
+                          torch.cat([st.flags for st in order]).double(), self.step.double()]).cpu().numpy()
+        ls = host[:4 * len(order)].reshape(-1, 4)
+        for f in host[4 * len(order):-1]:
+            self.nep.check_flags_value(int(f), "training step")
+        done = int(host[-1])
         rec = {"epoch": len(self.history) + 1, "loss": float((w[:, None] * ls).sum(0)[0] / w.sum()),
                "loss_e": float((w * ls[:, 1]).sum() / w.sum()), "loss_f": float((w * ls[:, 2]).sum() / w.sum()),
                "loss_v": float((w * ls[:, 3]).sum() / w.sum()), "seconds": secs,
-               "steps": int(self.step.item()) - 1,
-               "lr": self.nep.lr_schedule(int(self.step.item()) - 2, self.lr_start, self.lr_stop, self.n_warmup,
-                                          self.n_total)}
+               "steps": done - 1,
+               "lr": self.nep.lr_schedule(done - 2, self.lr_start, self.lr_stop, self.n_warmup, self.n_total)}
         self.history.append(rec)
         return rec
 
