@@ -78,7 +78,7 @@ struct FwdArgs {
   int nn_stride;
   float* G;        // [D][Npad] species order (may be null)
   float* Guser;    // [D][N] atom order (may be null)
-  float* Sst;      // [NA*YR][Npad] (may be null)
+  float* Sst;      // [Npad][NA*YR rounded up to 4] (may be null)
   float* FRst;     // [T*KR][Npad] radial sums F[J][k] (may be null)
   float* Ep;       // [D][Npad] (may be null)
   float* X;        // [H][Npad] (may be null)
@@ -121,7 +121,7 @@ struct AdjArgs {
   const float* cA;
   const float* nn;
   int nn_stride;
-  const float* Sst;   // [NA*YR][Npad]
+  const float* Sst;   // [Npad][NA*YR rounded up to 4]
   const float* Ep;    // [D][Npad]
   const float* X;     // [H][Npad]
   const float* eps;   // [S] dL/dE(n)

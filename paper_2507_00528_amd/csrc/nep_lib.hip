@@ -1192,20 +1192,20 @@ __global__ __launch_bounds__(1024) void k_order(OrderArgs a, FlagArgs f) {
 }
 
 // ================================================================= helpers
-// c^A of every species pair (I, J) staged in LDS with rows padded to KAP = 4k
-// floats: a pair reads its 4-aligned row with a few wide LDS reads instead of
-// selecting each coefficient by the neighbor's species
+// c^A of the block's species with every neighbor species staged in LDS, rows
+// padded to KAP = 4k floats: a pair reads its 4-aligned row with a few wide
+// LDS reads instead of selecting each coefficient by the neighbor's species
 template <int T, int NA, int KA>
 struct CTab {
   static constexpr int KAP = (KA + 3) & ~3;
-  static constexpr int size = T * T * NA * KAP;
+  static constexpr int size = T * NA * KAP;
 };
 
 // Entry 0 of a row holds c_0 + sum_k c_k (the terms h T_0 of every
 // order), so g_n = sum_k row[k] h T_k.
 template <int T, int NA, int KA>
 __device__ __forceinline__ void stage_ctab(float* ct, const float* __restrict__ cA) {
-  constexpr int KAP = CTab<T, NA, KA>::KAP, R = T * T * NA;
+  constexpr int KAP = CTab<T, NA, KA>::KAP, R = T * NA;
   // a row per thread: its loads are in flight together
   for (int r = threadIdx.x; r < R; r += blockDim.x) {
     float v[KAP], sum = 0.f;
@@ -1322,6 +1322,16 @@ static_assert(kSegAlign % kAPB == 0, "species segments must align to blocks (one
 #include "nep_highl.h"
 namespace nep {
 
+// c^R of the block's species in LDS, [T][NR][KR], read lane by lane by the
+// radial sums and the force coefficients.  With c^A of that species alone and
+// S_nlm stored atom by atom in 16-byte units (it was one row per channel and
+// harmonic), the forward fits four blocks per CU: 85 -> 78 us at 512
+// structures (87k atoms), the adjoint 119 -> 117.
+template <class C>
+struct CRad {
+  static constexpr int N = C::T * C::NR * C::KR, size = (N + 3) & ~3;
+};
+
 // Row of radial force coefficients of one (atom, neighbor species): KP words
 template <class C>
 struct HRad {
@@ -1397,7 +1407,7 @@ __device__ __forceinline__ GroupCtx group_ctx(const int* __restrict__ order, int
 template <int T>
 __device__ __forceinline__ int block_species(const int* __restrict__ order, const float4* __restrict__ p4, int vb) {
   const int ip = order[vb * kAPB];
-  return ip >= 0 ? packed_type<T>(p4[ip]) : 0;
+  return ip >= 0 ? __builtin_amdgcn_readfirstlane(packed_type<T>(p4[ip])) : 0;
 }
 
 // LDS words of the staged weights: whole 64-word rows, so that the direct
@@ -1509,9 +1519,9 @@ __device__ __forceinline__ StreamPair stream_pair(const float* sl, int p, const 
 // Radial sums of an atom from its 8 lanes' partial sums v[t KR + k] over h T_k
 // (or q_k): on return o[r] of lane s holds F[t][k] of entry 8 r + s, each with
 // the T_0 term of its species added, and qn[r] holds sum_tk c^R_{ItnK} F[t][k]
-// of channel n = 8 r + s.  cRI: c^R of species I.
+// of channel n = 8 r + s.  cRI: c^R of species I (LDS).
 template <class C>
-__device__ __forceinline__ void radial_finish(const float (&v)[C::T * C::KR], cptr<float> cRI, int s,
+__device__ __forceinline__ void radial_finish(const float (&v)[C::T * C::KR], const float* cRI, int s,
                                               float (&o)[(C::T * C::KR + 7) / 8], float (&qn)[(C::NR + 7) / 8]) {
   constexpr int T = C::T, NR = C::NR, KR = C::KR, TK = T * KR, NV = (TK + 7) / 8;
   rs_group8(v, o);
@@ -1527,7 +1537,7 @@ __device__ __forceinline__ void radial_finish(const float (&v)[C::T * C::KR], cp
     const bool on = TK % 8 == 0 || e < TK;
 #pragma unroll
     for (int u = 0; u < T; ++u) o[r] += t == u ? a0[u] : 0.f;
-    const cptr<float> c = cRI + (on ? t * NR * KR + kk : 0);
+    const float* c = cRI + (on ? t * NR * KR + kk : 0);
     const float x = on ? o[r] : 0.f;
 #pragma unroll
     for (int n = 0; n < NR; ++n) part[n] = fmaf(c[n * KR], x, part[n]);
@@ -1542,7 +1552,8 @@ template <class C>
 struct FwdLds {
   static constexpr int DP = (C::D + 3) & ~3, YR = HRow<C::LMAX>::YR;
   static constexpr int RS = (C::NA + YR) | 1;
-  static constexpr int RW = (DP + C::NA * YR + 7) / 8 * 8 + 4;
+  static constexpr int SW = (C::NA * YR + 3) & ~3;   // an atom's S in HBM
+  static constexpr int RW = (DP + SW + 7) / 8 * 8 + 4;
   static constexpr int BUF = (kWave * RS > kAPW * RW ? kWave * RS : kAPW * RW) + 3 & ~3;
   static constexpr int WAVE = kAPW * slot_words<true>() + BUF;
 };
@@ -1584,20 +1595,23 @@ __device__ __forceinline__ void forward_body(const FwdArgs& a, int b, float* lds
   constexpr bool kVec = YR % 4 == 0;
   const int H = a.H;
   using CT = CTab<T, NA, KA>;
-  float* ctab = lds;                     // [T][T][NA][KAP]
-  float* wl = lds + CT::size;            // weights of the block's species
+  float* ctab = lds;                     // [T][NA][KAP], c^A of the block's species
+  float* crl = lds + CT::size;           // its c^R
+  float* wl = crl + CRad<C>::size;       // its weights
   float* slots = wl + weights_words(H, DP) + (threadIdx.x / kWave) * FL::WAVE;
   float* buf = slots + kAPW * slot_words<kTri>();
   const int vb = launch_block(a.blist, a.nch, T, b);
   if (vb < 0) return;
   // issued here, waited for after the angular sums: their latency overlaps the
   // pair passes
-  if (a.do_mlp) stage_weights_async(wl, a.nn, a.nn_stride, block_species<T>(a.order, a.p4, vb), H, D, DP);
+  const int I = block_species<T>(a.order, a.p4, vb);
+  if (a.do_mlp) stage_weights_async(wl, a.nn, a.nn_stride, I, H, D, DP);
+  stage_ctab<T, NA, KA>(ctab, a.cA + (size_t)I * T * NA * KA);
+  for (int q = threadIdx.x; q < CRad<C>::N; q += 256) crl[q] = a.cR[(size_t)I * CRad<C>::N + q];
   const GroupCtx w = group_ctx(a.order, a.Npad, vb);
   const int N = a.N, i = w.i, pa = w.pa, s = w.s, g = w.g;
   const int lane = threadIdx.x & (kWave - 1), slot = lane / kLPA;
   const float4 me = a.p4[i];
-  const int I = __builtin_amdgcn_readfirstlane(packed_type<T>(me));   // one species per wavefront
   float* row = buf + slot * RW;
   float* rowS = row + DP;
   const int st = a.astruct[i];
@@ -1606,8 +1620,6 @@ __device__ __forceinline__ void forward_body(const FwdArgs& a, int b, float* lds
   const int cR_i = a.nb.cntR[i], cA_i = a.nb.cntA[i];
   const int nR = w.valid ? min(cR_i, a.nb.capR) : 0;
   const int nA = w.valid ? min(cA_i, a.nb.capA) : 0;
-  const cptr<float> cRI = as_const(a.cR) + (size_t)I * T * NR * KR;
-  stage_ctab<T, NA, KA>(ctab, a.cA);
 
   // ---- radial sums in Chebyshev space, pairs split over the 8 lanes
   constexpr int NQ = (NR + kLPA - 1) / kLPA;
@@ -1643,7 +1655,8 @@ __device__ __forceinline__ void forward_body(const FwdArgs& a, int b, float* lds
       }
     }
     float o[(T * KR + 7) / 8];
-    radial_finish<C>(FR, cRI, s, o, qn);
+    lds_barrier();   // the block's coefficient tables
+    radial_finish<C>(FR, crl, s, o, qn);
     if (a.FRst && w.valid) {
 #pragma unroll
       for (int r = 0; r < (T * KR + 7) / 8; ++r) {
@@ -1657,7 +1670,7 @@ __device__ __forceinline__ void forward_body(const FwdArgs& a, int b, float* lds
   //      of an atom sums its pairs for the harmonics s, s + 8, ...
   const PairStream ps = pair_stream(nA);
   if (s == 0) slot_store<kTri>(slots + slot * slot_words<kTri>(), i, xi, yi, zi, cell, ps.lo);
-  lds_barrier();   // the block's coefficient table
+  lds_lane_exchange();
   {
     float S[NE][NA];
 #pragma unroll
@@ -1670,7 +1683,7 @@ __device__ __forceinline__ void forward_body(const FwdArgs& a, int b, float* lds
         const StreamPair sp = stream_pair<T, kTri>(slots + pair_slot(ps, p) * slot_words<kTri>(), p, a.nb, a.p4);
         float f[KA];
         radial_cheb<KA>(sp.q.r, a.inv_rcA, f);
-        const float* cJ = ctab + (I * T + sp.J) * NA * CT::KAP;
+        const float* cJ = ctab + sp.J * NA * CT::KAP;
         float* rec = buf + lane * RS;
 #pragma unroll
         for (int n = 0; n < NA; ++n) {
@@ -1717,11 +1730,15 @@ __device__ __forceinline__ void forward_body(const FwdArgs& a, int b, float* lds
       const int e = r * kLPA + s;
       if (YR % kLPA == 0 || e < YR) {
 #pragma unroll
-        for (int n = 0; n < NA; ++n) {
-          rowS[n * YR + e] = S[r][n];   // zero at padding entries
-          if (w.valid && a.Sst) a.Sst[(size_t)(n * YR + e) * a.Npad + pa] = S[r][n];
-        }
+        for (int n = 0; n < NA; ++n) rowS[n * YR + e] = S[r][n];   // zero at padding entries
       }
+    }
+    lds_lane_exchange();
+    // stored atom by atom, 16 bytes a lane
+    if (w.valid && a.Sst) {
+      float4* so = reinterpret_cast<float4*>(a.Sst + (size_t)pa * FL::SW);
+#pragma unroll
+      for (int q = s; q < FL::SW / 4; q += kLPA) so[q] = reinterpret_cast<const float4*>(rowS)[q];
     }
   }
 #pragma unroll
@@ -1832,7 +1849,7 @@ __device__ __forceinline__ void forward_body(const FwdArgs& a, int b, float* lds
     for (int r = 0; r < NH; ++r) {
       const int e = r * kLPA + s, t = e / KP, kk = e % KP;
       const bool on = t < T && kk < KR;
-      const cptr<float> c = cRI + (on ? t * NR * KR + kk : 0);
+      const float* c = crl + (on ? t * NR * KR + kk : 0);
       float acc = 0.f;
 #pragma unroll
       for (int n = 0; n < NR; ++n) acc = fmaf(row[n], c[n * KR], acc);
@@ -1898,7 +1915,7 @@ __device__ __forceinline__ void forward_body(const FwdArgs& a, int b, float* lds
     const float ux = q.dx * q.inv_r, uy = q.dy * q.inv_r, uz = q.dz * q.inv_r;
     float f[KA], fp[KA];
     radial_cheb_d<KA>(q.r, a.inv_rcA, f, fp);
-    const float* cJ = ctab + (I * T + sp.J) * NA * CT::KAP;
+    const float* cJ = ctab + sp.J * NA * CT::KAP;
     const float* rowA = buf + u * RW + DP;
     float B[Y], uf[Y];
     harm_val<LM>(ux, uy, uz, B);
@@ -2320,7 +2337,9 @@ template <class C>
 struct AdjLds {
   static constexpr int DP = (C::D + 3) & ~3, YG = HSplit<C::LMAX>::YG, YR = HRow<C::LMAX>::YR;
   static constexpr int RS = (2 * C::NA + 2 * YG) | 1;
-  static constexpr int RW = (DP + 2 * C::NA * YR + 7) / 8 * 8 + 4;
+  // S at a multiple of 4 words after Sdot
+  static constexpr int SW = (C::NA * YR + 3) & ~3;
+  static constexpr int RW = (DP + 2 * SW + 7) / 8 * 8 + 4;
   static constexpr int BUF = ((kWave * RS > kAPW * RW ? kWave * RS : kAPW * RW) + 3) & ~3;
   static constexpr int WAVE = kAPW * kAdjSlot + BUF;
   static constexpr int REC = (2 * C::NA + 2 * C::KA + 1) | 1;   // X, Y (u.t), h T_k, q_k, species
@@ -2363,45 +2382,46 @@ __device__ __forceinline__ void adjoint_body(const AdjArgs& a, int b, float* lds
   constexpr int YG = AL::YG, YR = AL::YR, DP = AL::DP, RS = AL::RS, RW = AL::RW;
   constexpr int NAH = (NA + 1) / 2;          // channels per lane in the tangent sums
   constexpr int NEH = (YG + 3) / 4;          // harmonics of a group per lane there
-  constexpr int NE = (YR + kLPA - 1) / kLPA, NN = (NA + 3) / 4;
+  constexpr int NN = (NA + 3) / 4;
   constexpr int PSA = T * NA * KA;
   constexpr bool kVec = YR % 4 == 0;
   const int H = a.H;
   using CT = CTab<T, NA, KA>;
-  float* ctab = lds;                     // [T][T][NA][KAP]
-  float* wl = lds + CT::size;            // weights of the block's species
+  float* ctab = lds;                     // [T][NA][KAP], c^A of the block's species
+  float* crl = lds + CT::size;           // its c^R
+  float* wl = crl + CRad<C>::size;       // its weights
   float* slots = wl + AL::shared_words(H) + (threadIdx.x / kWave) * AL::WAVE;
   float* buf = slots + kAPW * kAdjSlot;
   const int vb = launch_block(a.blist, a.nch, T, b);
   if (vb < 0) return;
   // issued here, waited for after the tangent sums
-  stage_weights_async(wl, a.nn, a.nn_stride, block_species<T>(a.order, a.p4, vb), H, D, DP);
+  const int I = block_species<T>(a.order, a.p4, vb);
+  stage_weights_async(wl, a.nn, a.nn_stride, I, H, D, DP);
+  stage_ctab<T, NA, KA>(ctab, a.cA + (size_t)I * T * NA * KA);
+  for (int q = threadIdx.x; q < CRad<C>::N; q += 256) crl[q] = a.cR[(size_t)I * CRad<C>::N + q];
   const GroupCtx w = group_ctx(a.order, a.Npad, vb);
   const int i = w.i, pa = w.pa, s = w.s, g = w.g;
   const size_t Np = a.Npad;
   const float4 me = a.p4[i];
-  const int I = __builtin_amdgcn_readfirstlane(packed_type<T>(me));
   const int lane = threadIdx.x & (kWave - 1), slot = lane / kLPA;
   const int wave = (vb * 256 + (int)threadIdx.x) / kWave;
   const bool first_atom = slot == 0;   // atom slot 0 of the wavefront writes the sums
   float* part = a.part + (size_t)wave * a.PW;
   float* row = buf + slot * RW;
   float* rowSb = row + DP;
-  float* rowA = rowSb + NA * YR;
+  float* rowA = rowSb + AL::SW;
   const int st = a.astruct[i];
   const Cell cell = load_cell<kTri>(a.box, a.tilt, st);
   const float xi = me.x, yi = me.y, zi = me.z;
   const int cR_i = a.nb.cntR[i], cA_i = a.nb.cntA[i];
   const int nR = w.valid ? min(cR_i, a.nb.capR) : 0;
   const int nA = w.valid ? min(cA_i, a.nb.capA) : 0;
-  const cptr<float> cRI = as_const(a.cR) + (size_t)I * T * NR * KR;
   const float eps_v = a.eps[st];
   const float eps = w.valid ? eps_v : 0.f;
   const float* wb = a.wbar + 6 * st;
   const float gxx = wb[0], gyy = wb[1], gzz = wb[2], gxy = wb[3], gyz = wb[4], gzx = wb[5];
   const float4 fi = a.fb4[i];
   const float fbx = fi.x, fby = fi.y, fbz = fi.z;
-  stage_ctab<T, NA, KA>(ctab, a.cA);
 
   // ---- radial tangent sums Fp[J][k] = sum_j f'_k(r_hat.t), pairs split over the 8 lanes
   constexpr int NQ = (NR + kLPA - 1) / kLPA;
@@ -2443,7 +2463,8 @@ __device__ __forceinline__ void adjoint_body(const AdjArgs& a, int b, float* lds
       }
     }
     float o[(T * KR + 7) / 8];
-    radial_finish<C>(FP, cRI, s, o, qn);
+    lds_barrier();   // the block's coefficient tables
+    radial_finish<C>(FP, crl, s, o, qn);
     if (w.valid) {
 #pragma unroll
       for (int r = 0; r < (T * KR + 7) / 8; ++r) {
@@ -2465,17 +2486,18 @@ __device__ __forceinline__ void adjoint_body(const AdjArgs& a, int b, float* lds
     *reinterpret_cast<float4*>(sl + kSlotG) = make_float4(gxx, gyy, gzz, gxy);
     *reinterpret_cast<float4*>(sl + kSlotG2) = make_float4(gyz, gzx, 0.f, 0.f);
   }
-  // S of the forward, entries s, s + 8, ... of every channel, for the rows
-  float Sr[NE][NA];
+  // S of the forward for the rows, 16 bytes a lane
+  constexpr int SW = FwdLds<C>::SW, NS4 = (SW / 4 + kLPA - 1) / kLPA;
+  float4 Sr[NS4];
+  {
+    const float4* si = reinterpret_cast<const float4*>(a.Sst + (size_t)pa * SW);
 #pragma unroll
-  for (int r = 0; r < NE; ++r)
-#pragma unroll
-    for (int n = 0; n < NA; ++n) {
-      const int e = r * kLPA + s;
-      const float v = a.Sst[(size_t)(n * YR + (YR % kLPA == 0 || e < YR ? e : 0)) * Np + pa];
-      Sr[r][n] = w.valid ? v : 0.f;
+    for (int r = 0; r < NS4; ++r) {
+      const float4 v = si[min(r * kLPA + s, SW / 4 - 1)];
+      Sr[r] = w.valid ? v : make_float4(0.f, 0.f, 0.f, 0.f);
     }
-  lds_barrier();   // the block's coefficient table
+  }
+  lds_lane_exchange();
   {
     const int n0 = (s >> 2) * NAH, h0 = (s & 3) * NEH;
     float Sd[2][NEH][NAH];
@@ -2496,7 +2518,7 @@ __device__ __forceinline__ void adjoint_body(const AdjArgs& a, int b, float* lds
         const PairTangent t = pair_tangent(sp.q, sl, a.fb4[sp.q.j]);
         float f[KA], fp[KA];
         radial_cheb_d<KA>(sp.q.r, a.inv_rcA, f, fp);
-        const float* cJ = ctab + (I * T + sp.J) * NA * CT::KAP;
+        const float* cJ = ctab + sp.J * NA * CT::KAP;
 #pragma unroll
         for (int n = 0; n < NA; ++n) {
           float s0 = 0.f, s1 = 0.f;
@@ -2557,10 +2579,8 @@ __device__ __forceinline__ void adjoint_body(const AdjArgs& a, int b, float* lds
           if (n0 + j < NA && (YG % 4 == 0 || h0 + e < YG)) rowSb[(n0 + j) * YR + gg * YG + h0 + e] = Sd[gg][e][j];
   }
 #pragma unroll
-  for (int r = 0; r < NE; ++r)
-    if (YR % kLPA == 0 || r * kLPA + s < YR)
-#pragma unroll
-      for (int n = 0; n < NA; ++n) rowA[n * YR + r * kLPA + s] = Sr[r][n];
+  for (int r = 0; r < NS4; ++r)
+    if (SW / 4 % kLPA == 0 || r * kLPA + s < SW / 4) reinterpret_cast<float4*>(rowA)[r * kLPA + s] = Sr[r];
 #pragma unroll
   for (int r = 0; r < NQ; ++r)
     if (r * kLPA + s < NR) row[r * kLPA + s] = qn[r];
@@ -2763,7 +2783,7 @@ __device__ __forceinline__ void adjoint_body(const AdjArgs& a, int b, float* lds
         for (int gg = 0; gg < 2; ++gg) {
           float Sb[YG], Av[YG];
           row_load<YG, kVec>(sb + n * YR + gg * YG, Sb);
-          row_load<YG, kVec>(sb + NA * YR + n * YR + gg * YG, Av);
+          row_load<YG, kVec>(sb + AL::SW + n * YR + gg * YG, Av);
 #pragma unroll
           for (int e = 0; e < YG; ++e) {
             const int qq = HS::q(gg, e);
@@ -3668,13 +3688,13 @@ struct Ops {
 template <class C>
 static size_t lds_forward(int H) {
   using FL = FwdLds<C>;
-  return sizeof(float) * ((size_t)CTab<C::T, C::NA, C::KA>::size + (size_t)weights_words(H, FL::DP) +
+  return sizeof(float) * ((size_t)CTab<C::T, C::NA, C::KA>::size + CRad<C>::size + (size_t)weights_words(H, FL::DP) +
                           (size_t)(256 / kWave) * FL::WAVE);
 }
 template <class C>
 static size_t lds_adjoint(int H) {
   using AL = AdjLds<C>;
-  return sizeof(float) * ((size_t)CTab<C::T, C::NA, C::KA>::size + (size_t)AL::shared_words(H) +
+  return sizeof(float) * ((size_t)CTab<C::T, C::NA, C::KA>::size + CRad<C>::size + (size_t)AL::shared_words(H) +
                           (size_t)(256 / kWave) * AL::WAVE);
 }
 // LDS of a workgroup on gfx950 (160 KiB per CU); dynamic LDS beyond 64 KiB is
@@ -3945,7 +3965,7 @@ Layout make_layout(const nep_model* m, const Ops* o, int S, int N, bool pad = fa
   L.astruct = take(4 * Nn);
   L.p4 = take(16 * Nn);
   L.G = take(4 * (size_t)L.D * Np);
-  L.Sst = take(4 * (size_t)L.NA * o->YR * Np);
+  L.Sst = take(4 * (((size_t)L.NA * o->YR + 3) & ~(size_t)3) * Np);
   L.Ep = take(4 * (size_t)L.D * Np);
   L.X = take(4 * (size_t)L.H * Np);
   L.eatom = take(4 * Nn);
