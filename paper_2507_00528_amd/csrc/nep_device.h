@@ -469,6 +469,47 @@ __device__ __forceinline__ void rs_group8(const float (&x)[V], float (&out)[(V +
   rs_step(y2, out, Xor4Step{});
 }
 
+// The same over the L lanes (8, 16 or 32) of an atom: a total, the total over
+// the atoms of the wavefront (lanes with the same l mod L), and a
+// reduce-scatter with out[r] of lane s the sum of value L r + s.
+template <int L>
+__device__ __forceinline__ float grp_sum(float v) {
+  v = grp8_sum(v);
+  if constexpr (L >= 16) v += dpp<kDppRowRor8>(v);
+  if constexpr (L >= 32) v = xor16_sum(v);
+  return v;
+}
+template <int L>
+__device__ __forceinline__ float atoms_sum(float v) {
+  if constexpr (L <= 8) v += dpp<kDppRowRor8>(v);
+  if constexpr (L <= 16) v = xor16_sum(v);
+  return xor32_sum(v);
+}
+struct Xor16Step {
+  __device__ __forceinline__ float operator()(float e, float o) const {
+    const bool hi = threadIdx.x & 16;
+    const float send = hi ? e : o, keep = hi ? o : e;
+    return keep + __shfl_xor(send, 16, kWave);
+  }
+};
+template <int L, int V>
+__device__ __forceinline__ void rs_group(const float (&x)[V], float (&out)[(V + L - 1) / L]) {
+  if constexpr (L == 8) {
+    rs_group8(x, out);
+  } else {
+    constexpr int V8 = (V + 7) / 8, V16 = (V8 + 1) / 2;
+    float y[V8];
+    rs_group8(x, y);
+    if constexpr (L == 16) {
+      rs_step(y, out, DppStep<kDppRowRor8>{3});
+    } else {
+      float z[V16];
+      rs_step(y, z, DppStep<kDppRowRor8>{3});
+      rs_step(z, out, Xor16Step{});
+    }
+  }
+}
+
 // Image shift of a neighbor code: code = 9(sx+1) + 3(sy+1) + (sz+1).  The
 // quotients of code < 27 by 9 and of the remainder by 3 from 24-bit products
 // (full rate; a division by a constant takes a quarter-rate high product).

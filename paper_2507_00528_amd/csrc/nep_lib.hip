@@ -1306,15 +1306,16 @@ __global__ __launch_bounds__(256) void k_pack(int N, int T, const float* __restr
 }
 
 // ========================================================= atom groups
-// Per-atom kernels run 8 lanes per atom, 8 atoms per wavefront and 32 atoms
-// per block.  Lane s = l & 7 of an atom's group splits the radial pairs
-// (pairs k = s, s+8, ...); for the angular sums the group is 2 harmonic
-// groups x 4 pair slots: g = s >> 2 picks the harmonics (l = 1 and 4, or
-// l = 2 and 3; 12 each for l <= 4) and p = s & 3 the pairs k = p, p+4, ....
-// The hidden layer is split over hidden units mu = s, s+8, ....
-// Atoms are in species order with species segments aligned to 8, so every
-// wavefront evaluates a single species' network.
-constexpr int kLPA = 8;                    // lanes per atom
+// Per-atom kernels run L lanes per atom, 64 / L atoms per wavefront and 256 / L
+// per block (L = 8, or 16 or 32 in the forward and the adjoint of small
+// batches, group_lanes).  Lane s = l mod L of an atom's group takes the radial
+// pairs k = s, s + L, ... and the hidden units mu = s, s + L, ...; for the
+// angular descriptors the group is 2 harmonic groups x L / 2 channels:
+// g = s / (L / 2) picks the harmonics (l = 1 and 4, or l = 2 and 3; 12 each
+// for l <= 4) and p = s mod (L / 2) the channels n = p, p + L / 2, ....
+// Atoms are in species order with species segments aligned to 32, so every
+// block evaluates a single species' network.
+constexpr int kLPA = 8;                    // lanes per atom, and of the high-degree kernels
 constexpr int kAPB = 256 / kLPA;           // atoms per block
 constexpr int kAPW = kWave / kLPA;         // atoms per wavefront
 static_assert(kSegAlign % kAPB == 0, "species segments must align to blocks (one species per block)");
@@ -1385,13 +1386,14 @@ struct GroupCtx {
 
 // lane roles and the atom of this lane; every lane of the block stays alive
 // (lanes without an atom repeat one of the wavefront's, or atom 0)
+template <int L>
 __device__ __forceinline__ GroupCtx group_ctx(const int* __restrict__ order, int Npad, int vb) {
   GroupCtx c;
-  c.s = threadIdx.x & (kLPA - 1);
-  c.g = c.s >> 2;
-  c.p = c.s & 3;
-  c.al = threadIdx.x / kLPA;
-  c.pa = vb * kAPB + c.al;
+  c.s = threadIdx.x & (L - 1);
+  c.g = c.s / (L / 2);
+  c.p = c.s & (L / 2 - 1);
+  c.al = threadIdx.x / L;
+  c.pa = vb * (256 / L) + c.al;
   const int iraw = c.pa < Npad ? order[c.pa] : -1;
   c.valid = iraw >= 0;
   const unsigned long long vm = __ballot(c.valid);
@@ -1435,7 +1437,7 @@ __device__ __forceinline__ void stage_weights_async(float* wl, const float* __re
 __device__ __forceinline__ void wait_weights() { __builtin_amdgcn_s_waitcnt(0); }
 
 // ======================================================== angular pair stream
-// The angular pairs of a wavefront's 8 atoms form one stream, taken 64 at a
+// The angular pairs of a wavefront's atoms form one stream, taken 64 at a
 // time with one pair per lane: geometry, basis and harmonics are evaluated
 // once per pair.  (With the pairs split over 4 slots of an atom's lanes, both
 // harmonic groups evaluated them, and an atom with 5 pairs took as long as
@@ -1452,23 +1454,26 @@ constexpr int slot_words() {
   return 12;   // x y z i | Lx Ly Lz base | xy xz yz -; 4 mod 8, so the 8 slots start in different banks
 }
 
+template <int L>
 struct PairStream {
-  int cum[kAPW];   // stream position of slot v's first pair (wave-uniform)
+  static constexpr int APW = kWave / L;
+  int cum[APW];   // stream position of slot v's first pair (wave-uniform)
   int total;
   int lo, hi;      // this lane's own atom's pairs
 };
 
-// nA: the pairs of this lane's atom (the same in its 8 lanes)
-__device__ __forceinline__ PairStream pair_stream(int nA) {
-  PairStream st;
-  const int slot = (threadIdx.x & (kWave - 1)) / kLPA;
+// nA: the pairs of this lane's atom (the same in its L lanes)
+template <int L>
+__device__ __forceinline__ PairStream<L> pair_stream(int nA) {
+  PairStream<L> st;
+  const int slot = (threadIdx.x & (kWave - 1)) / L;
   int at = 0;
   st.lo = 0;
 #pragma unroll
-  for (int v = 0; v < kAPW; ++v) {
+  for (int v = 0; v < st.APW; ++v) {
     st.cum[v] = at;
     st.lo = v == slot ? at : st.lo;
-    at += __builtin_amdgcn_readlane(nA, v * kLPA);
+    at += __builtin_amdgcn_readlane(nA, v * L);
   }
   st.total = at;
   st.hi = st.lo + nA;
@@ -1476,10 +1481,11 @@ __device__ __forceinline__ PairStream pair_stream(int nA) {
 }
 
 // atom slot of stream position p
-__device__ __forceinline__ int pair_slot(const PairStream& st, int p) {
+template <int L>
+__device__ __forceinline__ int pair_slot(const PairStream<L>& st, int p) {
   int u = 0;
 #pragma unroll
-  for (int v = 1; v < kAPW; ++v) u += p >= st.cum[v] ? 1 : 0;
+  for (int v = 1; v < st.APW; ++v) u += p >= st.cum[v] ? 1 : 0;
   return u;
 }
 
@@ -1516,25 +1522,25 @@ __device__ __forceinline__ StreamPair stream_pair(const float* sl, int p, const 
   return r;
 }
 
-// Radial sums of an atom from its 8 lanes' partial sums v[t KR + k] over h T_k
-// (or q_k): on return o[r] of lane s holds F[t][k] of entry 8 r + s, each with
+// Radial sums of an atom from its L lanes' partial sums v[t KR + k] over h T_k
+// (or q_k): on return o[r] of lane s holds F[t][k] of entry L r + s, each with
 // the T_0 term of its species added, and qn[r] holds sum_tk c^R_{ItnK} F[t][k]
-// of channel n = 8 r + s.  cRI: c^R of species I (LDS).
-template <class C>
+// of channel n = L r + s.  cRI: c^R of species I (LDS).
+template <class C, int L>
 __device__ __forceinline__ void radial_finish(const float (&v)[C::T * C::KR], const float* cRI, int s,
-                                              float (&o)[(C::T * C::KR + 7) / 8], float (&qn)[(C::NR + 7) / 8]) {
-  constexpr int T = C::T, NR = C::NR, KR = C::KR, TK = T * KR, NV = (TK + 7) / 8;
-  rs_group8(v, o);
+                                              float (&o)[(C::T * C::KR + L - 1) / L], float (&qn)[(C::NR + L - 1) / L]) {
+  constexpr int T = C::T, NR = C::NR, KR = C::KR, TK = T * KR, NV = (TK + L - 1) / L;
+  rs_group<L>(v, o);
   float a0[T];
 #pragma unroll
-  for (int t = 0; t < T; ++t) a0[t] = __shfl(o[t * KR / 8], t * KR % 8, 8);
+  for (int t = 0; t < T; ++t) a0[t] = __shfl(o[t * KR / L], t * KR % L, L);
   float part[NR];
 #pragma unroll
   for (int n = 0; n < NR; ++n) part[n] = 0.f;
 #pragma unroll
   for (int r = 0; r < NV; ++r) {
-    const int e = r * 8 + s, t = e / KR, kk = e % KR;
-    const bool on = TK % 8 == 0 || e < TK;
+    const int e = r * L + s, t = e / KR, kk = e % KR;
+    const bool on = TK % L == 0 || e < TK;
 #pragma unroll
     for (int u = 0; u < T; ++u) o[r] += t == u ? a0[u] : 0.f;
     const float* c = cRI + (on ? t * NR * KR + kk : 0);
@@ -1542,20 +1548,21 @@ __device__ __forceinline__ void radial_finish(const float (&v)[C::T * C::KR], co
 #pragma unroll
     for (int n = 0; n < NR; ++n) part[n] = fmaf(c[n * KR], x, part[n]);
   }
-  rs_group8(part, qn);
+  rs_group<L>(part, qn);
 }
 
 // LDS of the forward per wavefront: the slot table, then the pair records of
 // the angular sums (g_n and the harmonics, odd stride) and, once they are
 // summed, the atoms' rows (G, then S or A in group order; stride 4 mod 8)
-template <class C>
+template <class C, int L>
 struct FwdLds {
+  static constexpr int APW = kWave / L;   // atoms per wavefront
   static constexpr int DP = (C::D + 3) & ~3, YR = HRow<C::LMAX>::YR;
   static constexpr int RS = (C::NA + YR) | 1;
   static constexpr int SW = (C::NA * YR + 3) & ~3;   // an atom's S in HBM
   static constexpr int RW = (DP + SW + 7) / 8 * 8 + 4;
-  static constexpr int BUF = (kWave * RS > kAPW * RW ? kWave * RS : kAPW * RW) + 3 & ~3;
-  static constexpr int WAVE = kAPW * slot_words<true>() + BUF;
+  static constexpr int BUF = (kWave * RS > APW * RW ? kWave * RS : APW * RW) + 3 & ~3;
+  static constexpr int WAVE = APW * slot_words<true>() + BUF;
 };
 
 // words [base + e], e = 0..W-1 (16-byte reads when the row allows)
@@ -1583,15 +1590,15 @@ __device__ __forceinline__ void row_load(const float* p, float (&v)[W]) {
 // gives E_i and E' = dE_i/dG (D1.1-D1.5).  With forces on, the atom's radial
 // force coefficients and every angular pair's partial force f_ij = dE_i/dr_ij
 // (C3.6) are stored for the force pass.
-// Launch index b (32 atoms of the species order); lds: lds_forward bytes.
-template <class C, bool kTri>
+// Launch index b (256 / L atoms of the species order); lds: lds_forward bytes.
+template <class C, bool kTri, int L>
 __device__ __forceinline__ void forward_body(const FwdArgs& a, int b, float* lds) {
   constexpr int T = C::T, NR = C::NR, NA = C::NA, KR = C::KR, KA = C::KA, Y = C::Y, D = C::D, LM = C::LMAX;
   constexpr int L3 = C::L3, L4 = C::L4, L5 = C::L5;
   using HS = HSplit<LM>;
-  using FL = FwdLds<C>;
+  using FL = FwdLds<C, L>;
   constexpr int YG = HS::YG, YR = HRow<LM>::YR, DP = FL::DP, RS = FL::RS, RW = FL::RW;
-  constexpr int NE = (YR + kLPA - 1) / kLPA;   // harmonics summed per lane
+  constexpr int NE = (YR + L - 1) / L;   // harmonics summed per lane
   constexpr bool kVec = YR % 4 == 0;
   const int H = a.H;
   using CT = CTab<T, NA, KA>;
@@ -1599,18 +1606,20 @@ __device__ __forceinline__ void forward_body(const FwdArgs& a, int b, float* lds
   float* crl = lds + CT::size;           // its c^R
   float* wl = crl + CRad<C>::size;       // its weights
   float* slots = wl + weights_words(H, DP) + (threadIdx.x / kWave) * FL::WAVE;
-  float* buf = slots + kAPW * slot_words<kTri>();
-  const int vb = launch_block(a.blist, a.nch, T, b);
-  if (vb < 0) return;
+  float* buf = slots + (kWave / L) * slot_words<kTri>();
+  // 32 atoms of one species, taken by L / 8 blocks
+  const int vs = launch_block(a.blist, a.nch, T, b / (L / 8));
+  if (vs < 0) return;
+  const int vb = vs * (L / 8) + b % (L / 8);
   // issued here, waited for after the angular sums: their latency overlaps the
   // pair passes
-  const int I = block_species<T>(a.order, a.p4, vb);
+  const int I = block_species<T>(a.order, a.p4, vs);
   if (a.do_mlp) stage_weights_async(wl, a.nn, a.nn_stride, I, H, D, DP);
   stage_ctab<T, NA, KA>(ctab, a.cA + (size_t)I * T * NA * KA);
   for (int q = threadIdx.x; q < CRad<C>::N; q += 256) crl[q] = a.cR[(size_t)I * CRad<C>::N + q];
-  const GroupCtx w = group_ctx(a.order, a.Npad, vb);
+  const GroupCtx w = group_ctx<L>(a.order, a.Npad, vb);
   const int N = a.N, i = w.i, pa = w.pa, s = w.s, g = w.g;
-  const int lane = threadIdx.x & (kWave - 1), slot = lane / kLPA;
+  const int lane = threadIdx.x & (kWave - 1), slot = lane / L;
   const float4 me = a.p4[i];
   float* row = buf + slot * RW;
   float* rowS = row + DP;
@@ -1621,9 +1630,9 @@ __device__ __forceinline__ void forward_body(const FwdArgs& a, int b, float* lds
   const int nR = w.valid ? min(cR_i, a.nb.capR) : 0;
   const int nA = w.valid ? min(cA_i, a.nb.capA) : 0;
 
-  // ---- radial sums in Chebyshev space, pairs split over the 8 lanes
-  constexpr int NQ = (NR + kLPA - 1) / kLPA;
-  float qn[NQ];   // channels s, s + 8, ...
+  // ---- radial sums in Chebyshev space, pairs split over the lanes
+  constexpr int NQ = (NR + L - 1) / L;
+  float qn[NQ];   // channels s, s + L, ...
   {
     float FR[T * KR];
 #pragma unroll
@@ -1634,15 +1643,15 @@ __device__ __forceinline__ void forward_body(const FwdArgs& a, int b, float* lds
     float4 p0 = make_float4(0.f, 0.f, 0.f, 0.f);
     if (s < nR) {
       e0 = li[s];
-      e1 = li[min(s + kLPA, nR - 1)];
+      e1 = li[min(s + L, nR - 1)];
       p0 = a.p4[e0 >> 5];
     }
-    for (int k = s; k < nR; k += kLPA) {
+    for (int k = s; k < nR; k += L) {
       const uint32_t e = e0;
       const float4 pj = p0;
       e0 = e1;
       p0 = a.p4[e1 >> 5];
-      e1 = li[min(k + 2 * kLPA, nR - 1)];
+      e1 = li[min(k + 2 * L, nR - 1)];
       const PairGeom q = packed_geom<kTri>(e, pj, xi, yi, zi, cell);
       float f[KR];
       radial_cheb<KR>(q.r, a.inv_rcR, f);
@@ -1654,21 +1663,21 @@ __device__ __forceinline__ void forward_body(const FwdArgs& a, int b, float* lds
         for (int kk = 0; kk < KR; ++kk) FR[t * KR + kk] = fmaf(m, f[kk], FR[t * KR + kk]);
       }
     }
-    float o[(T * KR + 7) / 8];
+    float o[(T * KR + L - 1) / L];
     lds_barrier();   // the block's coefficient tables
-    radial_finish<C>(FR, crl, s, o, qn);
+    radial_finish<C, L>(FR, crl, s, o, qn);
     if (a.FRst && w.valid) {
 #pragma unroll
-      for (int r = 0; r < (T * KR + 7) / 8; ++r) {
-        const int e = r * kLPA + s;
-        if (T * KR % 8 == 0 || e < T * KR) a.FRst[(size_t)e * a.Npad + pa] = o[r];
+      for (int r = 0; r < (T * KR + L - 1) / L; ++r) {
+        const int e = r * L + s;
+        if (T * KR % L == 0 || e < T * KR) a.FRst[(size_t)e * a.Npad + pa] = o[r];
       }
     }
   }
 
   // ---- angular sums S_nlm: one pair per lane writes g_n and B_lm, then lane s
-  //      of an atom sums its pairs for the harmonics s, s + 8, ...
-  const PairStream ps = pair_stream(nA);
+  //      of an atom sums its pairs for the harmonics s, s + L, ...
+  const PairStream<L> ps = pair_stream<L>(nA);
   if (s == 0) slot_store<kTri>(slots + slot * slot_words<kTri>(), i, xi, yi, zi, cell, ps.lo);
   lds_lane_exchange();
   {
@@ -1712,8 +1721,8 @@ __device__ __forceinline__ void forward_body(const FwdArgs& a, int b, float* lds
         for (int n = 0; n < NA; ++n) gn[n] = rec[n];
 #pragma unroll
         for (int r = 0; r < NE; ++r) {
-          const int e = r * kLPA + s;
-          const float b = rec[NA + (YR % kLPA == 0 || e < YR ? e : 0)];
+          const int e = r * L + s;
+          const float b = rec[NA + (YR % L == 0 || e < YR ? e : 0)];
 #pragma unroll
           for (int n = 0; n < NA; ++n) S[r][n] = fmaf(gn[n], b, S[r][n]);
         }
@@ -1727,8 +1736,8 @@ __device__ __forceinline__ void forward_body(const FwdArgs& a, int b, float* lds
     // the atoms' rows take the records' place
 #pragma unroll
     for (int r = 0; r < NE; ++r) {
-      const int e = r * kLPA + s;
-      if (YR % kLPA == 0 || e < YR) {
+      const int e = r * L + s;
+      if (YR % L == 0 || e < YR) {
 #pragma unroll
         for (int n = 0; n < NA; ++n) rowS[n * YR + e] = S[r][n];   // zero at padding entries
       }
@@ -1738,19 +1747,19 @@ __device__ __forceinline__ void forward_body(const FwdArgs& a, int b, float* lds
     if (w.valid && a.Sst) {
       float4* so = reinterpret_cast<float4*>(a.Sst + (size_t)pa * FL::SW);
 #pragma unroll
-      for (int q = s; q < FL::SW / 4; q += kLPA) so[q] = reinterpret_cast<const float4*>(rowS)[q];
+      for (int q = s; q < FL::SW / 4; q += L) so[q] = reinterpret_cast<const float4*>(rowS)[q];
     }
   }
 #pragma unroll
   for (int r = 0; r < NQ; ++r)
-    if (r * kLPA + s < NR) row[r * kLPA + s] = qn[r];
+    if (r * L + s < NR) row[r * L + s] = qn[r];
   lds_lane_exchange();
 
   // ---- angular descriptors, channel n and harmonic group g by the lane of
-  //      pair slot n mod 4 and group g
+  //      channel slot n mod (L / 2) and group g
   const int lA = g ? 2 : 1, lB = g ? 3 : 4;
   const int nAg = g ? HS::nA1 : HS::nA0;     // size of the first l block
-  for (int n = w.p; n < NA; n += 4) {
+  for (int n = w.p; n < NA; n += L / 2) {
     float Sn[YG];
     row_load<YG, kVec>(rowS + n * YR + g * YG, Sn);
     float qa = 0.f, qb = 0.f;
@@ -1773,7 +1782,7 @@ __device__ __forceinline__ void forward_body(const FwdArgs& a, int b, float* lds
   }
   if constexpr (C::YH > 0) {
     // q_nl of l = 5..L3, from k_high_desc
-    for (int v = NR + 4 * NA + s; v < NR + L3 * NA; v += kLPA) {
+    for (int v = NR + 4 * NA + s; v < NR + L3 * NA; v += L) {
       const float x = a.G[(size_t)v * a.Npad + pa];
       row[v] = w.valid ? x : 0.f;
     }
@@ -1783,9 +1792,9 @@ __device__ __forceinline__ void forward_body(const FwdArgs& a, int b, float* lds
   row_load<DP, true>(row, G);   // words past D are not used
   if (w.valid) {
 #pragma unroll
-    for (int r = 0; r < (D + kLPA - 1) / kLPA; ++r) {
-      const int v = r * kLPA + s;
-      if (D % kLPA == 0 || v < D) {
+    for (int r = 0; r < (D + L - 1) / L; ++r) {
+      const int v = r * L + s;
+      if (D % L == 0 || v < D) {
         const float x = row[v];
         if (a.G) a.G[(size_t)v * a.Npad + pa] = x;
         if (a.Guser) a.Guser[(size_t)v * N + i] = x;
@@ -1794,13 +1803,13 @@ __device__ __forceinline__ void forward_body(const FwdArgs& a, int b, float* lds
   }
   if (!a.do_mlp) return;
 
-  // ---- network: hidden units mu = s, s+8, ... (weights from LDS)
+  // ---- network: hidden units mu = s, s + L, ... (weights from LDS)
   const float* Wl = wl;
   float Ep[D];
 #pragma unroll
   for (int v = 0; v < D; ++v) Ep[v] = 0.f;
   float E = 0.f;
-  for (int mu = s; mu < H; mu += kLPA) {
+  for (int mu = s; mu < H; mu += L) {
     const float* wr = Wl + mu * DP;
     float z = Wl[H * DP + mu];
 #pragma unroll
@@ -1813,14 +1822,14 @@ __device__ __forceinline__ void forward_body(const FwdArgs& a, int b, float* lds
     for (int v = 0; v < D; ++v) Ep[v] = fmaf(sg, wr[v], Ep[v]);
     if (w.valid && a.X) a.X[(size_t)mu * a.Npad + pa] = x;
   }
-  // E' summed over the 8 lanes, scattered (entry v in lane v & 7), shared
+  // E' summed over the lanes, scattered (entry v in lane v mod L), shared
   // through the atom's LDS row (G there has been read)
   {
-    float eo[(D + 7) / 8];
-    rs_group8(Ep, eo);
+    float eo[(D + L - 1) / L];
+    rs_group<L>(Ep, eo);
 #pragma unroll
-    for (int r = 0; r < (D + 7) / 8; ++r) {
-      const int v = 8 * r + s;
+    for (int r = 0; r < (D + L - 1) / L; ++r) {
+      const int v = L * r + s;
       if (v < D) {
         row[v] = eo[r];
         if (w.valid && a.Ep) a.Ep[(size_t)v * a.Npad + pa] = eo[r];
@@ -1828,7 +1837,7 @@ __device__ __forceinline__ void forward_body(const FwdArgs& a, int b, float* lds
     }
     lds_lane_exchange();
   }
-  E = grp8_sum(E) + a.nn[(size_t)I * a.nn_stride + H * D + 2 * H];
+  E = grp_sum<L>(E) + a.nn[(size_t)I * a.nn_stride + H * D + 2 * H];
   if (w.valid) {
     if (s == 0) {
       if (a.eatom) a.eatom[i] = E;
@@ -1838,16 +1847,16 @@ __device__ __forceinline__ void forward_body(const FwdArgs& a, int b, float* lds
   if (!a.do_force) return;
 
   // ---- radial force coefficients h_Jk = sum_n E'_n c^R_{IJnk} for the force
-  //      pass, entry (J, k) by lane (J KP + k) mod 8; entry (J, 0) also takes
+  //      pass, entry (J, k) by lane (J KP + k) mod L; entry (J, 0) also takes
   //      sum_k h_Jk (the terms h T_0 of every order)
   {
-    constexpr int KP = HRad<C>::KP, NH = (T * KP + kLPA - 1) / kLPA;
+    constexpr int KP = HRad<C>::KP, NH = (T * KP + L - 1) / L;
     float hv[NH], sum[T];
 #pragma unroll
     for (int t = 0; t < T; ++t) sum[t] = 0.f;
 #pragma unroll
     for (int r = 0; r < NH; ++r) {
-      const int e = r * kLPA + s, t = e / KP, kk = e % KP;
+      const int e = r * L + s, t = e / KP, kk = e % KP;
       const bool on = t < T && kk < KR;
       const float* c = crl + (on ? t * NR * KR + kk : 0);
       float acc = 0.f;
@@ -1858,12 +1867,12 @@ __device__ __forceinline__ void forward_body(const FwdArgs& a, int b, float* lds
       for (int u = 0; u < T; ++u) sum[u] += t == u ? hv[r] : 0.f;
     }
 #pragma unroll
-    for (int t = 0; t < T; ++t) sum[t] = grp8_sum(sum[t]);
+    for (int t = 0; t < T; ++t) sum[t] = grp_sum<L>(sum[t]);
     if (w.valid) {
       float* ho = a.hrow + (size_t)i * T * KP;
 #pragma unroll
       for (int r = 0; r < NH; ++r) {
-        const int e = r * kLPA + s, t = e / KP;
+        const int e = r * L + s, t = e / KP;
         float v = hv[r];
 #pragma unroll
         for (int u = 0; u < T; ++u) v += (t == u && e == u * KP) ? sum[u] : 0.f;
@@ -1874,7 +1883,7 @@ __device__ __forceinline__ void forward_body(const FwdArgs& a, int b, float* lds
 
   // ---- A_nlm = sum_v E'_v dG_v/dS_nlm in place of S_nlm, lanes as for the
   //      angular descriptors
-  for (int n = w.p; n < NA; n += 4) {
+  for (int n = w.p; n < NA; n += L / 2) {
     float Sn[YG];
     row_load<YG, kVec>(rowS + n * YR + g * YG, Sn);
     const float eA = lA <= L3 ? row[NR + ((lA <= L3 ? lA : 1) - 1) * NA + n] : 0.f;
@@ -1956,10 +1965,10 @@ __device__ __forceinline__ void forward_body(const FwdArgs& a, int b, float* lds
   }
 }
 
-template <class C, bool kTri, int W>
+template <class C, bool kTri, int W, int L>
 __global__ __launch_bounds__(256, W) void k_forward(FwdArgs a) {
   extern __shared__ __align__(16) float lds[];
-  forward_body<C, kTri>(a, blockIdx.x, lds);
+  forward_body<C, kTri, L>(a, blockIdx.x, lds);
 }
 
 // Forces F_i = sum_j f_ij - f_ji (Eq. 3) and the atom's share of the virial.
@@ -2322,8 +2331,8 @@ __global__ __launch_bounds__(kRedBlk) void k_loss_final(int S, int N, float le, 
 //            Sbar = Gbar . dG/dS - E' . (d2G/dS2) Sdot  (the pairwise
 //            coupling that Algorithm 1 enumerates).
 // Outputs: per-atom vectors for the outer-product sums (W0, c^R) and, per
-// wavefront, the sums of the c^A, b0, w1, b1 partials over its 8 atoms.
-// Launch index b (32 atoms of the species order); lds: lds_adjoint bytes.
+// wavefront, the sums of the c^A, b0, w1, b1 partials over its atoms.
+// Launch index b (256 / L atoms of the species order); lds: lds_adjoint bytes.
 // Slot table of the adjoint: the forward's words, then F-bar and Gamma.
 constexpr int kSlotF = 12, kSlotG = 16, kSlotG2 = 20, kAdjSlot = 28;   // 4 mod 8
 
@@ -2333,15 +2342,16 @@ constexpr int kSlotF = 12, kSlotG = 16, kSlotG2 = 20, kAdjSlot = 28;   // 4 mod 
 // atoms' rows (Gdot or Gbar, Sdot or Sbar, S or A in group order; stride 4 mod 8).
 // Per block: the coefficient table and the weights, whose words hold the
 // coefficient gradient's records (16 pairs per wavefront) after the network.
-template <class C>
+template <class C, int L>
 struct AdjLds {
+  static constexpr int APW = kWave / L;
   static constexpr int DP = (C::D + 3) & ~3, YG = HSplit<C::LMAX>::YG, YR = HRow<C::LMAX>::YR;
   static constexpr int RS = (2 * C::NA + 2 * YG) | 1;
   // S at a multiple of 4 words after Sdot
   static constexpr int SW = (C::NA * YR + 3) & ~3;
   static constexpr int RW = (DP + 2 * SW + 7) / 8 * 8 + 4;
-  static constexpr int BUF = ((kWave * RS > kAPW * RW ? kWave * RS : kAPW * RW) + 3) & ~3;
-  static constexpr int WAVE = kAPW * kAdjSlot + BUF;
+  static constexpr int BUF = ((kWave * RS > APW * RW ? kWave * RS : APW * RW) + 3) & ~3;
+  static constexpr int WAVE = APW * kAdjSlot + BUF;
   static constexpr int REC = (2 * C::NA + 2 * C::KA + 1) | 1;   // X, Y (u.t), h T_k, q_k, species
   static constexpr int RECS = (256 / kWave) * 16 * REC;
   __host__ __device__ static int shared_words(int H) {
@@ -2373,16 +2383,16 @@ __device__ __forceinline__ PairTangent pair_tangent(const PairGeom& q, const flo
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-template <class C, bool kTri>
+template <class C, bool kTri, int L>
 __device__ __forceinline__ void adjoint_body(const AdjArgs& a, int b, float* lds) {
   constexpr int T = C::T, NR = C::NR, NA = C::NA, KR = C::KR, KA = C::KA, Y = C::Y, D = C::D, LM = C::LMAX;
   constexpr int L3 = C::L3, L4 = C::L4, L5 = C::L5;
   using HS = HSplit<LM>;
-  using AL = AdjLds<C>;
+  using AL = AdjLds<C, L>;
   constexpr int YG = AL::YG, YR = AL::YR, DP = AL::DP, RS = AL::RS, RW = AL::RW;
   constexpr int NAH = (NA + 1) / 2;          // channels per lane in the tangent sums
-  constexpr int NEH = (YG + 3) / 4;          // harmonics of a group per lane there
-  constexpr int NN = (NA + 3) / 4;
+  constexpr int HL = L / 2, NEH = (YG + HL - 1) / HL;          // harmonics of a group per lane there
+  constexpr int NN = (NA + HL - 1) / HL;
   constexpr int PSA = T * NA * KA;
   constexpr bool kVec = YR % 4 == 0;
   const int H = a.H;
@@ -2391,19 +2401,21 @@ __device__ __forceinline__ void adjoint_body(const AdjArgs& a, int b, float* lds
   float* crl = lds + CT::size;           // its c^R
   float* wl = crl + CRad<C>::size;       // its weights
   float* slots = wl + AL::shared_words(H) + (threadIdx.x / kWave) * AL::WAVE;
-  float* buf = slots + kAPW * kAdjSlot;
-  const int vb = launch_block(a.blist, a.nch, T, b);
-  if (vb < 0) return;
+  float* buf = slots + (kWave / L) * kAdjSlot;
+  // 32 atoms of one species, taken by L / 8 blocks
+  const int vs = launch_block(a.blist, a.nch, T, b / (L / 8));
+  if (vs < 0) return;
+  const int vb = vs * (L / 8) + b % (L / 8);
   // issued here, waited for after the tangent sums
-  const int I = block_species<T>(a.order, a.p4, vb);
+  const int I = block_species<T>(a.order, a.p4, vs);
   stage_weights_async(wl, a.nn, a.nn_stride, I, H, D, DP);
   stage_ctab<T, NA, KA>(ctab, a.cA + (size_t)I * T * NA * KA);
   for (int q = threadIdx.x; q < CRad<C>::N; q += 256) crl[q] = a.cR[(size_t)I * CRad<C>::N + q];
-  const GroupCtx w = group_ctx(a.order, a.Npad, vb);
+  const GroupCtx w = group_ctx<L>(a.order, a.Npad, vb);
   const int i = w.i, pa = w.pa, s = w.s, g = w.g;
   const size_t Np = a.Npad;
   const float4 me = a.p4[i];
-  const int lane = threadIdx.x & (kWave - 1), slot = lane / kLPA;
+  const int lane = threadIdx.x & (kWave - 1), slot = lane / L;
   const int wave = (vb * 256 + (int)threadIdx.x) / kWave;
   const bool first_atom = slot == 0;   // atom slot 0 of the wavefront writes the sums
   float* part = a.part + (size_t)wave * a.PW;
@@ -2423,8 +2435,8 @@ __device__ __forceinline__ void adjoint_body(const AdjArgs& a, int b, float* lds
   const float4 fi = a.fb4[i];
   const float fbx = fi.x, fby = fi.y, fbz = fi.z;
 
-  // ---- radial tangent sums Fp[J][k] = sum_j f'_k(r_hat.t), pairs split over the 8 lanes
-  constexpr int NQ = (NR + kLPA - 1) / kLPA;
+  // ---- radial tangent sums Fp[J][k] = sum_j f'_k(r_hat.t), pairs split over the lanes
+  constexpr int NQ = (NR + L - 1) / L;
   float qn[NQ];
   {
     float FP[T * KR];
@@ -2436,17 +2448,17 @@ __device__ __forceinline__ void adjoint_body(const AdjArgs& a, int b, float* lds
     float4 p0 = make_float4(0.f, 0.f, 0.f, 0.f), f0 = p0;
     if (s < nR) {
       e0 = li[s];
-      e1 = li[min(s + kLPA, nR - 1)];
+      e1 = li[min(s + L, nR - 1)];
       p0 = a.p4[e0 >> 5];
       f0 = a.fb4[e0 >> 5];
     }
-    for (int k = s; k < nR; k += kLPA) {
+    for (int k = s; k < nR; k += L) {
       const uint32_t e = e0;
       const float4 pj = p0, fj = f0;
       e0 = e1;
       p0 = a.p4[e1 >> 5];
       f0 = a.fb4[e1 >> 5];
-      e1 = li[min(k + 2 * kLPA, nR - 1)];
+      e1 = li[min(k + 2 * L, nR - 1)];
       const PairGeom q = packed_geom<kTri>(e, pj, xi, yi, zi, cell);
       const float tx = (fj.x - fbx) + gxx * q.dx + gxy * q.dy;
       const float ty = (fj.y - fby) + gyy * q.dy + gyz * q.dz;
@@ -2462,23 +2474,23 @@ __device__ __forceinline__ void adjoint_body(const AdjArgs& a, int b, float* lds
         for (int kk = 0; kk < KR; ++kk) FP[u * KR + kk] = fmaf(md, fp[kk], FP[u * KR + kk]);
       }
     }
-    float o[(T * KR + 7) / 8];
+    float o[(T * KR + L - 1) / L];
     lds_barrier();   // the block's coefficient tables
-    radial_finish<C>(FP, crl, s, o, qn);
+    radial_finish<C, L>(FP, crl, s, o, qn);
     if (w.valid) {
 #pragma unroll
-      for (int r = 0; r < (T * KR + 7) / 8; ++r) {
-        const int e = r * kLPA + s;
-        if (T * KR % 8 == 0 || e < T * KR) a.FPst[(size_t)e * Np + pa] = o[r];
+      for (int r = 0; r < (T * KR + L - 1) / L; ++r) {
+        const int e = r * L + s;
+        if (T * KR % L == 0 || e < T * KR) a.FPst[(size_t)e * Np + pa] = o[r];
       }
     }
   }
 
   // ---- angular tangent sums Sdot_nlm = sum_j g'_n (r_hat.t) B_lm + g_n grad B_lm . t:
   //      one pair per lane writes them for one harmonic group at a time; lane s
-  //      of an atom then sums its pairs for channels (s >> 2) NAH + j and the
-  //      harmonics (s & 3) NEH + e of the group
-  const PairStream ps = pair_stream(nA);
+  //      of an atom then sums its pairs for channels (s / HL) NAH + j and
+  //      the harmonics (s mod HL) NEH + e of the group
+  const PairStream<L> ps = pair_stream<L>(nA);
   if (s == 0) {
     float* sl = slots + slot * kAdjSlot;
     slot_store<kTri>(sl, i, xi, yi, zi, cell, ps.lo);
@@ -2487,19 +2499,19 @@ __device__ __forceinline__ void adjoint_body(const AdjArgs& a, int b, float* lds
     *reinterpret_cast<float4*>(sl + kSlotG2) = make_float4(gyz, gzx, 0.f, 0.f);
   }
   // S of the forward for the rows, 16 bytes a lane
-  constexpr int SW = FwdLds<C>::SW, NS4 = (SW / 4 + kLPA - 1) / kLPA;
+  constexpr int SW = FwdLds<C, L>::SW, NS4 = (SW / 4 + L - 1) / L;
   float4 Sr[NS4];
   {
     const float4* si = reinterpret_cast<const float4*>(a.Sst + (size_t)pa * SW);
 #pragma unroll
     for (int r = 0; r < NS4; ++r) {
-      const float4 v = si[min(r * kLPA + s, SW / 4 - 1)];
+      const float4 v = si[min(r * L + s, SW / 4 - 1)];
       Sr[r] = w.valid ? v : make_float4(0.f, 0.f, 0.f, 0.f);
     }
   }
   lds_lane_exchange();
   {
-    const int n0 = (s >> 2) * NAH, h0 = (s & 3) * NEH;
+    const int n0 = s / HL * NAH, h0 = (s & (HL - 1)) * NEH;
     float Sd[2][NEH][NAH];
 #pragma unroll
     for (int gg = 0; gg < 2; ++gg)
@@ -2559,7 +2571,7 @@ __device__ __forceinline__ void adjoint_body(const AdjArgs& a, int b, float* lds
           }
 #pragma unroll
           for (int e = 0; e < NEH; ++e) {
-            const int q = YG % 4 == 0 ? h0 + e : min(h0 + e, YG - 1);
+            const int q = YG % HL == 0 ? h0 + e : min(h0 + e, YG - 1);
             const float b = rp[2 * NA + 2 * q], c = rp[2 * NA + 2 * q + 1];
 #pragma unroll
             for (int j = 0; j < NAH; ++j) Sd[gg][e][j] = fmaf(gp[j], b, fmaf(gn[j], c, Sd[gg][e][j]));
@@ -2576,22 +2588,22 @@ __device__ __forceinline__ void adjoint_body(const AdjArgs& a, int b, float* lds
       for (int e = 0; e < NEH; ++e)
 #pragma unroll
         for (int j = 0; j < NAH; ++j)
-          if (n0 + j < NA && (YG % 4 == 0 || h0 + e < YG)) rowSb[(n0 + j) * YR + gg * YG + h0 + e] = Sd[gg][e][j];
+          if (n0 + j < NA && (YG % HL == 0 || h0 + e < YG)) rowSb[(n0 + j) * YR + gg * YG + h0 + e] = Sd[gg][e][j];
   }
 #pragma unroll
   for (int r = 0; r < NS4; ++r)
-    if (SW / 4 % kLPA == 0 || r * kLPA + s < SW / 4) reinterpret_cast<float4*>(rowA)[r * kLPA + s] = Sr[r];
+    if (SW / 4 % L == 0 || r * L + s < SW / 4) reinterpret_cast<float4*>(rowA)[r * L + s] = Sr[r];
 #pragma unroll
   for (int r = 0; r < NQ; ++r)
-    if (r * kLPA + s < NR) row[r * kLPA + s] = qn[r];
+    if (r * L + s < NR) row[r * L + s] = qn[r];
   lds_lane_exchange();
 
   // ---- Gdot of the angular descriptors, channel n and harmonic group g by the
-  //      lane of pair slot n mod 4 and group g
+  //      lane of channel slot n mod (L / 2) and group g
   const int nAg = g ? HS::nA1 : HS::nA0;
   const int lA = g ? 2 : 1, lB = g ? 3 : 4;
   const int lAc = lA <= L3 ? lA : 1, lBc = lB <= L3 ? lB : 1;
-  for (int n = w.p; n < NA; n += 4) {
+  for (int n = w.p; n < NA; n += L / 2) {
     float Sn[YG], Sdn[YG];
     row_load<YG, kVec>(rowA + n * YR + g * YG, Sn);
     row_load<YG, kVec>(rowSb + n * YR + g * YG, Sdn);
@@ -2617,7 +2629,7 @@ __device__ __forceinline__ void adjoint_body(const AdjArgs& a, int b, float* lds
   }
   if constexpr (C::YH > 0) {
     // Gdot of q_nl, l = 5..L3, from k_high_tangent
-    for (int v = NR + 4 * NA + s; v < NR + L3 * NA; v += kLPA) {
+    for (int v = NR + 4 * NA + s; v < NR + L3 * NA; v += L) {
       const float x = a.Gd[(size_t)v * Np + pa];
       row[v] = w.valid ? x : 0.f;
     }
@@ -2627,31 +2639,31 @@ __device__ __forceinline__ void adjoint_body(const AdjArgs& a, int b, float* lds
   row_load<DP, true>(row, Gd);   // words past D are not used
   if (w.valid) {
 #pragma unroll
-    for (int r = 0; r < (D + kLPA - 1) / kLPA; ++r) {
-      const int v = r * kLPA + s;
-      if (D % kLPA == 0 || v < D) a.Gd[(size_t)v * Np + pa] = row[v];
+    for (int r = 0; r < (D + L - 1) / L; ++r) {
+      const int v = r * L + s;
+      if (D % L == 0 || v < D) a.Gd[(size_t)v * Np + pa] = row[v];
     }
   }
   // E' of the descriptors this lane's Sbar and A need, loaded ahead of the network
   float epA[NN], epB[NN], ep4[NN], ep5[NN];
 #pragma unroll
   for (int r = 0; r < NN; ++r) {
-    const int n = min(w.p + 4 * r, NA - 1);
+    const int n = min(w.p + HL * r, NA - 1);
     epA[r] = a.Ep[(size_t)(NR + (lAc - 1) * NA + n) * Np + pa];
     epB[r] = a.Ep[(size_t)(NR + (lBc - 1) * NA + n) * Np + pa];
     ep4[r] = L4 ? a.Ep[(size_t)(NR + L3 * NA + n) * Np + pa] : 0.f;
     ep5[r] = L5 ? a.Ep[(size_t)(NR + L3 * NA + (L4 ? NA : 0) + n) * Np + pa] : 0.f;
   }
 
-  // ---- network adjoint, hidden units mu = s, s+8, ...
+  // ---- network adjoint, hidden units mu = s, s + L, ...
   const float* Wl = wl;
   {
     float Gb[D];
 #pragma unroll
     for (int v = 0; v < D; ++v) Gb[v] = 0.f;
-    const int RH = (H + kLPA - 1) / kLPA;
+    const int RH = (H + L - 1) / L;
     for (int r = 0; r < RH; ++r) {
-      const int mu = r * kLPA + s;
+      const int mu = r * L + s;
       const bool act = mu < H;
       const int mm = act ? mu : H - 1;
       const float* wr = Wl + mm * DP;
@@ -2667,24 +2679,24 @@ __device__ __forceinline__ void adjoint_body(const AdjArgs& a, int b, float* lds
 #pragma unroll
       for (int v = 0; v < D; ++v) Gb[v] = fmaf(be, wr[v], Gb[v]);
       if (live) a.beta[(size_t)mu * Np + pa] = be;
-      const float r0 = atoms8_sum(be);
-      const float r1 = atoms8_sum(live ? eps * x - sg * aa : 0.f);
+      const float r0 = atoms_sum<L>(be);
+      const float r1 = atoms_sum<L>(live ? eps * x - sg * aa : 0.f);
       if (act && first_atom) {
         part[PSA + mu] = r0;
         part[PSA + H + mu] = r1;
       }
     }
     {
-      const float r = atoms8_sum(s == 0 ? eps : 0.f);
+      const float r = atoms_sum<L>(s == 0 ? eps : 0.f);
       if (lane == 0) part[PSA + 2 * H] = r;
     }
     // Gbar to the row's first D words (Gdot there has been read)
-    float go[(D + 7) / 8];
-    rs_group8(Gb, go);
+    float go[(D + L - 1) / L];
+    rs_group<L>(Gb, go);
 #pragma unroll
-    for (int r = 0; r < (D + kLPA - 1) / kLPA; ++r) {
-      const int v = r * kLPA + s;
-      if (D % kLPA == 0 || v < D) {
+    for (int r = 0; r < (D + L - 1) / L; ++r) {
+      const int v = r * L + s;
+      if (D % L == 0 || v < D) {
         row[v] = go[r];
         // radial rows for the c^R gradient; l = 5..L3 for k_high_coef (the rows hold D entries)
         if (w.valid && (v < NR || (C::YH > 0 && v >= NR + 4 * NA && v < NR + L3 * NA))) a.Gbr[(size_t)v * Np + pa] = go[r];
@@ -2696,7 +2708,7 @@ __device__ __forceinline__ void adjoint_body(const AdjArgs& a, int b, float* lds
   // ---- Sbar and A of this lane's harmonic group, in place of Sdot and S
 #pragma unroll
   for (int r = 0; r < NN; ++r) {
-    const int n = w.p + 4 * r;
+    const int n = w.p + HL * r;
     if (n < NA) {
       float Sn[YG], Sdn[YG];
       row_load<YG, kVec>(rowA + n * YR + g * YG, Sn);
@@ -2845,10 +2857,10 @@ __device__ __forceinline__ void adjoint_body(const AdjArgs& a, int b, float* lds
     }
 }
 
-template <class C, bool kTri, int W>
+template <class C, bool kTri, int W, int L>
 __global__ __launch_bounds__(256, W) void k_adjoint(AdjArgs a) {
   extern __shared__ __align__(16) float lds[];
-  adjoint_body<C, kTri>(a, blockIdx.x, lds);
+  adjoint_body<C, kTri, L>(a, blockIdx.x, lds);
 }
 
 // Sums over the atoms of each species of an outer product,
@@ -3047,7 +3059,7 @@ struct LossArgs {
 // block b of species I's wavefront partials, pieces of the order's chunks as
 // for the outer-product sums
 struct PartArgs {
-  int PW, NB, T, nch, Q;
+  int PW, NB, T, nch, Q, apw;   // apw: atoms per wavefront of the adjoint
   const int* seg;
   const float* part;
   double* pp;
@@ -3058,7 +3070,7 @@ __device__ __forceinline__ void part_reduce_body(const PartArgs& a, int b, int I
     double sum = 0.0;
     for (int c = b / a.Q; c < a.nch; c += a.NB / a.Q) {
       const int start = a.seg[2 * (c * a.T + I)], count = a.seg[2 * (c * a.T + I) + 1];
-      const int w0 = start / kAPW, w1 = (start + count + kAPW - 1) / kAPW;
+      const int w0 = start / a.apw, w1 = (start + count + a.apw - 1) / a.apw;
       const int per = (w1 - w0 + a.Q - 1) / a.Q;
       int r = w0 + b % a.Q * per;
       const int r1 = min(w1, r + per);
@@ -3453,7 +3465,7 @@ __global__ __launch_bounds__(256, 2) void k_step(const StepArgs* pa) {
   NEP_BARRIER();
   // forward: descriptors, network, partial forces
   for_items(order_grid(a.fwd.nch, C::T), [&](int vb) {
-    forward_body<C, false>(item_args(a.fwd), vb, lds);
+    forward_body<C, false, kLPA>(item_args(a.fwd), vb, lds);
     __syncthreads();
   });
   NEP_BARRIER();
@@ -3471,7 +3483,7 @@ __global__ __launch_bounds__(256, 2) void k_step(const StepArgs* pa) {
   for_items(a.st.S, [&](int s) { struct_body(item_args(a.st), s, lds); });
   NEP_BARRIER();
   for_items(order_grid(a.adj.nch, C::T), [&](int vb) {
-    adjoint_body<C, false>(item_args(a.adj), vb, lds);
+    adjoint_body<C, false, kLPA>(item_args(a.adj), vb, lds);
     __syncthreads();
   });
   NEP_BARRIER();
@@ -3672,9 +3684,9 @@ enum HighKernel { kHighDesc, kHighForce, kHighTangent, kHighCoef };
 
 struct Ops {
   int T, NR, NA, KR, KA, L3, L4, L5, D, Y, PS, YH, YR;
-  void (*forward)(const FwdArgs&, dim3, hipStream_t, int);
+  void (*forward)(const FwdArgs&, int, hipStream_t, int, int);
   void (*force)(const ForceArgs&, hipStream_t, int);
-  void (*adjoint)(const AdjArgs&, dim3, hipStream_t, int);
+  void (*adjoint)(const AdjArgs&, int, hipStream_t, int, int);
   int KP;   // words of a radial force coefficient row
   size_t (*lds_fwd)(int);
   size_t (*lds_adj)(int);
@@ -3685,15 +3697,15 @@ struct Ops {
   bool padded;   // a size class: models up to its sizes run zero-padded
 };
 
-template <class C>
+template <class C, int L>
 static size_t lds_forward(int H) {
-  using FL = FwdLds<C>;
+  using FL = FwdLds<C, L>;
   return sizeof(float) * ((size_t)CTab<C::T, C::NA, C::KA>::size + CRad<C>::size + (size_t)weights_words(H, FL::DP) +
                           (size_t)(256 / kWave) * FL::WAVE);
 }
-template <class C>
+template <class C, int L>
 static size_t lds_adjoint(int H) {
-  using AL = AdjLds<C>;
+  using AL = AdjLds<C, L>;
   return sizeof(float) * ((size_t)CTab<C::T, C::NA, C::KA>::size + CRad<C>::size + (size_t)AL::shared_words(H) +
                           (size_t)(256 / kWave) * AL::WAVE);
 }
@@ -3709,25 +3721,28 @@ static void allow_lds(K* k, size_t bytes) {
 
 // forward_waves 2 and 3 are the forward compiled for 3 and for 4 wavefronts
 // per SIMD (168 and 128 registers); the adjoint is compiled for 2 and 3
-template <class C, int W>
+template <class C, int W, int L>
 static void launch_forward_w(const FwdArgs& a, dim3 grid, hipStream_t st) {
-  const size_t lds = lds_forward<C>(a.H);
+  const size_t lds = lds_forward<C, L>(a.H);
   if (a.tilt) {
-    allow_lds(&k_forward<C, true, W>, lds);
-    hipLaunchKernelGGL(HIP_KERNEL_NAME(k_forward<C, true, W>), grid, dim3(256), lds, st, a);
+    allow_lds(&k_forward<C, true, W, L>, lds);
+    hipLaunchKernelGGL(HIP_KERNEL_NAME(k_forward<C, true, W, L>), grid, dim3(256), lds, st, a);
   } else {
-    allow_lds(&k_forward<C, false, W>, lds);
-    hipLaunchKernelGGL(HIP_KERNEL_NAME(k_forward<C, false, W>), grid, dim3(256), lds, st, a);
+    allow_lds(&k_forward<C, false, W, L>, lds);
+    hipLaunchKernelGGL(HIP_KERNEL_NAME(k_forward<C, false, W, L>), grid, dim3(256), lds, st, a);
   }
 }
 template <class C>
-static void launch_forward(const FwdArgs& a, dim3 grid, hipStream_t st, int waves) {
+static void launch_forward(const FwdArgs& a, int blocks, hipStream_t st, int waves, int lanes) {
+  if (lanes == 32) return launch_forward_w<C, 2, 32>(a, dim3(4 * blocks), st);
+  if (lanes == 16) return launch_forward_w<C, 2, 16>(a, dim3(2 * blocks), st);
+  const dim3 grid(blocks);
   if constexpr (C::FIXED_WAVES != 0)
-    launch_forward_w<C, C::FIXED_WAVES>(a, grid, st);
+    launch_forward_w<C, C::FIXED_WAVES, kLPA>(a, grid, st);
   else if (waves == 2)
-    launch_forward_w<C, 3>(a, grid, st);
+    launch_forward_w<C, 3, kLPA>(a, grid, st);
   else
-    launch_forward_w<C, 4>(a, grid, st);
+    launch_forward_w<C, 4, kLPA>(a, grid, st);
 }
 template <class C, bool kTri>
 static void launch_force_t(const ForceArgs& a, hipStream_t st, int lanes) {
@@ -3745,25 +3760,28 @@ static void launch_force(const ForceArgs& a, hipStream_t st, int lanes) {
   else
     launch_force_t<C, false>(a, st, lanes);
 }
-template <class C, int W>
+template <class C, int W, int L>
 static void launch_adjoint_w(const AdjArgs& a, dim3 grid, hipStream_t st) {
-  const size_t lds = lds_adjoint<C>(a.H);
+  const size_t lds = lds_adjoint<C, L>(a.H);
   if (a.tilt) {
-    allow_lds(&k_adjoint<C, true, W>, lds);
-    hipLaunchKernelGGL(HIP_KERNEL_NAME(k_adjoint<C, true, W>), grid, dim3(256), lds, st, a);
+    allow_lds(&k_adjoint<C, true, W, L>, lds);
+    hipLaunchKernelGGL(HIP_KERNEL_NAME(k_adjoint<C, true, W, L>), grid, dim3(256), lds, st, a);
   } else {
-    allow_lds(&k_adjoint<C, false, W>, lds);
-    hipLaunchKernelGGL(HIP_KERNEL_NAME(k_adjoint<C, false, W>), grid, dim3(256), lds, st, a);
+    allow_lds(&k_adjoint<C, false, W, L>, lds);
+    hipLaunchKernelGGL(HIP_KERNEL_NAME(k_adjoint<C, false, W, L>), grid, dim3(256), lds, st, a);
   }
 }
 template <class C>
-static void launch_adjoint(const AdjArgs& a, dim3 grid, hipStream_t st, int waves) {
+static void launch_adjoint(const AdjArgs& a, int blocks, hipStream_t st, int waves, int lanes) {
+  if (lanes == 32) return launch_adjoint_w<C, 2, 32>(a, dim3(4 * blocks), st);
+  if (lanes == 16) return launch_adjoint_w<C, 2, 16>(a, dim3(2 * blocks), st);
+  const dim3 grid(blocks);
   if constexpr (C::FIXED_WAVES != 0)
-    launch_adjoint_w<C, C::FIXED_WAVES>(a, grid, st);
+    launch_adjoint_w<C, C::FIXED_WAVES, kLPA>(a, grid, st);
   else if (waves == 2)
-    launch_adjoint_w<C, 2>(a, grid, st);
+    launch_adjoint_w<C, 2, kLPA>(a, grid, st);
   else
-    launch_adjoint_w<C, 3>(a, grid, st);
+    launch_adjoint_w<C, 3, kLPA>(a, grid, st);
 }
 template <class C, bool kTri>
 static void launch_high_t(HighKernel k, const HighArgs& a, dim3 grid, hipStream_t st) {
@@ -3809,7 +3827,7 @@ static Ops make_ops() {
     occ = &step_occupancy<C>;
   }
   return Ops{C::T, C::NR, C::NA, C::KR, C::KA, C::L3, C::L4, C::L5, C::D, C::Y, C::PS, C::YH,
-             HRow<C::LMAX>::YR, &launch_forward<C>, &launch_force<C>, &launch_adjoint<C>, HRad<C>::KP, &lds_forward<C>, &lds_adjoint<C>, high, step, occ,
+             HRow<C::LMAX>::YR, &launch_forward<C>, &launch_force<C>, &launch_adjoint<C>, HRad<C>::KP, &lds_forward<C, kLPA>, &lds_adjoint<C, kLPA>, high, step, occ,
              C::FIXED_WAVES != 0};
 }
 
@@ -3898,8 +3916,19 @@ int64_t param_count(const nep_model* m) {
 
 size_t al(size_t x) { return (x + 255) & ~(size_t)255; }
 
+// Lanes per atom of the forward and the adjoint.  With few atoms a SIMD has one
+// wavefront or none, and the time is the instructions of one wavefront: more
+// lanes an atom shorten its pair loops, sums and hidden units, up to the
+// batch where 32 lanes (8 atoms a block) no longer fit one block per CU and
+// 16 lanes two; beyond, the work that more lanes repeat counts.  Training
+// step of the 3/4/5-body model in us with 8 / 16 / 32 lanes: 512 atoms
+// 91.5 / 72.7 / 68.1, 2048 atoms 94.4 / 76.4 / 73.4, 3072 atoms 96.5 / 80.1 /
+// 83.8, 8192 atoms 105.1 / 94.6 / 115.5, 12288 atoms 112.3 / 122.4 / 142.7.
+constexpr int kLanes32Atoms = 2048, kLanes16Atoms = 8192;
+int group_lanes(int N) { return N <= kLanes32Atoms ? 32 : N <= kLanes16Atoms ? 16 : kLPA; }
+
 struct Layout {
-  int N, S, T, D, Y, H, NR, TKR, Npad, nwaves, nch, PW, NA, capR, capA;
+  int N, S, T, D, Y, H, NR, TKR, Npad, lanes, nch, PW, NA, capR, capA;
   size_t order, seg, blist, bflags, astruct, p4, G, Sst, Ep, X, eatom, hrow, fA, wv, F, fb4, Es, Ws, eps, wbar, lpart,
       Gd, FRst, FPst, Gbr, beta, part, pp, w0part, crpart, Sh, Sdh, cgrid, cell, cpart, acell, aslot, cpos, spart,
       cur_step, bar, sargs, prm, Gtmp, total;
@@ -3925,8 +3954,9 @@ size_t reported_bytes(const Layout& L, const Ops* o, const nep_model* m, bool pa
   return sum;
 }
 
-// m: the model the kernels run (the class model when padded)
-Layout make_layout(const nep_model* m, const Ops* o, int S, int N, bool pad = false) {
+// m: the model the kernels run (the class model when padded); lanes: per atom
+// in the forward and the adjoint (each wavefront of which writes a row of part)
+Layout layout_of(const nep_model* m, const Ops* o, int S, int N, bool pad, int lanes) {
   Layout L{};
   L.N = N;
   L.S = S;
@@ -3949,7 +3979,7 @@ Layout make_layout(const nep_model* m, const Ops* o, int S, int N, bool pad = fa
   // units, so the rows a wavefront stores start in different memory channels
   L.Npad = (L.Npad + 63) / 64 * 64;
   if ((L.Npad / 64) % 2 == 0) L.Npad += 64;
-  L.nwaves = L.Npad / kAPW;
+  L.lanes = lanes;
   L.PW = L.T * m->n_ang * m->k_ang + 2 * L.H + 1;
   const size_t Np = L.Npad, Nn = (size_t)(N > 0 ? N : 1), Ss = (size_t)(S > 0 ? S : 1);
   size_t off = 0;
@@ -3985,7 +4015,7 @@ Layout make_layout(const nep_model* m, const Ops* o, int S, int N, bool pad = fa
   L.FPst = take(4 * (size_t)L.TKR * Np);
   L.Gbr = take(4 * (size_t)(o->YH > 0 ? L.D : L.NR) * Np);
   L.beta = take(4 * (size_t)L.H * Np);
-  L.part = take(4 * (size_t)L.nwaves * L.PW);
+  L.part = take(4 * (size_t)(L.Npad / (kWave / L.lanes)) * L.PW);
   L.pp = take(8 * (size_t)L.T * kPRChunksMax * L.PW);
   L.w0part = take(4 * (size_t)L.T * kOSBlocksMaxW * L.H * L.D);
   L.crpart = take(4 * (size_t)L.T * kOSBlocksMaxC * L.NR * L.TKR);
@@ -4006,7 +4036,22 @@ Layout make_layout(const nep_model* m, const Ops* o, int S, int N, bool pad = fa
   const size_t Pc = pad ? (size_t)param_count(m) : 0;
   L.prm = take(4 * Pc);
   L.Gtmp = take(pad ? 4 * (size_t)L.D * Nn : 0);
-  L.total = std::max(off, reported_bytes(L, o, m, pad));
+  L.total = off;
+  return L;
+}
+
+// The size reported is that of 8 lanes an atom: more lanes are taken where
+// their rows of part fit.
+Layout make_layout(const nep_model* m, const Ops* o, int S, int N, bool pad = false) {
+  Layout L = layout_of(m, o, S, N, pad, kLPA);
+  const size_t total = std::max(L.total, reported_bytes(L, o, m, pad));
+  for (int lanes = group_lanes(N); lanes > kLPA; lanes /= 2) {
+    const Layout more = layout_of(m, o, S, N, pad, lanes);
+    if (more.total > total) continue;
+    L = more;
+    break;
+  }
+  L.total = total;
   return L;
 }
 
@@ -4085,6 +4130,7 @@ struct Ctx {
   // the captured training step: Adam after the gradient, fused into its
   // final reduction
   const struct AdamFuse* adam = nullptr;
+  int lanes = kLPA;   // lanes per atom of the forward and the adjoint
   // the packed atoms of this call are in the workspace
   mutable bool packed = false;
   // a captured step whose neighbor build starts the replay (flags, step latch)
@@ -4251,7 +4297,7 @@ HighArgs high_args(const Ctx& c, const nep_neighbors* nb, const float* params, c
   const nep_model* m = c.m;
   h.N = c.L.N;
   h.Npad = c.L.Npad;
-  h.PW = c.L.PW;
+  h.PW = c.L.PW * (c.lanes / kLPA);   // its wavefronts hold 8 atoms: one of the adjoint's rows
   h.inv_rcA = 1.0f / m->rc_ang;
   h.order = at<int>(c.ws, c.L.order);
   h.astruct = at<int>(c.ws, c.L.astruct);
@@ -4294,7 +4340,7 @@ void launch_forward_pass(const Ctx& c, const nep_neighbors* nb, const float* par
   const HighArgs h = high_args(c, nb, params);
   run_pack(c, nb, pr);
   run_high(c, kHighDesc, h, pr);
-  NEP_LAUNCH(pr, "forward", c.o->forward(a, dim3(order_grid(c.L.nch, c.L.T)), c.st, c.tune.forward_waves));
+  NEP_LAUNCH(pr, "forward", c.o->forward(a, order_grid(c.L.nch, c.L.T), c.st, c.tune.forward_waves, c.lanes));
   if (a.do_mlp && a.do_force) run_high(c, kHighForce, h, pr);
 }
 
@@ -4412,7 +4458,7 @@ Split split_p(const Ctx& c) { return split_chunks(c.tune.reduce_chunks, kPRChunk
 
 PartArgs part_args(const Ctx& c) {
   const Split p = split_p(c);
-  return PartArgs{c.L.PW, p.NB, c.L.T, c.L.nch, p.Q, at<int>(c.ws, c.L.seg), at<float>(c.ws, c.L.part),
+  return PartArgs{c.L.PW, p.NB, c.L.T, c.L.nch, p.Q, kWave / c.lanes, at<int>(c.ws, c.L.seg), at<float>(c.ws, c.L.part),
                   at<double>(c.ws, c.L.pp)};
 }
 
@@ -4472,7 +4518,7 @@ void run_adjoint(const Ctx& c, const nep_neighbors* nb, const float* params, con
     const int T = m->n_types;
     const HighArgs h = high_args(c, nb, params, wbar);
     run_high(c, kHighTangent, h, pr);
-    NEP_LAUNCH(pr, "adjoint", c.o->adjoint(a, dim3(order_grid(c.L.nch, c.L.T)), c.st, c.tune.adjoint_waves));
+    NEP_LAUNCH(pr, "adjoint", c.o->adjoint(a, order_grid(c.L.nch, c.L.T), c.st, c.tune.adjoint_waves, c.lanes));
     run_high(c, kHighCoef, h, pr);
     {
       OuterReduceArgs ra;
@@ -4554,6 +4600,7 @@ int setup(Ctx& c, const nep_model* m, const nep_batch* b, void* ws, void* stream
   c.ws = ws;
   c.st = static_cast<hipStream_t>(stream);
   c.L = make_layout(c.m, c.o, b->n_struct, b->n_atom, r.pad);
+  c.lanes = c.L.lanes;
   return NEP_OK;
 }
 
@@ -4919,6 +4966,7 @@ int nep_train_step_graph_create_tuned(const nep_model* m, const nep_batch* b, ne
   int sgrid = 0;
   if (persistent) {
     if (!persistent_ok(c)) return NEP_ERR_ARG;
+    c.lanes = kLPA;   // its grid is sized for 8 lanes an atom
     slds = step_lds(c);
     sgrid = step_grid(c, slds);
     if (sgrid < kXCD) return NEP_ERR_HIP;
