@@ -1971,6 +1971,85 @@ __global__ __launch_bounds__(256, W) void k_forward(FwdArgs a) {
   forward_body<C, kTri, L>(a, blockIdx.x, lds);
 }
 
+// ====================================================================== MD
+// Velocity Verlet for the inference path, in eV, A, fs and amu: the
+// acceleration of atom i is F_i / m_i times kAccel, and 1 amu A^2/fs^2 is
+// 1/kAccel eV.
+constexpr float kAccel = 9.648533212e-3f;
+
+struct MDArgs {
+  int N, T;
+  const int* type;
+  const int* astruct;
+  const float* box;
+  const float* tilt;   // null: every cell orthorhombic
+  const float* mass;   // [T] amu
+  float* pos;          // [3][N]
+  float* vel;          // [3][N] A/fs
+  const float* F;      // [3][N] eV/A
+  float* ekin;         // [N] eV (kick only)
+  float hdt, dt;
+};
+
+__device__ __forceinline__ float inv_mass(const MDArgs& a, int i) {
+  const int t = a.type[i];
+  return (t >= 0 && t < a.T) ? kAccel / a.mass[t] : 0.f;
+}
+
+// Atom i's move between two force evaluations, f the force on it.  With kKick the half kick that
+// ends a step (forces at the current positions); with kDrift the half kick
+// that begins the next one, the drift and the wrap into the cell: [0, L) per
+// axis for an orthorhombic cell; for a triclinic one, minus the lattice vector
+// H floor(f) of the fractional coordinates f = H^-1 x.  The last kick (no
+// drift) also gives the kinetic energy per atom.
+template <bool kKick, bool kDrift>
+__device__ __forceinline__ void md_move(const MDArgs& a, int i, const float (&fi)[3]) {
+  const float im = inv_mass(a, i);
+  const float k = a.hdt * im;
+  float x[3], v2 = 0.f;
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    const size_t q = (size_t)c * a.N + i;
+    const float f = fi[c];
+    float v = a.vel[q];
+    if (kKick) v = fmaf(k, f, v);
+    if (kDrift) {
+      v = fmaf(k, f, v);
+      x[c] = fmaf(a.dt, v, a.pos[q]);
+    } else {
+      v2 = fmaf(v, v, v2);
+    }
+    a.vel[q] = v;
+  }
+  if (!kDrift) {
+    a.ekin[i] = im > 0.f ? 0.5f * v2 / im : 0.f;
+    return;
+  }
+  const int st = a.astruct[i];
+  const float Lx = a.box[3 * st], Ly = a.box[3 * st + 1], Lz = a.box[3 * st + 2];
+  const float xy = a.tilt ? a.tilt[3 * st] : 0.f, xz = a.tilt ? a.tilt[3 * st + 1] : 0.f,
+              yz = a.tilt ? a.tilt[3 * st + 2] : 0.f;
+  if (xy != 0.f || xz != 0.f || yz != 0.f) {
+    const float fc = x[2] / Lz;
+    const float fb = (x[1] - yz * fc) / Ly;
+    const float fa = (x[0] - xy * fb - xz * fc) / Lx;
+    const float ka = floorf(fa), kb = floorf(fb), kc = floorf(fc);
+    x[0] = x[0] - Lx * ka - xy * kb - xz * kc;
+    x[1] = x[1] - Ly * kb - yz * kc;
+    x[2] = x[2] - Lz * kc;
+  } else {
+    const float L[3] = {Lx, Ly, Lz};
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      x[c] -= L[c] * floorf(x[c] / L[c]);
+      if (x[c] >= L[c]) x[c] -= L[c];
+      if (!(x[c] >= 0.f)) x[c] = 0.f;
+    }
+  }
+#pragma unroll
+  for (int c = 0; c < 3; ++c) a.pos[(size_t)c * a.N + i] = x[c];
+}
+
 // Forces F_i = sum_j f_ij - f_ji (Eq. 3) and the atom's share of the virial.
 //
 // Radial part: f_ij = (sum_k h_i,Jk f'_k(r)) r_hat, and f_ji has the same
@@ -2022,7 +2101,7 @@ __device__ __forceinline__ int partner_find(const uint32_t* __restrict__ row, in
 }
 
 template <class C, bool kTri, int LPA>
-__device__ __forceinline__ void force_body(const ForceArgs& a, int vb, float* own) {
+__device__ __forceinline__ void force_body(const ForceArgs& a, int vb, float* own, const MDArgs* md = nullptr) {
   static_assert(LPA == 8 || LPA == 16, "8 or 16 lanes per atom");
   constexpr int T = C::T, KR = C::KR, KP = HRad<C>::KP, TK = T * KP, APB = 256 / LPA;
   const int s = threadIdx.x % LPA, al = threadIdx.x / LPA;
@@ -2111,6 +2190,10 @@ __device__ __forceinline__ void force_body(const ForceArgs& a, int vb, float* ow
       for (int q = 0; q < 3; ++q) a.Fuser[q * n + i] = r[q];
 #pragma unroll
     for (int q = 0; q < 6; ++q) a.wv[q * n + i] = r[3 + q];
+    if (md) {
+      const float f[3] = {r[0], r[1], r[2]};
+      md_move<true, true>(*md, i, f);
+    }
   }
 }
 
@@ -2118,6 +2201,15 @@ template <class C, bool kTri, int LPA>
 __global__ __launch_bounds__(256) void k_force(ForceArgs a) {
   __shared__ __align__(16) float own[force_lds_words<C, LPA>()];
   force_body<C, kTri, LPA>(a, xcd_block(), own);
+}
+
+// The force pass of an MD step that another follows: an atom's kick and drift
+// by the lane that holds its force (the positions are written, the packed
+// ones read).  Its own launch took 4 of 33 us a step of a 180-atom cell.
+template <class C, bool kTri>
+__global__ __launch_bounds__(256) void k_force_move(ForceArgs a, MDArgs md) {
+  __shared__ __align__(16) float own[force_lds_words<C, kForceLPA>()];
+  force_body<C, kTri, kForceLPA>(a, xcd_block(), own, &md);
 }
 
 // ==================================================================== loss
@@ -3583,85 +3675,15 @@ __global__ __launch_bounds__(256) void k_unpad_desc(PadDims d, int N, const floa
 }
 
 // ================================================================ dispatch
-// ====================================================================== MD
-// Velocity Verlet for the inference path, in eV, A, fs and amu: the
-// acceleration of atom i is F_i / m_i times kAccel, and 1 amu A^2/fs^2 is
-// 1/kAccel eV.
-constexpr float kAccel = 9.648533212e-3f;
-
-struct MDArgs {
-  int N, T;
-  const int* type;
-  const int* astruct;
-  const float* box;
-  const float* tilt;   // null: every cell orthorhombic
-  const float* mass;   // [T] amu
-  float* pos;          // [3][N]
-  float* vel;          // [3][N] A/fs
-  const float* F;      // [3][N] eV/A
-  float* ekin;         // [N] eV (kick only)
-  float hdt, dt;
-};
-
-__device__ __forceinline__ float inv_mass(const MDArgs& a, int i) {
-  const int t = a.type[i];
-  return (t >= 0 && t < a.T) ? kAccel / a.mass[t] : 0.f;
-}
-
-// One launch between two force evaluations.  With kKick the half kick that
-// ends a step (forces at the current positions); with kDrift the half kick
-// that begins the next one, the drift and the wrap into the cell: [0, L) per
-// axis for an orthorhombic cell; for a triclinic one, minus the lattice vector
-// H floor(f) of the fractional coordinates f = H^-1 x.  The last kick (no
-// drift) also gives the kinetic energy per atom.
+// A move of its own launch: the half kick and drift before the first force
+// evaluation of a call, and the half kick after the last one (whose forces the
+// energy sums follow).
 template <bool kKick, bool kDrift>
 __global__ __launch_bounds__(256) void k_md_move(MDArgs a) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= a.N) return;
-  const float im = inv_mass(a, i);
-  const float k = a.hdt * im;
-  float x[3], v2 = 0.f;
-#pragma unroll
-  for (int c = 0; c < 3; ++c) {
-    const size_t q = (size_t)c * a.N + i;
-    const float f = a.F[q];
-    float v = a.vel[q];
-    if (kKick) v = fmaf(k, f, v);
-    if (kDrift) {
-      v = fmaf(k, f, v);
-      x[c] = fmaf(a.dt, v, a.pos[q]);
-    } else {
-      v2 = fmaf(v, v, v2);
-    }
-    a.vel[q] = v;
-  }
-  if (!kDrift) {
-    a.ekin[i] = im > 0.f ? 0.5f * v2 / im : 0.f;
-    return;
-  }
-  const int st = a.astruct[i];
-  const float Lx = a.box[3 * st], Ly = a.box[3 * st + 1], Lz = a.box[3 * st + 2];
-  const float xy = a.tilt ? a.tilt[3 * st] : 0.f, xz = a.tilt ? a.tilt[3 * st + 1] : 0.f,
-              yz = a.tilt ? a.tilt[3 * st + 2] : 0.f;
-  if (xy != 0.f || xz != 0.f || yz != 0.f) {
-    const float fc = x[2] / Lz;
-    const float fb = (x[1] - yz * fc) / Ly;
-    const float fa = (x[0] - xy * fb - xz * fc) / Lx;
-    const float ka = floorf(fa), kb = floorf(fb), kc = floorf(fc);
-    x[0] = x[0] - Lx * ka - xy * kb - xz * kc;
-    x[1] = x[1] - Ly * kb - yz * kc;
-    x[2] = x[2] - Lz * kc;
-  } else {
-    const float L[3] = {Lx, Ly, Lz};
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      x[c] -= L[c] * floorf(x[c] / L[c]);
-      if (x[c] >= L[c]) x[c] -= L[c];
-      if (!(x[c] >= 0.f)) x[c] = 0.f;
-    }
-  }
-#pragma unroll
-  for (int c = 0; c < 3; ++c) a.pos[(size_t)c * a.N + i] = x[c];
+  const float f[3] = {a.F[i], a.F[(size_t)a.N + i], a.F[2 * (size_t)a.N + i]};
+  md_move<kKick, kDrift>(a, i, f);
 }
 
 // out[s] = sum of x over the atoms of structure s (float64, one block each)
@@ -3685,7 +3707,7 @@ enum HighKernel { kHighDesc, kHighForce, kHighTangent, kHighCoef };
 struct Ops {
   int T, NR, NA, KR, KA, L3, L4, L5, D, Y, PS, YH, YR;
   void (*forward)(const FwdArgs&, int, hipStream_t, int, int);
-  void (*force)(const ForceArgs&, hipStream_t, int);
+  void (*force)(const ForceArgs&, hipStream_t, int, const MDArgs*);
   void (*adjoint)(const AdjArgs&, int, hipStream_t, int, int);
   int KP;   // words of a radial force coefficient row
   size_t (*lds_fwd)(int);
@@ -3754,8 +3776,14 @@ static void launch_force_t(const ForceArgs& a, hipStream_t st, int lanes) {
     hipLaunchKernelGGL(HIP_KERNEL_NAME(k_force<C, kTri, 16>), grid, dim3(256), 0, st, a);
 }
 template <class C>
-static void launch_force(const ForceArgs& a, hipStream_t st, int lanes) {
-  if (a.tilt)
+static void launch_force(const ForceArgs& a, hipStream_t st, int lanes, const MDArgs* md) {
+  if (md) {
+    const dim3 grid((a.N + 256 / kForceLPA - 1) / (256 / kForceLPA));
+    if (a.tilt)
+      hipLaunchKernelGGL(HIP_KERNEL_NAME(k_force_move<C, true>), grid, dim3(256), 0, st, a, *md);
+    else
+      hipLaunchKernelGGL(HIP_KERNEL_NAME(k_force_move<C, false>), grid, dim3(256), 0, st, a, *md);
+  } else if (a.tilt)
     launch_force_t<C, true>(a, st, lanes);
   else
     launch_force_t<C, false>(a, st, lanes);
@@ -4375,7 +4403,7 @@ StructArgs struct_args(const Ctx& c, float* e_struct, float* virial, const nep_l
 
 void run_forward(const Ctx& c, const nep_neighbors* nb, const float* params, float* e_atom, float* e_struct,
                  float* force, float* virial, const nep_labels* lab, const float* lam, float* loss, int32_t* flags,
-                 Prof* pr, bool defer_loss = false, bool sums = true) {
+                 Prof* pr, bool defer_loss = false, const MDArgs* md = nullptr) {
   const int N = c.L.N, S = c.b->n_struct;
   if (N > 0) {
     FwdArgs a = fwd_args(c, nb, params);
@@ -4385,9 +4413,10 @@ void run_forward(const Ctx& c, const nep_neighbors* nb, const float* params, flo
       if (c.o->YH == 0) a.G = a.Ep = nullptr;
     }
     launch_forward_pass(c, nb, params, a, pr);
-    NEP_LAUNCH(pr, "force", c.o->force(force_args(c, a, force), c.st, c.tune.gather_lanes));
+    NEP_LAUNCH(pr, "force", c.o->force(force_args(c, a, force), c.st, c.tune.gather_lanes, md));
   }
-  if (S > 0 && sums) {
+  // an MD step that another follows needs no sums
+  if (S > 0 && !md) {
     const StructArgs s = struct_args(c, e_struct, virial, lab, lam);
     if (s.split)
       NEP_LAUNCH(pr, "struct_part",
@@ -4824,6 +4853,10 @@ int nep_energy_force_virial(const nep_model* m, const nep_batch* b, const nep_ne
   return hip_ok();
 }
 
+// MD steps between two species orders (5 of 33 us a step of a 180-atom cell,
+// 8 of 100 us with 9261 atoms)
+constexpr int kMDOrderSteps = 16;
+
 int nep_md_step(const nep_model* m, const nep_batch* b, float* pos, nep_neighbors* nb, const float* params,
                 const float* mass, float* vel, float* force, float dt, int32_t n_steps, float* e_pot, float* e_kin,
                 void* ws, int32_t* d_flags, void* stream) {
@@ -4850,16 +4883,16 @@ int nep_md_step(const nep_model* m, const nep_batch* b, float* pos, nep_neighbor
   a.hdt = 0.5f * dt;
   a.dt = dt;
   params = kernel_params(c, params);
-  // the energies are those of the last step: no sums before it (they and the
-  // separate kick and drift took 6 of 46 us a step of a 180-atom cell)
+  // The energies are those of the last step: no sums before it.  A step that
+  // another follows is the neighbor build, the forward and a force pass that
+  // also moves the atoms.  The species order holds for as long as the species
+  // do, which is the call; its ranking by pair count (for balance alone) is
+  // renewed now and then.
+  hipLaunchKernelGGL(HIP_KERNEL_NAME(k_md_move<false, true>), dim3(grid1(N)), dim3(256), 0, c.st, a);
   for (int k = 0; k < n_steps; ++k) {
-    if (k == 0)
-      hipLaunchKernelGGL(HIP_KERNEL_NAME(k_md_move<false, true>), dim3(grid1(N)), dim3(256), 0, c.st, a);
-    else
-      hipLaunchKernelGGL(HIP_KERNEL_NAME(k_md_move<true, true>), dim3(grid1(N)), dim3(256), 0, c.st, a);
-    run_neighbors(c, nb, d_flags, nullptr);
+    run_neighbors(c, nb, d_flags, nullptr, k % kMDOrderSteps == 0);
     run_forward(c, nb, params, nullptr, e_pot, force, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, false,
-                k + 1 == n_steps);
+                k + 1 < n_steps ? &a : nullptr);
   }
   hipLaunchKernelGGL(HIP_KERNEL_NAME(k_md_move<true, false>), dim3(grid1(N)), dim3(256), 0, c.st, a);
   if (e_kin && S > 0)
