@@ -37,7 +37,8 @@ struct NbrArgs {
   // all-pairs only)
   int cells, cell_min;
   int4* grid;    // [S] bins per axis (na, nb, nc, na nb nc), zero: all-pairs
-  int* cell;     // [N+1] bin counts, then bin start offsets; [N] = binned atoms
+  int* cell;     // [N] bin counts
+  int* start;    // [N+1] bin start offsets; [N] = binned atoms
   int* cpart;    // [N / kScanChunk + 1] per-chunk counts
   int* acell;    // [N] bin id of the atom, -1: all-pairs
   int* aslot;    // [N] slot in the bin

@@ -690,8 +690,8 @@ __global__ __launch_bounds__(kNbrThreads) void k_neighbors(NbrArgs a) {
 //
 // Bins of structure n have the ids atom_offset[n] + bin (< atom_offset[n+1]);
 // the bins are counted, scanned into start offsets, and the binned atoms
-// placed bin by bin as (x, y, z, j).  An atom whose lane buffer overflows is
-// left to the all-pairs kernel (acell[i] = -1), which runs afterwards.
+// placed bin by bin as (x, y, z, j).  An atom with more hits than its LDS row
+// holds is left to the all-pairs kernel (acell[i] = -1), which runs afterwards.
 constexpr int kCellMinAtoms = 1024;     // default smallest structure searched through cell lists
 constexpr int kCellMinAtomsLo = 64;     // smallest value a tuning may set
 constexpr double kCellPad = 0.05;
@@ -727,7 +727,7 @@ __device__ int4 cell_grid(const NbrArgs& a, int st) {
 template <bool kTri>
 __global__ __launch_bounds__(256) void k_cell_setup(NbrArgs a) {
   const int t = blockIdx.x * 256 + threadIdx.x;
-  if (t <= a.N) a.cell[t] = 0;
+  if (t < a.N) a.cell[t] = 0;
   if (t < a.S) a.grid[t] = cell_grid<kTri>(a, t);
 }
 
@@ -803,28 +803,43 @@ __global__ __launch_bounds__(256) void k_cell_part(int n, const int* __restrict_
   if (threadIdx.x == 0) part[blockIdx.x] = tot;
 }
 
-// counts -> start offsets in place over [0, n), and the total at [n]
-__global__ __launch_bounds__(256) void k_cell_start(int n, int* __restrict__ cell, const int* __restrict__ part) {
+// counts -> start offsets over [0, n), and the total at [n].  Up to
+// kScanDirect chunks every block sums the counts before its own (at most 60k
+// loads by the last block) instead of reading the sums of k_cell_part, whose
+// launch took 4 us.
+constexpr int kScanDirect = 16;
+__global__ __launch_bounds__(256) void k_cell_start(int n, const int* __restrict__ cnt, const int* __restrict__ part,
+                                                    int* __restrict__ start) {
   __shared__ int red[4];
   int off = 0;
-  for (int q = threadIdx.x; q < (int)blockIdx.x; q += 256) off += part[q];
+  if ((int)gridDim.x <= kScanDirect) {
+    const int4* c4 = reinterpret_cast<const int4*>(cnt);   // whole chunks of counts
+    const int n4 = (int)blockIdx.x * (kScanChunk / 4);
+#pragma unroll 4
+    for (int q = threadIdx.x; q < n4; q += 256) {
+      const int4 v = c4[q];
+      off += (v.x + v.y) + (v.z + v.w);
+    }
+  } else {
+    for (int q = threadIdx.x; q < (int)blockIdx.x; q += 256) off += part[q];
+  }
   int excl;
   off = block_exclusive_scan(off, excl, red);
   const int b = blockIdx.x * kScanChunk + threadIdx.x * 8;
   int v[8], sum = 0;
 #pragma unroll
   for (int q = 0; q < 8; ++q) {
-    v[q] = b + q < n ? cell[b + q] : 0;
+    v[q] = b + q < n ? cnt[b + q] : 0;
     sum += v[q];
   }
   const int tot = block_exclusive_scan(sum, excl, red);
   int run = off + excl;
 #pragma unroll
   for (int q = 0; q < 8; ++q) {
-    if (b + q < n) cell[b + q] = run;
+    if (b + q < n) start[b + q] = run;
     run += v[q];
   }
-  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) cell[n] = off + tot;
+  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) start[n] = off + tot;
 }
 
 // binned atoms bin by bin as (x, y, z, j)
@@ -833,22 +848,57 @@ __global__ __launch_bounds__(256) void k_cell_place(NbrArgs a) {
   if (i >= a.N) return;
   const int bin = a.acell[i];
   if (bin < 0) return;
-  a.cpos[a.cell[bin] + a.aslot[i]] =
+  a.cpos[a.start[bin] + a.aslot[i]] =
       make_float4(a.pos[i], a.pos[a.N + i], a.pos[2 * a.N + i], __int_as_float(i));
 }
 
-// Lists of the binned atoms, 8 lanes per atom taking the candidates of the 27
-// bins in turn.  Blocks take the atoms in bin order, so a block's atoms share
-// most of their candidates.
+// Lists of the binned atoms, 8 lanes per atom.  Blocks take the atoms in bin
+// order, so a block's atoms share most of their candidates.
+//
+// The 27 bins are 9 rows of three consecutive bins: lane s takes row s and all
+// lanes share row 8, so the bounds of every row are one set of loads and the
+// candidates of a row contiguous loads, eight in flight a lane.  As in the
+// all-pairs scan a first part only tests the distance; its hits, gathered in
+// the atom's LDS row, are decided 8 at a time, and the kept entries ranked by
+// (j, code) against the row, four to an LDS read.  (The candidates of one row
+// after another, each decided in full, were a chain of about 20 dependent
+// loads, and the ranking one LDS read per comparison: 33 us for 9261 atoms,
+// where a SIMD has one wavefront, now 14; 41 us for 27000 atoms, now 26.)
+constexpr int kCellHits = 8 * kNbrBuf;        // hits an atom may have
+constexpr int kCellRow = kCellHits + 4;       // LDS words of its row, padded to whole 16-byte reads
+
+// Stores the m entries of an LDS row (padded with 0xFFFFFFFF to a multiple of
+// 4) into list at their ranks below cap; lane s of 8 takes entries s, s + 8, ...
+__device__ __forceinline__ void store_ranked(const uint32_t* row, int m, int s, uint32_t* __restrict__ list, int cap) {
+  for (int g = 0; g < m; g += 32) {
+    uint32_t e[4];
+    int rank[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      e[u] = row[min(g + 8 * u + s, m - 1)];
+      rank[u] = 0;
+    }
+    for (int q = 0; q < m; q += 4) {
+      const uint4 v = *reinterpret_cast<const uint4*>(row + q);
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        rank[u] += (v.x < e[u] ? 1 : 0) + (v.y < e[u] ? 1 : 0) + (v.z < e[u] ? 1 : 0) + (v.w < e[u] ? 1 : 0);
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (g + 8 * u + s < m && rank[u] < cap) list[rank[u]] = e[u];
+  }
+}
+
 template <bool kTri>
 __global__ __launch_bounds__(kNbrThreads) void k_cell_neighbors(NbrArgs a) {
-  __shared__ uint32_t nbuf[kNbrThreads * (kNbrBuf + 1)];
+  __shared__ __align__(16) uint32_t rows[2][kNbrAPB * kCellRow];   // hits, then entries; angular entries
   // the first ceil(M / 32) blocks work, renumbered over the XCDs among themselves
-  const int M = a.cell[a.N], nbw = (M + kNbrAPB - 1) / kNbrAPB;
+  const int M = a.start[a.N], nbw = (M + kNbrAPB - 1) / kNbrAPB;
   if ((int)blockIdx.x >= nbw) return;
   const int b0 = xcd_block_of(blockIdx.x, nbw) * kNbrAPB;
   const int s = threadIdx.x & 7;
-  const int k = b0 + (int)(threadIdx.x >> 3);
+  const int al = (int)(threadIdx.x >> 3), k = b0 + al;
   const bool live = k < M;
   const float4 me = a.cpos[min(k, M - 1)];
   const int i = __float_as_int(me.w);
@@ -859,102 +909,140 @@ __global__ __launch_bounds__(kNbrThreads) void k_cell_neighbors(NbrArgs a) {
   const int base = a.aoff[st];
   const int loc = a.acell[i] - base;
   const int kc = loc % g.z, kb = (loc / g.z) % g.y, ka = loc / (g.y * g.z);
-  const PosTile t{a.pos, a.pos + a.N, a.pos + 2 * a.N, 0};
-  uint32_t* mybuf = nbuf + threadIdx.x;   // slot u at mybuf[kNbrThreads u]
-  int nR = 0, nA = 0;
-  uint32_t angmask = 0;
-  auto keep = [&](int j, int code, bool ang) {
-    if (nR < kNbrBuf) {
-      mybuf[kNbrThreads * nR] = ((uint32_t)j << 5) | (uint32_t)code;
-      angmask |= ang ? (1u << nR) : 0u;
-    }
-    ++nR;
-    nA += ang ? 1 : 0;
-  };
   // bins kc-1, kc, kc+1 of a row are consecutive ids, split in two runs when
   // the row wraps
   // (kc = 0: [0, 1] and [nc-1]; kc = nc-1: [0] and [nc-2, nc-1]; else [kc-1, kc+1])
   const bool edge = kc == 0 || kc == g.z - 1;
   const int r0lo = edge ? 0 : kc - 1, r0hi = kc == 0 ? 1 : (edge ? 0 : kc + 1);
-  const int r1lo = kc == 0 ? g.z - 1 : (edge ? g.z - 2 : 1), r1hi = edge ? g.z - 1 : 0;
-  int run = 0;   // candidates before the current run; lane s takes every 8th
-  if (live) {
-    for (int da = -1; da <= 1; ++da) {
-      const int xa = ka + da < 0 ? g.x - 1 : (ka + da == g.x ? 0 : ka + da);
-      for (int db = -1; db <= 1; ++db) {
-        const int yb = kb + db < 0 ? g.y - 1 : (kb + db == g.y ? 0 : kb + db);
-        const int row = base + (xa * g.y + yb) * g.z;
+  const int r1lo = kc == 0 ? g.z - 1 : g.z - 2, r1hi = g.z - 1;
+  struct Row {
+    int q0, n0, q1, n;   // first run [q0, q0 + n0), second from q1, n in both
+  };
+  auto row_of = [&](int r) {
+    const int da = r / 3 - 1, db = r % 3 - 1;
+    const int xa = ka + da < 0 ? g.x - 1 : (ka + da == g.x ? 0 : ka + da);
+    const int yb = kb + db < 0 ? g.y - 1 : (kb + db == g.y ? 0 : kb + db);
+    const int* cs = a.start + base + (xa * g.y + yb) * g.z;
+    Row w;
+    w.q0 = cs[r0lo];
+    w.n0 = cs[r0hi + 1] - w.q0;
+    w.q1 = cs[edge ? r1lo : r0lo];
+    w.n = w.n0 + (edge ? cs[edge ? r1hi + 1 : r0lo] - w.q1 : 0);
+    if (!live) w.n0 = w.n = 0;
+    return w;
+  };
+  const Row own = row_of(s), shared = row_of(8);
+  uint32_t* hit = rows[0] + al * kCellRow;
+  uint32_t* ang_row = rows[1] + al * kCellRow;
+  int T = 0;   // hits of the atom; those past kCellHits are counted only
+  // this lane's candidates first, first + step, ... of a row, 64 at a time
+  auto scan = [&](const Row& w, int first, int step) {
+    const int n = (w.n - first + step - 1) / step;
+    auto slot = [&](int t) {
+      const int x = first + t * step;
+      return x < w.n0 ? w.q0 + x : w.q1 + (x - w.n0);
+    };
+    for (int t0 = 0; __any(t0 < n); t0 += 64) {
+      uint32_t mask[2] = {0, 0};
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          const int lo = h ? r1lo : r0lo, hi = h ? r1hi : r0hi;
-          if (lo > hi) continue;
-          const int cb = a.cell[row + lo], ce = a.cell[row + hi + 1];
-          // four of this lane's candidates per step, their loads issued
-          // together (a run of three bins is about three candidates per lane)
-          for (int q0 = cb + ((s - run) & 7); q0 < ce; q0 += 32) {
-            float4 p[4];
+      for (int h = 0; h < 2; ++h) {
+        for (int b = 0; b < 32; b += 8) {
+          const int t1 = t0 + 32 * h + b;
+          if (!__any(t1 < n)) break;
+          float4 p[8];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) p[u] = a.cpos[min(q0 + 8 * u, ce - 1)];
+          for (int u = 0; u < 8; ++u) p[u] = a.cpos[min(slot(max(min(t1 + u, n - 1), 0)), M - 1)];
+          uint32_t m8 = 0;
 #pragma unroll
-            for (int u = 0; u < 4; ++u)
-              if (q0 + 8 * u < ce)
-                keep_one<kTri>(c, t, __float_as_int(p[u].w), p[u].x, p[u].y, p[u].z, mybuf, nR, nA, angmask, keep);
+          for (int u = 0; u < 8; ++u) {
+            float ex = p[u].x - c.xf, ey = p[u].y - c.yf, ez = p[u].z - c.zf;
+            if constexpr (kTri) {
+              float kx, ky, kz;
+              min_image<true>(c, ex, ey, ez, kx, ky, kz);
+            } else {
+              ex = fminf(fabsf(ex), fabsf(c.Lxf - fabsf(ex)));
+              ey = fminf(fabsf(ey), fabsf(c.Lyf - fabsf(ey)));
+              ez = fminf(fabsf(ez), fabsf(c.Lzf - fabsf(ez)));
+            }
+            m8 |= (t1 + u < n && ex * ex + ey * ey + ez * ez < c.outR2) ? (1u << u) : 0u;
           }
-          run += ce - cb;
+          mask[h] |= m8 << b;
         }
       }
-    }
-  }
-  __syncthreads();
-  int most = nR, ntv[8], atv[8];
-  uint32_t mtv[8];
+      const int cnt = __popc(mask[0]) + __popc(mask[1]);
+      int w0 = cnt;
 #pragma unroll
-  for (int d = 1; d < 8; d <<= 1) most = max(most, __shfl_xor(most, d, 8));
-  int totR = 0, totA = 0;
-#pragma unroll
-  for (int q = 0; q < 8; ++q) {
-    ntv[q] = __shfl(nR, q, 8);
-    atv[q] = __shfl(nA, q, 8);
-    mtv[q] = __shfl(angmask, q, 8);
-    totR += ntv[q];
-    totA += atv[q];
-  }
-  const bool spill = most > kNbrBuf;
-  if (live && !spill) {
-    const uint32_t* gbuf = nbuf + (threadIdx.x & ~7);
-    const size_t col = (size_t)i;
-    // the atom's entries, taken in lane order, are ranked k = s, s + 8, ...,
-    // so the 8 lanes share the work evenly whatever each lane found
-    for (int k = s; k < totR; k += 8) {
-      int q0 = 0, u0 = k;
-#pragma unroll
-      for (int q = 0; q < 7; ++q)
-        if (q == q0 && u0 >= ntv[q]) {
-          u0 -= ntv[q];
-          q0 = q + 1;
-        }
-      const uint32_t e = gbuf[q0 + kNbrThreads * u0];
-      uint32_t m0 = 0;
-#pragma unroll
-      for (int q = 0; q < 8; ++q) m0 = q == q0 ? mtv[q] : m0;
-      int rR = 0, rA = 0;
-#pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        for (int u2 = 0; u2 < ntv[q]; ++u2) {
-          const int lt = gbuf[q + kNbrThreads * u2] < e ? 1 : 0;
-          rR += lt;
-          rA += lt & (int)((mtv[q] >> u2) & 1u);
-        }
+      for (int d = 1; d < 8; d <<= 1) {
+        const int u = __shfl_up(w0, d, 8);
+        if (s >= d) w0 += u;
       }
-      if (rR < a.capR) a.idxR[col * a.capR + rR] = e;
-      if (((m0 >> u0) & 1u) && rA < a.capA) a.idxA[col * a.capA + rA] = e;
+      const int tot = __shfl(w0, 7, 8);
+      w0 += T - cnt;
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+        for (uint32_t m = mask[h]; m; m &= m - 1u, ++w0)
+          if (w0 < kCellHits) hit[w0] = (uint32_t)slot(t0 + 32 * h + __builtin_ctz(m));
+      T += tot;
     }
-    if (s == 0) {
-      a.cntR[i] = totR;
-      a.cntA[i] = totA;   // an overflow is flagged by the all-pairs launch that follows
+  };
+  scan(own, 0, 1);
+  scan(shared, s, 8);
+  lds_lane_exchange();
+  const bool spill = T > kCellHits;
+  if (spill) T = 0;
+  // the hits, 8 at a time; entry u of the row is written after hit u is read
+  const int sh = threadIdx.x & 24;
+  const bool up = threadIdx.x & 32;
+  const uint32_t below = (1u << s) - 1u;
+  int nR = 0, nA = 0;
+  float4 pn = me;
+  if (s < T) pn = a.cpos[hit[s]];
+  for (int k0 = 0; __any(k0 < T); k0 += 8) {
+    const bool on = k0 + s < T;
+    const float4 p = pn;
+    if (k0 + 8 + s < T) pn = a.cpos[hit[k0 + 8 + s]];
+    const int j = __float_as_int(p.w);
+    float ex = p.x - c.xf, ey = p.y - c.yf, ez = p.z - c.zf, kx, ky, kz;
+    min_image<kTri>(c, ex, ey, ez, kx, ky, kz);
+    const float r2 = ex * ex + ey * ey + ez * ez;
+    const int code = 13 - (int)fmaf(9.f, kx, fmaf(3.f, ky, kz));
+    bool in = on & ((j != i) | (code != 13));
+    bool ang = r2 < c.inA2;
+    // inside either shell the float64 predicate decides
+    const bool shR = r2 >= c.inR2, shA = !ang && r2 < c.outA2;
+    if (in && (shR || shA)) {
+      const double d2 = image_d2<kTri>(c, p.x, p.y, p.z, kx, ky, kz);
+      if (shR) in = d2 < c.rcR2;
+      if (shA) ang = d2 < c.rcA2;
     }
+    ang = ang && in;
+    const unsigned long long bR = __ballot(in), bA = __ballot(ang);
+    const uint32_t mR = ((up ? (uint32_t)(bR >> 32) : (uint32_t)bR) >> sh) & 255u;
+    const uint32_t mA = ((up ? (uint32_t)(bA >> 32) : (uint32_t)bA) >> sh) & 255u;
+    const uint32_t e = ((uint32_t)j << 5) | (uint32_t)(code & 31);
+    lds_lane_exchange();
+    if (in) hit[nR + __popc(mR & below)] = e;
+    if (ang) ang_row[nA + __popc(mA & below)] = e;
+    lds_lane_exchange();
+    nR += __popc(mR);
+    nA += __popc(mA);
   }
-  if (live && spill && s == 0) a.acell[i] = -1;
+  if (s < 4) {
+    hit[nR + s] = 0xFFFFFFFFu;
+    ang_row[nA + s] = 0xFFFFFFFFu;
+  }
+  lds_lane_exchange();
+  if (!live) return;
+  if (spill) {
+    if (s == 0) a.acell[i] = -1;
+    return;
+  }
+  store_ranked(hit, nR, s, a.idxR + (size_t)i * a.capR, a.capR);
+  store_ranked(ang_row, nA, s, a.idxA + (size_t)i * a.capA, a.capA);
+  if (s == 0) {
+    a.cntR[i] = nR;
+    a.cntA[i] = nA;   // an overflow is flagged by the all-pairs launch that follows
+  }
 }
 
 // Position of the key in a sorted row holding m valid entries (of cap), -1
@@ -3958,7 +4046,7 @@ int group_lanes(int N) { return N <= kLanes32Atoms ? 32 : N <= kLanes16Atoms ? 1
 struct Layout {
   int N, S, T, D, Y, H, NR, TKR, Npad, lanes, nch, PW, NA, capR, capA;
   size_t order, seg, blist, bflags, astruct, p4, G, Sst, Ep, X, eatom, hrow, fA, wv, F, fb4, Es, Ws, eps, wbar, lpart,
-      Gd, FRst, FPst, Gbr, beta, part, pp, w0part, crpart, Sh, Sdh, cgrid, cell, cpart, acell, aslot, cpos, spart,
+      Gd, FRst, FPst, Gbr, beta, part, pp, w0part, crpart, Sh, Sdh, cgrid, cell, cstart, cpart, acell, aslot, cpos, spart,
       cur_step, bar, sargs, prm, Gtmp, total;
 };
 
@@ -4051,6 +4139,7 @@ Layout layout_of(const nep_model* m, const Ops* o, int S, int N, bool pad, int l
   L.Sdh = take(4 * (size_t)Np * L.NA * o->YH);
   L.cgrid = take(16 * Ss);
   L.cell = take(4 * (Nn + 1));
+  L.cstart = take(4 * (Nn + 1));
   L.cpart = take(4 * (Nn / kScanChunk + 1));
   L.acell = take(4 * Nn);
   L.aslot = take(4 * Nn);
@@ -4227,6 +4316,7 @@ void run_neighbors(const Ctx& c, nep_neighbors* nb, int32_t* flags, Prof* pr, bo
   a.cells = N >= a.cell_min && (c.b->max_atoms == 0 || c.b->max_atoms >= a.cell_min);
   a.grid = at<int4>(c.ws, c.L.cgrid);
   a.cell = at<int>(c.ws, c.L.cell);
+  a.start = at<int>(c.ws, c.L.cstart);
   a.cpart = at<int>(c.ws, c.L.cpart);
   a.acell = at<int>(c.ws, c.L.acell);
   a.aslot = at<int>(c.ws, c.L.aslot);
@@ -4235,17 +4325,18 @@ void run_neighbors(const Ctx& c, nep_neighbors* nb, int32_t* flags, Prof* pr, bo
     const int nch = grid1(N, kScanChunk);
     if (a.tilt) {
       NEP_LAUNCH(pr, "cell_setup",
-                 hipLaunchKernelGGL(k_cell_setup<true>, dim3(grid1(max(N + 1, S), 256)), dim3(256), 0, c.st, a));
+                 hipLaunchKernelGGL(k_cell_setup<true>, dim3(grid1(max(N, S), 256)), dim3(256), 0, c.st, a));
       NEP_LAUNCH(pr, "cell_bin", hipLaunchKernelGGL(k_cell_bin<true>, dim3(grid1(N, 256)), dim3(256), 0, c.st, a));
     } else {
       NEP_LAUNCH(pr, "cell_setup",
-                 hipLaunchKernelGGL(k_cell_setup<false>, dim3(grid1(max(N + 1, S), 256)), dim3(256), 0, c.st, a));
+                 hipLaunchKernelGGL(k_cell_setup<false>, dim3(grid1(max(N, S), 256)), dim3(256), 0, c.st, a));
       NEP_LAUNCH(pr, "cell_bin", hipLaunchKernelGGL(k_cell_bin<false>, dim3(grid1(N, 256)), dim3(256), 0, c.st, a));
     }
-    NEP_LAUNCH(pr, "cell_part",
-               hipLaunchKernelGGL(k_cell_part, dim3(nch), dim3(256), 0, c.st, N, a.cell, a.cpart));
+    if (nch > kScanDirect)
+      NEP_LAUNCH(pr, "cell_part",
+                 hipLaunchKernelGGL(k_cell_part, dim3(nch), dim3(256), 0, c.st, N, a.cell, a.cpart));
     NEP_LAUNCH(pr, "cell_start",
-               hipLaunchKernelGGL(k_cell_start, dim3(nch), dim3(256), 0, c.st, N, a.cell, a.cpart));
+               hipLaunchKernelGGL(k_cell_start, dim3(nch), dim3(256), 0, c.st, N, a.cell, a.cpart, a.start));
     NEP_LAUNCH(pr, "cell_place", hipLaunchKernelGGL(k_cell_place, dim3(grid1(N, 256)), dim3(256), 0, c.st, a));
     if (a.tilt)
       NEP_LAUNCH(pr, "cell_neighbors", hipLaunchKernelGGL(k_cell_neighbors<true>, dim3(grid1(N, kNbrAPB)),
