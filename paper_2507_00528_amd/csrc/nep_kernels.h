@@ -62,6 +62,19 @@ __device__ __forceinline__ float atom_word(int type, int T, bool over_r, bool ov
   return __uint_as_float(t | (over_r ? kAtomOverR : 0u) | (over_a ? kAtomOverA : 0u));
 }
 
+// Flags of a neighbor build in a launch that follows it: each of its blocks
+// stores its own word and one block collects them (block 0 of the order
+// launch, or of a small batch an extra block of the forward).  In a captured
+// step that block also starts the replay's flag word and latches the step
+// (graph_head's part), so the step needs no launch for that.
+struct FlagArgs {
+  const int* bflags;
+  int n;       // 0: none
+  int* flags;
+  int* step;   // null outside a captured step
+  int* cur;
+};
+
 struct FwdArgs {
   int N, Npad, H;
   float inv_rcR, inv_rcA;
@@ -88,6 +101,7 @@ struct FwdArgs {
   float* hrow;     // [N][T][KP] radial force coefficients (atom order)
   float* fA;       // [N][capA][3] angular pair forces
   int do_mlp, do_force;
+  FlagArgs fl;
 };
 
 // Forces and per-atom virials from the forward's radial force coefficients

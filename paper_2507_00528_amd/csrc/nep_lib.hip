@@ -476,202 +476,6 @@ __device__ __forceinline__ void write_hits(const NbrArgs& a, const ScanCtx& c, c
   totA = nA;
 }
 
-// kCells: the cell search ran before and wrote the lists of the atoms with
-// acell[i] >= 0
-template <bool kTri, bool kCells>
-__global__ __launch_bounds__(kNbrThreads) void k_neighbors(NbrArgs a) {
-  // 8 slots past the tile: scan_hits reads candidates eight at a time
-  __shared__ float tx[kNbrTile + 8], ty[kNbrTile + 8], tz[kNbrTile + 8];
-  __shared__ uint32_t nbuf[kNbrThreads * (kNbrBuf + 1)];
-  __shared__ int jr[2];
-  const int s = threadIdx.x & 7;
-  const int b0 = xcd_block() * kNbrAPB;
-  const int i = b0 + (threadIdx.x >> 3);
-  const bool live = i < a.N;
-  const int ic = live ? i : a.N - 1;
-  // structure of the block's first atom (scalar search), then forward from it
-  const cptr<int> aoff = as_const(a.aoff);
-  int lo = 0, hi = a.S;
-  while (hi - lo > 1) {
-    const int mid = (lo + hi) >> 1;
-    if (aoff[mid] <= min(b0, a.N - 1)) lo = mid; else hi = mid;
-  }
-  while (lo + 1 < a.S && a.aoff[lo + 1] <= ic) ++lo;
-  const int st = lo;
-  const int a0 = max(a.aoff[st], 0), a1 = min(a.aoff[st + 1], a.N);
-  // the block's atoms are consecutive, so their structures cover [jr[0], jr[1])
-  if (threadIdx.x == 0) jr[0] = a0;
-  if (i == min(b0 + kNbrAPB - 1, a.N - 1) && s == 0) jr[1] = a1;
-  ScanCtx c;
-  const CellCheck ck = init_ctx<kTri>(a, st, ic, a.pos[ic], a.pos[a.N + ic], a.pos[2 * a.N + ic], c);
-  int fl = 0;
-  if (!ck.pos_ok) fl |= FL_POS;
-  bool ok = live;
-  if (!ck.box_ok) {
-    fl |= FL_BOX;
-    ok = false;
-  }
-  if (live && s == 0) {
-    a.astruct[i] = st;
-    const int ti = a.type[i];
-    if (ti < 0 || ti >= a.T) fl |= FL_TYPE;
-  }
-  // atoms whose lists the cell search wrote (it leaves acell[i] >= 0)
-  const bool mine = live && !(kCells && a.acell[ic] >= 0);
-  const int len = ok && mine ? a1 - a0 : 0;
-  const int jb = a0 + (len * s) / 8, je = a0 + (len * (s + 1)) / 8;
-  // after the cell search, a block with no atom left to scan walks no tiles
-  bool any = true;
-  if constexpr (kCells)
-    any = __syncthreads_or(len > 0);
-  else
-    __syncthreads();
-  const int jlo = jr[0], jhi = any ? jr[1] : jr[0];
-  // walks the tiles of [jlo, jhi); this lane scans [b, e) of each
-  auto sweep = [&](int b, int e, auto&& scan) {
-    for (int t0 = jlo; t0 < jhi; t0 += kNbrTile) {
-      const int tn = min(kNbrTile, jhi - t0);
-      for (int q = threadIdx.x; q < tn; q += kNbrThreads) {
-        tx[q] = a.pos[t0 + q];
-        ty[q] = a.pos[a.N + t0 + q];
-        tz[q] = a.pos[2 * a.N + t0 + q];
-      }
-      __syncthreads();
-      const PosTile t{tx, ty, tz, t0};
-      scan(t, max(b, t0), min(e, t0 + tn));
-      __syncthreads();
-    }
-  };
-  // one scan: each lane keeps its entries in an LDS buffer (angular
-  // membership as a bit mask), and after the 8-lane prefix copies them to
-  // their slots; a lane with more than kNbrBuf entries makes the whole block
-  // rescan and write directly
-  uint32_t* mybuf = nbuf + threadIdx.x;   // slot u at mybuf[kNbrThreads u]
-  int nR = 0, nA = 0;
-  uint32_t angmask = 0;
-  auto keep = [&](int j, int code, bool ang) {
-    if (nR < kNbrBuf) {
-      mybuf[kNbrThreads * nR] = ((uint32_t)j << 5) | (uint32_t)code;
-      angmask |= ang ? (1u << nR) : 0u;
-    }
-    ++nR;
-    nA += ang ? 1 : 0;
-  };
-  // Structures of a block that fit one tile (nearly always: at most two of its
-  // structures exceed 32 atoms) take the single-image scan in two parts: a
-  // distance test per candidate that only sets a bit (about 15 instructions),
-  // then the image code, the shell tests and the stores for the hits alone,
-  // spread evenly over the atom's lanes.  Deciding every candidate in one
-  // part took about 40 instructions each for the one in eleven that is kept
-  // (512 structures, 87k atoms: 57 us in one part, 41 us in two).
-  bool done = false;
-  int totR = 0, totA = 0;
-  if (jhi - jlo <= kNbrTile) {
-    for (int q = threadIdx.x; q < jhi - jlo; q += kNbrThreads) {
-      tx[q] = a.pos[jlo + q];
-      ty[q] = a.pos[a.N + jlo + q];
-      tz[q] = a.pos[2 * a.N + jlo + q];
-    }
-    __syncthreads();
-    const PosTile t{tx, ty, tz, jlo};
-    if (c.fast) {   // the same for the atom's 8 lanes
-      uint32_t mask[kNbrMasks];
-      scan_hits<kTri>(c, t, jb, je, mask);
-      int n = 0;
-#pragma unroll
-      for (int k = 0; k < kNbrMasks; ++k) n += __popc(mask[k]);
-      int w = n;
-#pragma unroll
-      for (int d = 1; d < 8; d <<= 1) {
-        const int u = __shfl_up(w, d, 8);
-        if (s >= d) w += u;
-      }
-      const int T = __shfl(w, 7, 8);
-      w -= n;
-      if (T <= 8 * kNbrBuf) {
-        uint32_t* gbuf = nbuf + (threadIdx.x & ~7);   // the atom's columns
-#pragma unroll
-        for (int k = 0; k < kNbrMasks; ++k)
-          for (uint32_t m = mask[k]; m; m &= m - 1u, ++w)
-            gbuf[kNbrThreads * (w >> 3) + (w & 7)] = (uint32_t)(jb - jlo + 32 * k + __builtin_ctz(m));
-        lds_lane_exchange();
-        write_hits<kTri>(a, c, t, gbuf, T, s, totR, totA);
-        done = true;
-      }
-    }
-    if (!done) scan_keep<kTri>(c, t, jb, je, mybuf, nR, nA, angmask, keep);
-    __syncthreads();   // a rescan below loads the tile again
-  } else {
-    sweep(jb, je,
-          [&](const PosTile& t, int b2, int e2) { scan_keep<kTri>(c, t, b2, e2, mybuf, nR, nA, angmask, keep); });
-  }
-  // inclusive prefix over the 8 lanes of the atom
-  int pR = nR, pA = nA;
-#pragma unroll
-  for (int d = 1; d < 8; d <<= 1) {
-    const int uR = __shfl_up(pR, d, 8), uA = __shfl_up(pA, d, 8);
-    if (s >= d) {
-      pR += uR;
-      pA += uA;
-    }
-  }
-  if (!done) {
-    totR = __shfl(pR, 7, 8);
-    totA = __shfl(pA, 7, 8);
-  }
-  int wR = pR - nR, wA = pA - nA;
-  const size_t col = (size_t)c.i;
-  const bool spill = nR > kNbrBuf;   // never after the two-part scan (nR is 0)
-  if (mine && !spill) {
-    for (int u = 0; u < nR; ++u) {
-      const uint32_t e = mybuf[kNbrThreads * u];
-      if (wR + u < a.capR) a.idxR[col * a.capR + wR + u] = e;
-      if ((angmask >> u) & 1u) {
-        if (wA < a.capA) a.idxA[col * a.capA + wA] = e;
-        ++wA;
-      }
-    }
-  }
-  if (__syncthreads_or(mine && spill)) {
-    auto write = [&](int j, int code, bool ang) {
-      const uint32_t e = ((uint32_t)j << 5) | (uint32_t)code;
-      if (wR < a.capR) a.idxR[col * a.capR + wR] = e;
-      ++wR;
-      if (ang) {
-        if (wA < a.capA) a.idxA[col * a.capA + wA] = e;
-        ++wA;
-      }
-    };
-    // angular entries are a subset, so a lane past the radial capacity may
-    // still have angular slots to fill
-    const bool wr = mine && spill && (wR < a.capR || wA < a.capA);
-    sweep(wr ? jb : 0, wr ? je : 0,
-          [&](const PosTile& t, int b2, int e2) { scan_range<kTri>(c, t, b2, e2, write); });
-  }
-  if (live && s == 0) {
-    if (mine) {
-      a.cntR[i] = totR;
-      a.cntA[i] = totA;
-    } else {   // counted by the cell search
-      totR = a.cntR[i];
-      totA = a.cntA[i];
-    }
-    if (totR > a.capR || totA > a.capA) fl |= FL_OVERFLOW;
-    a.p4[i] = make_float4(c.xf, c.yf, c.zf, atom_word(a.type[i], a.T, totR > a.capR, totA > a.capA));
-  }
-  if (!(live && s == 0)) fl = 0;
-  if (a.bflags) {
-    __shared__ int word;
-    if (threadIdx.x == 0) word = 0;
-    __syncthreads();
-    if (fl) atomicOr(&word, fl);
-    __syncthreads();
-    if (threadIdx.x == 0) a.bflags[blockIdx.x] = word;
-  } else if (fl) {
-    atomicOr(a.flags, fl);
-  }
-}
-
 // Cell-list search of large structures.  A structure of at least
 // kCellMinAtoms atoms whose cell takes the single-image decision is cut into
 // na x nb x nc bins along its edge vectors, each bin at least rc + kCellPad
@@ -1128,6 +932,80 @@ __device__ __forceinline__ int launch_block(const int* __restrict__ blist, int n
   return blist[(b % nch) * order_blocks(T) + b / nch];
 }
 
+// Order of a batch of up to kTypeOrderAtoms atoms: species segments with their
+// atoms in atom order, without the pair counts.  So few atoms leave most SIMDs
+// with one wavefront of 2 or 4 atoms, which have nothing to balance, and the
+// order then needs no launch after the neighbor build (5 us of a 58 us step of
+// 544 atoms): extra blocks of the build form it, 256 threads a chunk.
+constexpr int kTypeOrderAtoms = 8192;
+constexpr int kTypeOrdLds = (kOrdChunk / kWave + 1) * kOrdMaxT + kOrdChunk + order_stride(kOrdMaxT);   // ints
+__device__ __forceinline__ void type_order(const OrderArgs& a, int c, int* lds) {
+  constexpr int NV = kOrdChunk / kWave;
+  int* cnt = lds;                            // [NV][kOrdMaxT] atoms of 64 by species, then those before them
+  int* tot = cnt + NV * kOrdMaxT;            // [kOrdMaxT]
+  int* key = tot + kOrdMaxT;                 // [kOrdChunk] 64 species + rank among the 64, -1: not placed
+  int* ord = key + kOrdChunk;                // [stride]
+  const int T = a.T, stride = order_stride(T);
+  const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
+  const int n = min(a.N - c * kOrdChunk, kOrdChunk), len = min(stride, a.Npad - c * stride);
+  const int* type = a.type + c * kOrdChunk;
+  // loops of the chunk's own atoms, not unrolled: a block runs this once, with
+  // a cold instruction cache
+  int next = type[min((int)threadIdx.x, n - 1)];
+  for (int q = threadIdx.x; q < len; q += 256) ord[q] = -1;
+#pragma unroll 1
+  for (int q = threadIdx.x; q - lane < n; q += 256) {
+    const int t = q < n && next >= 0 && next < T ? next : -1;
+    next = type[min(q + 256, n - 1)];
+    int k = -1;
+#pragma unroll
+    for (int u = 0; u < kOrdMaxT; ++u) {
+      const unsigned long long m = __ballot(t == u);
+      if (t == u) k = kWave * u + __popcll(m & ((1ull << lane) - 1ull));
+      if (lane == u) cnt[q / kWave * kOrdMaxT + u] = __popcll(m);
+    }
+    key[q] = k;
+  }
+  __syncthreads();
+  if (wid < kOrdMaxT) {   // wavefront u scans species u
+    const int v = lane < (n + kWave - 1) / kWave ? cnt[lane * kOrdMaxT + wid] : 0;
+    int inc = v;
+#pragma unroll
+    for (int d = 1; d < NV; d <<= 1) {
+      const int x = __shfl_up(inc, d, kWave);
+      if (lane >= d) inc += x;
+    }
+    if (lane < NV) cnt[lane * kOrdMaxT + wid] = inc - v;
+    if (lane == NV - 1) tot[wid] = inc;
+  }
+  __syncthreads();
+  int start[kOrdMaxT], at = 0;
+#pragma unroll
+  for (int u = 0; u < kOrdMaxT; ++u) {
+    const int m = tot[u];
+    start[u] = at;
+    at += (m + kSegAlign - 1) / kSegAlign * kSegAlign;
+    if (u < T && (int)threadIdx.x == u) {
+      a.seg[2 * (c * T + u)] = c * stride + start[u];
+      a.seg[2 * (c * T + u) + 1] = m;
+    }
+  }
+#pragma unroll 1
+  for (int q = threadIdx.x; q < n; q += 256) {
+    const int k = key[q];
+    if (k < 0) continue;
+    const int t = k / kWave;
+    const int s0 = t == 0 ? start[0] : (t == 1 ? start[1] : (t == 2 ? start[2] : start[3]));
+    ord[s0 + cnt[q / kWave * kOrdMaxT + t] + k % kWave] = c * kOrdChunk + q;
+  }
+  __syncthreads();
+#pragma unroll 1
+  for (int q = threadIdx.x; q < len; q += 256) a.order[(size_t)c * stride + q] = ord[q];
+  const int nb = order_blocks(T);
+  for (int q = threadIdx.x; q < nb; q += 256)
+    a.blist[c * nb + q] = q * kSegAlign < len && ord[q * kSegAlign] >= 0 ? (c * stride) / kSegAlign + q : -1;
+}
+
 // LDS of order_body (ints): counts per 64 atoms and key, key offsets, the
 // chunk's positions, species counts
 constexpr int kOrdLds = (kOrdChunk / kWave + 1) * kOrdMaxT * kOrdBuckets + order_stride(kOrdMaxT) + 8;
@@ -1242,17 +1120,6 @@ __device__ __forceinline__ void order_body(const OrderArgs& a, int c, int* lds) 
   __syncthreads();
 }
 
-// Flags of a neighbor build: each of its blocks stores its own word, and block
-// 0 of the order launch, which follows, collects them.  In a captured step it
-// also starts the replay's flag word and latches the step (graph_head's part),
-// so the step needs no launch for that.
-struct FlagArgs {
-  const int* bflags;
-  int n;
-  int* flags;
-  int* step;   // null outside a captured step
-  int* cur;
-};
 __device__ __forceinline__ void collect_flags(const FlagArgs& f, int* lds) {
   if (threadIdx.x == 0) lds[0] = 0;
   __syncthreads();
@@ -1277,6 +1144,209 @@ __global__ __launch_bounds__(1024) void k_order(OrderArgs a, FlagArgs f) {
   __shared__ int lds[kOrdLds];
   if (blockIdx.x == 0) collect_flags(f, lds);
   order_body<1024>(a, blockIdx.x, lds);
+}
+
+// ========================================================== list building
+// kCells: the cell search ran before and wrote the lists of the atoms with
+// acell[i] >= 0.  The first nblk blocks build lists; any more form the species
+// order of a small batch, a chunk each.
+template <bool kTri, bool kCells>
+__global__ __launch_bounds__(kNbrThreads) void k_neighbors(NbrArgs a, int nblk, OrderArgs og) {
+  // 8 slots past the tile: scan_hits reads candidates eight at a time
+  __shared__ float tx[kNbrTile + 8], ty[kNbrTile + 8], tz[kNbrTile + 8];
+  __shared__ __align__(16) uint32_t nbuf[kNbrThreads * (kNbrBuf + 1)];
+  __shared__ int jr[2];
+  static_assert(kTypeOrdLds <= kNbrThreads * (kNbrBuf + 1), "the order's words fit the entry buffers");
+  if ((int)blockIdx.x >= nblk) {
+    type_order(og, blockIdx.x - nblk, reinterpret_cast<int*>(nbuf));
+    return;
+  }
+  const int s = threadIdx.x & 7;
+  const int b0 = xcd_block_of(blockIdx.x, nblk) * kNbrAPB;
+  const int i = b0 + (threadIdx.x >> 3);
+  const bool live = i < a.N;
+  const int ic = live ? i : a.N - 1;
+  // structure of the block's first atom (scalar search), then forward from it
+  const cptr<int> aoff = as_const(a.aoff);
+  int lo = 0, hi = a.S;
+  while (hi - lo > 1) {
+    const int mid = (lo + hi) >> 1;
+    if (aoff[mid] <= min(b0, a.N - 1)) lo = mid; else hi = mid;
+  }
+  while (lo + 1 < a.S && a.aoff[lo + 1] <= ic) ++lo;
+  const int st = lo;
+  const int a0 = max(a.aoff[st], 0), a1 = min(a.aoff[st + 1], a.N);
+  // the block's atoms are consecutive, so their structures cover [jr[0], jr[1])
+  if (threadIdx.x == 0) jr[0] = a0;
+  if (i == min(b0 + kNbrAPB - 1, a.N - 1) && s == 0) jr[1] = a1;
+  ScanCtx c;
+  const CellCheck ck = init_ctx<kTri>(a, st, ic, a.pos[ic], a.pos[a.N + ic], a.pos[2 * a.N + ic], c);
+  int fl = 0;
+  if (!ck.pos_ok) fl |= FL_POS;
+  bool ok = live;
+  if (!ck.box_ok) {
+    fl |= FL_BOX;
+    ok = false;
+  }
+  if (live && s == 0) {
+    a.astruct[i] = st;
+    const int ti = a.type[i];
+    if (ti < 0 || ti >= a.T) fl |= FL_TYPE;
+  }
+  // atoms whose lists the cell search wrote (it leaves acell[i] >= 0)
+  const bool mine = live && !(kCells && a.acell[ic] >= 0);
+  const int len = ok && mine ? a1 - a0 : 0;
+  const int jb = a0 + (len * s) / 8, je = a0 + (len * (s + 1)) / 8;
+  // after the cell search, a block with no atom left to scan walks no tiles
+  bool any = true;
+  if constexpr (kCells)
+    any = __syncthreads_or(len > 0);
+  else
+    __syncthreads();
+  const int jlo = jr[0], jhi = any ? jr[1] : jr[0];
+  // walks the tiles of [jlo, jhi); this lane scans [b, e) of each
+  auto sweep = [&](int b, int e, auto&& scan) {
+    for (int t0 = jlo; t0 < jhi; t0 += kNbrTile) {
+      const int tn = min(kNbrTile, jhi - t0);
+      for (int q = threadIdx.x; q < tn; q += kNbrThreads) {
+        tx[q] = a.pos[t0 + q];
+        ty[q] = a.pos[a.N + t0 + q];
+        tz[q] = a.pos[2 * a.N + t0 + q];
+      }
+      __syncthreads();
+      const PosTile t{tx, ty, tz, t0};
+      scan(t, max(b, t0), min(e, t0 + tn));
+      __syncthreads();
+    }
+  };
+  // one scan: each lane keeps its entries in an LDS buffer (angular
+  // membership as a bit mask), and after the 8-lane prefix copies them to
+  // their slots; a lane with more than kNbrBuf entries makes the whole block
+  // rescan and write directly
+  uint32_t* mybuf = nbuf + threadIdx.x;   // slot u at mybuf[kNbrThreads u]
+  int nR = 0, nA = 0;
+  uint32_t angmask = 0;
+  auto keep = [&](int j, int code, bool ang) {
+    if (nR < kNbrBuf) {
+      mybuf[kNbrThreads * nR] = ((uint32_t)j << 5) | (uint32_t)code;
+      angmask |= ang ? (1u << nR) : 0u;
+    }
+    ++nR;
+    nA += ang ? 1 : 0;
+  };
+  // Structures of a block that fit one tile (nearly always: at most two of its
+  // structures exceed 32 atoms) take the single-image scan in two parts: a
+  // distance test per candidate that only sets a bit (about 15 instructions),
+  // then the image code, the shell tests and the stores for the hits alone,
+  // spread evenly over the atom's lanes.  Deciding every candidate in one
+  // part took about 40 instructions each for the one in eleven that is kept
+  // (512 structures, 87k atoms: 57 us in one part, 41 us in two).
+  bool done = false;
+  int totR = 0, totA = 0;
+  if (jhi - jlo <= kNbrTile) {
+    for (int q = threadIdx.x; q < jhi - jlo; q += kNbrThreads) {
+      tx[q] = a.pos[jlo + q];
+      ty[q] = a.pos[a.N + jlo + q];
+      tz[q] = a.pos[2 * a.N + jlo + q];
+    }
+    __syncthreads();
+    const PosTile t{tx, ty, tz, jlo};
+    if (c.fast) {   // the same for the atom's 8 lanes
+      uint32_t mask[kNbrMasks];
+      scan_hits<kTri>(c, t, jb, je, mask);
+      int n = 0;
+#pragma unroll
+      for (int k = 0; k < kNbrMasks; ++k) n += __popc(mask[k]);
+      int w = n;
+#pragma unroll
+      for (int d = 1; d < 8; d <<= 1) {
+        const int u = __shfl_up(w, d, 8);
+        if (s >= d) w += u;
+      }
+      const int T = __shfl(w, 7, 8);
+      w -= n;
+      if (T <= 8 * kNbrBuf) {
+        uint32_t* gbuf = nbuf + (threadIdx.x & ~7);   // the atom's columns
+#pragma unroll
+        for (int k = 0; k < kNbrMasks; ++k)
+          for (uint32_t m = mask[k]; m; m &= m - 1u, ++w)
+            gbuf[kNbrThreads * (w >> 3) + (w & 7)] = (uint32_t)(jb - jlo + 32 * k + __builtin_ctz(m));
+        lds_lane_exchange();
+        write_hits<kTri>(a, c, t, gbuf, T, s, totR, totA);
+        done = true;
+      }
+    }
+    if (!done) scan_keep<kTri>(c, t, jb, je, mybuf, nR, nA, angmask, keep);
+    __syncthreads();   // a rescan below loads the tile again
+  } else {
+    sweep(jb, je,
+          [&](const PosTile& t, int b2, int e2) { scan_keep<kTri>(c, t, b2, e2, mybuf, nR, nA, angmask, keep); });
+  }
+  // inclusive prefix over the 8 lanes of the atom
+  int pR = nR, pA = nA;
+#pragma unroll
+  for (int d = 1; d < 8; d <<= 1) {
+    const int uR = __shfl_up(pR, d, 8), uA = __shfl_up(pA, d, 8);
+    if (s >= d) {
+      pR += uR;
+      pA += uA;
+    }
+  }
+  if (!done) {
+    totR = __shfl(pR, 7, 8);
+    totA = __shfl(pA, 7, 8);
+  }
+  int wR = pR - nR, wA = pA - nA;
+  const size_t col = (size_t)c.i;
+  const bool spill = nR > kNbrBuf;   // never after the two-part scan (nR is 0)
+  if (mine && !spill) {
+    for (int u = 0; u < nR; ++u) {
+      const uint32_t e = mybuf[kNbrThreads * u];
+      if (wR + u < a.capR) a.idxR[col * a.capR + wR + u] = e;
+      if ((angmask >> u) & 1u) {
+        if (wA < a.capA) a.idxA[col * a.capA + wA] = e;
+        ++wA;
+      }
+    }
+  }
+  if (__syncthreads_or(mine && spill)) {
+    auto write = [&](int j, int code, bool ang) {
+      const uint32_t e = ((uint32_t)j << 5) | (uint32_t)code;
+      if (wR < a.capR) a.idxR[col * a.capR + wR] = e;
+      ++wR;
+      if (ang) {
+        if (wA < a.capA) a.idxA[col * a.capA + wA] = e;
+        ++wA;
+      }
+    };
+    // angular entries are a subset, so a lane past the radial capacity may
+    // still have angular slots to fill
+    const bool wr = mine && spill && (wR < a.capR || wA < a.capA);
+    sweep(wr ? jb : 0, wr ? je : 0,
+          [&](const PosTile& t, int b2, int e2) { scan_range<kTri>(c, t, b2, e2, write); });
+  }
+  if (live && s == 0) {
+    if (mine) {
+      a.cntR[i] = totR;
+      a.cntA[i] = totA;
+    } else {   // counted by the cell search
+      totR = a.cntR[i];
+      totA = a.cntA[i];
+    }
+    if (totR > a.capR || totA > a.capA) fl |= FL_OVERFLOW;
+    a.p4[i] = make_float4(c.xf, c.yf, c.zf, atom_word(a.type[i], a.T, totR > a.capR, totA > a.capA));
+  }
+  if (!(live && s == 0)) fl = 0;
+  if (a.bflags) {
+    __shared__ int word;
+    if (threadIdx.x == 0) word = 0;
+    __syncthreads();
+    if (fl) atomicOr(&word, fl);
+    __syncthreads();
+    if (threadIdx.x == 0) a.bflags[blockIdx.x] = word;
+  } else if (fl) {
+    atomicOr(a.flags, fl);
+  }
 }
 
 // ================================================================= helpers
@@ -2056,6 +2126,10 @@ __device__ __forceinline__ void forward_body(const FwdArgs& a, int b, float* lds
 template <class C, bool kTri, int W, int L>
 __global__ __launch_bounds__(256, W) void k_forward(FwdArgs a) {
   extern __shared__ __align__(16) float lds[];
+  if (a.fl.n > 0 && blockIdx.x == gridDim.x - 1) {
+    collect_flags(a.fl, reinterpret_cast<int*>(lds));
+    return;
+  }
   forward_body<C, kTri, L>(a, blockIdx.x, lds);
 }
 
@@ -2391,25 +2465,34 @@ __device__ __forceinline__ void struct_accumulate(const StructArgs& a, int lo, i
   }
 }
 
-// block tree sum of acc[0..7]; the result is in red[q][0]
-__device__ __forceinline__ void struct_reduce(double (*red)[kRedBlk], const double* acc) {
+// block sum of acc[0..7] in a fixed order, the result in red[q][0]: over each
+// wavefront's lanes, then its four wavefronts
+__device__ __forceinline__ void struct_reduce(double (*red)[kRedBlk / kWave], const double* acc) {
+  const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
+  double v[8];
 #pragma unroll
-  for (int q = 0; q < 8; ++q) red[q][threadIdx.x] = acc[q];
+  for (int q = 0; q < 8; ++q) v[q] = acc[q];
+#pragma unroll
+  for (int d = kWave / 2; d > 0; d >>= 1)
+#pragma unroll
+    for (int q = 0; q < 8; ++q) v[q] += __shfl_xor(v[q], d, kWave);
+  if (lane == 0)
+#pragma unroll
+    for (int q = 0; q < 8; ++q) red[q][wid] = v[q];
   __syncthreads();
-  for (int st = kRedBlk / 2; st > 0; st >>= 1) {
-    if (threadIdx.x < st)
-#pragma unroll
-      for (int q = 0; q < 8; ++q) red[q][threadIdx.x] += red[q][threadIdx.x + st];
-    __syncthreads();
+  if (threadIdx.x < 8) {
+    double* r = red[threadIdx.x];
+    r[0] = (r[0] + r[1]) + (r[2] + r[3]);
   }
+  __syncthreads();
 }
 
 // Chunk partials of the large structures: a chunk of kStructChunk atoms
 // meets at most two structures of 2 kStructChunk atoms or more, those of its
 // first and last atoms (slots 0 and 1).
-// chunk vb; lds: 8 kRedBlk doubles
+// chunk vb; lds: kStructLds bytes
 __device__ __forceinline__ void struct_part_body(const StructArgs& a, int vb, void* lds) {
-  double (*red)[kRedBlk] = reinterpret_cast<double (*)[kRedBlk]>(lds);
+  double (*red)[kRedBlk / kWave] = reinterpret_cast<double (*)[kRedBlk / kWave]>(lds);
   const int c0 = vb * kStructChunk, c1 = min(c0 + kStructChunk, a.N);
   const int sa = find_struct(a.aoff, a.S, c0), sb = find_struct(a.aoff, a.S, c1 - 1);
   for (int h = 0; h < 2; ++h) {
@@ -2426,17 +2509,20 @@ __device__ __forceinline__ void struct_part_body(const StructArgs& a, int vb, vo
 }
 
 __global__ __launch_bounds__(kRedBlk) void k_struct_part(StructArgs a) {
-  __shared__ double red[8][kRedBlk];
+  __shared__ double red[8][kRedBlk / kWave];
   struct_part_body(a, blockIdx.x, red);
 }
 
-constexpr int kStructLds = 8 * kRedBlk * sizeof(double);
+constexpr int kStructLds = 8 * (kRedBlk / kWave) * sizeof(double);
 // structure s; lds: kStructLds bytes
 __device__ __forceinline__ void struct_body(const StructArgs& a, int s, void* lds) {
-  double (*red)[kRedBlk] = reinterpret_cast<double (*)[kRedBlk]>(lds);
+  double (*red)[kRedBlk / kWave] = reinterpret_cast<double (*)[kRedBlk / kWave]>(lds);
   const int a0 = a.aoff[s], a1 = a.aoff[s + 1];
   double acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
   const bool lab = a.Et != nullptr;
+  // component c (the energy, the six of the virial) is finished by thread c
+  const int c = threadIdx.x;
+  const float label = lab && c < 7 ? (c == 0 ? a.Et[s] : a.Wt[6 * s + c - 1]) : 0.f;
   if (a.split && a1 - a0 >= 2 * kStructChunk) {
     // chunk b holds this structure in slot 0 if it starts at or before the chunk
     for (int b = a0 / kStructChunk + threadIdx.x; b <= (a1 - 1) / kStructChunk; b += kRedBlk) {
@@ -2448,40 +2534,41 @@ __device__ __forceinline__ void struct_body(const StructArgs& a, int s, void* ld
     struct_accumulate(a, a0, a1, acc);
   }
   struct_reduce(red, acc);
-  if (threadIdx.x == 0) {
-    const double E = red[0][0];
-    a.Es[s] = (float)E;
-    if (a.Es_user) a.Es_user[s] = (float)E;
-    for (int c = 0; c < 6; ++c) {
-      a.Ws[6 * s + c] = (float)red[1 + c][0];
-      if (a.Ws_user) a.Ws_user[6 * s + c] = (float)red[1 + c][0];
+  if (threadIdx.x < kWave) {
+    const double v = c < 7 ? red[c < 7 ? c : 0][0] : 0.0;
+    const int n = a1 - a0;
+    if (c == 0) {
+      a.Es[s] = (float)v;
+      if (a.Es_user) a.Es_user[s] = (float)v;
+    } else if (c < 7) {
+      a.Ws[6 * s + c - 1] = (float)v;
+      if (a.Ws_user) a.Ws_user[6 * s + c - 1] = (float)v;
     }
     if (lab) {
-      const int n = a1 - a0;
-      double le = 0, lv = 0;
-      if (n > 0) {
-        const double e = (E - (double)a.Et[s]) / n;
-        le = e * e;
-        a.eps[s] = (float)(2.0 * a.le * e / ((double)a.S * n));
-        for (int c = 0; c < 6; ++c) {
-          const double wc = (red[1 + c][0] - (double)a.Wt[6 * s + c]) / n;
-          lv += wc * wc;
-          a.wbar[6 * s + c] = (float)(2.0 * a.lv * wc / (6.0 * a.S * n));
-        }
-      } else {
-        a.eps[s] = 0.f;
-        for (int c = 0; c < 6; ++c) a.wbar[6 * s + c] = 0.f;
+      const double e = n > 0 ? (v - (double)label) / n : 0.0;
+      if (c < 7) {
+        const float w = n > 0 ? (float)(2.0 * (c == 0 ? a.le : a.lv) * e / ((c == 0 ? 1.0 : 6.0) * ((double)a.S * n))) : 0.f;
+        if (c == 0)
+          a.eps[s] = w;
+        else
+          a.wbar[6 * s + c - 1] = w;
       }
-      a.lpart[3 * s] = le;
-      a.lpart[3 * s + 1] = red[7][0];
-      a.lpart[3 * s + 2] = lv;
+      const double sq = c < 7 ? e * e : 0.0;
+      double lv = 0.0;
+#pragma unroll
+      for (int u = 1; u < 7; ++u) lv += __shfl(sq, u, kWave);
+      if (c == 0) {
+        a.lpart[3 * s] = sq;
+        a.lpart[3 * s + 1] = red[7][0];
+        a.lpart[3 * s + 2] = lv;
+      }
     }
   }
   __syncthreads();   // red is read above before the next use of the LDS
 }
 
 __global__ __launch_bounds__(kRedBlk) void k_struct(StructArgs a) {
-  __shared__ double red[8][kRedBlk];
+  __shared__ double red[8][kRedBlk / kWave];
   struct_body(a, blockIdx.x, red);
 }
 
@@ -3310,14 +3397,20 @@ __global__ __launch_bounds__(256, 3) void k_outer_reduce(OuterReduceArgs a) {
 // lane sums.  Parameter layout: c^R [T][T][NR][KR], c^A [T][T][NA][KA], then
 // per species W0 [H][D], b0 [H], w1 [H], b1.
 // ==================================================================== Adam
+__device__ __forceinline__ void adam_update(float& th, float& m, float& v, float g, float lr, float b1, float b2,
+                                            float eps, float c1, float c2) {
+  m = b1 * m + (1.0f - b1) * g;
+  v = b2 * v + (1.0f - b2) * g * g;
+  th -= lr * (m / c1) / (sqrtf(v / c2) + eps);
+}
 __device__ __forceinline__ void adam_one(float* __restrict__ th, float* __restrict__ m, float* __restrict__ v,
                                          float g, float lr, float b1, float b2, float eps, float c1, float c2,
                                          int64_t q) {
-  const float mm = b1 * m[q] + (1.0f - b1) * g;
-  const float vv = b2 * v[q] + (1.0f - b2) * g * g;
+  float t = th[q], mm = m[q], vv = v[q];
+  adam_update(t, mm, vv, g, lr, b1, b2, eps, c1, c2);
   m[q] = mm;
   v[q] = vv;
-  th[q] -= lr * (mm / c1) / (sqrtf(vv / c2) + eps);
+  th[q] = t;
 }
 
 __global__ __launch_bounds__(256) void k_adam(int64_t P, float* __restrict__ th, float* __restrict__ m,
@@ -3369,27 +3462,28 @@ __device__ __forceinline__ int pad_col(const PadDims& d, int v) {
   return d.NRc + d.L3c * d.NAc + d.NAc + v;   // 5-body
 }
 
-__device__ __forceinline__ int64_t pad_index(const PadDims& d, int64_t q) {
-  const int64_t PR = (int64_t)d.T * d.T * d.NR * d.KR, PA = (int64_t)d.T * d.T * d.NA * d.KA;
-  const int64_t PRc = (int64_t)d.Tc * d.Tc * d.NRc * d.KRc, PAc = (int64_t)d.Tc * d.Tc * d.NAc * d.KAc;
+// 32-bit: a supported model has under 2^31 parameters
+__device__ __forceinline__ int pad_index(const PadDims& d, int q) {
+  const int PR = d.T * d.T * d.NR * d.KR, PA = d.T * d.T * d.NA * d.KA;
+  const int PRc = d.Tc * d.Tc * d.NRc * d.KRc, PAc = d.Tc * d.Tc * d.NAc * d.KAc;
   if (q < PR) {
-    const int64_t k = q % d.KR, n = (q / d.KR) % d.NR, J = (q / ((int64_t)d.KR * d.NR)) % d.T;
-    const int64_t I = q / ((int64_t)d.KR * d.NR * d.T);
+    const int k = q % d.KR, n = (q / d.KR) % d.NR, J = (q / (d.KR * d.NR)) % d.T;
+    const int I = q / (d.KR * d.NR * d.T);
     return ((I * d.Tc + J) * d.NRc + n) * d.KRc + k;
   }
   q -= PR;
   if (q < PA) {
-    const int64_t k = q % d.KA, n = (q / d.KA) % d.NA, J = (q / ((int64_t)d.KA * d.NA)) % d.T;
-    const int64_t I = q / ((int64_t)d.KA * d.NA * d.T);
+    const int k = q % d.KA, n = (q / d.KA) % d.NA, J = (q / (d.KA * d.NA)) % d.T;
+    const int I = q / (d.KA * d.NA * d.T);
     return PRc + ((I * d.Tc + J) * d.NAc + n) * d.KAc + k;
   }
   q -= PA;
-  const int64_t HD = (int64_t)d.H * d.D;
-  const int64_t blk = HD + 2 * d.H + 1, blkc = (int64_t)d.H * d.Dc + 2 * d.H + 1;
-  const int64_t I = q / blk, o = q % blk;
-  const int64_t base = PRc + PAc + I * blkc;
-  if (o < HD) return base + (o / d.D) * d.Dc + pad_col(d, (int)(o % d.D));
-  return base + (int64_t)d.H * d.Dc + (o - HD);   // b0, w1, b1
+  const int HD = d.H * d.D;
+  const int blk = HD + 2 * d.H + 1, blkc = d.H * d.Dc + 2 * d.H + 1;
+  const int I = q / blk, o = q % blk;
+  const int base = PRc + PAc + I * blkc;
+  if (o < HD) return base + (o / d.D) * d.Dc + pad_col(d, o % d.D);
+  return base + d.H * d.Dc + (o - HD);   // b0, w1, b1
 }
 
 struct GradArgs {
@@ -3424,7 +3518,9 @@ __device__ __forceinline__ bool adam_allowed(int* flags, int fl0, int st, float 
   return fl0 == 0 && st >= 1;
 }
 
-// block vb: parameters 16 vb .. 16 vb + 15
+// Block vb: parameters 16 vb .. 16 vb + 15.  What Adam needs is loaded, and its
+// rate and bias corrections formed, while the first partial sums are on their
+// way (as a chain after the sums: 5.3 us of a 58 us step of 544 atoms).
 __device__ __forceinline__ void grad_final_body(const GradArgs& a, int vb) {
   const int64_t q = ((int64_t)vb * 256 + threadIdx.x) >> 4;
   const int l = threadIdx.x & 15;
@@ -3433,11 +3529,23 @@ __device__ __forceinline__ void grad_final_body(const GradArgs& a, int vb) {
   const int PSA = a.T * a.NA * a.KA;
   const int HD = a.H * a.D, CR = a.NR * a.T * a.KR;
   double sum = 0.0;
+  const bool out = q < a.P && l == 0;
+  float th = 0.f, m = 0.f, v = 0.f;
+  int st = 0, fl0 = 0;
+  if (a.adam) {
+    st = *a.step;
+    fl0 = __hip_atomic_load(a.flags, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (out) {
+      th = a.th[q];
+      m = a.mm[q];
+      v = a.vv[q];
+    }
+  }
+  const float* fsrc = nullptr;
+  const double* dsrc = nullptr;
+  int stride = 0, rows = 0;
   if (q < a.P) {
-    const int qi = (int)(a.pad ? pad_index(a.pd, q) : q);
-    const float* fsrc = nullptr;
-    const double* dsrc = nullptr;
-    int stride = 0, rows = 0;
+    const int qi = a.pad ? pad_index(a.pd, (int)q) : (int)q;
     if (qi < P_R) {
       const int I = qi / (a.T * a.NR * a.KR), rem = qi % (a.T * a.NR * a.KR);
       const int t = rem / (a.NR * a.KR), n = (rem / a.KR) % a.NR, k = rem % a.KR;
@@ -3461,24 +3569,29 @@ __device__ __forceinline__ void grad_final_body(const GradArgs& a, int vb) {
         rows = a.PRC;
       }
     }
-    if (fsrc) {
-      for (int r = l; r < rows; r += 16) sum += (double)fsrc[(size_t)r * stride];
-    } else {
-      for (int r = l; r < rows; r += 16) sum += dsrc[(size_t)r * stride];
-    }
+    if (l < rows) sum = fsrc ? (double)fsrc[(size_t)l * stride] : dsrc[(size_t)l * stride];
+  }
+  float lr = 0.f, c1 = 1.f, c2 = 1.f;
+  if (a.adam) {
+    lr = lr_at(a.ad, (int64_t)(st - 1));
+    c1 = 1.0f - powf(a.ad.b1, (float)st);
+    c2 = 1.0f - powf(a.ad.b2, (float)st);
+  }
+  if (fsrc) {
+    for (int r = l + 16; r < rows; r += 16) sum += (double)fsrc[(size_t)r * stride];
+  } else {
+    for (int r = l + 16; r < rows; r += 16) sum += dsrc[(size_t)r * stride];
   }
 #pragma unroll
   for (int d = 8; d >= 1; d >>= 1) sum += __shfl_xor(sum, d, 16);
-  if (q < a.P && l == 0) {
+  if (out) {
     const float gq = (float)sum;
     a.grad[q] = gq;
-    if (a.adam) {
-      const int st = *a.step;
-      if (adam_allowed(a.flags, __hip_atomic_load(a.flags, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), st, gq)) {
-        const float lr = lr_at(a.ad, (int64_t)(st - 1));
-        const float c1 = 1.0f - powf(a.ad.b1, (float)st), c2 = 1.0f - powf(a.ad.b2, (float)st);
-        adam_one(a.th, a.mm, a.vv, gq, lr, a.ad.b1, a.ad.b2, a.ad.eps, c1, c2, q);
-      }
+    if (a.adam && adam_allowed(a.flags, fl0, st, gq)) {
+      adam_update(th, m, v, gq, lr, a.ad.b1, a.ad.b2, a.ad.eps, c1, c2);
+      a.mm[q] = m;
+      a.vv[q] = v;
+      a.th[q] = th;
     }
   }
 }
@@ -3712,27 +3825,27 @@ __global__ void k_step_head(StepArgs a, StepArgs* dst, int* flags, int* step, in
 // (PadDims and the layout maps stand before the final gradient reduction.)
 
 // class parameter q of the model, -1 where the model has none
-__device__ __forceinline__ int64_t unpad_index(const PadDims& d, int64_t q) {
-  const int64_t PRc = (int64_t)d.Tc * d.Tc * d.NRc * d.KRc, PAc = (int64_t)d.Tc * d.Tc * d.NAc * d.KAc;
-  const int64_t PR = (int64_t)d.T * d.T * d.NR * d.KR, PA = (int64_t)d.T * d.T * d.NA * d.KA;
+__device__ __forceinline__ int unpad_index(const PadDims& d, int q) {
+  const int PRc = d.Tc * d.Tc * d.NRc * d.KRc, PAc = d.Tc * d.Tc * d.NAc * d.KAc;
+  const int PR = d.T * d.T * d.NR * d.KR, PA = d.T * d.T * d.NA * d.KA;
   if (q < PRc) {
-    const int64_t k = q % d.KRc, n = (q / d.KRc) % d.NRc, J = (q / ((int64_t)d.KRc * d.NRc)) % d.Tc;
-    const int64_t I = q / ((int64_t)d.KRc * d.NRc * d.Tc);
+    const int k = q % d.KRc, n = (q / d.KRc) % d.NRc, J = (q / (d.KRc * d.NRc)) % d.Tc;
+    const int I = q / (d.KRc * d.NRc * d.Tc);
     return k < d.KR && n < d.NR && J < d.T && I < d.T ? ((I * d.T + J) * d.NR + n) * d.KR + k : -1;
   }
   q -= PRc;
   if (q < PAc) {
-    const int64_t k = q % d.KAc, n = (q / d.KAc) % d.NAc, J = (q / ((int64_t)d.KAc * d.NAc)) % d.Tc;
-    const int64_t I = q / ((int64_t)d.KAc * d.NAc * d.Tc);
+    const int k = q % d.KAc, n = (q / d.KAc) % d.NAc, J = (q / (d.KAc * d.NAc)) % d.Tc;
+    const int I = q / (d.KAc * d.NAc * d.Tc);
     return k < d.KA && n < d.NA && J < d.T && I < d.T ? PR + ((I * d.T + J) * d.NA + n) * d.KA + k : -1;
   }
   q -= PAc;
-  const int64_t blk = (int64_t)d.H * d.D + 2 * d.H + 1, blkc = (int64_t)d.H * d.Dc + 2 * d.H + 1;
-  const int64_t I = q / blkc, o = q % blkc;
+  const int blk = d.H * d.D + 2 * d.H + 1, blkc = d.H * d.Dc + 2 * d.H + 1;
+  const int I = q / blkc, o = q % blkc;
   if (I >= d.T) return -1;
-  const int64_t base = PR + PA + I * blk;
-  if (o >= (int64_t)d.H * d.Dc) return base + (int64_t)d.H * d.D + (o - (int64_t)d.H * d.Dc);   // b0, w1, b1
-  int v = (int)(o % d.Dc), col = -1;
+  const int base = PR + PA + I * blk;
+  if (o >= d.H * d.Dc) return base + d.H * d.D + (o - d.H * d.Dc);   // b0, w1, b1
+  int v = o % d.Dc, col = -1;
   if (v < d.NRc) {
     col = v < d.NR ? v : -1;
   } else if ((v -= d.NRc) < d.L3c * d.NAc) {
@@ -3751,7 +3864,7 @@ __global__ __launch_bounds__(256) void k_pad_params(PadDims d, int64_t Pc, const
                                                     float* __restrict__ pc) {
   const int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (q >= Pc) return;
-  const int64_t m = unpad_index(d, q);
+  const int64_t m = unpad_index(d, (int)q);
   pc[q] = m >= 0 ? p[m] : 0.f;
 }
 
@@ -3832,7 +3945,8 @@ static void allow_lds(K* k, size_t bytes) {
 // forward_waves 2 and 3 are the forward compiled for 3 and for 4 wavefronts
 // per SIMD (168 and 128 registers); the adjoint is compiled for 2 and 3
 template <class C, int W, int L>
-static void launch_forward_w(const FwdArgs& a, dim3 grid, hipStream_t st) {
+static void launch_forward_w(const FwdArgs& a, int blocks, hipStream_t st) {
+  const dim3 grid(blocks + (a.fl.n > 0 ? 1 : 0));   // an extra block for the flags
   const size_t lds = lds_forward<C, L>(a.H);
   if (a.tilt) {
     allow_lds(&k_forward<C, true, W, L>, lds);
@@ -3844,15 +3958,14 @@ static void launch_forward_w(const FwdArgs& a, dim3 grid, hipStream_t st) {
 }
 template <class C>
 static void launch_forward(const FwdArgs& a, int blocks, hipStream_t st, int waves, int lanes) {
-  if (lanes == 32) return launch_forward_w<C, 2, 32>(a, dim3(4 * blocks), st);
-  if (lanes == 16) return launch_forward_w<C, 2, 16>(a, dim3(2 * blocks), st);
-  const dim3 grid(blocks);
+  if (lanes == 32) return launch_forward_w<C, 2, 32>(a, 4 * blocks, st);
+  if (lanes == 16) return launch_forward_w<C, 2, 16>(a, 2 * blocks, st);
   if constexpr (C::FIXED_WAVES != 0)
-    launch_forward_w<C, C::FIXED_WAVES, kLPA>(a, grid, st);
+    launch_forward_w<C, C::FIXED_WAVES, kLPA>(a, blocks, st);
   else if (waves == 2)
-    launch_forward_w<C, 3, kLPA>(a, grid, st);
+    launch_forward_w<C, 3, kLPA>(a, blocks, st);
   else
-    launch_forward_w<C, 4, kLPA>(a, grid, st);
+    launch_forward_w<C, 4, kLPA>(a, blocks, st);
 }
 template <class C, bool kTri>
 static void launch_force_t(const ForceArgs& a, hipStream_t st, int lanes) {
@@ -4251,6 +4364,8 @@ struct Ctx {
   // the packed atoms of this call are in the workspace
   mutable bool packed = false;
   // a captured step whose neighbor build starts the replay (flags, step latch)
+  // a captured step whose forward collects the build's flags
+  mutable FlagArgs flag_words{};
   int* g_step = nullptr;
   int* g_cur = nullptr;
   // force cotangents of the caller (nep_vjp), packed with the atoms
@@ -4345,19 +4460,29 @@ void run_neighbors(const Ctx& c, nep_neighbors* nb, int32_t* flags, Prof* pr, bo
       NEP_LAUNCH(pr, "cell_neighbors", hipLaunchKernelGGL(k_cell_neighbors<false>, dim3(grid1(N, kNbrAPB)),
                                                           dim3(kNbrThreads), 0, c.st, a));
   }
+  const int nblk = grid1(N, kNbrAPB);
+  const bool by_type = with_order && N <= kTypeOrderAtoms;
+  // without an order launch behind it the build raises its flags itself, or in
+  // a captured step leaves their words to the forward
+  if (by_type && !c.g_step) a.bflags = nullptr;
   {
     auto* k = a.tilt ? (a.cells ? k_neighbors<true, true> : k_neighbors<true, false>)
                      : (a.cells ? k_neighbors<false, true> : k_neighbors<false, false>);
-    NEP_LAUNCH(pr, "neighbors", hipLaunchKernelGGL(k, dim3(grid1(N, kNbrAPB)), dim3(kNbrThreads), 0, c.st, a));
+    NEP_LAUNCH(pr, "neighbors", hipLaunchKernelGGL(k, dim3(nblk + (by_type ? c.L.nch : 0)), dim3(kNbrThreads), 0, c.st,
+                                                   a, nblk, order_args(c, nb)));
   }
   if (!with_order) return;   // the persistent step computes the species order itself
-  const FlagArgs fa{a.bflags, grid1(N, kNbrAPB), flags, c.g_step, c.g_cur};
-  NEP_LAUNCH(pr, "order",
-             hipLaunchKernelGGL(k_order, dim3(c.L.nch), dim3(1024), 0, c.st, order_args(c, nb), fa));
+  const FlagArgs fa{a.bflags, nblk, flags, c.g_step, c.g_cur};
+  if (!by_type)
+    NEP_LAUNCH(pr, "order",
+               hipLaunchKernelGGL(k_order, dim3(c.L.nch), dim3(1024), 0, c.st, order_args(c, nb), fa));
+  else if (c.g_step)
+    c.flag_words = fa;
 }
 
 FwdArgs fwd_args(const Ctx& c, const nep_neighbors* nb, const float* params) {
   FwdArgs a;
+  a.fl = c.flag_words;
   const nep_model* m = c.m;
   a.N = c.L.N;
   a.Npad = c.L.Npad;
