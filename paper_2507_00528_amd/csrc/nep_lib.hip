@@ -1279,8 +1279,43 @@ __global__ __launch_bounds__(kNbrThreads) void k_neighbors(NbrArgs a, int nblk, 
     if (!done) scan_keep<kTri>(c, t, jb, je, mybuf, nR, nA, angmask, keep);
     __syncthreads();   // a rescan below loads the tile again
   } else {
-    sweep(jb, je,
-          [&](const PosTile& t, int b2, int e2) { scan_keep<kTri>(c, t, b2, e2, mybuf, nR, nA, angmask, keep); });
+    // Structures that do not fit one tile together (one of nearly 1024 atoms
+    // and a neighbor): the first part tile by tile, the second from memory.
+    // Deciding every candidate in one part these few blocks took 33 us, the
+    // whole launch for 100 structures of 32 to 1024 atoms.
+    if (__syncthreads_and(len == 0 || (c.fast && len <= 256 * kNbrMasks))) {
+      uint32_t* gbuf = nbuf + (threadIdx.x & ~7);
+      int T = 0;
+      sweep(jb, je, [&](const PosTile& t, int b2, int e2) {
+        uint32_t mask[kNbrMasks];
+        scan_hits<kTri>(c, t, b2, e2, mask);
+        int n = 0;
+#pragma unroll
+        for (int k = 0; k < kNbrMasks; ++k) n += __popc(mask[k]);
+        int w = n;
+#pragma unroll
+        for (int d = 1; d < 8; d <<= 1) {
+          const int u = __shfl_up(w, d, 8);
+          if (s >= d) w += u;
+        }
+        const int tot = __shfl(w, 7, 8);
+        w += T - n;
+#pragma unroll
+        for (int k = 0; k < kNbrMasks; ++k)
+          for (uint32_t m = mask[k]; m; m &= m - 1u, ++w)
+            if (w < 8 * kNbrBuf) gbuf[kNbrThreads * (w >> 3) + (w & 7)] = (uint32_t)(b2 + 32 * k + __builtin_ctz(m));
+        T += tot;
+      });
+      done = T <= 8 * kNbrBuf;
+      if (done) {
+        lds_lane_exchange();
+        const PosTile all{a.pos, a.pos + a.N, a.pos + 2 * a.N, 0};
+        write_hits<kTri>(a, c, all, gbuf, T, s, totR, totA);
+      }
+    }
+    if (__syncthreads_or(!done))
+      sweep(done ? 0 : jb, done ? 0 : je,
+            [&](const PosTile& t, int b2, int e2) { scan_keep<kTri>(c, t, b2, e2, mybuf, nR, nA, angmask, keep); });
   }
   // inclusive prefix over the 8 lanes of the atom
   int pR = nR, pA = nA;
