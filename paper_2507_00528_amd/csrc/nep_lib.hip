@@ -1012,7 +1012,8 @@ constexpr int kOrdLds = (kOrdChunk / kWave + 1) * kOrdMaxT * kOrdBuckets + order
 
 // Chunk c with NT threads, which take its atoms NT at a time.  Rank of an atom
 // among the atoms of its key: lanes before it in its wavefront (one ballot per
-// distinct key), then the groups of 64 before it.
+// key bit; a loop over the distinct keys took 15 rounds), then the groups of
+// 64 before it.
 template <int NT>
 __device__ __forceinline__ void order_body(const OrderArgs& a, int c, int* lds) {
   constexpr int NR = kOrdChunk / NT, NWR = NT / kWave, NV = kOrdChunk / kWave;
@@ -1035,17 +1036,15 @@ __device__ __forceinline__ void order_body(const OrderArgs& a, int c, int* lds) 
   }
 #pragma unroll
   for (int r = 0; r < NR; ++r) {
-    rank[r] = 0;
     const int vw = r * NWR + wid;
-    unsigned long long rem = __ballot(key[r] >= 0);
-    while (rem) {
-      const int leader = __ffsll(rem) - 1;
-      const int kk = __shfl(key[r], leader, kWave);
-      const unsigned long long m = __ballot(key[r] == kk);
-      if (key[r] == kk) rank[r] = __popcll(m & below);
-      if (lane == leader) wcnt[vw * K + kk] = __popcll(m);
-      rem &= ~m;
+    unsigned long long m = __ballot(key[r] >= 0);   // lanes of this lane's key
+#pragma unroll
+    for (int bit = 0; (1 << bit) < kOrdMaxT * kOrdBuckets; ++bit) {
+      const unsigned long long b = __ballot((key[r] >> bit) & 1);
+      m &= (key[r] >> bit) & 1 ? b : ~b;
     }
+    rank[r] = __popcll(m & below);
+    if (key[r] >= 0 && rank[r] == 0) wcnt[vw * K + key[r]] = __popcll(m);
   }
   __syncthreads();
   for (int q = threadIdx.x; q < K; q += NT) {
@@ -1106,17 +1105,27 @@ __device__ __forceinline__ void order_body(const OrderArgs& a, int c, int* lds) 
     __syncthreads();
     return;
   }
-  for (int q = threadIdx.x; q < nb; q += NT) wcnt[q] = ord[q * kSegAlign] >= 0 ? a.cntA[ord[q * kSegAlign]] : -1;
-  __syncthreads();
+  int* place = wcnt + nb;
   for (int q = threadIdx.x; q < nb; q += NT) {
-    const int v = wcnt[q];
+    wcnt[q] = ord[q * kSegAlign] >= 0 ? a.cntA[ord[q * kSegAlign]] : -1;
+    place[q] = 0;
+  }
+  __syncthreads();
+  // a block's place: the blocks before it, a share of them per thread
+  constexpr int PT = NT / 128 > 0 ? NT / 128 : 1;
+  static_assert(order_blocks(kOrdMaxT) <= 128, "a thread group per share");
+  if ((int)threadIdx.x % 128 < nb) {
+    const int q = threadIdx.x % 128, v = wcnt[q];
     int r = 0;
-    for (int o = 0; o < nb; ++o) {
+    for (int o = threadIdx.x / 128; o < nb; o += PT) {
       const int x = wcnt[o];
       r += x > v || (x == v && o < q) ? 1 : 0;
     }
-    a.blist[c * nb + r] = v >= 0 ? (c * stride) / kSegAlign + q : -1;
+    atomicAdd(&place[q], r);
   }
+  __syncthreads();
+  for (int q = threadIdx.x; q < nb; q += NT)
+    a.blist[c * nb + place[q]] = wcnt[q] >= 0 ? (c * stride) / kSegAlign + q : -1;
   __syncthreads();
 }
 
