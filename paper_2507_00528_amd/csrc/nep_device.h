@@ -64,27 +64,7 @@ __device__ __forceinline__ float tanh_hw(float z) {
 
 // ------------------------------------------------------------------ radial
 // f_k(r) = (T_k(xi) + 1)/2 * f_c(r), xi = 2 (r/rc - 1)^2 - 1, and df_k/dr;
-// f_c(r) = (1 + cos(pi r / rc)) / 2.  Written as two FMAs per order (four
-// with the derivative).
-template <int K>
-__device__ __forceinline__ void radial_basis(float r, float inv_rc, float (&f)[K]) {
-  const float u = r * inv_rc;
-  const float x = u - 1.0f;
-  const float xi = fmaf(2.0f * x, x, -1.0f);
-  const float xi2 = 2.0f * xi;
-  const float hfc = fmaf(0.25f, cos_turns(0.5f * u), 0.25f);   // f_c / 2
-  float t0 = 1.0f, t1 = xi;
-  f[0] = 2.0f * hfc;
-  if (K > 1) f[1] = fmaf(xi, hfc, hfc);
-#pragma unroll
-  for (int k = 2; k < K; ++k) {
-    const float t2 = fmaf(xi2, t1, -t0);
-    f[k] = fmaf(t2, hfc, hfc);
-    t0 = t1;
-    t1 = t2;
-  }
-}
-
+// f_c(r) = (1 + cos(pi r / rc)) / 2.  Written as four FMAs per order.
 template <int K>
 __device__ __forceinline__ void radial_basis_d(float r, float inv_rc, float (&f)[K], float (&fp)[K]) {
   const float u = r * inv_rc;

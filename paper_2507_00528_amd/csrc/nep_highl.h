@@ -216,14 +216,16 @@ __device__ __forceinline__ void high_stage(const HighArgs& a, const HighGroup& g
     }
     const int k = gidx - base;
     const int i = a.order[gr.pa0 + u];
-    const int I = a.type[i], st = a.astruct[i];
+    const float4 pi = a.p4[i];
+    const int I = packed_type<T>(pi), st = a.astruct[i];
     const Cell cell = load_cell<kTri>(a.box, a.tilt, st);
     const size_t off = (size_t)i * a.nb.capA + k;
-    const PairGeom q = pair_geom<kTri>(a.nb.idxA[off], a.pos, a.N, a.pos[i], a.pos[a.N + i], a.pos[2 * a.N + i],
-                                       cell);
+    const uint32_t e = a.nb.idxA[off];
+    const float4 pj = a.p4[e >> 5];
+    const PairGeom q = packed_geom<kTri>(e, pj, pi.x, pi.y, pi.z, cell);
     float f[KA], fp[KA];
     radial_basis_d<KA>(q.r, a.inv_rcA, f, fp);
-    const int J = a.type[q.j];
+    const int J = packed_type<T>(pj);
     const float* cJ = a.cA + (size_t)(I * T + J) * NA * KA;
 #pragma unroll
     for (int n = 0; n < NA; ++n) {
@@ -300,14 +302,6 @@ __device__ __forceinline__ void high_walk(const HighArgs& a, const HighGroup& gr
 template <class C>
 __device__ __forceinline__ int high_row(int l, int n) {
   return C::NR + (l - 1) * C::NA + n;
-}
-
-// a descriptor-row value of this lane's degree, channel n
-template <class C>
-__device__ __forceinline__ float high_rowval(const float* __restrict__ rows, int Npad, int pa, const HighLane& h,
-                                            int n) {
-  const float v = rows[(size_t)high_row<C>(h.l, n) * Npad + pa];
-  return h.on ? v : 0.f;
 }
 
 // Stores the wave totals of the per-lane values vals[(l - 5) NA + n] to the
@@ -573,12 +567,12 @@ constexpr int high_table_stride(int w) { return (w + 63) / 64 * 64 + 8; }
 // neighbor j, geometry and the powers (x + iy)^k = R[k] + i I[k] of its
 // direction.
 struct HighPair {
-  int u, k, i, j, st;
+  int u, k, i, j, st, ti, tj;   // ti, tj: species
   float dx, dy, dz, r, ir, ux, uy, uz;
   float R[9], I[9];
 };
 
-template <bool kTri>
+template <int T, bool kTri>
 __device__ __forceinline__ HighPair high_pair(const HighArgs& a, const HighGroup& gr, int p) {
   HighPair g;
   int u = 0, base = 0;
@@ -593,9 +587,13 @@ __device__ __forceinline__ HighPair high_pair(const HighArgs& a, const HighGroup
   g.i = a.order[gr.pa0 + u];
   g.st = a.astruct[g.i];
   const Cell cell = load_cell<kTri>(a.box, a.tilt, g.st);
-  const PairGeom q = pair_geom<kTri>(a.nb.idxA[(size_t)g.i * a.nb.capA + g.k], a.pos, a.N, a.pos[g.i],
-                                     a.pos[a.N + g.i], a.pos[2 * a.N + g.i], cell);
+  const float4 pi = a.p4[g.i];
+  const uint32_t e = a.nb.idxA[(size_t)g.i * a.nb.capA + g.k];
+  const float4 pj = a.p4[e >> 5];
+  const PairGeom q = packed_geom<kTri>(e, pj, pi.x, pi.y, pi.z, cell);
   g.j = q.j;
+  g.ti = packed_type<T>(pi);
+  g.tj = packed_type<T>(pj);
   g.dx = q.dx;
   g.dy = q.dy;
   g.dz = q.dz;
@@ -691,10 +689,10 @@ __global__ __launch_bounds__(256) void k_high_force(HighArgs a) {
   for (int c0 = 0; c0 < gr.total; c0 += kWave) {
     const int p = c0 + lane;
     if (p < gr.total) {
-      const HighPair g = high_pair<kTri>(a, gr, p);
+      const HighPair g = high_pair<C::T, kTri>(a, gr, p);
       float f[KA], fp[KA];
       radial_basis_d<KA>(g.r, a.inv_rcA, f, fp);
-      const float* cJ = a.cA + (size_t)(a.type[g.i] * T + a.type[g.j]) * NA * KA;
+      const float* cJ = a.cA + (size_t)(g.ti * T + g.tj) * NA * KA;
       float gn[NA], gpn[NA];
 #pragma unroll
       for (int n = 0; n < NA; ++n) {
@@ -806,7 +804,7 @@ __global__ __launch_bounds__(kWave, C::NA <= 4 ? 3 : 1) void k_high_coef(HighArg
     const int p = c0 + lane;
     high_table_stage<C, true>(a, gr, tab, AS, tab + kAPW * AS);
     lds_lane_exchange();
-    const HighPair g = high_pair<kTri>(a, gr, p < gr.total ? p : 0);   // lanes past the chunk: pair 0, unused
+    const HighPair g = high_pair<C::T, kTri>(a, gr, p < gr.total ? p : 0);   // lanes past the chunk: pair 0, unused
     float f[KA], fp[KA];
     radial_basis_d<KA>(g.r, a.inv_rcA, f, fp);
     // t = (fbar_j - fbar_i) + Wbar d, as in the main adjoint
@@ -856,7 +854,7 @@ __global__ __launch_bounds__(kWave, C::NA <= 4 ? 3 : 1) void k_high_coef(HighArg
       rec[(S::RF + kk) * RS + lane] = f[kk];
       rec[(S::RFP + kk) * RS + lane] = fp[kk];
     }
-    rec[S::RJ * RS + lane] = __int_as_float(a.type[g.j]);
+    rec[S::RJ * RS + lane] = __int_as_float(g.tj);
     lds_lane_exchange();
     // four pairs per step, so their LDS reads are in flight together; pairs
     // past the chunk read pair 0 and add nothing

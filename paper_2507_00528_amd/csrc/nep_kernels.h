@@ -158,8 +158,7 @@ struct HighArgs {
   const int* astruct;
   const float* box;
   const float* tilt;
-  const float* pos;
-  const int* type;
+  const float4* p4;   // packed atoms
   PairLists nb;
   const float* cA;
   float* Sh;          // [Npad][YH][NA] sums S~ of the orthonormal harmonics

@@ -1444,27 +1444,6 @@ __device__ __forceinline__ Cell load_cell(const float* __restrict__ box, const f
   return c;
 }
 
-// d = x_j - x_i + sa a + sb b + sc c for the entry's image shift
-template <bool kTri>
-__device__ __forceinline__ PairGeom pair_geom(uint32_t e, const float* __restrict__ pos, int N, float xi, float yi,
-                                              float zi, const Cell& cl) {
-  PairGeom g;
-  g.j = (int)(e >> 5);
-  float sx, sy, sz;
-  decode_shift(e & 31u, sx, sy, sz);
-  g.dx = (pos[g.j] - xi) + sx * cl.Lx;
-  g.dy = (pos[N + g.j] - yi) + sy * cl.Ly;
-  g.dz = (pos[2 * N + g.j] - zi) + sz * cl.Lz;
-  if constexpr (kTri) {
-    g.dx += sy * cl.xy + sz * cl.xz;
-    g.dy += sz * cl.yz;
-  }
-  const float r2 = g.dx * g.dx + g.dy * g.dy + g.dz * g.dz;
-  g.inv_r = rsq_hw(r2);
-  g.r = r2 * g.inv_r;
-  return g;
-}
-
 // d = x_j - x_i + the entry's image shift, from the packed atom pj
 template <bool kTri>
 __device__ __forceinline__ PairGeom packed_geom(uint32_t e, const float4& pj, float xi, float yi, float zi,
@@ -1555,14 +1534,7 @@ struct HSplit {
   }
 };
 
-// B_q of compact entry i for this lane's harmonic group
-template <class HS, int Y>
-__device__ __forceinline__ float hsel(int g, int i, const float (&B)[Y]) {
-  const int q0 = HS::q(0, i), q1 = HS::q(1, i);
-  const float b0 = q0 >= 0 ? B[q0] : 0.f;
-  const float b1 = q1 >= 0 ? B[q1] : 0.f;
-  return g ? b1 : b0;
-}
+// C_lm of compact entry i for this lane's harmonic group
 template <class HS>
 __device__ __forceinline__ float csel(int g, int i) {
   const int q0 = HS::q(0, i), q1 = HS::q(1, i);
@@ -3670,11 +3642,6 @@ __device__ __forceinline__ void graph_head(int* flags, int* step, int* cur) {
 __global__ void k_graph_head(int* flags, int* step, int* cur) { graph_head(flags, step, cur); }
 
 
-__global__ void k_fill_i32(int* p, int n, int v) {
-  const int q = blockIdx.x * blockDim.x + threadIdx.x;
-  if (q < n) p[q] = v;
-}
-
 __global__ void k_fill_f32(float* p, int64_t n, float v) {
   const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (q < n) p[q] = v;
@@ -4166,8 +4133,6 @@ Resolved resolve(const nep_model* m) {
   return r;
 }
 
-const Ops* find_ops(const nep_model* m) { return resolve(m).o; }
-
 int model_valid(const nep_model* m) {
   if (!m) return NEP_ERR_ARG;
   if (m->n_types < 1 || m->n_types > 8 || m->n_rad < 1 || m->n_ang < 0 || m->k_rad < 1 || m->k_ang < 1 ||
@@ -4591,8 +4556,7 @@ HighArgs high_args(const Ctx& c, const nep_neighbors* nb, const float* params, c
   h.astruct = at<int>(c.ws, c.L.astruct);
   h.box = c.b->box;
   h.tilt = c.b->tilt;
-  h.pos = c.b->pos;
-  h.type = c.b->type;
+  h.p4 = at<float4>(c.ws, c.L.p4);
   h.nb = pair_lists(c, nb);
   h.cA = params + (size_t)m->n_types * m->n_types * m->n_rad * m->k_rad;
   h.Sh = at<float>(c.ws, c.L.Sh);
