@@ -315,8 +315,7 @@ int nep_train_step_graph_create(const nep_model* model, const nep_batch* batch, 
  *   gather_lanes    lanes per atom of the force pass, 8 or 16 [16]
  *   forward_waves   forward kernel compiled for 3 wavefronts per SIMD (2) or for 4,
  *                   with fewer registers (3) [3; 2 with degrees l > 4]
- *   adjoint_waves   wavefronts per SIMD the adjoint kernel is compiled for, 2 or 3
- *                   [3; 2 with degrees l > 4]
+ *   adjoint_waves   wavefronts per SIMD the adjoint kernel is compiled for, 2 or 3 [3]
  *   reverse_branch  0, 1 or 2, without effect: the reverse index it placed is
  *                   no longer built (the force pass finds partners itself)
  * A value out of range is NEP_ERR_ARG. */

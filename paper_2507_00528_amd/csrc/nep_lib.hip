@@ -4351,7 +4351,8 @@ struct Tune {
 };
 
 Tune default_tune(const Ops* o) {
-  return Tune{0, kOSBlocksW, kOSBlocksC, kPRChunks, kCellMinAtoms, kForceLPA, o->YH > 0 ? 2 : 3, o->YH > 0 ? 2 : 3};
+  // degrees l > 4: forward 2 (at 3, 1 us slower of 230), adjoint 3 (at 2, 7 us slower)
+  return Tune{0, kOSBlocksW, kOSBlocksC, kPRChunks, kCellMinAtoms, kForceLPA, o->YH > 0 ? 2 : 3, 3};
 }
 
 struct Ctx {

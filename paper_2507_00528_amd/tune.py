@@ -159,12 +159,13 @@ def tune_workload(name, reps, log):
     space = dict(SPACE)
     if dev.max_atoms < 512:          # no structure reaches any cell-list threshold tried
         space.pop("cell_min_atoms")
-    if sizes.l3 > 4:                 # the library's adjoint default with degrees l > 4
-        space["adjoint_waves"] = [2, 3]
+    if sizes.l3 > 4:                 # the library's forward default with degrees l > 4
+        space["forward_waves"] = [2, 3]
     log(f"[tune] {name}: {S} structures, {N} atoms, class {size_class(model, dev)}")
     t0 = time.time()
     best, best_ms, base_ms, table = search(
-        lambda c: time_graph(nep, model, dev, labels, (1.0, 1.0, 0.1), theta, N, S, c, reps, stream), space,
+        lambda c: time_graph(nep, model, dev, labels, (1.0, 1.0, 0.1), theta, N, S, c, reps, stream, warmup=100),
+        space,
         log=log)
     log(f"[tune] {name}: default {base_ms:.4f} ms -> tuned {best_ms:.4f} ms {nondefault(best, space)} "
         f"({len(table)} settings, {time.time() - t0:.0f} s)")
