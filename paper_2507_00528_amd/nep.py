@@ -294,8 +294,8 @@ NEP_FLAG_BARRIER = 64
 class TrainStepGraph:
     """One captured training step (neighbors, forward, loss, adjoint, Adam);
     replays advance the device step counter.  With cached_neighbors the graph
-    skips the neighbor build and reuses the lists (and the species order in ws) from an earlier build_neighbors call.  With
-    persistent everything after the neighbor build runs as one persistent
+    skips the neighbor build and reuses the lists (and the species order in
+    ws) from an earlier build_neighbors call.  With persistent everything after the neighbor build runs as one persistent
     launch (NEP_GRAPH_PERSISTENT).  tuning: launch choices (nep_tuning) as a
     dict, None for the defaults, or "cache" for the autotuner's choice for
     this model and batch size class (defaults when it has none)."""
