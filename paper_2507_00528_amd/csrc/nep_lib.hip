@@ -3413,10 +3413,12 @@ __global__ __launch_bounds__(256, 3) void k_outer_reduce(OuterReduceArgs a) {
 // lane sums.  Parameter layout: c^R [T][T][NR][KR], c^A [T][T][NA][KA], then
 // per species W0 [H][D], b0 [H], w1 [H], b1.
 // ==================================================================== Adam
+// One parameter's update.  The fused forms are written out, so that the
+// captured step and the eager one round alike.
 __device__ __forceinline__ void adam_update(float& th, float& m, float& v, float g, float lr, float b1, float b2,
                                             float eps, float c1, float c2) {
-  m = b1 * m + (1.0f - b1) * g;
-  v = b2 * v + (1.0f - b2) * g * g;
+  m = fmaf(1.0f - b1, g, b1 * m);
+  v = fmaf((1.0f - b2) * g, g, b2 * v);
   th -= lr * (m / c1) / (sqrtf(v / c2) + eps);
 }
 __device__ __forceinline__ void adam_one(float* __restrict__ th, float* __restrict__ m, float* __restrict__ v,
