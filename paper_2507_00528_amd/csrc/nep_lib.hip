@@ -905,6 +905,12 @@ constexpr int kOrdBuckets = 64;
 constexpr int kOrdMaxT = 4;    // species of the compiled shapes
 constexpr int kSegAlign = 32;  // species segments start on multiples of the atoms per block
 __host__ __device__ constexpr int order_stride(int T) { return kOrdChunk + T * kSegAlign; }
+// Positions that chunk c writes: its own and, by the last one, the rest of the
+// array, whose size is rounded up past the chunks (-1 there: the kernels of
+// degrees l > 4 read every position).
+__device__ __forceinline__ int order_len(int c, int nch, int T, int Npad) {
+  return c + 1 < nch ? order_stride(T) : Npad - c * order_stride(T);
+}
 
 __device__ __forceinline__ int order_key(int t, int T, int nA) {
   if (t < 0 || t >= T) return -1;
@@ -912,7 +918,7 @@ __device__ __forceinline__ int order_key(int t, int T, int nA) {
 }
 
 struct OrderArgs {
-  int N, Npad, T, nch;
+  int N, Npad, T, nch;   // Npad: positions of the array, at least those of the chunks
   const int* type;
   const int* cntA;
   int* seg;     // [nch][T][2] species segment start and count
@@ -947,12 +953,12 @@ __device__ __forceinline__ void type_order(const OrderArgs& a, int c, int* lds) 
   int* ord = key + kOrdChunk;                // [stride]
   const int T = a.T, stride = order_stride(T);
   const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
-  const int n = min(a.N - c * kOrdChunk, kOrdChunk), len = min(stride, a.Npad - c * stride);
+  const int n = min(a.N - c * kOrdChunk, kOrdChunk), len = order_len(c, a.nch, T, a.Npad);
   const int* type = a.type + c * kOrdChunk;
   // loops of the chunk's own atoms, not unrolled: a block runs this once, with
   // a cold instruction cache
   int next = type[min((int)threadIdx.x, n - 1)];
-  for (int q = threadIdx.x; q < len; q += 256) ord[q] = -1;
+  for (int q = threadIdx.x; q < stride; q += 256) ord[q] = -1;
 #pragma unroll 1
   for (int q = threadIdx.x; q - lane < n; q += 256) {
     const int t = q < n && next >= 0 && next < T ? next : -1;
@@ -1000,10 +1006,10 @@ __device__ __forceinline__ void type_order(const OrderArgs& a, int c, int* lds) 
   }
   __syncthreads();
 #pragma unroll 1
-  for (int q = threadIdx.x; q < len; q += 256) a.order[(size_t)c * stride + q] = ord[q];
+  for (int q = threadIdx.x; q < len; q += 256) a.order[(size_t)c * stride + q] = q < stride ? ord[q] : -1;
   const int nb = order_blocks(T);
   for (int q = threadIdx.x; q < nb; q += 256)
-    a.blist[c * nb + q] = q * kSegAlign < len && ord[q * kSegAlign] >= 0 ? (c * stride) / kSegAlign + q : -1;
+    a.blist[c * nb + q] = ord[q * kSegAlign] >= 0 ? (c * stride) / kSegAlign + q : -1;
 }
 
 // LDS of order_body (ints): counts per 64 atoms and key, key offsets, the
@@ -1093,8 +1099,8 @@ __device__ __forceinline__ void order_body(const OrderArgs& a, int c, int* lds) 
       ord[s0 + off[key[r]] + wcnt[(r * NWR + wid) * K + key[r]] + rank[r]] = c * kOrdChunk + r * NT + threadIdx.x;
     }
   __syncthreads();
-  const int len = min(stride, a.Npad - c * stride);
-  for (int q = threadIdx.x; q < len; q += NT) a.order[(size_t)c * stride + q] = ord[q];
+  const int len = order_len(c, a.nch, T, a.Npad);
+  for (int q = threadIdx.x; q < len; q += NT) a.order[(size_t)c * stride + q] = q < stride ? ord[q] : -1;
   // blocks by their first atom's pair count (its largest), descending; up to 4
   // chunks give every block a CU of its own, so their order does not matter
   // (and sorting them took 2 us of a 180-atom MD step)
