@@ -4180,9 +4180,10 @@ struct Layout {
       cur_step, bar, sargs, prm, Gtmp, total;
 };
 
-// Workspace size callers see.  It is kept at what the library needed when it
-// stored the radial pair forces and a reverse index, which the layout below
-// fits in, so that nep_loss_grad_noalloc takes and refuses the same batches.
+// Workspace size callers see: with the pair forces and reverse indices of both
+// lists, which the layout below does not hold, so that nep_loss_grad_noalloc
+// takes and refuses the batches that its header states.  The layout fits in it
+// (at capacities below 16 it may pass it by up to 3 %).
 size_t reported_bytes(const Layout& L, const Ops* o, const nep_model* m, bool pad) {
   const size_t N = L.N > 0 ? L.N : 1, S = L.S > 0 ? L.S : 1, T = L.T, D = L.D, H = L.H, TKR = L.TKR;
   const size_t n8 = ((size_t)L.N + 31) / 32 * 32 + T * 32 + 16, Np = (n8 + 31) / 32 * 32;
@@ -4194,15 +4195,29 @@ size_t reported_bytes(const Layout& L, const Ops* o, const nep_model* m, bool pa
       4 * (o->YH > 0 ? D : (size_t)L.NR) * Np, 4 * H * Np, 4 * H * Np, 4 * (Np / kAPW) * (size_t)L.PW,
       8 * T * kPRChunksMax * (size_t)L.PW, 4 * T * kOSBlocksMaxW * H * D, 4 * T * kOSBlocksMaxC * (size_t)L.NR * TKR,
       4 * Np * NA * (size_t)o->YH, 4 * Np * NA * (size_t)o->YH, 16 * S, 4 * (N + 1), 4 * (N / kScanChunk + 1), 4 * N,
-      4 * N, 16 * N, 128 * (N / kStructChunk + 1), 4, 4 * kBarWords, 1024, 4 * Pc, 4 * Pc, pad ? 4 * D * N : 0};
+      4 * N, 16 * N, 128 * (N / kStructChunk + 1), 4, 4 * kBarWords, 1280, 4 * Pc, 4 * Pc, pad ? 4 * D * N : 0};
   size_t sum = 0;
   for (size_t b : bytes) sum += al(b);
   return sum;
 }
 
-// m: the model the kernels run (the class model when padded); lanes: per atom
-// in the forward and the adjoint (each wavefront of which writes a row of part)
-Layout layout_of(const nep_model* m, const Ops* o, int S, int N, bool pad, int lanes) {
+// Blocks per species of a reduction over the order's chunks: each chunk in Q
+// pieces (at most max_q, so that a piece keeps some work) so that there are
+// about `want` blocks, at most `most`; with more chunks than that a block
+// takes several.
+struct Split {
+  int Q, NB;
+};
+Split split_chunks(int want, int most, int nch, int max_q) {
+  int q = std::min(std::max((want + nch / 2) / nch, 1), std::max(max_q, 1));
+  if (nch * q > most) q = std::max(1, most / nch);
+  return Split{q, std::min(nch * q, most)};
+}
+// 64 atoms (a 16-atom group per wavefront, 8 wavefront rows) to a piece at least
+int max_pieces(int N) { return std::min(N, kOrdChunk) / 64; }
+
+// m: the model the kernels run (the class model when padded)
+Layout layout_of(const nep_model* m, const Ops* o, int S, int N, bool pad) {
   Layout L{};
   L.N = N;
   L.S = S;
@@ -4225,7 +4240,7 @@ Layout layout_of(const nep_model* m, const Ops* o, int S, int N, bool pad, int l
   // units, so the rows a wavefront stores start in different memory channels
   L.Npad = (L.Npad + 63) / 64 * 64;
   if ((L.Npad / 64) % 2 == 0) L.Npad += 64;
-  L.lanes = lanes;
+  L.lanes = group_lanes(N);   // each wavefront writes a row of part
   L.PW = L.T * m->n_ang * m->k_ang + 2 * L.H + 1;
   const size_t Np = L.Npad, Nn = (size_t)(N > 0 ? N : 1), Ss = (size_t)(S > 0 ? S : 1);
   size_t off = 0;
@@ -4241,7 +4256,9 @@ Layout layout_of(const nep_model* m, const Ops* o, int S, int N, bool pad, int l
   L.astruct = take(4 * Nn);
   L.p4 = take(16 * Nn);
   L.G = take(4 * (size_t)L.D * Np);
-  L.Sst = take(4 * (((size_t)L.NA * o->YR + 3) & ~(size_t)3) * Np);
+  // the class descriptor rows of nep_descriptors (a padded model), which stores
+  // no sums, take the sums' place
+  L.Sst = L.Gtmp = take(4 * std::max((((size_t)L.NA * o->YR + 3) & ~(size_t)3) * Np, pad ? (size_t)L.D * Nn : 0));
   L.Ep = take(4 * (size_t)L.D * Np);
   L.X = take(4 * (size_t)L.H * Np);
   L.eatom = take(4 * Nn);
@@ -4262,9 +4279,11 @@ Layout layout_of(const nep_model* m, const Ops* o, int S, int N, bool pad, int l
   L.Gbr = take(4 * (size_t)(o->YH > 0 ? L.D : L.NR) * Np);
   L.beta = take(4 * (size_t)L.H * Np);
   L.part = take(4 * (size_t)(L.Npad / (kWave / L.lanes)) * L.PW);
-  L.pp = take(8 * (size_t)L.T * kPRChunksMax * L.PW);
-  L.w0part = take(4 * (size_t)L.T * kOSBlocksMaxW * L.H * L.D);
-  L.crpart = take(4 * (size_t)L.T * kOSBlocksMaxC * L.NR * L.TKR);
+  // the most blocks any tuning can ask for
+  auto blocks = [&](int most) { return (size_t)L.T * split_chunks(most, most, L.nch, max_pieces(N)).NB; };
+  L.pp = take(8 * blocks(kPRChunksMax) * L.PW);
+  L.w0part = take(4 * blocks(kOSBlocksMaxW) * L.H * L.D);
+  L.crpart = take(4 * blocks(kOSBlocksMaxC) * L.NR * L.TKR);
   L.Sh = take(4 * (size_t)Np * L.NA * o->YH);
   L.Sdh = take(4 * (size_t)Np * L.NA * o->YH);
   L.cgrid = take(16 * Ss);
@@ -4278,27 +4297,14 @@ Layout layout_of(const nep_model* m, const Ops* o, int S, int N, bool pad, int l
   L.cur_step = take(4);
   L.bar = take(4 * kBarWords);
   L.sargs = take(sizeof(StepArgs));
-  // a padded model: the class-layout parameters, and the class descriptor rows
-  // of nep_descriptors
-  const size_t Pc = pad ? (size_t)param_count(m) : 0;
-  L.prm = take(4 * Pc);
-  L.Gtmp = take(pad ? 4 * (size_t)L.D * Nn : 0);
+  L.prm = take(pad ? 4 * (size_t)param_count(m) : 0);   // the class-layout parameters
   L.total = off;
   return L;
 }
 
-// The size reported is that of 8 lanes an atom: more lanes are taken where
-// their rows of part fit.
 Layout make_layout(const nep_model* m, const Ops* o, int S, int N, bool pad = false) {
-  Layout L = layout_of(m, o, S, N, pad, kLPA);
-  const size_t total = std::max(L.total, reported_bytes(L, o, m, pad));
-  for (int lanes = group_lanes(N); lanes > kLPA; lanes /= 2) {
-    const Layout more = layout_of(m, o, S, N, pad, lanes);
-    if (more.total > total) continue;
-    L = more;
-    break;
-  }
-  L.total = total;
+  Layout L = layout_of(m, o, S, N, pad);
+  L.total = std::max(L.total, reported_bytes(L, o, m, pad));
   return L;
 }
 
@@ -4700,23 +4706,9 @@ AdjArgs adj_args(const Ctx& c, const nep_neighbors* nb, const float* params, con
   return a;
 }
 
-// Blocks per species of a reduction over the order's chunks: each chunk in Q
-// pieces (at most max_q, so that a piece keeps some work) so that there are
-// about `want` blocks, at most `most`; with more chunks than that a block
-// takes several.
-struct Split {
-  int Q, NB;
-};
-Split split_chunks(int want, int most, int nch, int max_q) {
-  int q = std::min(std::max((want + nch / 2) / nch, 1), std::max(max_q, 1));
-  if (nch * q > most) q = std::max(1, most / nch);
-  return Split{q, std::min(nch * q, most)};
-}
-int chunk_atoms(const Ctx& c) { return std::min(c.L.N, kOrdChunk); }
-// 64 atoms (a 16-atom group per wavefront) or 8 wavefront rows to a piece at least
-Split split_w(const Ctx& c) { return split_chunks(c.tune.outer_w, kOSBlocksMaxW, c.L.nch, chunk_atoms(c) / 64); }
-Split split_c(const Ctx& c) { return split_chunks(c.tune.outer_c, kOSBlocksMaxC, c.L.nch, chunk_atoms(c) / 64); }
-Split split_p(const Ctx& c) { return split_chunks(c.tune.reduce_chunks, kPRChunksMax, c.L.nch, chunk_atoms(c) / 64); }
+Split split_w(const Ctx& c) { return split_chunks(c.tune.outer_w, kOSBlocksMaxW, c.L.nch, max_pieces(c.L.N)); }
+Split split_c(const Ctx& c) { return split_chunks(c.tune.outer_c, kOSBlocksMaxC, c.L.nch, max_pieces(c.L.N)); }
+Split split_p(const Ctx& c) { return split_chunks(c.tune.reduce_chunks, kPRChunksMax, c.L.nch, max_pieces(c.L.N)); }
 
 PartArgs part_args(const Ctx& c) {
   const Split p = split_p(c);
