@@ -3932,6 +3932,7 @@ struct Ops {
   int KP;   // words of a radial force coefficient row
   size_t (*lds_fwd)(int);
   size_t (*lds_adj)(int);
+  size_t (*lds_adj16)(int);   // the adjoint at 16 lanes an atom
   void (*high)(HighKernel, const HighArgs&, dim3, hipStream_t);   // null without degrees l > 4
   // persistent step (null with degrees l > 4): launch, and resident blocks per CU
   void (*step)(const StepArgs*, int, size_t, hipStream_t);
@@ -4075,7 +4076,8 @@ static Ops make_ops() {
     occ = &step_occupancy<C>;
   }
   return Ops{C::T, C::NR, C::NA, C::KR, C::KA, C::L3, C::L4, C::L5, C::D, C::Y, C::PS, C::YH,
-             HRow<C::LMAX>::YR, &launch_forward<C>, &launch_force<C>, &launch_adjoint<C>, HRad<C>::KP, &lds_forward<C, kLPA>, &lds_adjoint<C, kLPA>, high, step, occ,
+             HRow<C::LMAX>::YR, &launch_forward<C>, &launch_force<C>, &launch_adjoint<C>, HRad<C>::KP, &lds_forward<C, kLPA>, &lds_adjoint<C, kLPA>,
+             &lds_adjoint<C, 16>, high, step, occ,
              C::FIXED_WAVES != 0};
 }
 
@@ -4170,8 +4172,13 @@ size_t al(size_t x) { return (x + 255) & ~(size_t)255; }
 // step of the 3/4/5-body model in us with 8 / 16 / 32 lanes: 512 atoms
 // 91.5 / 72.7 / 68.1, 2048 atoms 94.4 / 76.4 / 73.4, 3072 atoms 96.5 / 80.1 /
 // 83.8, 8192 atoms 105.1 / 94.6 / 115.5, 12288 atoms 112.3 / 122.4 / 142.7.
+// A model whose rows of 8 atoms a wavefront pass the LDS in the adjoint (four
+// species, degrees up to 8, hidden 252 to 256) takes 16 lanes at any size.
 constexpr int kLanes32Atoms = 2048, kLanes16Atoms = 8192;
-int group_lanes(int N) { return N <= kLanes32Atoms ? 32 : N <= kLanes16Atoms ? 16 : kLPA; }
+int group_lanes(const Ops* o, int H, int N) {
+  if (N <= kLanes32Atoms) return 32;
+  return N <= kLanes16Atoms || o->lds_adj(H) > kMaxLds ? 16 : kLPA;
+}
 
 struct Layout {
   int N, S, T, D, Y, H, NR, TKR, Npad, lanes, nch, PW, NA, capR, capA;
@@ -4240,7 +4247,7 @@ Layout layout_of(const nep_model* m, const Ops* o, int S, int N, bool pad) {
   // units, so the rows a wavefront stores start in different memory channels
   L.Npad = (L.Npad + 63) / 64 * 64;
   if ((L.Npad / 64) % 2 == 0) L.Npad += 64;
-  L.lanes = group_lanes(N);   // each wavefront writes a row of part
+  L.lanes = group_lanes(o, L.H, N);   // each wavefront writes a row of part
   L.PW = L.T * m->n_ang * m->k_ang + 2 * L.H + 1;
   const size_t Np = L.Npad, Nn = (size_t)(N > 0 ? N : 1), Ss = (size_t)(S > 0 ? S : 1);
   size_t off = 0;
@@ -4827,7 +4834,7 @@ int model_supported(const nep_model* m, Resolved* out = nullptr) {
   if (rc) return rc;
   const Resolved r = resolve(m);
   if (!r.o) return NEP_ERR_ARG;
-  if (r.o->lds_adj(m->hidden) > kMaxLds || r.o->lds_fwd(m->hidden) > kMaxLds) return NEP_ERR_ARG;
+  if (r.o->lds_adj16(m->hidden) > kMaxLds || r.o->lds_fwd(m->hidden) > kMaxLds) return NEP_ERR_ARG;
   if (out) *out = r;
   return NEP_OK;
 }

@@ -1,8 +1,11 @@
-"""The workspace size callers allocate (nep_loss_grad_noalloc
+"""What the library takes: hidden sizes up to 256 in every compiled shape and
+size class, and the workspace size callers allocate (nep_loss_grad_noalloc
 compares it with its 64 MiB scratch) for models of ordinary capacities: the
 sum of the arrays of both lists' pair forces and reverse indices, however the
 library lays out what it keeps.  Host functions only, no GPU."""
 import random
+
+import pytest
 
 from paper_2507_00528_amd import nep
 
@@ -14,6 +17,11 @@ PADDED = [(T, 12, 8, 12, 12, l, 2, 1) for l in (4, 8) for T in (1, 2, 3, 4)] + [
 
 def _model(shape, hidden, cap_rad=64, cap_ang=32):
     return nep.Model(*shape, hidden, 6.0, 4.0, cap_rad, cap_ang)
+
+
+@pytest.mark.parametrize("shape", EXACT + PADDED)
+def test_every_hidden_size_runs(shape):
+    assert [H for H in range(1, 257) if not nep.model_supported(_model(shape, H))] == []
 
 
 def _bytes(shape, hidden, cap_rad, cap_ang, S, N):
@@ -42,7 +50,7 @@ def _bytes(shape, hidden, cap_rad, cap_ang, S, N):
 def test_workspace_size_of_ordinary_capacities():
     rng = random.Random(5)
     for _ in range(4000):
-        shape, H = rng.choice(EXACT + PADDED), rng.choice([1, 8, 16, 30, 50, 100, 250])
+        shape, H = rng.choice(EXACT + PADDED), rng.choice([1, 8, 16, 30, 50, 100, 256])
         cap_rad = rng.choice([16, 32, 64, 200])
         cap_ang = min(cap_rad, rng.choice([8, 16, 32]))
         N = int(2 ** rng.uniform(0, 22))
