@@ -104,7 +104,7 @@ def search(measure, space=None, min_gain=0.01, max_passes=3, log=None):
 
 def nondefault(choices: dict, space=None) -> dict:
     """Only the choices that differ from the defaults (the first value of each
-    choice in `space`), the form the cache keeps."""
+    choice in `space`), the form the cache keeps its measurements in."""
     d = {k: v[0] for k, v in (space or SPACE).items()}
     return {k: v for k, v in choices.items() if d.get(k, DEFAULTS.get(k)) != v}
 
@@ -169,7 +169,8 @@ def tune_workload(name, reps, log):
         log=log)
     log(f"[tune] {name}: default {base_ms:.4f} ms -> tuned {best_ms:.4f} ms {nondefault(best, space)} "
         f"({len(table)} settings, {time.time() - t0:.0f} s)")
-    return size_class(model, dev), {"tuning": nondefault(best, space), "ms": best_ms, "default_ms": base_ms,
+    # in full: also where the defaults win, the choices that were found best are what a graph runs
+    return size_class(model, dev), {"tuning": best, "ms": best_ms, "default_ms": base_ms,
                                     "workload": name, "atoms": N, "structures": S,
                                     "measurements": [{"choices": nondefault(c, space), "ms": ms} for c, ms in table]}
 
