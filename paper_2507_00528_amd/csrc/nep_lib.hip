@@ -8,6 +8,7 @@
 #include <cstring>
 #include <mutex>
 #include <new>
+#include <type_traits>
 #include <vector>
 
 #include "../../include/nep.h"
@@ -1679,6 +1680,61 @@ __device__ __forceinline__ int pair_slot(const PairStream<L>& st, int p) {
   return u;
 }
 
+// The adjoint's tangent sums in wavefronts of many pairs an atom.  An atom's own
+// L lanes would run through up to 64 pairs of a chunk while the lanes of the
+// atoms without pairs in it wait; so 2^k groups of L lanes an atom take every
+// 2^k-th of its pairs, and their sums are added and sent to the atom's own
+// lanes.  Adjoint of 90,000 atoms in us without and with it: 22 pairs an atom
+// 234 / 234, 28 298 / 278, 42 459 / 392, 75 908 / 669; at 19 and fewer, below
+// the line, the same kernel.  (In the forward, whose sums are half as many, it
+// spilled at four wavefronts per SIMD: 314 -> 318 us of a step at 7 pairs; with
+// degrees l > 4, whose adjoint spills as it is, 570 -> 585 us at 7 pairs.)
+constexpr int kSharePairs = 192;   // pairs of a wavefront
+template <int L>
+struct ChunkShare {
+  int k;       // wave-uniform
+  int t, t1;   // this lane's first pair and the end of its atom's, in the chunk
+  int src;     // lane that holds this atom's sums, -1: the chunk has no pair of it
+};
+template <int L>
+__device__ __forceinline__ ChunkShare<L> chunk_share(const PairStream<L>& ps, int c0, const float* slots, int words) {
+  constexpr int APW = kWave / L;
+  const int lane = threadIdx.x & (kWave - 1), slot = lane / L;
+  const int u0 = pair_slot(ps, c0), u1 = pair_slot(ps, min(c0 + kWave, ps.total) - 1);
+  ChunkShare<L> c;
+  c.k = 0;
+#pragma unroll
+  for (int k = 1; (1 << k) <= APW; ++k) c.k += (u1 - u0 + 1) << k <= APW ? 1 : 0;
+  const int v = u0 + (slot >> c.k), u = min(v, APW - 1);
+  const int lo = __float_as_int(slots[u * words + kSlotBase]);
+  const int hi = u + 1 < APW ? __float_as_int(slots[(u + 1) * words + kSlotBase]) : ps.total;
+  c.t = max(lo - c0, 0) + (slot & ((1 << c.k) - 1));
+  c.t1 = v <= u1 ? min(hi - c0, kWave) : 0;
+  c.src = slot >= u0 && slot <= u1 ? ((slot - u0) << c.k) * L + lane % L : -1;
+  return c;
+}
+// adds the groups' partial sums v to the sums S of the atom's own lanes
+template <int L, int R, int N>
+__device__ __forceinline__ void chunk_add(const ChunkShare<L>& c, float (&v)[R][N], float (&S)[R][N]) {
+  // lane bits 3, 4, 5 as far as they tell the groups of an atom apart
+  constexpr int bit0 = L == 8 ? 3 : L == 16 ? 4 : 5;
+  auto each = [&](auto&& f) {
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+      for (int n = 0; n < N; ++n) f(v[r][n], S[r][n]);
+  };
+  if constexpr (bit0 <= 3)
+    if (c.k > 0) each([](float& x, float&) { x += dpp<kDppRowRor8>(x); });
+  if constexpr (bit0 <= 4)
+    if (c.k > 4 - bit0) each([](float& x, float&) { x = xor16_sum(x); });
+  if (c.k > 5 - bit0) each([](float& x, float&) { x = xor32_sum(x); });
+  each([&](float& x, float& y) {
+    x = __shfl(x, max(c.src, 0), kWave);
+    y += c.src >= 0 ? x : 0.f;
+  });
+}
+
 template <bool kTri>
 __device__ __forceinline__ void slot_store(float* sl, int i, float x, float y, float z, const Cell& c, int base) {
   *reinterpret_cast<float4*>(sl + kSlotX) = make_float4(x, y, z, __int_as_float(i));
@@ -2825,67 +2881,86 @@ __device__ __forceinline__ void adjoint_body(const AdjArgs& a, int b, float* lds
       for (int e = 0; e < NEH; ++e)
 #pragma unroll
         for (int j = 0; j < NAH; ++j) Sd[gg][e][j] = 0.f;
-    for (int c0 = 0; c0 < ps.total; c0 += kWave) {
-      const int p = c0 + lane;
-      const bool on = p < ps.total;
-      float B[Y], gbt[Y];
-      float* rec = buf + lane * RS;
-      if (on) {
-        const float* sl = slots + pair_slot(ps, p) * kAdjSlot;
-        const StreamPair sp = stream_pair<T, kTri>(sl, p, a.nb, a.p4);
-        const PairTangent t = pair_tangent(sp.q, sl, a.fb4[sp.q.j]);
-        float f[KA], fp[KA];
-        radial_cheb_d<KA>(sp.q.r, a.inv_rcA, f, fp);
-        const float* cJ = ctab + sp.J * NA * CT::KAP;
-#pragma unroll
-        for (int n = 0; n < NA; ++n) {
-          float s0 = 0.f, s1 = 0.f;
-#pragma unroll
-          for (int kk = 0; kk < KA; ++kk) {
-            const float c = cJ[n * CT::KAP + kk];
-            s0 = fmaf(c, f[kk], s0);
-            s1 = fmaf(c, fp[kk], s1);
-          }
-          rec[2 * n] = s0;
-          rec[2 * n + 1] = s1 * t.dt;
-        }
-        harm_val<LM>(t.ux, t.uy, t.uz, B);
-        // grad B . t = grad b(u) . (t - (u.t) u) / r
-        harm_dir<LM>(t.ux, t.uy, t.uz, t.wx, t.wy, t.wz, gbt);
-      }
-#pragma unroll
-      for (int gg = 0; gg < 2; ++gg) {
+    auto tangent = [&](auto shared) {
+      for (int c0 = 0; c0 < ps.total; c0 += kWave) {
+        const int p = c0 + lane;
+        const bool on = p < ps.total;
+        float B[Y], gbt[Y];
+        float* rec = buf + lane * RS;
         if (on) {
+          const float* sl = slots + pair_slot(ps, p) * kAdjSlot;
+          const StreamPair sp = stream_pair<T, kTri>(sl, p, a.nb, a.p4);
+          const PairTangent t = pair_tangent(sp.q, sl, a.fb4[sp.q.j]);
+          float f[KA], fp[KA];
+          radial_cheb_d<KA>(sp.q.r, a.inv_rcA, f, fp);
+          const float* cJ = ctab + sp.J * NA * CT::KAP;
 #pragma unroll
-          for (int e = 0; e < YG; ++e) {
-            const int q = HS::q(gg, e);
-            rec[2 * NA + 2 * e] = q >= 0 ? B[q >= 0 ? q : 0] : 0.f;
-            rec[2 * NA + 2 * e + 1] = q >= 0 ? gbt[q >= 0 ? q : 0] : 0.f;
+          for (int n = 0; n < NA; ++n) {
+            float s0 = 0.f, s1 = 0.f;
+#pragma unroll
+            for (int kk = 0; kk < KA; ++kk) {
+              const float c = cJ[n * CT::KAP + kk];
+              s0 = fmaf(c, f[kk], s0);
+              s1 = fmaf(c, fp[kk], s1);
+            }
+            rec[2 * n] = s0;
+            rec[2 * n + 1] = s1 * t.dt;
           }
+          harm_val<LM>(t.ux, t.uy, t.uz, B);
+          // grad B . t = grad b(u) . (t - (u.t) u) / r
+          harm_dir<LM>(t.ux, t.uy, t.uz, t.wx, t.wy, t.wz, gbt);
         }
-        lds_lane_exchange();
-        const int t1 = min(ps.hi - c0, kWave);
+#pragma unroll
+        for (int gg = 0; gg < 2; ++gg) {
+          if (on) {
+#pragma unroll
+            for (int e = 0; e < YG; ++e) {
+              const int q = HS::q(gg, e);
+              rec[2 * NA + 2 * e] = q >= 0 ? B[q >= 0 ? q : 0] : 0.f;
+              rec[2 * NA + 2 * e + 1] = q >= 0 ? gbt[q >= 0 ? q : 0] : 0.f;
+            }
+          }
+          lds_lane_exchange();
+          auto sums = [&](float (&S)[NEH][NAH], int t, int t1, int step) {
 #pragma unroll 2
-        for (int t = max(ps.lo - c0, 0); t < t1; ++t) {
-          const float* rp = buf + t * RS;
-          float gn[NAH], gp[NAH];
+            for (; t < t1; t += step) {
+              const float* rp = buf + t * RS;
+              float gn[NAH], gp[NAH];
 #pragma unroll
-          for (int j = 0; j < NAH; ++j) {
-            const int n = min(n0 + j, NA - 1);   // an odd channel count repeats the last, unused
-            gn[j] = rp[2 * n];
-            gp[j] = rp[2 * n + 1];
+              for (int j = 0; j < NAH; ++j) {
+                const int n = min(n0 + j, NA - 1);   // an odd channel count repeats the last, unused
+                gn[j] = rp[2 * n];
+                gp[j] = rp[2 * n + 1];
+              }
+#pragma unroll
+              for (int e = 0; e < NEH; ++e) {
+                const int q = YG % HL == 0 ? h0 + e : min(h0 + e, YG - 1);
+                const float b = rp[2 * NA + 2 * q], c = rp[2 * NA + 2 * q + 1];
+#pragma unroll
+                for (int j = 0; j < NAH; ++j) S[e][j] = fmaf(gp[j], b, fmaf(gn[j], c, S[e][j]));
+              }
+            }
+          };
+          if constexpr (shared) {
+            const ChunkShare<L> cs = chunk_share(ps, c0, slots, kAdjSlot);
+            float S[NEH][NAH];
+#pragma unroll
+            for (int e = 0; e < NEH; ++e)
+#pragma unroll
+              for (int j = 0; j < NAH; ++j) S[e][j] = 0.f;
+            sums(S, cs.t, cs.t1, 1 << cs.k);
+            chunk_add(cs, S, Sd[gg]);
+          } else {
+            sums(Sd[gg], max(ps.lo - c0, 0), min(ps.hi - c0, kWave), 1);
           }
-#pragma unroll
-          for (int e = 0; e < NEH; ++e) {
-            const int q = YG % HL == 0 ? h0 + e : min(h0 + e, YG - 1);
-            const float b = rp[2 * NA + 2 * q], c = rp[2 * NA + 2 * q + 1];
-#pragma unroll
-            for (int j = 0; j < NAH; ++j) Sd[gg][e][j] = fmaf(gp[j], b, fmaf(gn[j], c, Sd[gg][e][j]));
-          }
+          lds_lane_exchange();
         }
-        lds_lane_exchange();
       }
-    }
+    };
+    if (C::YH == 0 && ps.total > kSharePairs)
+      tangent(std::bool_constant<C::YH == 0>{});
+    else
+      tangent(std::false_type{});
     wait_weights();   // before the stores below, as in the forward
     // the atoms' rows take the records' place
 #pragma unroll
