@@ -2325,11 +2325,17 @@ constexpr int force_lds_words() {
 
 // Position of key in the angular list of atom j (m entries, row 16-byte
 // aligned when vec), -1 if it was cut off: the count of smaller entries, 8 per
-// step.
+// step, of a list of more than 16 in the 16 that halving leaves (force pass of
+// 90,000 atoms with 75 entries an atom: 374 us with the whole list counted,
+// 249 so; 176 and 135 with 42, the same with up to 15).
 __device__ __forceinline__ int partner_find(const uint32_t* __restrict__ row, int m, int cap, bool vec, uint32_t key) {
   int below = 0;
   bool hit = false;
-  for (int b = 0; b < m; b += 8) {
+  while (m - below > 16) {
+    const int mid = below + (((m - below) / 2) & ~7);
+    if (row[mid] <= key) below = mid; else m = mid;
+  }
+  for (int b = below; b < m; b += 8) {
     uint32_t v[8];
     if (vec && b + 8 <= cap) {
       const uint4 x = *reinterpret_cast<const uint4*>(row + b);

@@ -59,3 +59,24 @@ def test_calls_match_oracle(name, density, copies):
     np.testing.assert_allclose(loss, c.loss, rtol=1e-4)
     for blk, sl in param_blocks(c.sizes).items():
         assert rel(grad[sl], c.grad[sl]) < TOL_F, blk
+
+
+@pytest.mark.parametrize("cap_rad,cap_ang", [(60, 17), (64, 24), (90, 27), (61, 33), (120, 40)])
+def test_long_lists_cut_at_their_capacity(cap_rad, cap_ang):
+    """The force pass finds a pair's other entry in a cut list of more than 16
+    entries, at every row alignment, or that it was cut off."""
+    from test_gpu_force import cut, reference
+    rng = np.random.default_rng(53)
+    c = Case(synth.SIZES_LARGE, [_cell(rng, n, 0.14, s) for n, s in ((64, 0.0), (90, 0.1))], with_oracle=False)
+    r = DeviceRun(c, cap_rad=cap_rad, cap_ang=cap_ang)
+    r.neighbors()
+    counts = r.nbrs.cnt_ang.cpu().numpy()
+    print(f"[dense cut {cap_rad}/{cap_ang}] N={r.N} pairs {counts.min()} to {counts.max()}", flush=True)
+    assert counts.max() > cap_ang > 16
+    _, e_s, F, W = r.efw()
+    ref = [reference(c.oracle, c.theta, st, (cut(p[0], cap_rad), cut(p[1], cap_ang)))
+           for st, p in zip(c.structures, c.nbrs)]
+    sizes = np.diff(c.batch.atom_offset)
+    assert rel(e_s / sizes, np.array([q[0] for q in ref]) / sizes) < TOL_E
+    assert rel(F, np.concatenate([q[1] for q in ref], 0)) < TOL_F
+    assert rel(W, np.stack([q[2] for q in ref])) < TOL_F
