@@ -1605,7 +1605,22 @@ __device__ __forceinline__ int block_species(const int* __restrict__ order, cons
 
 // LDS words of the staged weights: whole 64-word rows, so that the direct
 // loads below never write past them
-__host__ __device__ constexpr int weights_words(int H, int DP) { return (H * DP + 2 * H + 63) / 64 * 64; }
+// Rows of D = DP - 2 or DP - 3 words hold b0 and w1 of their unit behind W0.  With
+// that and c^R in the records' words the adjoint of the 3/4/5-body model keeps two
+// blocks per CU up to hidden 256 (from 244 on it was one: 483 -> 260 us at hidden
+// 256 and 90,000 atoms).
+__host__ __device__ constexpr bool weights_in_row(int D, int DP) { return DP - D >= 2; }
+__host__ __device__ constexpr int weights_words(int H, int D, int DP) {
+  return (H * DP + (weights_in_row(D, DP) ? 0 : 2 * H) + 63) / 64 * 64;
+}
+template <int D, int DP>
+__device__ __forceinline__ float weight_b0(const float* wl, int H, int mu) {
+  return wl[weights_in_row(D, DP) ? mu * DP + D : H * DP + mu];
+}
+template <int D, int DP>
+__device__ __forceinline__ float weight_w1(const float* wl, int H, int mu) {
+  return wl[weights_in_row(D, DP) ? mu * DP + D + 1 : H * DP + H + mu];
+}
 
 // Species I's W0 (rows padded to DP words), b0 and w1 into LDS with direct
 // global-to-LDS loads (gfx950 global_load_lds_dword: each wavefront writes
@@ -1615,13 +1630,15 @@ __host__ __device__ constexpr int weights_words(int H, int DP) { return (H * DP 
 // padding words (d >= D, never read) receive W0[0][0].
 __device__ __forceinline__ void stage_weights_async(float* wl, const float* __restrict__ nn, int nn_stride, int I,
                                                     int H, int D, int DP) {
-  const int WS = H * DP + 2 * H, WSP = weights_words(H, DP);
+  const bool in_row = weights_in_row(D, DP);
+  const int WS = H * DP + 2 * H, WSP = weights_words(H, D, DP);
   const float* w = nn + (size_t)I * nn_stride;
   const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave, nw = blockDim.x / kWave;
   for (int c0 = wv * kWave; c0 < WSP; c0 += nw * kWave) {
     const int q = c0 + lane;
     const int mu = q / DP, d = q % DP;
-    const int src = q < H * DP ? (d < D ? mu * D + d : 0) : (q < WS ? H * D + (q - H * DP) : 0);
+    const int tail = in_row && d < D + 2 ? H * D + (d - D) * H + mu : 0;   // b0, w1 or padding
+    const int src = q < H * DP ? (d < D ? mu * D + d : tail) : (!in_row && q < WS ? H * D + (q - H * DP) : 0);
     __builtin_amdgcn_global_load_lds(w + src, (__attribute__((address_space(3))) void*)(wl + c0), 4, 0, 0);
   }
 }
@@ -1851,7 +1868,7 @@ __device__ __forceinline__ void forward_body(const FwdArgs& a, int b, float* lds
   float* ctab = lds;                     // [T][NA][KAP], c^A of the block's species
   float* crl = lds + CT::size;           // its c^R
   float* wl = crl + CRad<C>::size;       // its weights
-  float* slots = wl + weights_words(H, DP) + (threadIdx.x / kWave) * FL::WAVE;
+  float* slots = wl + weights_words(H, D, DP) + (threadIdx.x / kWave) * FL::WAVE;
   float* buf = slots + (kWave / L) * slot_words<kTri>();
   // 32 atoms of one species, taken by L / 8 blocks
   const int vs = launch_block(a.blist, a.nch, T, b / (L / 8));
@@ -2057,11 +2074,11 @@ __device__ __forceinline__ void forward_body(const FwdArgs& a, int b, float* lds
   float E = 0.f;
   for (int mu = s; mu < H; mu += L) {
     const float* wr = Wl + mu * DP;
-    float z = Wl[H * DP + mu];
+    float z = weight_b0<D, DP>(Wl, H, mu);
 #pragma unroll
     for (int v = 0; v < D; ++v) z = fmaf(wr[v], G[v], z);
     const float x = tanh_hw(z);
-    const float w1 = Wl[H * DP + H + mu];
+    const float w1 = weight_w1<D, DP>(Wl, H, mu);
     E = fmaf(w1, x, E);
     const float sg = w1 * (1.0f - x * x);
 #pragma unroll
@@ -2723,7 +2740,7 @@ struct AdjLds {
   static constexpr int REC = (2 * C::NA + 2 * C::KA + 1) | 1;   // X, Y (u.t), h T_k, q_k, species
   static constexpr int RECS = (256 / kWave) * 16 * REC;
   __host__ __device__ static int shared_words(int H) {
-    const int w = weights_words(H, DP);
+    const int w = weights_words(H, C::D, DP);
     return ((w > RECS ? w : RECS) + 3) & ~3;
   }
 };
@@ -2766,8 +2783,7 @@ __device__ __forceinline__ void adjoint_body(const AdjArgs& a, int b, float* lds
   const int H = a.H;
   using CT = CTab<T, NA, KA>;
   float* ctab = lds;                     // [T][NA][KAP], c^A of the block's species
-  float* crl = lds + CT::size;           // its c^R
-  float* wl = crl + CRad<C>::size;       // its weights
+  float* wl = lds + CT::size;            // its weights
   float* slots = wl + AL::shared_words(H) + (threadIdx.x / kWave) * AL::WAVE;
   float* buf = slots + (kWave / L) * kAdjSlot;
   // 32 atoms of one species, taken by L / 8 blocks
@@ -2778,12 +2794,15 @@ __device__ __forceinline__ void adjoint_body(const AdjArgs& a, int b, float* lds
   const int I = block_species<T>(a.order, a.p4, vs);
   stage_weights_async(wl, a.nn, a.nn_stride, I, H, D, DP);
   stage_ctab<T, NA, KA>(ctab, a.cA + (size_t)I * T * NA * KA);
-  for (int q = threadIdx.x; q < CRad<C>::N; q += 256) crl[q] = a.cR[(size_t)I * CRad<C>::N + q];
   const GroupCtx w = group_ctx<L>(a.order, a.Npad, vb);
   const int i = w.i, pa = w.pa, s = w.s, g = w.g;
   const size_t Np = a.Npad;
   const float4 me = a.p4[i];
   const int lane = threadIdx.x & (kWave - 1), slot = lane / L;
+  // c^R of the species where the wavefront's records come later
+  static_assert(CRad<C>::N <= AL::BUF, "the coefficients fit the records' words");
+  float* crl = buf;
+  for (int q = lane; q < CRad<C>::N; q += kWave) crl[q] = a.cR[(size_t)I * CRad<C>::N + q];
   const int wave = (vb * 256 + (int)threadIdx.x) / kWave;
   const bool first_atom = slot == 0;   // atom slot 0 of the wavefront writes the sums
   float* part = a.part + (size_t)wave * a.PW;
@@ -3061,7 +3080,7 @@ __device__ __forceinline__ void adjoint_body(const AdjArgs& a, int b, float* lds
       const bool live = act && w.valid;
       const float x = live ? xv : 0.f;
       const float sg = 1.0f - x * x;
-      const float ws = Wl[H * DP + H + mm] * sg;
+      const float ws = weight_w1<D, DP>(Wl, H, mm) * sg;
       const float be = live ? ws * (eps + 2.0f * x * aa) : 0.f;
 #pragma unroll
       for (int v = 0; v < D; ++v) Gb[v] = fmaf(be, wr[v], Gb[v]);
@@ -4030,7 +4049,6 @@ struct Ops {
   int KP;   // words of a radial force coefficient row
   size_t (*lds_fwd)(int);
   size_t (*lds_adj)(int);
-  size_t (*lds_adj16)(int);   // the adjoint at 16 lanes an atom
   void (*high)(HighKernel, const HighArgs&, dim3, hipStream_t);   // null without degrees l > 4
   // persistent step (null with degrees l > 4): launch, and resident blocks per CU
   void (*step)(const StepArgs*, int, size_t, hipStream_t);
@@ -4041,13 +4059,13 @@ struct Ops {
 template <class C, int L>
 static size_t lds_forward(int H) {
   using FL = FwdLds<C, L>;
-  return sizeof(float) * ((size_t)CTab<C::T, C::NA, C::KA>::size + CRad<C>::size + (size_t)weights_words(H, FL::DP) +
+  return sizeof(float) * ((size_t)CTab<C::T, C::NA, C::KA>::size + CRad<C>::size + (size_t)weights_words(H, C::D, FL::DP) +
                           (size_t)(256 / kWave) * FL::WAVE);
 }
 template <class C, int L>
 static size_t lds_adjoint(int H) {
   using AL = AdjLds<C, L>;
-  return sizeof(float) * ((size_t)CTab<C::T, C::NA, C::KA>::size + CRad<C>::size + (size_t)AL::shared_words(H) +
+  return sizeof(float) * ((size_t)CTab<C::T, C::NA, C::KA>::size + (size_t)AL::shared_words(H) +
                           (size_t)(256 / kWave) * AL::WAVE);
 }
 // LDS of a workgroup on gfx950 (160 KiB per CU); dynamic LDS beyond 64 KiB is
@@ -4174,8 +4192,7 @@ static Ops make_ops() {
     occ = &step_occupancy<C>;
   }
   return Ops{C::T, C::NR, C::NA, C::KR, C::KA, C::L3, C::L4, C::L5, C::D, C::Y, C::PS, C::YH,
-             HRow<C::LMAX>::YR, &launch_forward<C>, &launch_force<C>, &launch_adjoint<C>, HRad<C>::KP, &lds_forward<C, kLPA>, &lds_adjoint<C, kLPA>,
-             &lds_adjoint<C, 16>, high, step, occ,
+             HRow<C::LMAX>::YR, &launch_forward<C>, &launch_force<C>, &launch_adjoint<C>, HRad<C>::KP, &lds_forward<C, kLPA>, &lds_adjoint<C, kLPA>, high, step, occ,
              C::FIXED_WAVES != 0};
 }
 
@@ -4270,13 +4287,12 @@ size_t al(size_t x) { return (x + 255) & ~(size_t)255; }
 // step of the 3/4/5-body model in us with 8 / 16 / 32 lanes: 512 atoms
 // 91.5 / 72.7 / 68.1, 2048 atoms 94.4 / 76.4 / 73.4, 3072 atoms 96.5 / 80.1 /
 // 83.8, 8192 atoms 105.1 / 94.6 / 115.5, 12288 atoms 112.3 / 122.4 / 142.7.
-// A model whose rows of 8 atoms a wavefront pass the LDS in the adjoint (four
-// species, degrees up to 8, hidden 252 to 256) takes 16 lanes at any size.
+// The 3-body model, degrees up to 8 and the padded classes change sides at the
+// same sizes within 3 %: at 2048 and 8192 atoms 72.8 / 58.3 / 55.4 and
+// 84.4 / 73.4 / 88.6, 135.7 / 125.1 / 122.8 and 160.3 / 159.9 / 174.9, and
+// (three species) 94.3 / 71.4 / 71.5 and 113.7 / 116.6 / 138.5.
 constexpr int kLanes32Atoms = 2048, kLanes16Atoms = 8192;
-int group_lanes(const Ops* o, int H, int N) {
-  if (N <= kLanes32Atoms) return 32;
-  return N <= kLanes16Atoms || o->lds_adj(H) > kMaxLds ? 16 : kLPA;
-}
+int group_lanes(int N) { return N <= kLanes32Atoms ? 32 : N <= kLanes16Atoms ? 16 : kLPA; }
 
 struct Layout {
   int N, S, T, D, Y, H, NR, TKR, Npad, lanes, nch, PW, NA, capR, capA;
@@ -4345,7 +4361,7 @@ Layout layout_of(const nep_model* m, const Ops* o, int S, int N, bool pad) {
   // units, so the rows a wavefront stores start in different memory channels
   L.Npad = (L.Npad + 63) / 64 * 64;
   if ((L.Npad / 64) % 2 == 0) L.Npad += 64;
-  L.lanes = group_lanes(o, L.H, N);   // each wavefront writes a row of part
+  L.lanes = group_lanes(N);   // each wavefront writes a row of part
   L.PW = L.T * m->n_ang * m->k_ang + 2 * L.H + 1;
   const size_t Np = L.Npad, Nn = (size_t)(N > 0 ? N : 1), Ss = (size_t)(S > 0 ? S : 1);
   size_t off = 0;
@@ -4932,7 +4948,7 @@ int model_supported(const nep_model* m, Resolved* out = nullptr) {
   if (rc) return rc;
   const Resolved r = resolve(m);
   if (!r.o) return NEP_ERR_ARG;
-  if (r.o->lds_adj16(m->hidden) > kMaxLds || r.o->lds_fwd(m->hidden) > kMaxLds) return NEP_ERR_ARG;
+  if (r.o->lds_adj(m->hidden) > kMaxLds || r.o->lds_fwd(m->hidden) > kMaxLds) return NEP_ERR_ARG;
   if (out) *out = r;
   return NEP_OK;
 }

@@ -1,7 +1,7 @@
 """Batches above 8192 atoms, where the forward and the adjoint run 8 lanes an
 atom, for the models that the small batches of the other tests take through 16
-or 32 lanes; and the one model whose adjoint takes 16 lanes at any size.
-Against the FP64 oracle, as copies of one group of structures."""
+or 32 lanes; and the model whose adjoint needs the most LDS.  Against the FP64
+oracle, as copies of one group of structures."""
 import numpy as np
 import pytest
 
@@ -19,7 +19,7 @@ SIZES = {
     "l8": synth.SIZES_L8,
     "three_species": synth.NEPSizes(n_types=3, n_rad=4, n_ang=3, k_rad=6, k_ang=5, l3=4, l4=2, l5=1, hidden=12),
     "l6": synth.NEPSizes(n_rad=4, n_ang=3, k_rad=6, k_ang=5, l3=6, l4=2, l5=0, hidden=12),
-    # four species, degrees up to 8, hidden 256: rows of 8 atoms pass the LDS
+    # four species, degrees up to 8, hidden 256: 163,328 of 163,840 bytes
     "hidden256": synth.NEPSizes(n_types=3, n_rad=4, n_ang=3, k_rad=6, k_ang=5, l3=5, l4=0, l5=0, hidden=256),
 }
 _CASE = {}
