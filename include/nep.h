@@ -287,10 +287,10 @@ typedef struct {
 #define NEP_GRAPH_CACHED_NEIGHBORS 1
 
 /* graph_flags bit NEP_GRAPH_PERSISTENT: everything after the neighbor build
- * (species order, forward, force gather, per-structure sums and loss of
+ * (species order, forward, force pass, per-structure sums and loss of
  * Eqs. 9-12, adjoint, gradient reductions and Adam) runs as one persistent
  * launch whose phases are separated by a software grid barrier, in place of
- * about ten separate launches.  The grid takes as many blocks as are resident
+ * six or seven separate launches.  The grid takes as many blocks as are resident
  * at once.  Same results as the separate launches up to the order of
  * floating-point sums.  NEP_ERR_ARG for triclinic batches (tilt != NULL),
  * empty batches and models with 3-body degrees l > 4; the caller then uses
@@ -315,7 +315,9 @@ int nep_train_step_graph_create(const nep_model* model, const nep_batch* batch, 
  *   gather_lanes    lanes per atom of the force pass, 8 or 16 [16]
  *   forward_waves   forward kernel compiled for 3 wavefronts per SIMD (2) or for 4,
  *                   with fewer registers (3) [3; 2 with degrees l > 4]
- *   adjoint_waves   wavefronts per SIMD the adjoint kernel is compiled for, 2 or 3 [3]
+ *   adjoint_waves   wavefronts per SIMD the adjoint kernel is compiled for, 2 or 3 [3];
+ *                   both without effect up to 8192 atoms (16 or 32 lanes an atom) and
+ *                   in the zero-padded size classes, which have one build each
  *   reverse_branch  0, 1 or 2, without effect: the reverse index it placed is
  *                   no longer built (the force pass finds partners itself)
  * A value out of range is NEP_ERR_ARG. */

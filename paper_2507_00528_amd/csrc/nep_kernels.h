@@ -5,10 +5,10 @@
 //   -> forces and virials -> per-structure loss and cotangents -> adjoint (tangent
 //   pass, network adjoint, parameter partials) -> W0 reduction -> final gradient
 //   reduction -> Adam.
-// Per-atom kernels run in "species order": atoms grouped by species, each
-// group padded to a multiple of 8 atoms, and 8 lanes per atom, so every
-// wavefront evaluates one species' network.  Padding atoms have no neighbors
-// and write nothing.
+// Per-atom kernels run in "species order": per chunk of 2048 atoms grouped by
+// species, each group starting on a multiple of 32 positions, and 8, 16 or 32
+// lanes per atom, so every block evaluates one species' network.  Positions
+// without an atom write nothing.
 #pragma once
 #include "nep_device.h"
 

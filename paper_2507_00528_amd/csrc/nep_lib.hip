@@ -17,11 +17,12 @@
 namespace nep {
 
 // =============================================================== neighbors
-// One thread per atom i scans the atoms j of its own structure.  For each j
-// the per-axis test |(x_j - x_i) + s L| < rc keeps the candidate shifts, and
-// every candidate (j, s) is tested exactly with the float64 predicate of
-// Eq. 2, evaluated without fused multiply-add.  j runs ascending and the
-// shifts in code order, so the lists come out in canonical order.
+// The lists of an atom i hold the (j, s) of its own structure that pass the
+// float64 predicate of Eq. 2, evaluated without fused multiply-add, in canonical
+// order: j ascending, then the shifts in code order.  Where a cell may hold
+// several images of j within rc, the per-axis test |(x_j - x_i) + s L| < rc
+// keeps the candidate shifts and each is tested.
+//
 // IEEE double product and sum with one rounding each.  The library is built
 // with floating-point contraction, and d^2 = (dx dx + dy dy) + dz dz of the
 // predicate must not become fused multiply-adds (a pair within an ulp of rc
@@ -51,8 +52,7 @@ __device__ __forceinline__ unsigned axis_candidates(double d0, double L, double 
 
 // One atom per group of 8 lanes; lane s scans the s-th contiguous eighth of
 // the atom's structure, so concatenating the lanes' entries in lane order
-// keeps the canonical (j, code) order.  A count pass and an exclusive scan
-// over the group give each lane its write offset; a second pass writes.
+// keeps the canonical (j, code) order.
 //
 // Fast decision.  When every cell edge is at least 2(rc + delta) and at most
 // kNbrFastL, at most one image of j lies within rc + delta, and the single
@@ -609,7 +609,7 @@ __global__ __launch_bounds__(256) void k_cell_part(int n, const int* __restrict_
 }
 
 // counts -> start offsets over [0, n), and the total at [n].  Up to
-// kScanDirect chunks every block sums the counts before its own (at most 60k
+// kScanDirect chunks every block sums the counts before its own (at most 30,720
 // loads by the last block) instead of reading the sums of k_cell_part, whose
 // launch took 4 us.
 constexpr int kScanDirect = 16;
@@ -2478,7 +2478,7 @@ __global__ __launch_bounds__(256) void k_force(ForceArgs a) {
 
 // The force pass of an MD step that another follows: an atom's kick and drift
 // by the lane that holds its force (the positions are written, the packed
-// ones read).  Its own launch took 4 of 33 us a step of a 180-atom cell.
+// ones read).  Its own launch took 4 us a step of a 180-atom cell, now 27 us.
 template <class C, bool kTri>
 __global__ __launch_bounds__(256) void k_force_move(ForceArgs a, MDArgs md) {
   __shared__ __align__(16) float own[force_lds_words<C, kForceLPA>()];
@@ -3536,8 +3536,9 @@ __global__ __launch_bounds__(256, 3) void k_outer_reduce(OuterReduceArgs a) {
 // lane sums.  Parameter layout: c^R [T][T][NR][KR], c^A [T][T][NA][KA], then
 // per species W0 [H][D], b0 [H], w1 [H], b1.
 // ==================================================================== Adam
-// One parameter's update.  The fused forms are written out, so that the
-// captured step and the eager one round alike.
+// One parameter's update, with the fused forms written out so that the captured
+// step and the eager one round the moments alike.  (c1 and c2 are formed in
+// single precision on the device and in double on the host.)
 __device__ __forceinline__ void adam_update(float& th, float& m, float& v, float g, float lr, float b1, float b2,
                                             float eps, float c1, float c2) {
   m = fmaf(1.0f - b1, g, b1 * m);
@@ -3774,7 +3775,7 @@ __global__ void k_fill_f32(float* p, int64_t n, float v) {
 
 // ============================================================ persistent step
 // The whole step after the neighbor build in one launch: the species order,
-// forward, force gather, per-structure sums and loss, adjoint, gradient
+// forward, force pass, per-structure sums and loss, adjoint, gradient
 // reductions and Adam, as phases of one persistent grid separated by a
 // software grid barrier.  The grid holds as many blocks as are resident at
 // once, each phase deals its work items (the blocks of the separate kernels)
@@ -4508,11 +4509,11 @@ struct Ctx {
   int lanes = kLPA;   // lanes per atom of the forward and the adjoint
   // the packed atoms of this call are in the workspace
   mutable bool packed = false;
-  // a captured step whose neighbor build starts the replay (flags, step latch)
-  // a captured step whose forward collects the build's flags
-  mutable FlagArgs flag_words{};
+  // a captured step whose order launch or forward starts the replay (flags, step
+  // latch): the step counter and its latch, and the flag words left to the forward
   int* g_step = nullptr;
   int* g_cur = nullptr;
+  mutable FlagArgs flag_words{};
   // force cotangents of the caller (nep_vjp), packed with the atoms
   const float* fbar = nullptr;
 };
@@ -4679,7 +4680,6 @@ ForceArgs force_args(const Ctx& c, const FwdArgs& f, float* user) {
   return a;
 }
 
-// forward + forces + per-structure sums (+ loss when labels given)
 // arguments of the kernels of degrees l > 4 (wbar only for the adjoint's)
 HighArgs high_args(const Ctx& c, const nep_neighbors* nb, const float* params, const float* wbar = nullptr) {
   HighArgs h;
@@ -5199,8 +5199,8 @@ int nep_energy_force_virial(const nep_model* m, const nep_batch* b, const nep_ne
   return hip_ok();
 }
 
-// MD steps between two species orders (5 of 33 us a step of a 180-atom cell,
-// 8 of 100 us with 9261 atoms)
+// MD steps between two species orders (formed every step it took 5 us of the
+// step of a 180-atom cell, now 27, and 8 of that of 9261 atoms, now 73)
 constexpr int kMDOrderSteps = 16;
 
 int nep_md_step(const nep_model* m, const nep_batch* b, float* pos, nep_neighbors* nb, const float* params,
@@ -5375,7 +5375,7 @@ int nep_train_step_graph_create_tuned(const nep_model* m, const nep_batch* b, ne
   } else {
     if ((graph_flags & NEP_GRAPH_CACHED_NEIGHBORS) != 0 || c.L.N == 0) {
       hipLaunchKernelGGL(k_graph_head, dim3(1), dim3(64), 0, cap, d_flags, d_step, cur);
-    } else {   // by the order launch of the neighbor build
+    } else {   // by the order launch of the neighbor build, or with up to 8192 atoms the forward
       c.g_step = d_step;
       c.g_cur = cur;
     }

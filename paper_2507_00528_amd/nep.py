@@ -304,10 +304,11 @@ class TrainStepGraph:
     """One captured training step (neighbors, forward, loss, adjoint, Adam);
     replays advance the device step counter.  With cached_neighbors the graph
     skips the neighbor build and reuses the lists (and the species order in
-    ws) from an earlier build_neighbors call.  With persistent everything after the neighbor build runs as one persistent
-    launch (NEP_GRAPH_PERSISTENT).  tuning: launch choices (nep_tuning) as a
-    dict, None for the defaults, or "cache" for the autotuner's choice for
-    this model and batch size class (defaults when it has none)."""
+    ws) from an earlier build_neighbors call.  With persistent everything
+    after the neighbor build runs as one persistent launch
+    (NEP_GRAPH_PERSISTENT).  tuning: launch choices (nep_tuning) as a dict,
+    None for the defaults, or "cache" for the autotuner's choice for this
+    model and batch size class (defaults when it has none)."""
 
     def __init__(self, model, batch, nbrs, labels, lam, params, m, v, grad, loss, step, ws, flags,
                  lr_start=1e-3, lr_stop=1e-3, n_warmup=0, n_total=0, beta1=0.9, beta2=0.999, eps=1e-8,
