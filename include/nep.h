@@ -316,8 +316,9 @@ int nep_train_step_graph_create(const nep_model* model, const nep_batch* batch, 
  *   forward_waves   forward kernel compiled for 3 wavefronts per SIMD (2) or for 4,
  *                   with fewer registers (3) [3; 2 with degrees l > 4]
  *   adjoint_waves   wavefronts per SIMD the adjoint kernel is compiled for, 2 or 3 [3];
- *                   both without effect up to 8192 atoms (16 or 32 lanes an atom) and
- *                   in the zero-padded size classes, which have one build each
+ *                   both without effect on batches that run 16 or 32 lanes an atom (up to
+ *                   8192 atoms, 10240 without degrees l > 4, 14336 with at most 16
+ *                   descriptors) and in the zero-padded size classes: one build each
  *   reverse_branch  0, 1 or 2, without effect: the reverse index it placed is
  *                   no longer built (the force pass finds partners itself)
  * A value out of range is NEP_ERR_ARG. */

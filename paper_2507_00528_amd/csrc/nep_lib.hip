@@ -4286,14 +4286,19 @@ size_t al(size_t x) { return (x + 255) & ~(size_t)255; }
 // batch where 32 lanes (8 atoms a block) no longer fit one block per CU and
 // 16 lanes two; beyond, the work that more lanes repeat counts.  Training
 // step of the 3/4/5-body model in us with 8 / 16 / 32 lanes: 512 atoms
-// 91.5 / 72.7 / 68.1, 2048 atoms 94.4 / 76.4 / 73.4, 3072 atoms 96.5 / 80.1 /
-// 83.8, 8192 atoms 105.1 / 94.6 / 115.5, 12288 atoms 112.3 / 122.4 / 142.7.
-// The 3-body model, degrees up to 8 and the padded classes change sides at the
-// same sizes within 3 %: at 2048 and 8192 atoms 72.8 / 58.3 / 55.4 and
-// 84.4 / 73.4 / 88.6, 135.7 / 125.1 / 122.8 and 160.3 / 159.9 / 174.9, and
-// (three species) 94.3 / 71.4 / 71.5 and 113.7 / 116.6 / 138.5.
-constexpr int kLanes32Atoms = 2048, kLanes16Atoms = 8192;
-int group_lanes(int N) { return N <= kLanes32Atoms ? 32 : N <= kLanes16Atoms ? 16 : kLPA; }
+// 81.2 / 61.9 / 56.7, 2048 atoms 80.3 / 64.0 / 60.6, 3072 atoms 82.2 / 67.4 /
+// 66.1, 8192 atoms 94.8 / 84.8 / 102.5; with 8 / 16, 10240 atoms 106.3 / 97.8,
+// 11264 atoms 107.9 / 116.6.  The 3-body model is the same (10240 atoms 94.5 /
+// 86.9, 11264 atoms 93.4 / 94.9).  Models of up to 16 descriptors have less to
+// repeat (one species, 14336 atoms 77.0 / 72.6, 16384 atoms 71.8 / 72.9), those
+// of degrees up to 8 and the padded classes more (8192 atoms 160.3 / 159.9 and,
+// three species, 113.7 / 116.6, 6144 atoms 154.2 / 145.4 and 105.8 / 91.6).  At 32
+// lanes all change sides between 2048 and 3072 atoms.
+constexpr int kLanes32Atoms = 2048, kLanes16Wide = 8192, kLanes16Atoms = 10240, kLanes16Small = 14336;
+int group_lanes(const Ops* o, int N) {
+  const int line = o->padded || o->YH > 0 ? kLanes16Wide : o->D <= 16 ? kLanes16Small : kLanes16Atoms;
+  return N <= kLanes32Atoms ? 32 : N <= line ? 16 : kLPA;
+}
 
 struct Layout {
   int N, S, T, D, Y, H, NR, TKR, Npad, lanes, nch, PW, NA, capR, capA;
@@ -4362,7 +4367,7 @@ Layout layout_of(const nep_model* m, const Ops* o, int S, int N, bool pad) {
   // units, so the rows a wavefront stores start in different memory channels
   L.Npad = (L.Npad + 63) / 64 * 64;
   if ((L.Npad / 64) % 2 == 0) L.Npad += 64;
-  L.lanes = group_lanes(N);   // each wavefront writes a row of part
+  L.lanes = group_lanes(o, N);   // each wavefront writes a row of part
   L.PW = L.T * m->n_ang * m->k_ang + 2 * L.H + 1;
   const size_t Np = L.Npad, Nn = (size_t)(N > 0 ? N : 1), Ss = (size_t)(S > 0 ? S : 1);
   size_t off = 0;

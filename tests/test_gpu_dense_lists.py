@@ -40,8 +40,8 @@ def _case(name, density):
 
 
 @pytest.mark.parametrize("name,density,copies", [
-    ("large", 0.12, 1), ("large", 0.12, 9), ("large", 0.12, 33), ("large", 0.25, 1), ("large", 0.25, 9),
-    ("large", 0.25, 33), ("small", 0.12, 33), ("mono", 0.2, 33), ("l8", 0.12, 33), ("three_species", 0.2, 9),
+    ("large", 0.12, 1), ("large", 0.12, 9), ("large", 0.12, 41), ("large", 0.25, 1), ("large", 0.25, 9),
+    ("large", 0.25, 41), ("small", 0.12, 41), ("mono", 0.2, 57), ("l8", 0.12, 33), ("three_species", 0.2, 9),
     ("three_species", 0.2, 33)])
 def test_calls_match_oracle(name, density, copies):
     c = _case(name, density)

@@ -1,7 +1,8 @@
-"""Batches above 8192 atoms, where the forward and the adjoint run 8 lanes an
-atom, for the models that the small batches of the other tests take through 16
-or 32 lanes; and the model whose adjoint needs the most LDS.  Against the FP64
-oracle, as copies of one group of structures."""
+"""Batches where the forward and the adjoint run 8 lanes an atom (above 8192
+atoms with degrees l > 4 and in the padded classes, 14336 with at most 16
+descriptors, else 10240), for the models that the small batches of the other
+tests take through 16 or 32 lanes; and the model whose adjoint needs the most
+LDS.  Against the FP64 oracle, as copies of one group of structures."""
 import numpy as np
 import pytest
 
@@ -39,9 +40,9 @@ def _case(name, tilted=False):
 
 
 @pytest.mark.parametrize("name,tilted,copies", [
-    ("hidden256", False, 1), ("hidden256", False, 33), ("small", False, 33), ("mono", False, 33), ("l8", False, 33),
-    ("three_species", False, 33), ("l6", False, 33),
-    ("large", True, 1), ("large", True, 9), ("large", True, 33), ("l8", True, 1), ("l8", True, 33),
+    ("hidden256", False, 1), ("hidden256", False, 33), ("large", False, 40), ("large", False, 41),
+    ("small", False, 41), ("mono", False, 56), ("mono", False, 57), ("l8", False, 33), ("three_species", False, 33),
+    ("l6", False, 33), ("large", True, 1), ("large", True, 9), ("large", True, 41), ("l8", True, 1), ("l8", True, 33),
     ("three_species", True, 9), ("three_species", True, 33)])
 def test_calls_match_oracle(name, tilted, copies):
     c = _case(name, tilted)
@@ -67,7 +68,7 @@ def test_captured_step_at_both_occupancies(name, waves):
     import torch
     from paper_2507_00528_amd import nep
     c = _case(name)
-    r = DeviceRun(_Copies(c, 33))
+    r = DeviceRun(_Copies(c, 57))
     print(f"[lanes {name}] waves={waves} N={r.N}", flush=True)
     P = r.params.numel()
     z = lambda n: torch.zeros(n, device="cuda")
@@ -94,7 +95,7 @@ def test_one_md_call_equals_single_step_calls(name):
     import torch
     from paper_2507_00528_amd import md, nep
     c = _case(name)
-    k, n = 33, 18
+    k, n = 41, 18
     got = []
     for calls, per in ((1, n), (n, 1)):
         r = DeviceRun(_Copies(c, k))
