@@ -42,15 +42,15 @@ def _ptr(t):
         raise ValueError("tensor must live on the GPU")
     if not t.is_contiguous():
         raise ValueError("tensor must be contiguous")
-    return C.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _stream(stream=None):
     """The stream's handle; by default the current device's current stream
     (0.3 us of host time a call, a torch.cuda.Stream object for it 2.7)."""
     if stream is not None:
-        return C.c_void_p(stream.cuda_stream)
-    return C.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
+        return stream.cuda_stream
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _want(t, dtype, numel, name):
@@ -95,10 +95,14 @@ def param_count(model: Model) -> int:
     return _param_count(model.c())
 
 
-def descriptor_count(model: Model) -> int:
-    v = _lib.load().nep_descriptor_count(C.byref(model.c()))
+def _descriptor_count(m: _lib.NepModel) -> int:
+    v = _lib.load().nep_descriptor_count(C.byref(m))
     _check(int(v) if v < 0 else 0, "nep_descriptor_count")
     return int(v)
+
+
+def descriptor_count(model: Model) -> int:
+    return _descriptor_count(model.c())
 
 
 def model_supported(model: Model) -> bool:
@@ -163,9 +167,10 @@ def build_neighbors(model, batch: DeviceBatch, nbrs: Neighbors, ws, flags, strea
 
 
 def descriptors(model, batch, nbrs, params, G, ws, stream=None):
-    _want(params, torch.float32, param_count(model), "params")
-    _want(G, torch.float32, descriptor_count(model) * batch.n_atom, "G")
-    _check(_lib.load().nep_descriptors(C.byref(model.c()), C.byref(batch.c()), C.byref(nbrs.c()), _ptr(params),
+    m = model.c()
+    _want(params, torch.float32, _param_count(m), "params")
+    _want(G, torch.float32, _descriptor_count(m) * batch.n_atom, "G")
+    _check(_lib.load().nep_descriptors(C.byref(m), C.byref(batch.c()), C.byref(nbrs.c()), _ptr(params),
                                        _ptr(G), _ptr(ws), _stream(stream)), "nep_descriptors")
 
 
@@ -209,14 +214,15 @@ def _lam(lam):
 
 def loss_grad(model, batch, nbrs, params, labels: Labels, lam, loss, grad, ws, flags, e_struct=None, force=None,
               virial=None, stream=None):
-    P = param_count(model)
+    m = model.c()
+    P = _param_count(m)
     _want(params, torch.float32, P, "params")
     _want(grad, torch.float32, P, "grad")
     _want(loss, torch.float32, 4, "loss")
     _want(labels.energy, torch.float32, batch.n_struct, "labels.energy")
     _want(labels.force, torch.float32, 3 * batch.n_atom, "labels.force")
     _want(labels.virial, torch.float32, 6 * batch.n_struct, "labels.virial")
-    _check(_lib.load().nep_loss_grad(C.byref(model.c()), C.byref(batch.c()), C.byref(nbrs.c()), _ptr(params),
+    _check(_lib.load().nep_loss_grad(C.byref(m), C.byref(batch.c()), C.byref(nbrs.c()), _ptr(params),
                                      C.byref(labels.c()), C.byref(_lam(lam)), _ptr(loss), _ptr(grad),
                                      _ptr(e_struct), _ptr(force), _ptr(virial), _ptr(ws), _ptr(flags),
                                      _stream(stream)), "nep_loss_grad")
@@ -230,7 +236,8 @@ def loss_grad_noalloc(model, batch, nbrs, params, labels: Labels, lam, loss, gra
     """Neighbor build plus loss and gradient with the library's static device
     scratch in place of a workspace (nep_loss_grad_noalloc); nothing is
     allocated.  Calls on one GPU share the scratch and must not overlap."""
-    P = param_count(model)
+    m = model.c()
+    P = _param_count(m)
     _want(params, torch.float32, P, "params")
     _want(grad, torch.float32, P, "grad")
     _want(loss, torch.float32, 4, "loss")
@@ -238,7 +245,7 @@ def loss_grad_noalloc(model, batch, nbrs, params, labels: Labels, lam, loss, gra
     _want(labels.energy, torch.float32, batch.n_struct, "labels.energy")
     _want(labels.force, torch.float32, 3 * batch.n_atom, "labels.force")
     _want(labels.virial, torch.float32, 6 * batch.n_struct, "labels.virial")
-    _check(_lib.load().nep_loss_grad_noalloc(C.byref(model.c()), C.byref(batch.c()), C.byref(nbrs.c()),
+    _check(_lib.load().nep_loss_grad_noalloc(C.byref(m), C.byref(batch.c()), C.byref(nbrs.c()),
                                              _ptr(params), C.byref(labels.c()), C.byref(_lam(lam)), _ptr(loss),
                                              _ptr(grad), _ptr(e_struct), _ptr(force), _ptr(virial), _ptr(flags),
                                              _stream(stream)), "nep_loss_grad_noalloc")

@@ -14,7 +14,7 @@ def test_default_stream_is_the_current_one():
     seen = []
 
     def look():
-        seen.append((nep._stream().value or 0, torch.cuda.current_stream().cuda_stream))
+        seen.append((nep._stream(), torch.cuda.current_stream().cuda_stream))
 
     look()
     with torch.cuda.stream(side):
@@ -25,4 +25,4 @@ def test_default_stream_is_the_current_one():
     look()
     assert all(a == b for a, b in seen)
     assert seen[1][0] == side.cuda_stream != seen[0][0] == seen[2][0] == seen[3][0]
-    assert (nep._stream(side).value or 0) == side.cuda_stream
+    assert nep._stream(side) == side.cuda_stream
