@@ -3111,19 +3111,25 @@ __device__ __forceinline__ void adjoint_body(const AdjArgs& a, int b, float* lds
   }
   lds_lane_exchange();
 
-  // ---- Sbar and A of this lane's harmonic group, in place of Sdot and S
+  // ---- Sbar and A of this lane's harmonic group, in place of Sdot and S.  With
+  //      degrees l > 4 group and channel slot are taken anew: the row offsets and
+  //      harmonic constants of the first pass were otherwise kept over the network
+  //      and spilled (87,471 atoms: 52 -> 12 bytes a lane, 109 -> 97.5 us).  The
+  //      others spill nothing, and forming them again took 0.3 % of their step.
+  const int gb = C::YH > 0 ? opaque_int(g) : g, pb = C::YH > 0 ? opaque_int(w.p) : w.p;
+  const int lAb = gb ? 2 : 1, lBb = gb ? 3 : 4, nAb = gb ? HS::nA1 : HS::nA0;
 #pragma unroll
   for (int r = 0; r < NN; ++r) {
-    const int n = w.p + HL * r;
+    const int n = pb + HL * r;
     if (n < NA) {
       float Sn[YG], Sdn[YG];
-      row_load<YG, kVec>(rowA + n * YR + g * YG, Sn);
-      row_load<YG, kVec>(rowSb + n * YR + g * YG, Sdn);
+      row_load<YG, kVec>(rowA + n * YR + gb * YG, Sn);
+      row_load<YG, kVec>(rowSb + n * YR + gb * YG, Sdn);
       // E' and Gbar of the descriptors built from these sums
-      const float bA = row[NR + (lAc - 1) * NA + n], bB = row[NR + (lBc - 1) * NA + n];
-      const float eA = (w.valid && lA <= L3) ? epA[r] : 0.f;
-      const float eB = (w.valid && lB <= L3) ? epB[r] : 0.f;
-      const float gA = lA <= L3 ? bA : 0.f, gB = lB <= L3 ? bB : 0.f;
+      const float bA = row[NR + ((lAb <= L3 ? lAb : 1) - 1) * NA + n], bB = row[NR + ((lBb <= L3 ? lBb : 1) - 1) * NA + n];
+      const float eA = (w.valid && lAb <= L3) ? epA[r] : 0.f;
+      const float eB = (w.valid && lBb <= L3) ? epB[r] : 0.f;
+      const float gA = lAb <= L3 ? bA : 0.f, gB = lBb <= L3 ? bB : 0.f;
       float o[5] = {0.f, 0.f, 0.f, 0.f, 0.f}, od[5] = {0.f, 0.f, 0.f, 0.f, 0.f};
       float e4 = 0.f, g4 = 0.f, e5 = 0.f, g5 = 0.f, P = 0.f, SS = 0.f;
       if constexpr (L4 != 0) {
@@ -3132,21 +3138,21 @@ __device__ __forceinline__ void adjoint_body(const AdjArgs& a, int b, float* lds
         sym_proj(sym_mul(M, M), o);
         sym_proj(sym_mul(Md, M), od);
         const float b = row[NR + L3 * NA + n];
-        e4 = (w.valid && g == 1) ? ep4[r] : 0.f;
-        g4 = g == 1 ? b : 0.f;
+        e4 = (w.valid && gb == 1) ? ep4[r] : 0.f;
+        g4 = gb == 1 ? b : 0.f;
       }
       if constexpr (L5 != 0) {
         P = Sn[0] * Sn[0] + Sn[1] * Sn[1] + Sn[2] * Sn[2];
         SS = Sn[0] * Sdn[0] + Sn[1] * Sdn[1] + Sn[2] * Sdn[2];
         const float b = row[NR + L3 * NA + (L4 ? NA : 0) + n];
-        e5 = (w.valid && g == 0) ? ep5[r] : 0.f;
-        g5 = g == 0 ? b : 0.f;
+        e5 = (w.valid && gb == 0) ? ep5[r] : 0.f;
+        g5 = gb == 0 ? b : 0.f;
       }
 #pragma unroll
       for (int e = 0; e < YG; ++e) {
-        const bool real = g ? HRow<LM>::real(1, e) : HRow<LM>::real(0, e);
-        const float c2 = 2.0f * csel<HS>(g, e);
-        const float eL = e < nAg ? eA : eB, gL = e < nAg ? gA : gB;
+        const bool real = gb ? HRow<LM>::real(1, e) : HRow<LM>::real(0, e);
+        const float c2 = 2.0f * csel<HS>(gb, e);
+        const float eL = e < nAb ? eA : eB, gL = e < nAb ? gA : gB;
         float Av = c2 * eL * Sn[e];
         float Sb = c2 * (gL * Sn[e] - eL * Sdn[e]);
         if (e < 5) {
@@ -3157,8 +3163,8 @@ __device__ __forceinline__ void adjoint_body(const AdjArgs& a, int b, float* lds
           Av += 4.0f * e5 * P * Sn[e];
           Sb += 4.0f * g5 * P * Sn[e] - e5 * (8.0f * SS * Sn[e] + 4.0f * P * Sdn[e]);
         }
-        rowA[n * YR + g * YG + e] = real ? Av : 0.f;
-        rowSb[n * YR + g * YG + e] = real ? Sb : 0.f;
+        rowA[n * YR + gb * YG + e] = real ? Av : 0.f;
+        rowSb[n * YR + gb * YG + e] = real ? Sb : 0.f;
       }
     }
   }
